@@ -1,15 +1,15 @@
 // GEMM launchers of a stage: fprop (z = x W^T + b, a = act(z)), dgrad (dx = dz W_b, fused with
 // the previous layer's activation derivative) and wgrad (dW = dz^T x, db = column sums of dz).
 //
-// This file holds the shape-generic, bounds-checked SIMT kernel (fp32 FMA, LDS-tiled) that
-// serves the fp32 mode and any bf16 shape the MFMA kernels do not take, and the dispatch
-// between the two.
+// This file holds the shape-generic, bounds-checked SIMT kernel (fp32 FMA, LDS-tiled) that serves bf16
+// shapes the MFMA kernels do not take, and the dispatch.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
 
 #include "device_utils.h"
+#include "gemm_any.h"
 #include "gemm_mfma.h"
 #include "kernels.h"
 
@@ -100,15 +100,11 @@ __global__ __launch_bounds__(kThreads) void gemm_simt_kernel(int M, int N, int K
 }
 
 template <int EPI>
-hipError_t simt(hipStream_t s, int elt, int M, int N, int K, const void* A, long sam, long sak, const void* B, long sbk,
-                long sbn, const EpiArgs& e) {
+hipError_t simt(hipStream_t s, int M, int N, int K, const void* A, long sam, long sak, const void* B, long sbk, long sbn,
+                const EpiArgs& e) {
   dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM);
-  if (elt == ELT_BF16)
-    hipLaunchKernelGGL((gemm_simt_kernel<uint16_t, EPI>), grid, dim3(kThreads), 0, s, M, N, K, (const uint16_t*)A, sam,
-                       sak, (const uint16_t*)B, sbk, sbn, e);
-  else
-    hipLaunchKernelGGL((gemm_simt_kernel<float, EPI>), grid, dim3(kThreads), 0, s, M, N, K, (const float*)A, sam, sak,
-                       (const float*)B, sbk, sbn, e);
+  hipLaunchKernelGGL((gemm_simt_kernel<uint16_t, EPI>), grid, dim3(kThreads), 0, s, M, N, K, (const uint16_t*)A, sam, sak,
+                     (const uint16_t*)B, sbk, sbn, e);
   return hipGetLastError();
 }
 
@@ -352,19 +348,23 @@ hipError_t launch_fprop(hipStream_t s, int elt, int M, int N, int K, const void*
   if (elt == ELT_BF16 && mfma_fprop_supported(M, N, K))
     return mfma_fprop(s, M, N, K, (const uint16_t*)x, (const uint16_t*)W, bias, act, (uint16_t*)d_out, (uint16_t*)a_out,
                       nullptr, (const uint16_t*)addend);
+  if (elt == ELT_F32)
+    return f32_fprop(s, M, N, K, (const float*)x, (const float*)W, bias, act, (float*)d_out, (float*)a_out);
   EpiArgs e{};
   e.bias = bias; e.d_out = d_out; e.a_out = a_out; e.act = act;
-  return simt<EPI_FPROP>(s, elt, M, N, K, x, K, 1, W, 1, K, e);
+  return simt<EPI_FPROP>(s, M, N, K, x, K, 1, W, 1, K, e);
 }
 
 hipError_t launch_dgrad(hipStream_t s, int elt, int M, int N, int K, const void* dz, const void* Wb, const void* d_prev,
                         void* out, int relu_mask) {
   if (elt == ELT_BF16 && mfma_dgrad_supported(M, N, K))
     return mfma_dgrad(s, M, N, K, (const uint16_t*)dz, (const uint16_t*)Wb, (const uint16_t*)d_prev, (uint16_t*)out, relu_mask);
+  if (elt == ELT_F32)
+    return f32_dgrad(s, M, N, K, (const float*)dz, (const float*)Wb, (const float*)d_prev, (float*)out, relu_mask);
   EpiArgs e{};
   e.a_out = out; e.d_prev = d_prev; e.relu_mask = relu_mask;
   // out[M x K] = dz[M x N] . Wb[N x K]: contraction over N
-  return simt<EPI_DGRAD>(s, elt, M, K, N, dz, N, 1, Wb, K, 1, e);
+  return simt<EPI_DGRAD>(s, M, K, N, dz, N, 1, Wb, K, 1, e);
 }
 
 void set_sum_sink(std::vector<SumJob>* sink) { g_sum_sink = sink; }
@@ -451,16 +451,21 @@ hipError_t launch_act_backward_colsum(hipStream_t s, int elt, int M, int N, cons
 }
 
 size_t wgrad_scratch_floats(int elt, int M, int N, int K) {
-  return elt == ELT_BF16 && mfma_wgrad_supported(M, N, K) ? mfma_wgrad_scratch_floats(M, N, K) : 0;
+  if (elt == ELT_F32) {
+    const int splits = f32_wgrad_splits(M, N, K);
+    return splits > 1 ? (size_t)splits * N * K : 0;
+  }
+  return mfma_wgrad_supported(M, N, K) ? mfma_wgrad_scratch_floats(M, N, K) : 0;
 }
 
 hipError_t launch_wgrad(hipStream_t s, int elt, int M, int N, int K, const void* dz, const void* x, float* gW, float* partial) {
   if (elt == ELT_BF16 && mfma_wgrad_supported(M, N, K))
     return mfma_wgrad(s, M, N, K, (const uint16_t*)dz, (const uint16_t*)x, gW, partial);
+  if (elt == ELT_F32) return f32_wgrad(s, M, N, K, (const float*)dz, (const float*)x, gW, partial);
   EpiArgs e{};
   e.c_f32 = gW;
   // gW[N x K] = dz^T[N x M] . x[M x K]: contraction over M
-  return simt<EPI_STORE_F32>(s, elt, N, K, M, dz, 1, N, x, K, 1, e);
+  return simt<EPI_STORE_F32>(s, N, K, M, dz, 1, N, x, K, 1, e);
 }
 
 }  // namespace tp

@@ -1,0 +1,768 @@
+// Matrix-core GEMMs for whatever the tuned bf16 kernels do not take: every product of the fp32 mode
+// (v_mfma_f32_16x16x4_f32: fp32 operands, fp32 accumulation), dense and convolution, and the bf16 convolutions of
+// any kernel size, image size and channel count that is a multiple of 8 (v_mfma_f32_16x16x32_bf16).
+//
+// One kernel template; what differs between the products is where the 16-byte chunks of an operand's k tile come from
+// (the loaders below).  A k tile is 128 bytes of the contraction index per row: 32 fp32 or 64 bf16 values.  Copies go
+// global -> LDS without registers, NS stages deep, each lane with an address of its own: positions outside the image
+// and k values past the end of the contraction read a block of zeros, rows past the edge repeat the last row (computed,
+// never stored).  fp32 operands whose rows are no whole 16-byte units are copied word by word (VEC = 1).
+//
+// The MFMA takes one k value per lane and operand in fp32; which four k values a step's lanes hold is free as long as
+// both operands agree.  Lane (i, g) = (lane % 16, lane / 16) holds chunk 4 s + g of row i in step s, so an operand that
+// lies k-contiguous is read with one 16-byte LDS read per step and its four words feed four MFMAs; the bf16 MFMA wants
+// exactly that chunk.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "conv.h"
+#include "device_utils.h"
+#include "gemm_any.h"
+#include "kernels.h"
+#include "mfma_common.h"
+
+namespace tp {
+
+namespace {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+__device__ uint4 g_zero_chunk;  // what copies of nothing read
+
+__device__ __forceinline__ const char* zero_chunk() { return reinterpret_cast<const char*>(&g_zero_chunk); }
+
+// 16 or 4 bytes per lane, global -> LDS address + lane * (16 or 4)
+template <int BYTES>
+__device__ __forceinline__ void dma_addr(uint32_t lds_byte_addr, const void* lane_ptr) {
+  static_assert(BYTES == 16 || BYTES == 4, "copies of one chunk or one word per lane");
+  if constexpr (BYTES == 16)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_byte_addr), "v"(lane_ptr) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(lds_byte_addr), "v"(lane_ptr) : "memory");
+}
+
+// ---- LDS stages --------------------------------------------------------------------------------
+// k-contiguous operand: [R rows][8 chunks of 16 bytes], chunk c of row r in slot c ^ ((r / 2) % 8): the 16 rows of a
+// fragment read fall into different banks.
+// k-strided operand: [k][R rows], chunks of a k row XORed by a function of k chosen so that the k rows one fragment
+// read touches at once lie in different banks (as far as the row is long enough).
+template <class T>
+struct Elem;
+template <>
+struct Elem<float> {
+  static constexpr int kChunk = 4;  // values per 16 bytes
+};
+template <>
+struct Elem<uint16_t> {
+  static constexpr int kChunk = 8;
+};
+template <class T>
+constexpr int kTileK = 8 * Elem<T>::kChunk;  // k values of one stage
+
+template <class T, int R>
+__device__ __forceinline__ int col_swizzle(int k) {
+  constexpr int row_bytes = R * (int)sizeof(T);
+  if constexpr (sizeof(T) == 4) {  // a read: one word of rows k = 16 s + 4 g + j, g = 0 .. 3
+    if constexpr (row_bytes >= 256) return 4 * ((k >> 2) & 3);
+    else return 4 * ((k >> 2) & 1);
+  } else {  // a read: rows 32 s + 8 g + 0 .. 3, 32 bytes each; half a wave (two values of g) at a time
+    constexpr int chunks = row_bytes / 16;
+    const int hi = 2 * ((k >> 3) & 1);
+    if constexpr (chunks >= 16) return (4 * (k & 3)) ^ hi;
+    else if constexpr (chunks >= 8) return (4 * ((k >> 1) & 1)) ^ hi;
+    else return hi;
+  }
+}
+
+// What both sides of the MFMA need for one step: four fp32 words or eight bf16 values per lane
+template <class T>
+struct Frag;
+template <>
+struct Frag<float> {
+  float v[4];
+};
+template <>
+struct Frag<uint16_t> {
+  bf16x8 v;
+};
+
+template <class T, int R>
+__device__ __forceinline__ Frag<T> row_frag(const char* lds, int rbase, int step, int lane) {
+  const int r = rbase + (lane & 15);
+  const int c = (4 * step + (lane >> 4)) ^ ((r >> 1) & 7);
+  const uint4 u = *reinterpret_cast<const uint4*>(lds + r * 128 + c * 16);
+  return __builtin_bit_cast(Frag<T>, u);
+}
+
+template <class T, int R>
+__device__ __forceinline__ Frag<T> col_frag(const char* lds, int rbase, int step, int lane) {
+  const int i = lane & 15, g = lane >> 4;
+  if constexpr (sizeof(T) == 4) {
+    Frag<T> f;
+    const int r = rbase + i;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int k = 16 * step + 4 * g + j;
+      f.v[j] = *reinterpret_cast<const float*>(lds + k * (R * 4) + ((r >> 2) ^ col_swizzle<T, R>(k)) * 16 + (r & 3) * 4);
+    }
+    return f;
+  } else {
+    // ds_read_b64_tr_b16: lane s of a group of 16 points at 4 consecutive values of k row k0 + s/4 and receives rows
+    // k0 .. k0+3 of column c0 + s
+    const int k = 32 * step + 8 * g + (i >> 2);
+    const int col = rbase + 4 * (i & 3);
+    typedef __attribute__((address_space(3))) shortx4* lds_ptr;
+    const char* lo = lds + k * (R * 2) + ((col >> 3) ^ col_swizzle<T, R>(k)) * 16 + (col & 7) * 2;
+    const char* hi = lo + 4 * (R * 2);  // k + 4: the same swizzle
+    const shortx4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(lo));
+    const shortx4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(hi));
+    Frag<T> f;
+    f.v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+    return f;
+  }
+}
+
+// acc += (A . B^T of one step), transposed: register r of a lane is column 4 (lane / 16) + r of row lane % 16.
+// CH chains: an fp32 sum is kept in CH = 4 parts, one per word of the chunk, where the registers allow it (small wave
+// tiles), and added up at the end -- a quarter of the rounding steps in every chain (half the error of one long chain,
+// measured 4.1e-7 -> 2.1e-7 at K = 512) and four independent MFMAs in a row.
+template <int CH>
+__device__ __forceinline__ void multiply(const Frag<float>& a, const Frag<float>& b, floatx4 (&acc)[CH]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc[j % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.v[j], a.v[j], acc[j % CH], 0, 0, 0);
+}
+template <int CH>
+__device__ __forceinline__ void multiply(const Frag<uint16_t>& a, const Frag<uint16_t>& b, floatx4 (&acc)[CH]) {
+  acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.v, a.v, acc[0], 0, 0, 0);
+}
+
+// ---- loaders -----------------------------------------------------------------------------------
+// Where a lane's piece (one chunk, or one word with VEC = 1) of copy t lies in the stage: row and k of a k-contiguous
+// stage, k and row of a k-strided one.
+template <class T, int R, int NW, int VEC>
+struct RowSpot {
+  static constexpr int kPieceBytes = VEC * (int)sizeof(T);
+  static constexpr int kPerRow = 128 / kPieceBytes;
+  static constexpr int kInstr = R * kPerRow / 64;
+  static constexpr int kPerWave = kInstr / NW;
+  static_assert(kInstr % NW == 0 && kPerWave > 0, "copies do not divide among the waves");
+  static __device__ __forceinline__ void at(int t, int wave, int lane, int& r, int& k) {
+    const int flat = 64 * (wave + NW * t) + lane;
+    r = flat / kPerRow;
+    const int byte = (flat % kPerRow) * kPieceBytes;
+    const int chunk = (byte >> 4) ^ ((r >> 1) & 7);
+    k = chunk * Elem<T>::kChunk + (byte & 15) / (int)sizeof(T);
+  }
+};
+template <class T, int R, int NW, int VEC>
+struct ColSpot {
+  static constexpr int kPieceBytes = VEC * (int)sizeof(T);
+  static constexpr int kPerK = R / VEC;
+  static constexpr int kInstr = kTileK<T> * kPerK / 64;
+  static constexpr int kPerWave = kInstr / NW;
+  static_assert(kInstr % NW == 0 && kPerWave > 0, "copies do not divide among the waves");
+  static __device__ __forceinline__ void at(int t, int wave, int lane, int& r, int& k) {
+    const int flat = 64 * (wave + NW * t) + lane;
+    k = flat / kPerK;
+    const int byte = (flat % kPerK) * kPieceBytes;
+    const int chunk = (byte >> 4) ^ col_swizzle<T, R>(k);
+    r = chunk * Elem<T>::kChunk + (byte & 15) / (int)sizeof(T);
+  }
+};
+
+// A matrix as it lies in memory.  Row: element (r, k) at base[r * ld + k];  Col: at base[k * ld + r].
+struct DenseDesc {
+  const void* base;
+  int ld, rows, K;  // K: extent of the contraction; k >= K reads zero
+};
+
+template <class T, int R, int NW, int VEC>
+struct DenseRow {
+  using Desc = DenseDesc;
+  using Spot = RowSpot<T, R, NW, VEC>;
+  static constexpr int kPerWave = Spot::kPerWave;
+  const T* p[kPerWave];
+  int k[kPerWave], K;
+  __device__ __forceinline__ void init(const Desc& d, int r0, int wave, int lane) {
+    K = d.K;
+#pragma unroll
+    for (int t = 0; t < kPerWave; ++t) {
+      int r;
+      Spot::at(t, wave, lane, r, k[t]);
+      p[t] = (const T*)d.base + (size_t)min(r0 + r, d.rows - 1) * d.ld + k[t];
+    }
+  }
+  __device__ __forceinline__ const void* source(int t, int tile) const {
+    const int k0 = tile * kTileK<T>;
+    return k0 + k[t] < K ? (const char*)(p[t] + k0) : zero_chunk();
+  }
+  static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
+    return row_frag<T, R>(lds, rbase, step, lane);
+  }
+};
+
+template <class T, int R, int NW, int VEC>
+struct DenseCol {
+  using Desc = DenseDesc;
+  using Spot = ColSpot<T, R, NW, VEC>;
+  static constexpr int kPerWave = Spot::kPerWave;
+  const T* p[kPerWave];
+  int k[kPerWave], K, ld;
+  __device__ __forceinline__ void init(const Desc& d, int r0, int wave, int lane) {
+    K = d.K;
+    ld = d.ld;
+#pragma unroll
+    for (int t = 0; t < kPerWave; ++t) {
+      int r;
+      Spot::at(t, wave, lane, r, k[t]);
+      p[t] = (const T*)d.base + (size_t)k[t] * d.ld + min(r0 + r, d.rows - VEC);
+    }
+  }
+  __device__ __forceinline__ const void* source(int t, int tile) const {
+    const int k0 = tile * kTileK<T>;
+    return k0 + k[t] < K ? (const char*)(p[t] + (size_t)k0 * ld) : zero_chunk();
+  }
+  static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
+    return col_frag<T, R>(lds, rbase, step, lane);
+  }
+};
+
+// Exact quotient of n by div: n * ceil(2^32 / div) >> 32 for every n with n * div < 2^32
+struct FastDiv {
+  uint32_t mul, div;
+  __device__ __forceinline__ void get(int n, int& q, int& r) const {
+    q = div == 1 ? n : (int)__umulhi((uint32_t)n, mul);
+    r = n - q * (int)div;
+  }
+};
+
+// Rows are the pixels of a grid [imgs][H][W]; k runs over (tap, channel).  Forward (DX = false): output pixels reading
+// the input at S*(h, w) + tap - Pd.  Input gradient (DX = true): input pixels reading dz where (h, w) + Pd - tap is a
+// whole output position.
+struct GatherRowDesc {
+  const void* base;  // [imgs][SH][SW][C]
+  int rows, H, W;    // the grid the rows run over
+  int SH, SW;        // the grid that is read
+  int C, K;          // channels; kernel taps * C
+  int S, Pd;
+  FastDiv by_c, by_r;
+};
+template <class T, int R, int NW, int VEC, bool DX>
+struct GatherRow {
+  using Desc = GatherRowDesc;
+  using Spot = RowSpot<T, R, NW, VEC>;
+  static constexpr int kPerWave = Spot::kPerWave;
+  Desc d;
+  int img[kPerWave], hw[kPerWave], k[kPerWave];
+  __device__ __forceinline__ void init(const Desc& desc, int r0, int wave, int lane) {
+    d = desc;
+#pragma unroll
+    for (int t = 0; t < kPerWave; ++t) {
+      int r;
+      Spot::at(t, wave, lane, r, k[t]);
+      const int p = min(r0 + r, d.rows - 1);
+      const int q = p / d.W, w = p - q * d.W;
+      img[t] = q / d.H;
+      const int h = q - img[t] * d.H;
+      hw[t] = DX ? (h + d.Pd) << 16 | (w + d.Pd) : (h * d.S) << 16 | (w * d.S);
+    }
+  }
+  __device__ __forceinline__ const void* source(int t, int tile) const {
+    int tap, c, kh, kw;
+    const int kk = tile * kTileK<T> + k[t];
+    d.by_c.get(kk, tap, c);
+    d.by_r.get(tap, kh, kw);
+    int sh, sw;
+    bool ok = kk < d.K;
+    if (DX) {
+      sh = (hw[t] >> 16) - kh;
+      sw = (hw[t] & 0xffff) - kw;
+      if (d.S == 2) {
+        ok = ok && !((sh | sw) & 1);
+        sh >>= 1;
+        sw >>= 1;
+      }
+    } else {
+      sh = (hw[t] >> 16) + kh - d.Pd;
+      sw = (hw[t] & 0xffff) + kw - d.Pd;
+    }
+    ok = ok && (unsigned)sh < (unsigned)d.SH && (unsigned)sw < (unsigned)d.SW;
+    return ok ? (const char*)((const T*)d.base + ((size_t)(img[t] * d.SH + sh) * d.SW + sw) * d.C + c) : zero_chunk();
+  }
+  static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
+    return row_frag<T, R>(lds, rbase, step, lane);
+  }
+};
+
+// The weights of the input gradient: row n = input channel, k = (tap, output channel), element at
+// base[co * taps * Cin + tap * Cin + n].
+struct WeightColDesc {
+  const void* base;
+  int cin, taps, cout;
+  FastDiv by_cout;
+};
+template <class T, int R, int NW, int VEC>
+struct WeightCol {
+  using Desc = WeightColDesc;
+  using Spot = ColSpot<T, R, NW, VEC>;
+  static constexpr int kPerWave = Spot::kPerWave;
+  Desc d;
+  int n[kPerWave], k[kPerWave];
+  __device__ __forceinline__ void init(const Desc& desc, int r0, int wave, int lane) {
+    d = desc;
+#pragma unroll
+    for (int t = 0; t < kPerWave; ++t) {
+      int r;
+      Spot::at(t, wave, lane, r, k[t]);
+      n[t] = min(r0 + r, d.cin - VEC);
+    }
+  }
+  __device__ __forceinline__ const void* source(int t, int tile) const {
+    int tap, co;
+    d.by_cout.get(tile * kTileK<T> + k[t], tap, co);
+    return tap < d.taps ? (const char*)((const T*)d.base + ((size_t)co * d.taps + tap) * d.cin + n[t]) : zero_chunk();
+  }
+  static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
+    return col_frag<T, R>(lds, rbase, step, lane);
+  }
+};
+
+// The input as the weight gradient reads it: row n = (tap, input channel), k = output pixel.
+struct GatherColDesc {
+  const void* base;  // [imgs][SH][SW][C]
+  int H, W;          // output grid
+  int SH, SW, C, K;  // K: output pixels
+  int S, Pd, N;      // N: taps * C
+  FastDiv by_c, by_r;
+};
+template <class T, int R, int NW, int VEC>
+struct GatherCol {
+  using Desc = GatherColDesc;
+  using Spot = ColSpot<T, R, NW, VEC>;
+  static constexpr int kPerWave = Spot::kPerWave;
+  Desc d;
+  int c[kPerWave], dh[kPerWave], dw[kPerWave], k[kPerWave];
+  __device__ __forceinline__ void init(const Desc& desc, int r0, int wave, int lane) {
+    d = desc;
+#pragma unroll
+    for (int t = 0; t < kPerWave; ++t) {
+      int r, tap, kh, kw;
+      Spot::at(t, wave, lane, r, k[t]);
+      d.by_c.get(min(r0 + r, d.N - VEC), tap, c[t]);
+      d.by_r.get(tap, kh, kw);
+      dh[t] = kh - d.Pd;
+      dw[t] = kw - d.Pd;
+    }
+  }
+  __device__ __forceinline__ const void* source(int t, int tile) const {
+    const uint32_t p = (uint32_t)tile * kTileK<T> + k[t];
+    const uint32_t q = p / (uint32_t)d.W, w = p - q * d.W;
+    const uint32_t img = q / (uint32_t)d.H, h = q - img * d.H;
+    const int sh = (int)h * d.S + dh[t], sw = (int)w * d.S + dw[t];
+    const bool ok = p < (uint32_t)d.K && (unsigned)sh < (unsigned)d.SH && (unsigned)sw < (unsigned)d.SW;
+    return ok ? (const char*)((const T*)d.base + ((size_t)(img * d.SH + sh) * d.SW + sw) * d.C + c[t]) : zero_chunk();
+  }
+  static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
+    return col_frag<T, R>(lds, rbase, step, lane);
+  }
+};
+
+// ---- epilogues: four consecutive columns n .. n+3 (count of them inside the matrix) of row m ----
+// fp32.  vec: whole 16-byte units everywhere.
+struct EpiFpropF32 {
+  const float* bias;
+  float *d_out, *a_out;
+  int act, ldc, vec;
+  __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
+    const size_t i = (size_t)m * ldc + n;
+    float a[4], d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float z = v[j] + bias[j < count ? n + j : n];
+      a[j] = act_forward(z, act);
+      d[j] = d_out ? act_derivative(z, act) : 0.f;
+    }
+    if (vec && count == 4) {
+      if (d_out) *reinterpret_cast<float4*>(d_out + i) = make_float4(d[0], d[1], d[2], d[3]);
+      *reinterpret_cast<float4*>(a_out + i) = make_float4(a[0], a[1], a[2], a[3]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j < count) {
+          if (d_out) d_out[i + j] = d[j];
+          a_out[i + j] = a[j];
+        }
+    }
+  }
+};
+struct EpiDgradF32 {
+  const float* d_prev;  // saved act'(z) of the layer before, with relu_mask its ReLU output, or null
+  float* out;
+  int ldc, relu_mask, vec;
+  __device__ __forceinline__ float through(float v, float d) const { return relu_mask ? (d > 0.f ? v : 0.f) : v * d; }
+  __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
+    const size_t i = (size_t)m * ldc + n;
+    if (vec && count == 4) {
+      float4 o = make_float4(v[0], v[1], v[2], v[3]);
+      if (d_prev) {
+        const float4 d = *reinterpret_cast<const float4*>(d_prev + i);
+        o = make_float4(through(o.x, d.x), through(o.y, d.y), through(o.z, d.z), through(o.w, d.w));
+      }
+      *reinterpret_cast<float4*>(out + i) = o;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j < count) out[i + j] = d_prev ? through(v[j], d_prev[i + j]) : v[j];
+    }
+  }
+};
+// fp32 partial result of contraction range `split`
+struct EpiPartial {
+  float* out;
+  int ldc, vec;
+  size_t split_stride;
+  __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int split) const {
+    float* p = out + (size_t)split * split_stride + (size_t)m * ldc + n;
+    if (vec && count == 4) {
+      *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j < count) p[j] = v[j];
+    }
+  }
+};
+// bf16: the epilogues of the tuned kernels
+template <class E>
+struct EpiBf16 {
+  E e;
+  __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
+    e.quad(m, n, count, v[0], v[1], v[2], v[3]);
+  }
+};
+
+// ---- the kernel --------------------------------------------------------------------------------
+// grid = (output tiles, contraction ranges of `per` k tiles each).
+// U k tiles are waited for, multiplied and replaced between two barriers.
+// KG > 1: KG groups of WGM x WGN waves share the output tile, group g takes every KG-th run of U k tiles of the range, with
+// stage buffers of its own; all groups meet at the same barriers, and the first one adds up and stores the tile.
+template <class T, int BM, int BN, int WGM, int WGN, int NS, int KG, int U, class AL, class BL, class Epi>
+__global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_any_kernel(int M, int N, int KT, int per, typename AL::Desc ad,
+                                                                       typename BL::Desc bd, Epi epi, TileMap map) {
+  constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, NW = WGM * WGN;
+  constexpr int kABytes = BM * 128, kStage = (BM + BN) * 128;
+  constexpr int kLoads = AL::kPerWave + BL::kPerWave;
+  static_assert((NS - 2) * U * kLoads < 64, "too many copies in flight for vmcnt");
+  static_assert(KG == 1 || (KG - 1) * BM * BN * 4 <= KG * NS * U * kStage, "the groups' tiles do not fit the stages");
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+
+  const int lane = threadIdx.x & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = wave_all / NW, wave = wave_all % NW;
+  const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
+  int tile_m, tile_n;
+  map.get(blockIdx.x, tile_m, tile_n);
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int first = blockIdx.y * per, last = min(KT, first + per) - 1;  // k tiles of this range (at least one)
+  char* stages = lds + group * (NS * U * kStage);
+  const uint32_t lds_base = lds_addr_of(stages);
+
+  constexpr int CH = sizeof(T) == 4 && TM * TN <= 4 ? 4 : 1;
+  floatx4 acc[TM][TN][CH];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int c = 0; c < CH; ++c) acc[i][j][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  AL a;
+  BL b;
+  a.init(ad, m0, wave, lane);
+  b.init(bd, n0, wave, lane);
+  // tiles past the end copy the last tile again into a stage nobody reads, so that every iteration has the same
+  // number of copies in flight
+  auto issue = [&](int tile, int stage) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = min(tile + u, last);
+      const uint32_t dst = lds_base + (stage * U + u) * kStage;
+#pragma unroll
+      for (int q = 0; q < AL::kPerWave; ++q)
+        dma_addr<AL::Spot::kPieceBytes>(dst + (wave + NW * q) * 64 * AL::Spot::kPieceBytes, a.source(q, t));
+#pragma unroll
+      for (int q = 0; q < BL::kPerWave; ++q)
+        dma_addr<BL::Spot::kPieceBytes>(dst + kABytes + (wave + NW * q) * 64 * BL::Spot::kPieceBytes, b.source(q, t));
+    }
+  };
+#pragma unroll
+  for (int st = 0; st < NS - 1; ++st) issue(first + (group + KG * st) * U, st);
+  int rd = 0, wr = NS - 1;
+  for (int k0 = first; k0 <= last; k0 += KG * U) {
+    const int kt = k0 + group * U;
+    wait_vmcnt<(NS - 2) * U * kLoads>();
+    lds_barrier();  // tiles kt .. kt + U - 1 visible to the group's waves; everybody is done reading stage `wr`
+    issue(kt + KG * U * (NS - 1), wr);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const char* la = stages + (rd * U + u) * kStage;
+      const char* lb = la + kABytes;
+      if (KG * U > 1 && kt + u > last) continue;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        Frag<T> fa[TM], fb[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[i] = AL::frag(la, wm + 16 * i, s, lane);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[j] = BL::frag(lb, wn + 16 * j, s, lane);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) multiply(fa[i], fb[j], acc[i][j]);
+      }
+    }
+    rd = rd + 1 == NS ? 0 : rd + 1;
+    wr = wr + 1 == NS ? 0 : wr + 1;
+  }
+  wait_vmcnt<0>();  // the trailing copies land before the LDS is reused or given back
+
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      if constexpr (CH == 4) acc[i][j][0] = (acc[i][j][0] + acc[i][j][1]) + (acc[i][j][2] + acc[i][j][3]);
+  if constexpr (KG > 1) {
+    lds_barrier();  // every group is done with its stages
+    floatx4* tiles = reinterpret_cast<floatx4*>(lds);
+    auto at = [&](int g, int i, int j) -> floatx4& { return tiles[((((g - 1) * NW + wave) * TM + i) * TN + j) * 64 + lane]; };
+    if (group > 0)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) at(group, i, j) = acc[i][j][0];
+    lds_barrier();
+    if (group > 0) return;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int g = 1; g < KG; ++g) acc[i][j][0] += at(g, i, j);
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = m0 + wm + 16 * i + (lane & 15);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + wn + 16 * j + 4 * (lane >> 4);
+      if (m < M && n < N) epi.quad(m, n, min(4, N - n), acc[i][j][0], blockIdx.y);
+    }
+  }
+}
+
+template <class T, int BM, int BN, int WGM, int WGN, int NS, int KG, int U, class AL, class BL, class Epi>
+hipError_t launch_any(hipStream_t s, int M, int N, int KT, int splits, const typename AL::Desc& ad, const typename BL::Desc& bd,
+                      const Epi& epi) {
+  constexpr size_t lds_bytes = (size_t)KG * NS * U * (BM + BN) * 128;
+  static_assert(lds_bytes <= 160 * 1024, "stages do not fit the LDS of a CU");
+  auto kernel = gemm_any_kernel<T, BM, BN, WGM, WGN, NS, KG, U, AL, BL, Epi>;
+  if (lds_bytes > 64 * 1024) {
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    if (attr != hipSuccess) return attr;
+  }
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int per = (KT + splits - 1) / splits;
+  const int ranges = (KT + per - 1) / per;  // every one of them has a tile to sum; ranges == splits by any_splits
+  if (ranges != splits) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n, ranges), dim3(64 * WGM * WGN * KG), lds_bytes, s, M, N, KT, per, ad, bd, epi,
+                     make_tile_map(tiles_m, tiles_n));
+  return hipGetLastError();
+}
+
+enum class Tile { k32, k64, k128 };
+inline int tile_edge(Tile t) { return t == Tile::k32 ? 32 : t == Tile::k64 ? 64 : 128; }
+inline long blocks_of(Tile t, int M, int N) {
+  const int e = tile_edge(t);
+  return (long)((M + e - 1) / e) * ((N + e - 1) / e);
+}
+
+// The tile with the least (rounds of 256 workgroups) x (time of one), a larger tile being up to this much faster per
+// output (operand traffic, barriers); 32 x 32 is there to spread small outputs over the chip.
+inline Tile pick_tile(int M, int N) {
+  struct { Tile t; int rate; } const cand[] = {{Tile::k128, 100}, {Tile::k64, 90}, {Tile::k32, 55}};
+  Tile best = Tile::k32;
+  double best_cost = -1;
+  for (const auto& c : cand) {
+    const long e = tile_edge(c.t);
+    const double cost = (double)((blocks_of(c.t, M, N) + 255) / 256) * e * e / c.rate;
+    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = c.t; }
+  }
+  return best;
+}
+
+// Contraction ranges of a product whose output has too few tiles for the chip (weight gradients): as many as give every
+// CU a workgroup, each at least 8 k tiles long, and none of them empty.
+inline int any_splits(long blocks, int KT) {
+  long s = std::min<long>(256 / std::max<long>(blocks, 1), KT / 8);
+  if (s <= 1) return 1;
+  const int per = (int)((KT + s - 1) / s);
+  return (KT + per - 1) / per;
+}
+
+inline bool aligned16(const void* a, const void* b = nullptr, const void* c = nullptr) {
+  return (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15) == 0;
+}
+inline FastDiv fast_div(int d) { return FastDiv{d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d), (uint32_t)d}; }
+
+// Loader class templates with the element type and vector width filled in per product
+template <class T, int VEC> struct FpropDense {
+  template <int R, int NW> using A = DenseRow<T, R, NW, VEC>;
+  template <int R, int NW> using B = DenseRow<T, R, NW, VEC>;
+};
+template <class T, int VEC> struct DgradDense {
+  template <int R, int NW> using A = DenseRow<T, R, NW, VEC>;
+  template <int R, int NW> using B = DenseCol<T, R, NW, VEC>;
+};
+template <class T, int VEC> struct WgradDense {
+  template <int R, int NW> using A = DenseCol<T, R, NW, VEC>;
+  template <int R, int NW> using B = DenseCol<T, R, NW, VEC>;
+};
+template <class T, int VEC> struct FpropConv {
+  template <int R, int NW> using A = GatherRow<T, R, NW, VEC, false>;
+  template <int R, int NW> using B = DenseRow<T, R, NW, VEC>;
+};
+template <class T, int VEC> struct DgradConv {
+  template <int R, int NW> using A = GatherRow<T, R, NW, VEC, true>;
+  template <int R, int NW> using B = WeightCol<T, R, NW, VEC>;
+};
+template <class T, int VEC> struct WgradConv {
+  template <int R, int NW> using A = DenseCol<T, R, NW, VEC>;
+  template <int R, int NW> using B = GatherCol<T, R, NW, VEC>;
+};
+
+// The tiles.  fp32 products are bound by the matrix cores where the output fills the chip (157 TFLOP/s nominal; four
+// waves, operand traffic of a 64 x 64 tile is 16 bytes per clock and CU) and by the chain barrier -> LDS reads -> MFMAs
+// of a single workgroup where it does not.  So: 128 x 128, three stages (96 KB); 64 x 64, four stages (64 KB, two
+// workgroups on a CU); and 32 x 32 on two groups of waves with two k tiles between barriers (64 KB).  Measured in fp32,
+// 32 / 64 / 128 tile, forward: 128 x 1024 x 1024 9.9 / 26 / 80 us, 1024^3 29 / 27 / 80 us, 2048^3 195 / 157 / 152 us
+// (113 TFLOP/s); 32 x 512 x 512 6.5 us.  (The fp32 FMA kernel before: 160 us, 140 us, -, 45 us.)  The 32 x 32 tile on
+// one group of waves with eight stages: 12.8 us at 128 x 1024 x 1024; on four groups 10.3 us.
+template <class T, class P, class AD, class BD, class Epi>
+hipError_t run(hipStream_t s, int M, int N, int K, const AD& ad, const BD& bd, const Epi& epi, int splits = 1) {
+  const int KT = (K + kTileK<T> - 1) / kTileK<T>;
+  switch (pick_tile(M, N)) {
+    case Tile::k128:
+      return launch_any<T, 128, 128, 2, 2, 3, 1, 1, typename P::template A<128, 4>, typename P::template B<128, 4>>(s, M, N, KT, splits, ad, bd, epi);
+    case Tile::k64:
+      return launch_any<T, 64, 64, 2, 2, 4, 1, 1, typename P::template A<64, 4>, typename P::template B<64, 4>>(s, M, N, KT, splits, ad, bd, epi);
+    default:
+      return launch_any<T, 32, 32, 2, 2, 2, 2, 2, typename P::template A<32, 4>, typename P::template B<32, 4>>(s, M, N, KT, splits, ad, bd, epi);
+  }
+}
+
+}  // namespace
+
+// ---- dense, fp32 -------------------------------------------------------------------------------
+hipError_t f32_fprop(hipStream_t s, int M, int N, int K, const float* x, const float* W, const float* bias, int act, float* d_out,
+                     float* a_out) {
+  const DenseDesc a{x, K, M, K}, b{W, K, N, K};
+  const EpiFpropF32 e{bias, d_out, a_out, act, N, N % 4 == 0 && aligned16(d_out, a_out)};
+  if (K % 4 == 0 && aligned16(x, W)) return run<float, FpropDense<float, 4>>(s, M, N, K, a, b, e);
+  return run<float, FpropDense<float, 1>>(s, M, N, K, a, b, e);
+}
+
+hipError_t f32_dgrad(hipStream_t s, int M, int N, int K, const float* dz, const float* Wb, const float* d_prev, float* out,
+                     int relu_mask) {
+  // out[M x K] = dz[M x N] . Wb[N x K]: contraction over N
+  const DenseDesc a{dz, N, M, N}, b{Wb, K, K, N};
+  const EpiDgradF32 e{d_prev, out, K, relu_mask, K % 4 == 0 && aligned16(d_prev, out)};
+  if (N % 4 == 0 && K % 4 == 0 && aligned16(dz, Wb)) return run<float, DgradDense<float, 4>>(s, M, K, N, a, b, e);
+  return run<float, DgradDense<float, 1>>(s, M, K, N, a, b, e);
+}
+
+int f32_wgrad_splits(int M, int N, int K) { return any_splits(blocks_of(pick_tile(N, K), N, K), (M + 31) / 32); }
+
+hipError_t f32_wgrad(hipStream_t s, int M, int N, int K, const float* dz, const float* x, float* gW, float* partial) {
+  // gW[N x K] = dz^T[N x M] . x[M x K]: contraction over M
+  const int splits = partial ? f32_wgrad_splits(M, N, K) : 1;
+  const DenseDesc a{dz, N, N, M}, b{x, K, K, M};
+  float* out = splits > 1 ? partial : gW;
+  const EpiPartial e{out, K, K % 4 == 0 && aligned16(out), (size_t)N * K};
+  const hipError_t err = N % 4 == 0 && K % 4 == 0 && aligned16(dz, x)
+                             ? run<float, WgradDense<float, 4>>(s, N, K, M, a, b, e, splits)
+                             : run<float, WgradDense<float, 1>>(s, N, K, M, a, b, e, splits);
+  if (err != hipSuccess || splits == 1) return err;
+  return launch_sum_partials(s, (size_t)N * K, splits, partial, gW);
+}
+
+// ---- convolutions ------------------------------------------------------------------------------
+bool conv_any_supported(int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout) {
+  const long taps = (long)ksize * ksize, pin = (long)imgs * H * W;
+  const long c = std::max(cin, cout);
+  // image edges fit 15 bits, pixel numbers 30, and every k value (up to a tile past the end) has an exact quotient by the
+  // channel count
+  return H + ksize < 32768 && W + ksize < 32768 && pin < (1l << 30) && (taps * c + 64) * c < (1l << 32) &&
+         (elt == ELT_F32 || (cin % 8 == 0 && cout % 8 == 0));
+}
+
+hipError_t conv_any_fprop(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout, const void* x,
+                          const void* wgt, const float* bias, int act, void* d_out, void* a_out) {
+  const int Ho = H / stride, Wo = W / stride, P = imgs * Ho * Wo, K = ksize * ksize * cin;
+  const GatherRowDesc a{x, P, Ho, Wo, H, W, cin, K, stride, (ksize - 1) / 2, fast_div(cin), fast_div(ksize)};
+  const DenseDesc b{wgt, K, cout, K};
+  const bool vec = aligned16(x, wgt);
+  if (elt == ELT_BF16) {
+    if (!vec) return hipErrorNotSupported;
+    return run<uint16_t, FpropConv<uint16_t, 8>>(s, P, cout, K, a, b, EpiBf16<EpiFprop>{{bias, (uint16_t*)d_out, (uint16_t*)a_out, act, cout}});
+  }
+  const EpiFpropF32 e{bias, (float*)d_out, (float*)a_out, act, cout, cout % 4 == 0 && aligned16(d_out, a_out)};
+  if (cin % 4 == 0 && vec) return run<float, FpropConv<float, 4>>(s, P, cout, K, a, b, e);
+  return run<float, FpropConv<float, 1>>(s, P, cout, K, a, b, e);
+}
+
+hipError_t conv_any_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout, const void* dz,
+                          const void* wb, const void* d_prev, void* out, int relu_mask) {
+  const int taps = ksize * ksize, P = imgs * H * W, K = taps * cout;
+  const GatherRowDesc a{dz, P, H, W, H / stride, W / stride, cout, K, stride, (ksize - 1) / 2, fast_div(cout), fast_div(ksize)};
+  const WeightColDesc b{wb, cin, taps, cout, fast_div(cout)};
+  const bool vec = aligned16(dz, wb);
+  if (elt == ELT_BF16) {
+    if (!vec) return hipErrorNotSupported;
+    return run<uint16_t, DgradConv<uint16_t, 8>>(s, P, cin, K, a, b, EpiBf16<EpiDgrad>{{(const uint16_t*)d_prev, (uint16_t*)out, cin, relu_mask}});
+  }
+  const EpiDgradF32 e{(const float*)d_prev, (float*)out, cin, relu_mask, cin % 4 == 0 && aligned16(d_prev, out)};
+  if (cin % 4 == 0 && cout % 4 == 0 && vec) return run<float, DgradConv<float, 4>>(s, P, cin, K, a, b, e);
+  return run<float, DgradConv<float, 1>>(s, P, cin, K, a, b, e);
+}
+
+int conv_any_wgrad_splits(int elt, int pixels, int cin, int cout, int ksize) {
+  const int N = ksize * ksize * cin, tile_k = elt == ELT_BF16 ? kTileK<uint16_t> : kTileK<float>;
+  return any_splits(blocks_of(pick_tile(cout, N), cout, N), (pixels + tile_k - 1) / tile_k);
+}
+
+hipError_t conv_any_wgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout, const void* dz,
+                          const void* x, float* gW, float* partial) {
+  const int Ho = H / stride, Wo = W / stride, P = imgs * Ho * Wo, N = ksize * ksize * cin;
+  const int splits = conv_any_wgrad_splits(elt, P, cin, cout, ksize);
+  const DenseDesc a{dz, cout, cout, P};
+  const GatherColDesc b{x, Ho, Wo, H, W, cin, P, stride, (ksize - 1) / 2, N, fast_div(cin), fast_div(ksize)};
+  float* out = splits > 1 ? partial : gW;
+  const EpiPartial e{out, N, N % 4 == 0 && aligned16(out), (size_t)cout * N};
+  const bool vec = aligned16(dz, x);
+  hipError_t err;
+  if (elt == ELT_BF16) {
+    if (!vec) return hipErrorNotSupported;
+    err = run<uint16_t, WgradConv<uint16_t, 8>>(s, cout, N, P, a, b, e, splits);
+  } else if (cin % 4 == 0 && cout % 4 == 0 && vec) {
+    err = run<float, WgradConv<float, 4>>(s, cout, N, P, a, b, e, splits);
+  } else {
+    err = run<float, WgradConv<float, 1>>(s, cout, N, P, a, b, e, splits);
+  }
+  if (err != hipSuccess || splits == 1) return err;
+  return launch_sum_partials(s, (size_t)cout * N, splits, partial, gW);
+}
+
+}  // namespace tp

@@ -1,0 +1,52 @@
+"""The matrix-core kernels for shapes outside the tuned bf16 ones (kernels_gemm_any.hip), at the edges of their tiles:
+one layer's forward, input gradient and weight gradient against fp64."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _rel(got, ref):
+    return float(np.linalg.norm(got.astype(np.float64) - ref) / np.linalg.norm(ref))
+
+
+def _sum_tol(terms):
+    """fp32 sum of `terms` products in one chain: every step rounds a partial sum by at most 2^-24 of it; with random
+    signs that is below 2^-24 sqrt(terms / 3) of the result, and the bound used is twice that (at least 4 ulp)."""
+    return max(2.0 ** -22, 2.0 * 2.0 ** -24 * np.sqrt(terms / 3.0))
+
+
+def _stage(layer, params, rows, dtype):
+    from paper_2509_23241_amd.runner import GpuStage
+    return GpuStage([layer], params, dtype=dtype, mb=rows, n=1, stage_index=1, num_stages=2, policy="latest", lam=0.1,
+                    lr=0.0, momentum=0.0, ring_capacity=1, max_in_flight=1)
+
+
+def _run(st, x, dy):
+    import torch
+    y, _ = st.forward(0, 0, torch.from_numpy(x).cuda().to(st.tdtype))
+    dx, _ = st.backward(0, torch.from_numpy(dy).cuda().to(st.tdtype))
+    out = y.float().cpu().numpy(), dx.float().cpu().numpy(), st.unpack(st.grad.cpu().numpy())
+    st.close()
+    return out
+
+
+@pytest.mark.parametrize("rows,fin,fout", [
+    (1, 1, 1), (31, 33, 35), (32, 32, 32), (33, 36, 100),     # 32 x 32 tiles: less than one, one, one and a bit
+    (1030, 1028, 1000),                                       # 64 x 64 tiles, 16-byte rows
+    (1023, 1021, 1027),                                       # 64 x 64 tiles, rows copied word by word
+    (2050, 2052, 2048), (2049, 2047, 2051),                   # 128 x 128 tiles, both ways of copying
+    (2100, 40, 36), (2100, 41, 39),                           # weight gradient over several row ranges, with a remainder
+])
+def test_dense_fp32(rows, fin, fout):
+    rng = np.random.default_rng(rows + fin)
+    W = (rng.standard_normal((fout, fin)) / np.sqrt(fin)).astype(np.float32)
+    b = rng.standard_normal(fout).astype(np.float32)
+    x = rng.standard_normal((rows, fin)).astype(np.float32)
+    dy = rng.standard_normal((rows, fout)).astype(np.float32)
+    y, dx, (gw, gb) = _run(_stage((fin, fout, "none"), [W, b], rows, "f32"), x, dy)
+    x64, W64, dy64 = x.astype(np.float64), W.astype(np.float64), dy.astype(np.float64)
+    assert _rel(y, x64 @ W64.T + b) <= _sum_tol(fin)
+    assert _rel(dx, dy64 @ W64) <= _sum_tol(fout)
+    assert _rel(gw, dy64.T @ x64) <= _sum_tol(rows)
+    assert _rel(gb, dy64.sum(0)) <= _sum_tol(rows)
