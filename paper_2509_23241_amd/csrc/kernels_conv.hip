@@ -10,15 +10,17 @@
 // (s*oh + kh - pad, s*ow + kw - pad); dgrad visits, for an input pixel, the taps whose output position
 // (h - kh + pad) / s, (w - kw + pad) / s is whole.
 //
-// This file holds the shape-generic, bounds-checked SIMT kernel (fp32 FMA, LDS-tiled), used for
-// the fp32 mode, for kernel sizes and channel counts the matrix-core kernels do not take and as their reference.  wgrad contracts over all pixels of the mini-batch, so it is
-// split over pixel ranges; a second kernel adds the partial results in a fixed order.
+// This file holds the dispatch and the shape-generic, bounds-checked SIMT kernel (fp32 FMA, LDS-tiled) for what none of
+// the matrix-core kernels takes: bf16 with channel counts that are no multiples of 8 or tensors that are not 16-byte
+// aligned.  wgrad contracts over all pixels of the mini-batch, so it is split over pixel ranges; a second kernel adds
+// the partial results in a fixed order.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
 
 #include "conv.h"
+#include "gemm_any.h"
 #include "kernels.h"
 #include "device_utils.h"
 
@@ -360,6 +362,7 @@ int conv_wgrad_splits(int pixels, int cin, int cout, int ksize) {
 size_t conv_wgrad_scratch_floats(int pixels, int cin, int cout, int ksize) {
   int splits = conv_wgrad_splits(pixels, cin, cout, ksize);
   if (ksize == 3) splits = std::max(splits, conv_mfma_wgrad_max_splits(pixels, cin, cout));
+  for (const int elt : {ELT_F32, ELT_BF16}) splits = std::max(splits, conv_any_wgrad_splits(elt, pixels, cin, cout, ksize));
   if (ksize == 7 && cin <= 8 && cout % 64 == 0) splits = std::max(splits, conv_stem_wgrad_splits(pixels, cout));
   return (size_t)splits * cout * ksize * ksize * cin;
 }
@@ -375,6 +378,10 @@ hipError_t launch_conv_fprop(hipStream_t s, int elt, int imgs, int H, int W, int
   if (ksize == 3 && elt == 1 && zeros && conv_mfma_supported(imgs, H, W, stride, cin, cout))
     return conv_mfma_fprop(s, imgs, H, W, stride, cin, cout, (const uint16_t*)x, (const uint16_t*)wgt, bias, act,
                            (uint16_t*)d_out, (uint16_t*)a_out, (const uint16_t*)zeros);
+  if (conv_any_supported(elt, imgs, H, W, ksize, stride, cin, cout)) {
+    const hipError_t e = conv_any_fprop(s, elt, imgs, H, W, ksize, stride, cin, cout, x, wgt, bias, act, d_out, a_out);
+    if (e != hipErrorNotSupported) return e;
+  }
   const ConvGeom g{imgs, H, W, cin, cout, stride, H / stride, W / stride, ksize, (ksize - 1) / 2};
   const int P = imgs * g.Ho * g.Wo;
   dim3 grid((cout + BN - 1) / BN, (P + BM - 1) / BM);
@@ -394,6 +401,10 @@ hipError_t launch_conv_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int
   if (ksize == 3 && elt == 1 && zeros && conv_mfma_supported(imgs, H, W, stride, cin, cout))
     return conv_mfma_dgrad(s, imgs, H, W, stride, cin, cout, (const uint16_t*)dz, (const uint16_t*)wb,
                            (const uint16_t*)d_prev, (uint16_t*)out, (const uint16_t*)zeros, relu_mask);
+  if (conv_any_supported(elt, imgs, H, W, ksize, stride, cin, cout)) {
+    const hipError_t e = conv_any_dgrad(s, elt, imgs, H, W, ksize, stride, cin, cout, dz, wb, d_prev, out, relu_mask);
+    if (e != hipErrorNotSupported) return e;
+  }
   const ConvGeom g{imgs, H, W, cin, cout, stride, H / stride, W / stride, ksize, (ksize - 1) / 2};
   const int P = imgs * H * W;
   dim3 grid((cin + BN - 1) / BN, (P + BM - 1) / BM);
@@ -412,6 +423,10 @@ hipError_t launch_conv_wgrad(hipStream_t s, int elt, int imgs, int H, int W, int
   if (ksize == 3 && elt == 1 && zeros && conv_mfma_supported(imgs, H, W, stride, cin, cout))
     return conv_mfma_wgrad(s, imgs, H, W, stride, cin, cout, (const uint16_t*)dz, (const uint16_t*)x, gW, partial,
                            (const uint16_t*)zeros);
+  if (conv_any_supported(elt, imgs, H, W, ksize, stride, cin, cout)) {
+    const hipError_t e = conv_any_wgrad(s, elt, imgs, H, W, ksize, stride, cin, cout, dz, x, gW, partial);
+    if (e != hipErrorNotSupported) return e;
+  }
   const ConvGeom g{imgs, H, W, cin, cout, stride, H / stride, W / stride, ksize, (ksize - 1) / 2};
   const int P = imgs * g.Ho * g.Wo;  // the contraction runs over output pixels
   const int splits = conv_wgrad_splits(P, cin, cout, ksize);

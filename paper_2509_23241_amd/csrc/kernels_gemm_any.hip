@@ -194,6 +194,8 @@ struct DenseRow {
       p[t] = (const T*)d.base + (size_t)min(r0 + r, d.rows - 1) * d.ld + k[t];
     }
   }
+  using Tile = int;
+  __device__ __forceinline__ Tile tile(int tile) const { return tile; }
   __device__ __forceinline__ const void* source(int t, int tile) const {
     const int k0 = tile * kTileK<T>;
     return k0 + k[t] < K ? (const char*)(p[t] + k0) : zero_chunk();
@@ -220,6 +222,8 @@ struct DenseCol {
       p[t] = (const T*)d.base + (size_t)k[t] * d.ld + min(r0 + r, d.rows - VEC);
     }
   }
+  using Tile = int;
+  __device__ __forceinline__ Tile tile(int tile) const { return tile; }
   __device__ __forceinline__ const void* source(int t, int tile) const {
     const int k0 = tile * kTileK<T>;
     return k0 + k[t] < K ? (const char*)(p[t] + (size_t)k0 * ld) : zero_chunk();
@@ -229,11 +233,12 @@ struct DenseCol {
   }
 };
 
-// Exact quotient of n by div: n * ceil(2^32 / div) >> 32 for every n with n * div < 2^32
+// Quotient and remainder by a divisor known on the host: n * ceil(2^32 / div) >> 32 is exact for every n with
+// n * div < 2^32; mul = 0 where that does not cover the range (or div is 1): a division.
 struct FastDiv {
   uint32_t mul, div;
   __device__ __forceinline__ void get(int n, int& q, int& r) const {
-    q = div == 1 ? n : (int)__umulhi((uint32_t)n, mul);
+    q = mul ? (int)__umulhi((uint32_t)n, mul) : n / (int)div;
     r = n - q * (int)div;
   }
 };
@@ -254,42 +259,63 @@ struct GatherRow {
   using Desc = GatherRowDesc;
   using Spot = RowSpot<T, R, NW, VEC>;
   static constexpr int kPerWave = Spot::kPerWave;
+  // A lane's copies lie in rows that are NW * 8 (or, word by word, NW * 2) apart, so with the swizzle repeating every 16
+  // rows they have one k value (two) between them: the division into tap and channel is done once per tile and value.
+  static constexpr int kKinds = VEC == 1 ? 2 : 1;
+  static_assert(NW % 4 == 0, "which copies share a k value");
   Desc d;
-  int img[kPerWave], hw[kPerWave], k[kPerWave];
+  const T* image[kPerWave];
+  int hw[kPerWave], k[kKinds];
   __device__ __forceinline__ void init(const Desc& desc, int r0, int wave, int lane) {
     d = desc;
 #pragma unroll
     for (int t = 0; t < kPerWave; ++t) {
-      int r;
-      Spot::at(t, wave, lane, r, k[t]);
+      int r, kt;
+      Spot::at(t, wave, lane, r, kt);
+      if (t < kKinds) k[t] = kt;
       const int p = min(r0 + r, d.rows - 1);
-      const int q = p / d.W, w = p - q * d.W;
-      img[t] = q / d.H;
-      const int h = q - img[t] * d.H;
+      const int q = p / d.W, w = p - q * d.W, img = q / d.H, h = q - img * d.H;
+      image[t] = (const T*)d.base + (size_t)img * d.SH * d.SW * d.C;
       hw[t] = DX ? (h + d.Pd) << 16 | (w + d.Pd) : (h * d.S) << 16 | (w * d.S);
     }
   }
-  __device__ __forceinline__ const void* source(int t, int tile) const {
-    int tap, c, kh, kw;
-    const int kk = tile * kTileK<T> + k[t];
-    d.by_c.get(kk, tap, c);
-    d.by_r.get(tap, kh, kw);
+  struct Tile {
+    int kh[kKinds], kw[kKinds], c[kKinds];  // kh: out of every image where the k value is past the end
+  };
+  __device__ __forceinline__ Tile tile(int tile) const {
+    Tile o;
+#pragma unroll
+    for (int i = 0; i < kKinds; ++i) {
+      int tap;
+      const int kk = tile * kTileK<T> + k[i];
+      d.by_c.get(kk, tap, o.c[i]);
+      d.by_r.get(tap, o.kh[i], o.kw[i]);
+      if (!DX) {
+        o.kh[i] -= d.Pd;
+        o.kw[i] -= d.Pd;
+      }
+      if (kk >= d.K) o.kh[i] = 1 << 20;
+    }
+    return o;
+  }
+  __device__ __forceinline__ const void* source(int t, const Tile& o) const {
+    const int i = t % kKinds;
     int sh, sw;
-    bool ok = kk < d.K;
+    bool ok = true;
     if (DX) {
-      sh = (hw[t] >> 16) - kh;
-      sw = (hw[t] & 0xffff) - kw;
+      sh = (hw[t] >> 16) - o.kh[i];
+      sw = (hw[t] & 0xffff) - o.kw[i];
       if (d.S == 2) {
-        ok = ok && !((sh | sw) & 1);
+        ok = !((sh | sw) & 1);
         sh >>= 1;
         sw >>= 1;
       }
     } else {
-      sh = (hw[t] >> 16) + kh - d.Pd;
-      sw = (hw[t] & 0xffff) + kw - d.Pd;
+      sh = (hw[t] >> 16) + o.kh[i];
+      sw = (hw[t] & 0xffff) + o.kw[i];
     }
     ok = ok && (unsigned)sh < (unsigned)d.SH && (unsigned)sw < (unsigned)d.SW;
-    return ok ? (const char*)((const T*)d.base + ((size_t)(img[t] * d.SH + sh) * d.SW + sw) * d.C + c) : zero_chunk();
+    return ok ? (const char*)(image[t] + (uint32_t)((sh * d.SW + sw) * d.C + o.c[i])) : zero_chunk();
   }
   static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
     return row_frag<T, R>(lds, rbase, step, lane);
@@ -319,6 +345,8 @@ struct WeightCol {
       n[t] = min(r0 + r, d.cin - VEC);
     }
   }
+  using Tile = int;
+  __device__ __forceinline__ Tile tile(int tile) const { return tile; }
   __device__ __forceinline__ const void* source(int t, int tile) const {
     int tap, co;
     d.by_cout.get(tile * kTileK<T> + k[t], tap, co);
@@ -332,10 +360,9 @@ struct WeightCol {
 // The input as the weight gradient reads it: row n = (tap, input channel), k = output pixel.
 struct GatherColDesc {
   const void* base;  // [imgs][SH][SW][C]
-  int H, W;          // output grid
   int SH, SW, C, K;  // K: output pixels
   int S, Pd, N;      // N: taps * C
-  FastDiv by_c, by_r;
+  FastDiv by_c, by_r, by_w, by_h;  // by_w, by_h: the output grid
 };
 template <class T, int R, int NW, int VEC>
 struct GatherCol {
@@ -356,12 +383,15 @@ struct GatherCol {
       dw[t] = kw - d.Pd;
     }
   }
+  using Tile = int;
+  __device__ __forceinline__ Tile tile(int tile) const { return tile; }
   __device__ __forceinline__ const void* source(int t, int tile) const {
-    const uint32_t p = (uint32_t)tile * kTileK<T> + k[t];
-    const uint32_t q = p / (uint32_t)d.W, w = p - q * d.W;
-    const uint32_t img = q / (uint32_t)d.H, h = q - img * d.H;
-    const int sh = (int)h * d.S + dh[t], sw = (int)w * d.S + dw[t];
-    const bool ok = p < (uint32_t)d.K && (unsigned)sh < (unsigned)d.SH && (unsigned)sw < (unsigned)d.SW;
+    const int p = tile * kTileK<T> + k[t];
+    int q, img, h, w;
+    d.by_w.get(p, q, w);
+    d.by_h.get(q, img, h);
+    const int sh = h * d.S + dh[t], sw = w * d.S + dw[t];
+    const bool ok = p < d.K && (unsigned)sh < (unsigned)d.SH && (unsigned)sw < (unsigned)d.SW;
     return ok ? (const char*)((const T*)d.base + ((size_t)(img * d.SH + sh) * d.SW + sw) * d.C + c[t]) : zero_chunk();
   }
   static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
@@ -489,12 +519,14 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_any_kernel(int M, in
     for (int u = 0; u < U; ++u) {
       const int t = min(tile + u, last);
       const uint32_t dst = lds_base + (stage * U + u) * kStage;
+      const typename AL::Tile at = a.tile(t);
+      const typename BL::Tile bt = b.tile(t);
 #pragma unroll
       for (int q = 0; q < AL::kPerWave; ++q)
-        dma_addr<AL::Spot::kPieceBytes>(dst + (wave + NW * q) * 64 * AL::Spot::kPieceBytes, a.source(q, t));
+        dma_addr<AL::Spot::kPieceBytes>(dst + (wave + NW * q) * 64 * AL::Spot::kPieceBytes, a.source(q, at));
 #pragma unroll
       for (int q = 0; q < BL::kPerWave; ++q)
-        dma_addr<BL::Spot::kPieceBytes>(dst + kABytes + (wave + NW * q) * 64 * BL::Spot::kPieceBytes, b.source(q, t));
+        dma_addr<BL::Spot::kPieceBytes>(dst + kABytes + (wave + NW * q) * 64 * BL::Spot::kPieceBytes, b.source(q, bt));
     }
   };
 #pragma unroll
@@ -582,40 +614,64 @@ hipError_t launch_any(hipStream_t s, int M, int N, int KT, int splits, const typ
   return hipGetLastError();
 }
 
-enum class Tile { k32, k64, k128 };
-inline int tile_edge(Tile t) { return t == Tile::k32 ? 32 : t == Tile::k64 ? 64 : 128; }
-inline long blocks_of(Tile t, int M, int N) {
-  const int e = tile_edge(t);
-  return (long)((M + e - 1) / e) * ((N + e - 1) / e);
-}
-
-// The tile with the least (rounds of 256 workgroups) x (time of one), a larger tile being up to this much faster per
-// output (operand traffic, barriers); 32 x 32 is there to spread small outputs over the chip.
-inline Tile pick_tile(int M, int N) {
-  struct { Tile t; int rate; } const cand[] = {{Tile::k128, 100}, {Tile::k64, 90}, {Tile::k32, 55}};
-  Tile best = Tile::k32;
-  double best_cost = -1;
-  for (const auto& c : cand) {
-    const long e = tile_edge(c.t);
-    const double cost = (double)((blocks_of(c.t, M, N) + 255) / 256) * e * e / c.rate;
-    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = c.t; }
-  }
-  return best;
-}
+// The tiles, and the time of one k tile on a CU that holds one workgroup (t1) and two (t2), in ns; the wide fp32 tile
+// and 128 x 128 leave room for one.  fp32 products are bound by the matrix cores where the output fills the chip and by
+// the chain barrier -> LDS reads -> MFMAs of a single workgroup where it does not; bf16 ones (convolutions) by the
+// address arithmetic of the copies and that chain.  Hence two groups of waves per workgroup on the small tiles and eight
+// waves on the large ones.  Measured (us): fp32 dense 128 x 1024 x 1024 9.9 (32 x 32) / 26 / 80, 2048^3 195 / 157 /
+// 152 (113 TFLOP/s), 32 x 512 x 512 6.5 -- the fp32 FMA kernel before: 160, -, 45.  fp32 3x3, 16 images of 32 x 32, 64
+// channels, forward / dx / dW: 64 x 64 on one group of waves with four stages 21.5 / 21.7 / 22.2, on two groups with two
+// stages 18.9 / 18.7 / 16.9 (FMA kernel 300 / 230 / 72).  bf16 3x3, 44 images of 64 x 64, 48 channels, forward: 64 x 64
+// 35.2, 128 x 64 26.3, 128 x 128 49.8 (FMA kernel 400).
+enum class Tile { k32, k64, k128x64, k128 };
+struct TileCost {
+  Tile t;
+  int bm, bn, t1, t2;
+};
+constexpr TileCost kTilesF32[] = {{Tile::k32, 32, 32, 300, 400}, {Tile::k64, 64, 64, 880, 1220}, {Tile::k128, 128, 128, 2300, 4600}};
+constexpr TileCost kTilesBf16[] = {{Tile::k32, 32, 32, 200, 300}, {Tile::k64, 64, 64, 350, 550}, {Tile::k128x64, 128, 64, 580, 950},
+                                   {Tile::k128, 128, 128, 850, 1700}};
 
 // Contraction ranges of a product whose output has too few tiles for the chip (weight gradients): as many as give every
 // CU a workgroup, each at least 8 k tiles long, and none of them empty.
 inline int any_splits(long blocks, int KT) {
-  long s = std::min<long>(256 / std::max<long>(blocks, 1), KT / 8);
+  const long s = std::min<long>(256 / std::max<long>(blocks, 1), KT / 8);
   if (s <= 1) return 1;
   const int per = (int)((KT + s - 1) / s);
   return (KT + per - 1) / per;
 }
 
+// The tile with the least time for all its workgroups on 256 CUs.  split: the contraction may be cut into ranges, so that
+// a long one fills the chip with large tiles too; `ranges` receives their number.
+template <class T>
+Tile pick_tile(int M, int N, int KT, bool split, int* ranges) {
+  Tile best = Tile::k32;
+  double best_cost = -1;
+  auto consider = [&](const TileCost& c) {
+    const long blocks = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    const int r = split ? any_splits(blocks, KT) : 1;
+    const long all = blocks * r, rest = all % 512;
+    const double cost = ((double)(all / 512) * c.t2 + (rest == 0 ? 0 : rest <= 256 ? c.t1 : c.t2)) * ((KT + r - 1) / r);
+    if (best_cost < 0 || cost < best_cost) {
+      best_cost = cost;
+      best = c.t;
+      *ranges = r;
+    }
+  };
+  if constexpr (sizeof(T) == 4)
+    for (const TileCost& c : kTilesF32) consider(c);
+  else
+    for (const TileCost& c : kTilesBf16) consider(c);
+  return best;
+}
+
 inline bool aligned16(const void* a, const void* b = nullptr, const void* c = nullptr) {
   return (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15) == 0;
 }
-inline FastDiv fast_div(int d) { return FastDiv{d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d), (uint32_t)d}; }
+// a divisor of numbers up to `limit`
+inline FastDiv fast_div(int d, long limit) {
+  return FastDiv{d == 1 || limit * d >= (1l << 32) ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d), (uint32_t)d};
+}
 
 // Loader class templates with the element type and vector width filled in per product
 template <class T, int VEC> struct FpropDense {
@@ -643,24 +699,28 @@ template <class T, int VEC> struct WgradConv {
   template <int R, int NW> using B = GatherCol<T, R, NW, VEC>;
 };
 
-// The tiles.  fp32 products are bound by the matrix cores where the output fills the chip (157 TFLOP/s nominal; four
-// waves, operand traffic of a 64 x 64 tile is 16 bytes per clock and CU) and by the chain barrier -> LDS reads -> MFMAs
-// of a single workgroup where it does not.  So: 128 x 128, three stages (96 KB); 64 x 64, four stages (64 KB, two
-// workgroups on a CU); and 32 x 32 on two groups of waves with two k tiles between barriers (64 KB).  Measured in fp32,
-// 32 / 64 / 128 tile, forward: 128 x 1024 x 1024 9.9 / 26 / 80 us, 1024^3 29 / 27 / 80 us, 2048^3 195 / 157 / 152 us
-// (113 TFLOP/s); 32 x 512 x 512 6.5 us.  (The fp32 FMA kernel before: 160 us, 140 us, -, 45 us.)  The 32 x 32 tile on
-// one group of waves with eight stages: 12.8 us at 128 x 1024 x 1024; on four groups 10.3 us.
 template <class T, class P, class AD, class BD, class Epi>
-hipError_t run(hipStream_t s, int M, int N, int K, const AD& ad, const BD& bd, const Epi& epi, int splits = 1) {
+hipError_t run(hipStream_t s, int M, int N, int K, const AD& ad, const BD& bd, const Epi& epi, bool split = false) {
   const int KT = (K + kTileK<T> - 1) / kTileK<T>;
-  switch (pick_tile(M, N)) {
-    case Tile::k128:
-      return launch_any<T, 128, 128, 2, 2, 3, 1, 1, typename P::template A<128, 4>, typename P::template B<128, 4>>(s, M, N, KT, splits, ad, bd, epi);
-    case Tile::k64:
-      return launch_any<T, 64, 64, 2, 2, 4, 1, 1, typename P::template A<64, 4>, typename P::template B<64, 4>>(s, M, N, KT, splits, ad, bd, epi);
-    default:
-      return launch_any<T, 32, 32, 2, 2, 2, 2, 2, typename P::template A<32, 4>, typename P::template B<32, 4>>(s, M, N, KT, splits, ad, bd, epi);
+  int ranges = 1;
+#define TP_ANY(BM, BN, WGM, WGN, NS, KG, U)                                                                              \
+  launch_any<T, BM, BN, WGM, WGN, NS, KG, U, typename P::template A<BM, WGM * WGN>, typename P::template B<BN, WGM * WGN>>( \
+      s, M, N, KT, ranges, ad, bd, epi)
+  switch (pick_tile<T>(M, N, KT, split, &ranges)) {
+    case Tile::k128: return TP_ANY(128, 128, 4, 2, 3, 1, 1);
+    case Tile::k128x64:
+      if constexpr (sizeof(T) == 2) return TP_ANY(128, 64, 4, 2, 3, 1, 1);
+      [[fallthrough]];  // not among the fp32 tiles
+    case Tile::k64: return TP_ANY(64, 64, 2, 2, 2, 2, 1);
+    default: return TP_ANY(32, 32, 2, 2, 2, 2, 2);
   }
+#undef TP_ANY
+}
+template <class T>
+int ranges_of(int M, int N, int K) {
+  int ranges = 1;
+  pick_tile<T>(M, N, (K + kTileK<T> - 1) / kTileK<T>, true, &ranges);
+  return ranges;
 }
 
 }  // namespace
@@ -683,17 +743,18 @@ hipError_t f32_dgrad(hipStream_t s, int M, int N, int K, const float* dz, const 
   return run<float, DgradDense<float, 1>>(s, M, K, N, a, b, e);
 }
 
-int f32_wgrad_splits(int M, int N, int K) { return any_splits(blocks_of(pick_tile(N, K), N, K), (M + 31) / 32); }
+int f32_wgrad_splits(int M, int N, int K) { return ranges_of<float>(N, K, M); }
 
 hipError_t f32_wgrad(hipStream_t s, int M, int N, int K, const float* dz, const float* x, float* gW, float* partial) {
   // gW[N x K] = dz^T[N x M] . x[M x K]: contraction over M
-  const int splits = partial ? f32_wgrad_splits(M, N, K) : 1;
+  const bool split = partial != nullptr;
+  const int splits = split ? f32_wgrad_splits(M, N, K) : 1;
   const DenseDesc a{dz, N, N, M}, b{x, K, K, M};
   float* out = splits > 1 ? partial : gW;
   const EpiPartial e{out, K, K % 4 == 0 && aligned16(out), (size_t)N * K};
   const hipError_t err = N % 4 == 0 && K % 4 == 0 && aligned16(dz, x)
-                             ? run<float, WgradDense<float, 4>>(s, N, K, M, a, b, e, splits)
-                             : run<float, WgradDense<float, 1>>(s, N, K, M, a, b, e, splits);
+                             ? run<float, WgradDense<float, 4>>(s, N, K, M, a, b, e, split)
+                             : run<float, WgradDense<float, 1>>(s, N, K, M, a, b, e, split);
   if (err != hipSuccess || splits == 1) return err;
   return launch_sum_partials(s, (size_t)N * K, splits, partial, gW);
 }
@@ -701,17 +762,16 @@ hipError_t f32_wgrad(hipStream_t s, int M, int N, int K, const float* dz, const 
 // ---- convolutions ------------------------------------------------------------------------------
 bool conv_any_supported(int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout) {
   const long taps = (long)ksize * ksize, pin = (long)imgs * H * W;
-  const long c = std::max(cin, cout);
-  // image edges fit 15 bits, pixel numbers 30, and every k value (up to a tile past the end) has an exact quotient by the
-  // channel count
-  return H + ksize < 32768 && W + ksize < 32768 && pin < (1l << 30) && (taps * c + 64) * c < (1l << 32) &&
+  // image edges fit 15 bits; pixel numbers, k values and offsets inside an image 31
+  return H + ksize < 32768 && W + ksize < 32768 && pin < (1l << 30) && taps * std::max(cin, cout) < (1l << 30) &&
+         (long)H * W * std::max(cin, cout) < (1l << 31) &&
          (elt == ELT_F32 || (cin % 8 == 0 && cout % 8 == 0));
 }
 
 hipError_t conv_any_fprop(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout, const void* x,
                           const void* wgt, const float* bias, int act, void* d_out, void* a_out) {
   const int Ho = H / stride, Wo = W / stride, P = imgs * Ho * Wo, K = ksize * ksize * cin;
-  const GatherRowDesc a{x, P, Ho, Wo, H, W, cin, K, stride, (ksize - 1) / 2, fast_div(cin), fast_div(ksize)};
+  const GatherRowDesc a{x, P, Ho, Wo, H, W, cin, K, stride, (ksize - 1) / 2, fast_div(cin, K + 64), fast_div(ksize, K + 64)};
   const DenseDesc b{wgt, K, cout, K};
   const bool vec = aligned16(x, wgt);
   if (elt == ELT_BF16) {
@@ -726,8 +786,8 @@ hipError_t conv_any_fprop(hipStream_t s, int elt, int imgs, int H, int W, int ks
 hipError_t conv_any_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout, const void* dz,
                           const void* wb, const void* d_prev, void* out, int relu_mask) {
   const int taps = ksize * ksize, P = imgs * H * W, K = taps * cout;
-  const GatherRowDesc a{dz, P, H, W, H / stride, W / stride, cout, K, stride, (ksize - 1) / 2, fast_div(cout), fast_div(ksize)};
-  const WeightColDesc b{wb, cin, taps, cout, fast_div(cout)};
+  const GatherRowDesc a{dz, P, H, W, H / stride, W / stride, cout, K, stride, (ksize - 1) / 2, fast_div(cout, K + 64), fast_div(ksize, K + 64)};
+  const WeightColDesc b{wb, cin, taps, cout, fast_div(cout, K + 64)};
   const bool vec = aligned16(dz, wb);
   if (elt == ELT_BF16) {
     if (!vec) return hipErrorNotSupported;
@@ -739,8 +799,8 @@ hipError_t conv_any_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int ks
 }
 
 int conv_any_wgrad_splits(int elt, int pixels, int cin, int cout, int ksize) {
-  const int N = ksize * ksize * cin, tile_k = elt == ELT_BF16 ? kTileK<uint16_t> : kTileK<float>;
-  return any_splits(blocks_of(pick_tile(cout, N), cout, N), (pixels + tile_k - 1) / tile_k);
+  const int N = ksize * ksize * cin;
+  return elt == ELT_BF16 ? ranges_of<uint16_t>(cout, N, pixels) : ranges_of<float>(cout, N, pixels);
 }
 
 hipError_t conv_any_wgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout, const void* dz,
@@ -748,18 +808,18 @@ hipError_t conv_any_wgrad(hipStream_t s, int elt, int imgs, int H, int W, int ks
   const int Ho = H / stride, Wo = W / stride, P = imgs * Ho * Wo, N = ksize * ksize * cin;
   const int splits = conv_any_wgrad_splits(elt, P, cin, cout, ksize);
   const DenseDesc a{dz, cout, cout, P};
-  const GatherColDesc b{x, Ho, Wo, H, W, cin, P, stride, (ksize - 1) / 2, N, fast_div(cin), fast_div(ksize)};
+  const GatherColDesc b{x, H, W, cin, P, stride, (ksize - 1) / 2, N, fast_div(cin, N), fast_div(ksize, N), fast_div(Wo, P + 64), fast_div(Ho, P + 64)};
   float* out = splits > 1 ? partial : gW;
   const EpiPartial e{out, N, N % 4 == 0 && aligned16(out), (size_t)cout * N};
   const bool vec = aligned16(dz, x);
   hipError_t err;
   if (elt == ELT_BF16) {
     if (!vec) return hipErrorNotSupported;
-    err = run<uint16_t, WgradConv<uint16_t, 8>>(s, cout, N, P, a, b, e, splits);
+    err = run<uint16_t, WgradConv<uint16_t, 8>>(s, cout, N, P, a, b, e, true);
   } else if (cin % 4 == 0 && cout % 4 == 0 && vec) {
-    err = run<float, WgradConv<float, 4>>(s, cout, N, P, a, b, e, splits);
+    err = run<float, WgradConv<float, 4>>(s, cout, N, P, a, b, e, true);
   } else {
-    err = run<float, WgradConv<float, 1>>(s, cout, N, P, a, b, e, splits);
+    err = run<float, WgradConv<float, 1>>(s, cout, N, P, a, b, e, true);
   }
   if (err != hipSuccess || splits == 1) return err;
   return launch_sum_partials(s, (size_t)cout * N, splits, partial, gW);

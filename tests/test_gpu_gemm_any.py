@@ -50,3 +50,46 @@ def test_dense_fp32(rows, fin, fout):
     assert _rel(dx, dy64 @ W64) <= _sum_tol(fout)
     assert _rel(gw, dy64.T @ x64) <= _sum_tol(rows)
     assert _rel(gb, dy64.sum(0)) <= _sum_tol(rows)
+
+
+def _conv_reference(x, W, b, dy, stride):
+    """fp64 convolution and its gradients (torch on the CPU); NHWC tensors."""
+    import torch
+    xt = torch.from_numpy(x.astype(np.float64)).permute(0, 3, 1, 2).requires_grad_(True)
+    Wt = torch.from_numpy(W.astype(np.float64)).permute(0, 3, 1, 2).requires_grad_(True)
+    y = torch.nn.functional.conv2d(xt, Wt, torch.from_numpy(b.astype(np.float64)), stride=stride, padding=(W.shape[1] - 1) // 2)
+    y.backward(torch.from_numpy(dy.astype(np.float64)).permute(0, 3, 1, 2))
+    back = lambda t: t.detach().permute(0, 2, 3, 1).numpy()
+    return back(y), back(xt.grad), back(Wt.grad)
+
+
+@pytest.mark.parametrize("dtype,imgs,H,W,cin,cout,k,stride", [
+    ("f32", 2, 5, 7, 3, 6, 3, 1),         # words, 32 x 32 tiles, every border
+    ("f32", 3, 6, 10, 4, 12, 5, 2),       # 16-byte chunks that straddle taps inside a k tile, stride 2
+    ("f32", 1, 4, 4, 20, 8, 1, 1),        # 1x1: the division by a kernel edge of one
+    ("f32", 40, 24, 24, 68, 64, 3, 1),    # 64 x 64 tiles, weight gradient over many ranges
+    ("f32", 150, 16, 16, 128, 132, 3, 1), # 128 x 128 tiles
+    ("bf16", 2, 6, 5, 8, 16, 3, 1),       # 32 x 32 tiles, image sizes that are no powers of two
+    ("bf16", 3, 12, 20, 24, 40, 7, 2),
+    ("bf16", 40, 24, 24, 64, 72, 3, 1),   # 64 x 64
+    ("bf16", 90, 28, 28, 48, 56, 3, 1),   # 128 x 64
+    ("bf16", 180, 20, 20, 96, 128, 5, 1), # 128 x 128
+])
+def test_convolution(dtype, imgs, H, W, cin, cout, k, stride):
+    from synth_inputs import round_bf16
+    rng = np.random.default_rng(imgs * H + k)
+    cast = round_bf16 if dtype == "bf16" else (lambda t: t.astype(np.float32))
+    wgt = cast(rng.standard_normal((cout, k, k, cin)) / np.sqrt(k * k * cin)).astype(np.float32)
+    b = rng.standard_normal(cout).astype(np.float32)
+    x = cast(rng.standard_normal((imgs, H, W, cin))).astype(np.float32)
+    dy = cast(rng.standard_normal((imgs, H // stride, W // stride, cout))).astype(np.float32)
+    y, dx, (gw, gb) = _run(_stage(("conv", cin, cout, H, W, "none", stride, k), [wgt, b], imgs, dtype),
+                           x.reshape(imgs, -1), dy.reshape(imgs, -1))
+    ry, rdx, rgw = _conv_reference(x, wgt, b, dy, stride)
+    # bf16: products of bf16 values are exact in fp32, the sums are fp32, the stored result is rounded once (2^-9 of it)
+    store = 2.0 ** -9 if dtype == "bf16" else 0.0
+    pixels = imgs * (H // stride) * (W // stride)
+    assert _rel(y.reshape(ry.shape), ry) <= _sum_tol(k * k * cin) + store
+    assert _rel(dx.reshape(rdx.shape), rdx) <= _sum_tol(k * k * cout) + store
+    assert _rel(gw, rgw) <= _sum_tol(pixels)
+    assert _rel(gb, dy.astype(np.float64).sum((0, 1, 2))) <= _sum_tol(pixels)
