@@ -1,17 +1,19 @@
-// Matrix-core GEMMs for whatever the tuned bf16 kernels do not take: every product of the fp32 mode
-// (v_mfma_f32_16x16x4_f32: fp32 operands, fp32 accumulation), dense and convolution, and the bf16 convolutions of
-// any kernel size, image size and channel count that is a multiple of 8 (v_mfma_f32_16x16x32_bf16).
+// Matrix-core GEMMs for whatever the tuned bf16 kernels do not take: every product of the fp32 mode, dense and
+// convolution, and the bf16 convolutions of any kernel size, image size and channel count that is a multiple of 8.
+//
+// Forward products and input gradients keep the arithmetic of a plain fp32 loop: every output is ONE chain of fused
+// multiply-adds over the contraction index in ascending order (v_mfma_f32_16x16x4_f32 adds its four products one after
+// the other, lowest k first, rounding each time -- checked against fmaf bit for bit).  What feeds a ReLU or a pooling is
+// therefore the same to the last bit whatever tile it was formed in, and the same as the bounds-checked FMA kernels of
+// kernels_gemm.hip and kernels_conv.hip give.  bf16 operands are widened on their way out of LDS.  Weight gradients are
+// sums over thousands of rows and feed no decision: they may be formed over several row ranges, in bf16 with
+// v_mfma_f32_16x16x32_bf16.
 //
 // One kernel template; what differs between the products is where the 16-byte chunks of an operand's k tile come from
 // (the loaders below).  A k tile is 128 bytes of the contraction index per row: 32 fp32 or 64 bf16 values.  Copies go
-// global -> LDS without registers, NS stages deep, each lane with an address of its own: positions outside the image
-// and k values past the end of the contraction read a block of zeros, rows past the edge repeat the last row (computed,
-// never stored).  fp32 operands whose rows are no whole 16-byte units are copied word by word (VEC = 1).
-//
-// The MFMA takes one k value per lane and operand in fp32; which four k values a step's lanes hold is free as long as
-// both operands agree.  Lane (i, g) = (lane % 16, lane / 16) holds chunk 4 s + g of row i in step s, so an operand that
-// lies k-contiguous is read with one 16-byte LDS read per step and its four words feed four MFMAs; the bf16 MFMA wants
-// exactly that chunk.
+// global -> LDS without registers, each lane with an address of its own: positions outside the image and k values past
+// the end of the contraction read a block of zeros, rows past the edge repeat the last row (computed, never stored).
+// fp32 operands whose rows are no whole 16-byte units are copied word by word (VEC = 1).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -61,81 +63,90 @@ struct Elem<uint16_t> {
 template <class T>
 constexpr int kTileK = 8 * Elem<T>::kChunk;  // k values of one stage
 
-template <class T, int R>
+// How a product is summed: Chain = one fp32 chain per output in ascending k, Free = bf16 matrix instructions
+struct Chain {};
+struct Free {};
+
+template <class T, class Sum, int R>
 __device__ __forceinline__ int col_swizzle(int k) {
-  constexpr int row_bytes = R * (int)sizeof(T);
-  if constexpr (sizeof(T) == 4) {  // a read: one word of rows k = 16 s + 4 g + j, g = 0 .. 3
-    if constexpr (row_bytes >= 256) return 4 * ((k >> 2) & 3);
-    else return 4 * ((k >> 2) & 1);
-  } else {  // a read: rows 32 s + 8 g + 0 .. 3, 32 bytes each; half a wave (two values of g) at a time
-    constexpr int chunks = row_bytes / 16;
+  constexpr int chunks = R * (int)sizeof(T) / 16;  // per k row
+  if constexpr (sizeof(T) == 4) {  // a read: 64 bytes of rows 4 m + g, g = 0 .. 3
+    return chunks >= 16 ? 4 * (k & 3) : 4 * ((k >> 1) & 1);
+  } else if constexpr (__is_same(Sum, Chain)) {  // 32 bytes of rows 4 m + g
+    return chunks >= 16 ? 2 * (k & 3) : chunks >= 8 ? 2 * ((k >> 1) & 1) : 0;
+  } else {  // 32 bytes of rows 32 s + 8 g + 0 .. 3; half a wave (two values of g) at a time
     const int hi = 2 * ((k >> 3) & 1);
-    if constexpr (chunks >= 16) return (4 * (k & 3)) ^ hi;
-    else if constexpr (chunks >= 8) return (4 * ((k >> 1) & 1)) ^ hi;
-    else return hi;
+    return chunks >= 16 ? (4 * (k & 3)) ^ hi : chunks >= 8 ? (4 * ((k >> 1) & 1)) ^ hi : hi;
   }
 }
 
-// What both sides of the MFMA need for one step: four fp32 words or eight bf16 values per lane
-template <class T>
+// What one side of the matrix instructions needs for a step of 32 k values.  Lane (i, g) = (lane % 16, lane / 16) holds
+//   Chain: k = 4 m + g of row i for m = 0 .. 7 (instruction m covers 4 m .. 4 m + 3);  Free: k = 8 g .. 8 g + 7 of row i.
+template <class Sum>
 struct Frag;
 template <>
-struct Frag<float> {
-  float v[4];
+struct Frag<Chain> {
+  float v[8];
 };
 template <>
-struct Frag<uint16_t> {
+struct Frag<Free> {
   bf16x8 v;
 };
+template <class T>
+constexpr int kSteps = kTileK<T> / 32;
 
-template <class T, int R>
-__device__ __forceinline__ Frag<T> row_frag(const char* lds, int rbase, int step, int lane) {
-  const int r = rbase + (lane & 15);
-  const int c = (4 * step + (lane >> 4)) ^ ((r >> 1) & 7);
-  const uint4 u = *reinterpret_cast<const uint4*>(lds + r * 128 + c * 16);
-  return __builtin_bit_cast(Frag<T>, u);
+template <class T, class Sum, int R>
+__device__ __forceinline__ Frag<Sum> row_frag(const char* lds, int rbase, int step, int lane) {
+  const int r = rbase + (lane & 15), g = lane >> 4;
+  const char* row = lds + r * 128;
+  const int swz = (r >> 1) & 7;
+  Frag<Sum> f;
+  if constexpr (__is_same(Sum, Free)) {
+    f.v = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(row + (((4 * step + g) ^ swz) << 4)));
+  } else if constexpr (sizeof(T) == 4) {
+#pragma unroll
+    for (int m = 0; m < 8; ++m) f.v[m] = *reinterpret_cast<const float*>(row + ((m ^ swz) << 4) + 4 * g);
+  } else {
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+      f.v[m] = bf16_to_float(*reinterpret_cast<const uint16_t*>(row + (((4 * step + (m >> 1)) ^ swz) << 4) + 8 * (m & 1) + 2 * g));
+  }
+  return f;
 }
 
-template <class T, int R>
-__device__ __forceinline__ Frag<T> col_frag(const char* lds, int rbase, int step, int lane) {
+template <class T, class Sum, int R>
+__device__ __forceinline__ Frag<Sum> col_frag(const char* lds, int rbase, int step, int lane) {
   const int i = lane & 15, g = lane >> 4;
-  if constexpr (sizeof(T) == 4) {
-    Frag<T> f;
-    const int r = rbase + i;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = 16 * step + 4 * g + j;
-      f.v[j] = *reinterpret_cast<const float*>(lds + k * (R * 4) + ((r >> 2) ^ col_swizzle<T, R>(k)) * 16 + (r & 3) * 4);
-    }
-    return f;
-  } else {
+  Frag<Sum> f;
+  if constexpr (__is_same(Sum, Free)) {
     // ds_read_b64_tr_b16: lane s of a group of 16 points at 4 consecutive values of k row k0 + s/4 and receives rows
     // k0 .. k0+3 of column c0 + s
     const int k = 32 * step + 8 * g + (i >> 2);
     const int col = rbase + 4 * (i & 3);
     typedef __attribute__((address_space(3))) shortx4* lds_ptr;
-    const char* lo = lds + k * (R * 2) + ((col >> 3) ^ col_swizzle<T, R>(k)) * 16 + (col & 7) * 2;
+    const char* lo = lds + k * (R * 2) + ((col >> 3) ^ col_swizzle<T, Sum, R>(k)) * 16 + (col & 7) * 2;
     const char* hi = lo + 4 * (R * 2);  // k + 4: the same swizzle
     const shortx4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(lo));
     const shortx4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(hi));
-    Frag<T> f;
     f.v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
-    return f;
+  } else {
+    constexpr int C = Elem<T>::kChunk;
+    const int r = rbase + i;
+    const char* at = lds + g * (R * (int)sizeof(T)) + ((r / C) ^ col_swizzle<T, Sum, R>(g)) * 16 + (r % C) * (int)sizeof(T);
+#pragma unroll
+    for (int m = 0; m < 8; ++m)  // k = 32 step + 4 m + g: the swizzle depends on g alone
+      f.v[m] = to_float(*reinterpret_cast<const T*>(at + (32 * step + 4 * m) * (R * (int)sizeof(T))));
   }
+  return f;
 }
 
-// acc += (A . B^T of one step), transposed: register r of a lane is column 4 (lane / 16) + r of row lane % 16.
-// CH chains: an fp32 sum is kept in CH = 4 parts, one per word of the chunk, where the registers allow it (small wave
-// tiles), and added up at the end -- a quarter of the rounding steps in every chain (half the error of one long chain,
-// measured 4.1e-7 -> 2.1e-7 at K = 512) and four independent MFMAs in a row.
-template <int CH>
-__device__ __forceinline__ void multiply(const Frag<float>& a, const Frag<float>& b, floatx4 (&acc)[CH]) {
+// acc += (A . B^T of one step), transposed: register r of a lane is column 4 (lane / 16) + r of row lane % 16
+__device__ __forceinline__ void multiply(const Frag<Chain>& a, const Frag<Chain>& b, floatx4& acc) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) acc[j % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.v[j], a.v[j], acc[j % CH], 0, 0, 0);
+  for (int m = 0; m < 8; ++m) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(b.v[m], a.v[m], acc, 0, 0, 0);
 }
-template <int CH>
-__device__ __forceinline__ void multiply(const Frag<uint16_t>& a, const Frag<uint16_t>& b, floatx4 (&acc)[CH]) {
-  acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.v, a.v, acc[0], 0, 0, 0);
+__device__ __forceinline__ void multiply(const Frag<Free>& a, const Frag<Free>& b, floatx4& acc) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.v, a.v, acc, 0, 0, 0);
 }
 
 // ---- loaders -----------------------------------------------------------------------------------
@@ -156,7 +167,7 @@ struct RowSpot {
     k = chunk * Elem<T>::kChunk + (byte & 15) / (int)sizeof(T);
   }
 };
-template <class T, int R, int NW, int VEC>
+template <class T, class Sum, int R, int NW, int VEC>
 struct ColSpot {
   static constexpr int kPieceBytes = VEC * (int)sizeof(T);
   static constexpr int kPerK = R / VEC;
@@ -167,7 +178,7 @@ struct ColSpot {
     const int flat = 64 * (wave + NW * t) + lane;
     k = flat / kPerK;
     const int byte = (flat % kPerK) * kPieceBytes;
-    const int chunk = (byte >> 4) ^ col_swizzle<T, R>(k);
+    const int chunk = (byte >> 4) ^ col_swizzle<T, Sum, R>(k);
     r = chunk * Elem<T>::kChunk + (byte & 15) / (int)sizeof(T);
   }
 };
@@ -178,7 +189,7 @@ struct DenseDesc {
   int ld, rows, K;  // K: extent of the contraction; k >= K reads zero
 };
 
-template <class T, int R, int NW, int VEC>
+template <class T, class Sum, int R, int NW, int VEC>
 struct DenseRow {
   using Desc = DenseDesc;
   using Spot = RowSpot<T, R, NW, VEC>;
@@ -200,15 +211,15 @@ struct DenseRow {
     const int k0 = tile * kTileK<T>;
     return k0 + k[t] < K ? (const char*)(p[t] + k0) : zero_chunk();
   }
-  static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
-    return row_frag<T, R>(lds, rbase, step, lane);
+  static __device__ __forceinline__ Frag<Sum> frag(const char* lds, int rbase, int step, int lane) {
+    return row_frag<T, Sum, R>(lds, rbase, step, lane);
   }
 };
 
-template <class T, int R, int NW, int VEC>
+template <class T, class Sum, int R, int NW, int VEC>
 struct DenseCol {
   using Desc = DenseDesc;
-  using Spot = ColSpot<T, R, NW, VEC>;
+  using Spot = ColSpot<T, Sum, R, NW, VEC>;
   static constexpr int kPerWave = Spot::kPerWave;
   const T* p[kPerWave];
   int k[kPerWave], K, ld;
@@ -228,8 +239,8 @@ struct DenseCol {
     const int k0 = tile * kTileK<T>;
     return k0 + k[t] < K ? (const char*)(p[t] + (size_t)k0 * ld) : zero_chunk();
   }
-  static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
-    return col_frag<T, R>(lds, rbase, step, lane);
+  static __device__ __forceinline__ Frag<Sum> frag(const char* lds, int rbase, int step, int lane) {
+    return col_frag<T, Sum, R>(lds, rbase, step, lane);
   }
 };
 
@@ -254,7 +265,7 @@ struct GatherRowDesc {
   int S, Pd;
   FastDiv by_c, by_r;
 };
-template <class T, int R, int NW, int VEC, bool DX>
+template <class T, class Sum, int R, int NW, int VEC, bool DX>
 struct GatherRow {
   using Desc = GatherRowDesc;
   using Spot = RowSpot<T, R, NW, VEC>;
@@ -317,8 +328,8 @@ struct GatherRow {
     ok = ok && (unsigned)sh < (unsigned)d.SH && (unsigned)sw < (unsigned)d.SW;
     return ok ? (const char*)(image[t] + (uint32_t)((sh * d.SW + sw) * d.C + o.c[i])) : zero_chunk();
   }
-  static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
-    return row_frag<T, R>(lds, rbase, step, lane);
+  static __device__ __forceinline__ Frag<Sum> frag(const char* lds, int rbase, int step, int lane) {
+    return row_frag<T, Sum, R>(lds, rbase, step, lane);
   }
 };
 
@@ -329,10 +340,10 @@ struct WeightColDesc {
   int cin, taps, cout;
   FastDiv by_cout;
 };
-template <class T, int R, int NW, int VEC>
+template <class T, class Sum, int R, int NW, int VEC>
 struct WeightCol {
   using Desc = WeightColDesc;
-  using Spot = ColSpot<T, R, NW, VEC>;
+  using Spot = ColSpot<T, Sum, R, NW, VEC>;
   static constexpr int kPerWave = Spot::kPerWave;
   Desc d;
   int n[kPerWave], k[kPerWave];
@@ -352,8 +363,8 @@ struct WeightCol {
     d.by_cout.get(tile * kTileK<T> + k[t], tap, co);
     return tap < d.taps ? (const char*)((const T*)d.base + ((size_t)co * d.taps + tap) * d.cin + n[t]) : zero_chunk();
   }
-  static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
-    return col_frag<T, R>(lds, rbase, step, lane);
+  static __device__ __forceinline__ Frag<Sum> frag(const char* lds, int rbase, int step, int lane) {
+    return col_frag<T, Sum, R>(lds, rbase, step, lane);
   }
 };
 
@@ -364,10 +375,10 @@ struct GatherColDesc {
   int S, Pd, N;      // N: taps * C
   FastDiv by_c, by_r, by_w, by_h;  // by_w, by_h: the output grid
 };
-template <class T, int R, int NW, int VEC>
+template <class T, class Sum, int R, int NW, int VEC>
 struct GatherCol {
   using Desc = GatherColDesc;
-  using Spot = ColSpot<T, R, NW, VEC>;
+  using Spot = ColSpot<T, Sum, R, NW, VEC>;
   static constexpr int kPerWave = Spot::kPerWave;
   Desc d;
   int c[kPerWave], dh[kPerWave], dw[kPerWave], k[kPerWave];
@@ -394,16 +405,22 @@ struct GatherCol {
     const bool ok = p < d.K && (unsigned)sh < (unsigned)d.SH && (unsigned)sw < (unsigned)d.SW;
     return ok ? (const char*)((const T*)d.base + ((size_t)(img * d.SH + sh) * d.SW + sw) * d.C + c[t]) : zero_chunk();
   }
-  static __device__ __forceinline__ Frag<T> frag(const char* lds, int rbase, int step, int lane) {
-    return col_frag<T, R>(lds, rbase, step, lane);
+  static __device__ __forceinline__ Frag<Sum> frag(const char* lds, int rbase, int step, int lane) {
+    return col_frag<T, Sum, R>(lds, rbase, step, lane);
   }
 };
 
 // ---- epilogues: four consecutive columns n .. n+3 (count of them inside the matrix) of row m ----
-// fp32.  vec: whole 16-byte units everywhere.
-struct EpiFpropF32 {
+// vec: whole units of four values everywhere.
+template <class T>
+__device__ __forceinline__ void store4(T* p, const float (&v)[4]) {
+  if constexpr (sizeof(T) == 4) *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  else *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+}
+template <class T>
+struct EpiForward {
   const float* bias;
-  float *d_out, *a_out;
+  T *d_out, *a_out;
   int act, ldc, vec;
   __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
     const size_t i = (size_t)m * ldc + n;
@@ -415,36 +432,40 @@ struct EpiFpropF32 {
       d[j] = d_out ? act_derivative(z, act) : 0.f;
     }
     if (vec && count == 4) {
-      if (d_out) *reinterpret_cast<float4*>(d_out + i) = make_float4(d[0], d[1], d[2], d[3]);
-      *reinterpret_cast<float4*>(a_out + i) = make_float4(a[0], a[1], a[2], a[3]);
+      if (d_out) store4(d_out + i, d);
+      store4(a_out + i, a);
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         if (j < count) {
-          if (d_out) d_out[i + j] = d[j];
-          a_out[i + j] = a[j];
+          if (d_out) d_out[i + j] = from_float<T>(d[j]);
+          a_out[i + j] = from_float<T>(a[j]);
         }
     }
   }
 };
-struct EpiDgradF32 {
-  const float* d_prev;  // saved act'(z) of the layer before, with relu_mask its ReLU output, or null
-  float* out;
+template <class T>
+struct EpiInputGrad {
+  const T* d_prev;  // saved act'(z) of the layer before, with relu_mask its ReLU output, or null
+  T* out;
   int ldc, relu_mask, vec;
-  __device__ __forceinline__ float through(float v, float d) const { return relu_mask ? (d > 0.f ? v : 0.f) : v * d; }
   __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
     const size_t i = (size_t)m * ldc + n;
-    if (vec && count == 4) {
-      float4 o = make_float4(v[0], v[1], v[2], v[3]);
+    float o[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      o[j] = v[j];
       if (d_prev) {
-        const float4 d = *reinterpret_cast<const float4*>(d_prev + i);
-        o = make_float4(through(o.x, d.x), through(o.y, d.y), through(o.z, d.z), through(o.w, d.w));
+        const float d = to_float(d_prev[j < count ? i + j : i]);
+        o[j] = relu_mask ? (d > 0.f ? v[j] : 0.f) : v[j] * d;
       }
-      *reinterpret_cast<float4*>(out + i) = o;
+    }
+    if (vec && count == 4) {
+      store4(out + i, o);
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        if (j < count) out[i + j] = d_prev ? through(v[j], d_prev[i + j]) : v[j];
+        if (j < count) out[i + j] = from_float<T>(o[j]);
     }
   }
 };
@@ -464,49 +485,33 @@ struct EpiPartial {
     }
   }
 };
-// bf16: the epilogues of the tuned kernels
-template <class E>
-struct EpiBf16 {
-  E e;
-  __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
-    e.quad(m, n, count, v[0], v[1], v[2], v[3]);
-  }
-};
-
 // ---- the kernel --------------------------------------------------------------------------------
-// grid = (output tiles, contraction ranges of `per` k tiles each).
-// U k tiles are waited for, multiplied and replaced between two barriers.
-// KG > 1: KG groups of WGM x WGN waves share the output tile, group g takes every KG-th run of U k tiles of the range, with
-// stage buffers of its own; all groups meet at the same barriers, and the first one adds up and stores the tile.
-template <class T, int BM, int BN, int WGM, int WGN, int NS, int KG, int U, class AL, class BL, class Epi>
-__global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_any_kernel(int M, int N, int KT, int per, typename AL::Desc ad,
-                                                                       typename BL::Desc bd, Epi epi, TileMap map) {
+// grid = (output tiles, contraction ranges of `per` k tiles each).  U k tiles are waited for, multiplied and replaced
+// between two barriers; NS runs of U tiles are in LDS.  The fragments of a step are read while the step before it is
+// multiplied, so that a wave that has its SIMD to itself waits for LDS once per barrier and not once per step.
+template <class T, class Sum, int BM, int BN, int WGM, int WGN, int NS, int U, class AL, class BL, class Epi>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_any_kernel(int M, int N, int KT, int per, typename AL::Desc ad,
+                                                                  typename BL::Desc bd, Epi epi, TileMap map) {
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, NW = WGM * WGN;
   constexpr int kABytes = BM * 128, kStage = (BM + BN) * 128;
   constexpr int kLoads = AL::kPerWave + BL::kPerWave;
   static_assert((NS - 2) * U * kLoads < 64, "too many copies in flight for vmcnt");
-  static_assert(KG == 1 || (KG - 1) * BM * BN * 4 <= KG * NS * U * kStage, "the groups' tiles do not fit the stages");
   extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int lane = threadIdx.x & 63;
-  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int group = wave_all / NW, wave = wave_all % NW;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
   int tile_m, tile_n;
   map.get(blockIdx.x, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int first = blockIdx.y * per, last = min(KT, first + per) - 1;  // k tiles of this range (at least one)
-  char* stages = lds + group * (NS * U * kStage);
-  const uint32_t lds_base = lds_addr_of(stages);
+  const uint32_t lds_base = lds_addr_of(lds);
 
-  constexpr int CH = sizeof(T) == 4 && TM * TN <= 4 ? 4 : 1;
-  floatx4 acc[TM][TN][CH];
+  floatx4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int c = 0; c < CH; ++c) acc[i][j][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   AL a;
   BL b;
@@ -530,76 +535,55 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_any_kernel(int M, in
     }
   };
 #pragma unroll
-  for (int st = 0; st < NS - 1; ++st) issue(first + (group + KG * st) * U, st);
+  for (int st = 0; st < NS - 1; ++st) issue(first + st * U, st);
   int rd = 0, wr = NS - 1;
-  for (int k0 = first; k0 <= last; k0 += KG * U) {
-    const int kt = k0 + group * U;
+  for (int kt = first; kt <= last; kt += U) {
     wait_vmcnt<(NS - 2) * U * kLoads>();
-    lds_barrier();  // tiles kt .. kt + U - 1 visible to the group's waves; everybody is done reading stage `wr`
-    issue(kt + KG * U * (NS - 1), wr);
+    lds_barrier();  // tiles kt .. kt + U - 1 visible to all waves; everybody is done reading stage `wr`
+    issue(kt + U * (NS - 1), wr);
+    const char* run = lds + rd * (U * kStage);
+    Frag<Sum> fa[2][TM], fb[2][TN];
+    auto fetch = [&](int q) {  // step q of the run
+      const char* la = run + (q / kSteps<T>) * kStage;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const char* la = stages + (rd * U + u) * kStage;
-      const char* lb = la + kABytes;
-      if (KG * U > 1 && kt + u > last) continue;
+      for (int i = 0; i < TM; ++i) fa[q & 1][i] = AL::frag(la, wm + 16 * i, q % kSteps<T>, lane);
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        Frag<T> fa[TM], fb[TN];
+      for (int j = 0; j < TN; ++j) fb[q & 1][j] = BL::frag(la + kABytes, wn + 16 * j, q % kSteps<T>, lane);
+    };
+    fetch(0);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[i] = AL::frag(la, wm + 16 * i, s, lane);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[j] = BL::frag(lb, wn + 16 * j, s, lane);
+    for (int q = 0; q < U * kSteps<T>; ++q) {
+      if (q + 1 < U * kSteps<T>) fetch(q + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if (U == 1 || kt + q / kSteps<T> <= last)  // wave uniform
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) multiply(fa[i], fb[j], acc[i][j]);
-      }
+          for (int j = 0; j < TN; ++j) multiply(fa[q & 1][i], fb[q & 1][j], acc[i][j]);
+      __builtin_amdgcn_sched_barrier(0);
     }
     rd = rd + 1 == NS ? 0 : rd + 1;
     wr = wr + 1 == NS ? 0 : wr + 1;
   }
-  wait_vmcnt<0>();  // the trailing copies land before the LDS is reused or given back
+  wait_vmcnt<0>();  // the trailing copies land before the LDS is given back
 
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-      if constexpr (CH == 4) acc[i][j][0] = (acc[i][j][0] + acc[i][j][1]) + (acc[i][j][2] + acc[i][j][3]);
-  if constexpr (KG > 1) {
-    lds_barrier();  // every group is done with its stages
-    floatx4* tiles = reinterpret_cast<floatx4*>(lds);
-    auto at = [&](int g, int i, int j) -> floatx4& { return tiles[((((g - 1) * NW + wave) * TM + i) * TN + j) * 64 + lane]; };
-    if (group > 0)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) at(group, i, j) = acc[i][j][0];
-    lds_barrier();
-    if (group > 0) return;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int g = 1; g < KG; ++g) acc[i][j][0] += at(g, i, j);
-  }
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int m = m0 + wm + 16 * i + (lane & 15);
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int n = n0 + wn + 16 * j + 4 * (lane >> 4);
-      if (m < M && n < N) epi.quad(m, n, min(4, N - n), acc[i][j][0], blockIdx.y);
+      if (m < M && n < N) epi.quad(m, n, min(4, N - n), acc[i][j], blockIdx.y);
     }
   }
 }
 
-template <class T, int BM, int BN, int WGM, int WGN, int NS, int KG, int U, class AL, class BL, class Epi>
+template <class T, class Sum, int BM, int BN, int WGM, int WGN, int NS, int U, class AL, class BL, class Epi>
 hipError_t launch_any(hipStream_t s, int M, int N, int KT, int splits, const typename AL::Desc& ad, const typename BL::Desc& bd,
                       const Epi& epi) {
-  constexpr size_t lds_bytes = (size_t)KG * NS * U * (BM + BN) * 128;
+  constexpr size_t lds_bytes = (size_t)NS * U * (BM + BN) * 128;
   static_assert(lds_bytes <= 160 * 1024, "stages do not fit the LDS of a CU");
-  auto kernel = gemm_any_kernel<T, BM, BN, WGM, WGN, NS, KG, U, AL, BL, Epi>;
+  auto kernel = gemm_any_kernel<T, Sum, BM, BN, WGM, WGN, NS, U, AL, BL, Epi>;
   if (lds_bytes > 64 * 1024) {
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
@@ -609,28 +593,38 @@ hipError_t launch_any(hipStream_t s, int M, int N, int KT, int splits, const typ
   const int per = (KT + splits - 1) / splits;
   const int ranges = (KT + per - 1) / per;  // every one of them has a tile to sum; ranges == splits by any_splits
   if (ranges != splits) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n, ranges), dim3(64 * WGM * WGN * KG), lds_bytes, s, M, N, KT, per, ad, bd, epi,
+  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n, ranges), dim3(64 * WGM * WGN), lds_bytes, s, M, N, KT, per, ad, bd, epi,
                      make_tile_map(tiles_m, tiles_n));
   return hipGetLastError();
 }
 
-// The tiles, and the time of one k tile on a CU that holds one workgroup (t1) and two (t2), in ns; the wide fp32 tile
-// and 128 x 128 leave room for one.  fp32 products are bound by the matrix cores where the output fills the chip and by
-// the chain barrier -> LDS reads -> MFMAs of a single workgroup where it does not; bf16 ones (convolutions) by the
-// address arithmetic of the copies and that chain.  Hence two groups of waves per workgroup on the small tiles and eight
-// waves on the large ones.  Measured (us): fp32 dense 128 x 1024 x 1024 9.9 (32 x 32) / 26 / 80, 2048^3 195 / 157 /
-// 152 (113 TFLOP/s), 32 x 512 x 512 6.5 -- the fp32 FMA kernel before: 160, -, 45.  fp32 3x3, 16 images of 32 x 32, 64
-// channels, forward / dx / dW: 64 x 64 on one group of waves with four stages 21.5 / 21.7 / 22.2, on two groups with two
-// stages 18.9 / 18.7 / 16.9 (FMA kernel 300 / 230 / 72).  bf16 3x3, 44 images of 64 x 64, 48 channels, forward: 64 x 64
-// 35.2, 128 x 64 26.3, 128 x 128 49.8 (FMA kernel 400).
-enum class Tile { k32, k64, k128x64, k128 };
+// The tiles, and the time of one k tile on a CU that holds one workgroup (t1) and two (t2), in ns; 128 x 128 leaves room
+// for one.  Chains in fp32 are bound by the matrix cores where the output fills the chip and by the chain barrier -> LDS
+// read -> MFMAs of a lone workgroup where it does not: four waves and four k tiles between barriers on the smallest
+// tile, eight waves on the others.  Measured (us), the FMA kernel before in brackets: fp32 dense 32 x 512 x 512 7.0 [45],
+// 128 x 1024 x 1024 11.6 / 27.6 / 83 with 32 / 64 / 128 tiles [160], 1024^3 33 / 28 / 82, 2048^3 210 / 169 / 160 (108
+// TFLOP/s).  fp32 3x3 on 16 images of 32 x 32, 64 channels: forward 22 / 19 / 55 [300], dx 23 / 19 / 48 [230]; with the
+// fragments read step by step in front of their MFMAs 64 x 64 took 21.5.  bf16 3x3, 44 images of 64 x 64, 48 channels,
+// forward: 144 / 113 / 237 [400] (26 on bf16 matrix instructions, which do not keep the order of the sum).
+enum class Tile { k32, k64, k128 };
 struct TileCost {
   Tile t;
-  int bm, bn, t1, t2;
+  int edge, t1, t2;
 };
-constexpr TileCost kTilesF32[] = {{Tile::k32, 32, 32, 300, 400}, {Tile::k64, 64, 64, 880, 1220}, {Tile::k128, 128, 128, 2300, 4600}};
-constexpr TileCost kTilesBf16[] = {{Tile::k32, 32, 32, 200, 300}, {Tile::k64, 64, 64, 350, 550}, {Tile::k128x64, 128, 64, 580, 950},
-                                   {Tile::k128, 128, 128, 850, 1700}};
+template <class T, class Sum>
+struct Tiles;
+template <>
+struct Tiles<float, Chain> {
+  static constexpr TileCost cost[] = {{Tile::k32, 32, 270, 480}, {Tile::k64, 64, 850, 1300}, {Tile::k128, 128, 2450, 4900}};
+};
+template <>
+struct Tiles<uint16_t, Chain> {
+  static constexpr TileCost cost[] = {{Tile::k32, 32, 660, 930}, {Tile::k64, 64, 1770, 2900}};
+};
+template <>
+struct Tiles<uint16_t, Free> {
+  static constexpr TileCost cost[] = {{Tile::k32, 32, 200, 300}, {Tile::k64, 64, 350, 550}, {Tile::k128, 128, 800, 1600}};
+};
 
 // Contraction ranges of a product whose output has too few tiles for the chip (weight gradients): as many as give every
 // CU a workgroup, each at least 8 k tiles long, and none of them empty.
@@ -641,14 +635,16 @@ inline int any_splits(long blocks, int KT) {
   return (KT + per - 1) / per;
 }
 
+inline long blocks_of(int edge, int M, int N) { return (long)((M + edge - 1) / edge) * ((N + edge - 1) / edge); }
+
 // The tile with the least time for all its workgroups on 256 CUs.  split: the contraction may be cut into ranges, so that
 // a long one fills the chip with large tiles too; `ranges` receives their number.
-template <class T>
+template <class T, class Sum>
 Tile pick_tile(int M, int N, int KT, bool split, int* ranges) {
   Tile best = Tile::k32;
   double best_cost = -1;
-  auto consider = [&](const TileCost& c) {
-    const long blocks = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+  for (const TileCost& c : Tiles<T, Sum>::cost) {
+    const long blocks = blocks_of(c.edge, M, N);
     const int r = split ? any_splits(blocks, KT) : 1;
     const long all = blocks * r, rest = all % 512;
     const double cost = ((double)(all / 512) * c.t2 + (rest == 0 ? 0 : rest <= 256 ? c.t1 : c.t2)) * ((KT + r - 1) / r);
@@ -657,11 +653,7 @@ Tile pick_tile(int M, int N, int KT, bool split, int* ranges) {
       best = c.t;
       *ranges = r;
     }
-  };
-  if constexpr (sizeof(T) == 4)
-    for (const TileCost& c : kTilesF32) consider(c);
-  else
-    for (const TileCost& c : kTilesBf16) consider(c);
+  }
   return best;
 }
 
@@ -673,53 +665,56 @@ inline FastDiv fast_div(int d, long limit) {
   return FastDiv{d == 1 || limit * d >= (1l << 32) ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d), (uint32_t)d};
 }
 
-// Loader class templates with the element type and vector width filled in per product
-template <class T, int VEC> struct FpropDense {
-  template <int R, int NW> using A = DenseRow<T, R, NW, VEC>;
-  template <int R, int NW> using B = DenseRow<T, R, NW, VEC>;
+// Loader class templates with the element type, kind of sum and vector width filled in per product
+template <class T, class Sum, int VEC> struct FpropDense {
+  template <int R, int NW> using A = DenseRow<T, Sum, R, NW, VEC>;
+  template <int R, int NW> using B = DenseRow<T, Sum, R, NW, VEC>;
 };
-template <class T, int VEC> struct DgradDense {
-  template <int R, int NW> using A = DenseRow<T, R, NW, VEC>;
-  template <int R, int NW> using B = DenseCol<T, R, NW, VEC>;
+template <class T, class Sum, int VEC> struct DgradDense {
+  template <int R, int NW> using A = DenseRow<T, Sum, R, NW, VEC>;
+  template <int R, int NW> using B = DenseCol<T, Sum, R, NW, VEC>;
 };
-template <class T, int VEC> struct WgradDense {
-  template <int R, int NW> using A = DenseCol<T, R, NW, VEC>;
-  template <int R, int NW> using B = DenseCol<T, R, NW, VEC>;
+template <class T, class Sum, int VEC> struct WgradDense {
+  template <int R, int NW> using A = DenseCol<T, Sum, R, NW, VEC>;
+  template <int R, int NW> using B = DenseCol<T, Sum, R, NW, VEC>;
 };
-template <class T, int VEC> struct FpropConv {
-  template <int R, int NW> using A = GatherRow<T, R, NW, VEC, false>;
-  template <int R, int NW> using B = DenseRow<T, R, NW, VEC>;
+template <class T, class Sum, int VEC> struct FpropConv {
+  template <int R, int NW> using A = GatherRow<T, Sum, R, NW, VEC, false>;
+  template <int R, int NW> using B = DenseRow<T, Sum, R, NW, VEC>;
 };
-template <class T, int VEC> struct DgradConv {
-  template <int R, int NW> using A = GatherRow<T, R, NW, VEC, true>;
-  template <int R, int NW> using B = WeightCol<T, R, NW, VEC>;
+template <class T, class Sum, int VEC> struct DgradConv {
+  template <int R, int NW> using A = GatherRow<T, Sum, R, NW, VEC, true>;
+  template <int R, int NW> using B = WeightCol<T, Sum, R, NW, VEC>;
 };
-template <class T, int VEC> struct WgradConv {
-  template <int R, int NW> using A = DenseCol<T, R, NW, VEC>;
-  template <int R, int NW> using B = GatherCol<T, R, NW, VEC>;
+template <class T, class Sum, int VEC> struct WgradConv {
+  template <int R, int NW> using A = DenseCol<T, Sum, R, NW, VEC>;
+  template <int R, int NW> using B = GatherCol<T, Sum, R, NW, VEC>;
 };
 
-template <class T, class P, class AD, class BD, class Epi>
+template <class T, class Sum, template <class, class, int> class Product, int VEC, class AD, class BD, class Epi>
 hipError_t run(hipStream_t s, int M, int N, int K, const AD& ad, const BD& bd, const Epi& epi, bool split = false) {
+  using P = Product<T, Sum, VEC>;
   const int KT = (K + kTileK<T> - 1) / kTileK<T>;
   int ranges = 1;
-#define TP_ANY(BM, BN, WGM, WGN, NS, KG, U)                                                                              \
-  launch_any<T, BM, BN, WGM, WGN, NS, KG, U, typename P::template A<BM, WGM * WGN>, typename P::template B<BN, WGM * WGN>>( \
+#define TP_ANY(E, WGM, WGN, NS, U)                                                                                           \
+  launch_any<T, Sum, E, E, WGM, WGN, NS, U, typename P::template A<E, WGM * WGN>, typename P::template B<E, WGM * WGN>>( \
       s, M, N, KT, ranges, ad, bd, epi)
-  switch (pick_tile<T>(M, N, KT, split, &ranges)) {
-    case Tile::k128: return TP_ANY(128, 128, 4, 2, 3, 1, 1);
-    case Tile::k128x64:
-      if constexpr (sizeof(T) == 2) return TP_ANY(128, 64, 4, 2, 3, 1, 1);
-      [[fallthrough]];  // not among the fp32 tiles
-    case Tile::k64: return TP_ANY(64, 64, 2, 2, 2, 2, 1);
-    default: return TP_ANY(32, 32, 2, 2, 2, 2, 2);
+  switch (pick_tile<T, Sum>(M, N, KT, split, &ranges)) {
+    case Tile::k128:
+      if constexpr (!(sizeof(T) == 2 && __is_same(Sum, Chain))) return TP_ANY(128, 4, 2, 3, 1);
+      [[fallthrough]];  // not among those tiles
+    case Tile::k64: return TP_ANY(64, 4, 2, 2, 2);
+    default:
+      // with more workgroups than CUs, four of them on a CU at 32 KB each instead of two at 64 KB
+      if (blocks_of(32, M, N) * ranges <= 256) return TP_ANY(32, 2, 2, 2, 4);
+      return TP_ANY(32, 2, 2, 2, 2);
   }
 #undef TP_ANY
 }
-template <class T>
+template <class T, class Sum>
 int ranges_of(int M, int N, int K) {
   int ranges = 1;
-  pick_tile<T>(M, N, (K + kTileK<T> - 1) / kTileK<T>, true, &ranges);
+  pick_tile<T, Sum>(M, N, (K + kTileK<T> - 1) / kTileK<T>, true, &ranges);
   return ranges;
 }
 
@@ -729,21 +724,21 @@ int ranges_of(int M, int N, int K) {
 hipError_t f32_fprop(hipStream_t s, int M, int N, int K, const float* x, const float* W, const float* bias, int act, float* d_out,
                      float* a_out) {
   const DenseDesc a{x, K, M, K}, b{W, K, N, K};
-  const EpiFpropF32 e{bias, d_out, a_out, act, N, N % 4 == 0 && aligned16(d_out, a_out)};
-  if (K % 4 == 0 && aligned16(x, W)) return run<float, FpropDense<float, 4>>(s, M, N, K, a, b, e);
-  return run<float, FpropDense<float, 1>>(s, M, N, K, a, b, e);
+  const EpiForward<float> e{bias, d_out, a_out, act, N, N % 4 == 0 && aligned16(d_out, a_out)};
+  if (K % 4 == 0 && aligned16(x, W)) return run<float, Chain, FpropDense, 4>(s, M, N, K, a, b, e);
+  return run<float, Chain, FpropDense, 1>(s, M, N, K, a, b, e);
 }
 
 hipError_t f32_dgrad(hipStream_t s, int M, int N, int K, const float* dz, const float* Wb, const float* d_prev, float* out,
                      int relu_mask) {
   // out[M x K] = dz[M x N] . Wb[N x K]: contraction over N
   const DenseDesc a{dz, N, M, N}, b{Wb, K, K, N};
-  const EpiDgradF32 e{d_prev, out, K, relu_mask, K % 4 == 0 && aligned16(d_prev, out)};
-  if (N % 4 == 0 && K % 4 == 0 && aligned16(dz, Wb)) return run<float, DgradDense<float, 4>>(s, M, K, N, a, b, e);
-  return run<float, DgradDense<float, 1>>(s, M, K, N, a, b, e);
+  const EpiInputGrad<float> e{d_prev, out, K, relu_mask, K % 4 == 0 && aligned16(out)};
+  if (N % 4 == 0 && K % 4 == 0 && aligned16(dz, Wb)) return run<float, Chain, DgradDense, 4>(s, M, K, N, a, b, e);
+  return run<float, Chain, DgradDense, 1>(s, M, K, N, a, b, e);
 }
 
-int f32_wgrad_splits(int M, int N, int K) { return ranges_of<float>(N, K, M); }
+int f32_wgrad_splits(int M, int N, int K) { return ranges_of<float, Chain>(N, K, M); }
 
 hipError_t f32_wgrad(hipStream_t s, int M, int N, int K, const float* dz, const float* x, float* gW, float* partial) {
   // gW[N x K] = dz^T[N x M] . x[M x K]: contraction over M
@@ -753,8 +748,8 @@ hipError_t f32_wgrad(hipStream_t s, int M, int N, int K, const float* dz, const 
   float* out = splits > 1 ? partial : gW;
   const EpiPartial e{out, K, K % 4 == 0 && aligned16(out), (size_t)N * K};
   const hipError_t err = N % 4 == 0 && K % 4 == 0 && aligned16(dz, x)
-                             ? run<float, WgradDense<float, 4>>(s, N, K, M, a, b, e, split)
-                             : run<float, WgradDense<float, 1>>(s, N, K, M, a, b, e, split);
+                             ? run<float, Chain, WgradDense, 4>(s, N, K, M, a, b, e, split)
+                             : run<float, Chain, WgradDense, 1>(s, N, K, M, a, b, e, split);
   if (err != hipSuccess || splits == 1) return err;
   return launch_sum_partials(s, (size_t)N * K, splits, partial, gW);
 }
@@ -776,11 +771,11 @@ hipError_t conv_any_fprop(hipStream_t s, int elt, int imgs, int H, int W, int ks
   const bool vec = aligned16(x, wgt);
   if (elt == ELT_BF16) {
     if (!vec) return hipErrorNotSupported;
-    return run<uint16_t, FpropConv<uint16_t, 8>>(s, P, cout, K, a, b, EpiBf16<EpiFprop>{{bias, (uint16_t*)d_out, (uint16_t*)a_out, act, cout}});
+    return run<uint16_t, Chain, FpropConv, 8>(s, P, cout, K, a, b, EpiForward<uint16_t>{bias, (uint16_t*)d_out, (uint16_t*)a_out, act, cout, aligned16(d_out, a_out)});
   }
-  const EpiFpropF32 e{bias, (float*)d_out, (float*)a_out, act, cout, cout % 4 == 0 && aligned16(d_out, a_out)};
-  if (cin % 4 == 0 && vec) return run<float, FpropConv<float, 4>>(s, P, cout, K, a, b, e);
-  return run<float, FpropConv<float, 1>>(s, P, cout, K, a, b, e);
+  const EpiForward<float> e{bias, (float*)d_out, (float*)a_out, act, cout, cout % 4 == 0 && aligned16(d_out, a_out)};
+  if (cin % 4 == 0 && vec) return run<float, Chain, FpropConv, 4>(s, P, cout, K, a, b, e);
+  return run<float, Chain, FpropConv, 1>(s, P, cout, K, a, b, e);
 }
 
 hipError_t conv_any_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout, const void* dz,
@@ -791,16 +786,16 @@ hipError_t conv_any_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int ks
   const bool vec = aligned16(dz, wb);
   if (elt == ELT_BF16) {
     if (!vec) return hipErrorNotSupported;
-    return run<uint16_t, DgradConv<uint16_t, 8>>(s, P, cin, K, a, b, EpiBf16<EpiDgrad>{{(const uint16_t*)d_prev, (uint16_t*)out, cin, relu_mask}});
+    return run<uint16_t, Chain, DgradConv, 8>(s, P, cin, K, a, b, EpiInputGrad<uint16_t>{(const uint16_t*)d_prev, (uint16_t*)out, cin, relu_mask, aligned16(out)});
   }
-  const EpiDgradF32 e{(const float*)d_prev, (float*)out, cin, relu_mask, cin % 4 == 0 && aligned16(d_prev, out)};
-  if (cin % 4 == 0 && cout % 4 == 0 && vec) return run<float, DgradConv<float, 4>>(s, P, cin, K, a, b, e);
-  return run<float, DgradConv<float, 1>>(s, P, cin, K, a, b, e);
+  const EpiInputGrad<float> e{(const float*)d_prev, (float*)out, cin, relu_mask, cin % 4 == 0 && aligned16(out)};
+  if (cin % 4 == 0 && cout % 4 == 0 && vec) return run<float, Chain, DgradConv, 4>(s, P, cin, K, a, b, e);
+  return run<float, Chain, DgradConv, 1>(s, P, cin, K, a, b, e);
 }
 
 int conv_any_wgrad_splits(int elt, int pixels, int cin, int cout, int ksize) {
   const int N = ksize * ksize * cin;
-  return elt == ELT_BF16 ? ranges_of<uint16_t>(cout, N, pixels) : ranges_of<float>(cout, N, pixels);
+  return elt == ELT_BF16 ? ranges_of<uint16_t, Free>(cout, N, pixels) : ranges_of<float, Chain>(cout, N, pixels);
 }
 
 hipError_t conv_any_wgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout, const void* dz,
@@ -815,11 +810,11 @@ hipError_t conv_any_wgrad(hipStream_t s, int elt, int imgs, int H, int W, int ks
   hipError_t err;
   if (elt == ELT_BF16) {
     if (!vec) return hipErrorNotSupported;
-    err = run<uint16_t, WgradConv<uint16_t, 8>>(s, cout, N, P, a, b, e, true);
+    err = run<uint16_t, Free, WgradConv, 8>(s, cout, N, P, a, b, e, true);
   } else if (cin % 4 == 0 && cout % 4 == 0 && vec) {
-    err = run<float, WgradConv<float, 4>>(s, cout, N, P, a, b, e, true);
+    err = run<float, Chain, WgradConv, 4>(s, cout, N, P, a, b, e, true);
   } else {
-    err = run<float, WgradConv<float, 1>>(s, cout, N, P, a, b, e, true);
+    err = run<float, Chain, WgradConv, 1>(s, cout, N, P, a, b, e, true);
   }
   if (err != hipSuccess || splits == 1) return err;
   return launch_sum_partials(s, (size_t)cout * N, splits, partial, gW);
