@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void attn_softmax_bwd_kernel(int S, size_t row
 }
 
 // ---- fused forward --------------------------------------------------------------------------------
-// One workgroup = 256 queries of one (sequence, head): 8 waves x 32 queries.  It walks over the keys
+// One workgroup = 256 (128) queries of one (sequence, head): 8 (4) waves x 32 queries.  It walks over the keys
 // in blocks of 64; K [64 keys][dh] and V [64 keys][dh] of a block are copied global -> LDS (three
 // stages in flight) and shared by the eight waves.  Per wave and block:
 //   S^T = K Q^T     the transposed score tile: MFMA rows = keys, columns = the wave's queries.  Every
@@ -236,11 +236,15 @@ __global__ __launch_bounds__(256) void attn_softmax_bwd_kernel(int S, size_t row
 // divided by the row sums and turned through LDS for 16-byte row stores; lse = max + log(sum) (natural
 // logarithm of the scaled scores) is what the backward pass recomputes the probabilities from.
 // No score matrix reaches memory.
-constexpr int kFlashWaves = 8, kFlashStages = 3, kFlashQ = 32 * kFlashWaves;
+// Any number of tokens: rows past the last token repeat it, in the last key block as among the queries.  A repeated key
+// comes after every real query, so the causal mask removes it; a repeated query is not stored.
+// Four waves per workgroup instead of eight where that many workgroups would not fill the chip, and on short
+// sequences, whose last waves would have no queries (see flash_waves).
+constexpr int kFlashStages = 3;
 
 template <int DH>
 __device__ __forceinline__ bf16x8 flash_v_frag(const uint16_t* lds, int dbase, int g16, int lane) {
-  using VT = ColDma<DH, kFlashWaves>;  // only its chunk swizzle is used, which does not depend on the wave count
+  using VT = ColDma<DH, 4>;  // only its chunk swizzle is used, which does not depend on the wave count
   const int g = lane >> 4, s = lane & 15;
   const int k = g16 * 16 + 4 * (g >> 1) + (s >> 2);       // keys {0-3} / {4-7} of the group, +8 below
   const int col = dbase + 16 * (g & 1) + 4 * (s & 3);
@@ -253,11 +257,11 @@ __device__ __forceinline__ bf16x8 flash_v_frag(const uint16_t* lds, int dbase, i
   return __builtin_bit_cast(bf16x8, v);
 }
 
-template <int DH>
-__global__ __launch_bounds__(64 * kFlashWaves) void attn_flash_fwd_kernel(int S, int heads, const uint16_t* __restrict__ qkv,
-                                                                          uint16_t* __restrict__ out, float* __restrict__ lse,
-                                                                          float scale_log2) {
-  constexpr int NW = kFlashWaves, NS = kFlashStages;
+template <int DH, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int heads, const uint16_t* __restrict__ qkv,
+                                                                 uint16_t* __restrict__ out, float* __restrict__ lse,
+                                                                 float scale_log2) {
+  constexpr int NS = kFlashStages, kFlashQ = 32 * NW;
   constexpr int HALVES = DH / 64, TN = DH / 32;
   using KT = RowDma<64, NW>;   // 64 keys x one 64-wide chunk of the head dimension
   using VT = ColDma<DH, NW>;   // [64 keys][DH]
@@ -276,7 +280,7 @@ __global__ __launch_bounds__(64 * kFlashWaves) void attn_flash_fwd_kernel(int S,
   const int D = heads * DH, ld = 3 * D;
   const int q0 = (gridDim.y - 1 - blockIdx.y) * kFlashQ;
   const int qw = q0 + wave * 32;                           // first query of this wave
-  const bool active = qw < S;                              // S is a multiple of 64: a wave is whole or absent
+  const bool active = qw < S;
   const uint16_t* qbase = qkv + (size_t)zb * S * ld + zh * DH;
   const uint16_t* kbase = qbase + D;
   const uint16_t* vbase = qbase + 2 * D;
@@ -285,7 +289,7 @@ __global__ __launch_bounds__(64 * kFlashWaves) void attn_flash_fwd_kernel(int S,
   // Q fragments (B operand: column = query lane % 32, 8 consecutive head-dimension values)
   bf16x8 qf[DH / 16];
   {
-    const uint16_t* qrow = qbase + (size_t)(active ? qw + (lane & 31) : 0) * ld + 8 * half;
+    const uint16_t* qrow = qbase + (size_t)min(qw + (lane & 31), S - 1) * ld + 8 * half;
 #pragma unroll
     for (int kk = 0; kk < DH / 16; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qrow + kk * 16));
   }
@@ -293,22 +297,32 @@ __global__ __launch_bounds__(64 * kFlashWaves) void attn_flash_fwd_kernel(int S,
 #pragma unroll
   for (int kk = 0; kk < DH / 16; ++kk) asm volatile("" : "+v"(qf[kk]));  // the compiler's own wait for these loads lands here
 
-  KT kt;
-  VT vt;
+  KT kt, kt_last;
+  VT vt, vt_last;
+  const int short_block = S / 64, keys_left = S - 64 * short_block;  // the last block, where it is not whole
   kt.init(ld, 0, 64, wave, lane);
   vt.init(ld, 0, DH, wave, lane);
-  const int nkb = min(S, q0 + kFlashQ) / 64;  // key blocks any query of the workgroup can see
+  kt_last.init(ld, 0, max(keys_left, 1), wave, lane);
+  vt_last.init(ld, 0, DH, wave, lane, max(keys_left, 1) - 1);
+  const int nkb = (min(S, q0 + kFlashQ) + 63) / 64;  // key blocks any query of the workgroup can see
   auto issue_block = [&](int blk, int st) {
     const int kb = min(blk, nkb - 1);  // blocks past the end re-read the last one into a stage nobody reads again
     const uint32_t dst = lds_base + st * kStageBytes;
     const uint16_t* ksrc = kbase + (size_t)kb * 64 * ld;
     const uint16_t* vsrc = vbase + (size_t)kb * 64 * ld;
+    const bool whole = kb != short_block;  // wave uniform
+    KT k = kt;
+    VT v = vt;
+#pragma unroll
+    for (int t = 0; t < KT::kPerWave; ++t) k.voff[t] = whole ? kt.voff[t] : kt_last.voff[t];
+#pragma unroll
+    for (int t = 0; t < VT::kPerWave; ++t) v.voff[t] = whole ? vt.voff[t] : vt_last.voff[t];
 #pragma unroll
     for (int c = 0; c < HALVES; ++c)
 #pragma unroll
-      for (int t = 0; t < KT::kPerWave; ++t) kt.issue_one(t, dst + c * KT::kBytes, ksrc + c * 64, wave);
+      for (int t = 0; t < KT::kPerWave; ++t) k.issue_one(t, dst + c * KT::kBytes, ksrc + c * 64, wave);
 #pragma unroll
-    for (int t = 0; t < VT::kPerWave; ++t) vt.issue_one(t, dst + kKBytes, vsrc, wave);
+    for (int t = 0; t < VT::kPerWave; ++t) v.issue_one(t, dst + kKBytes, vsrc, wave);
   };
 #pragma unroll
   for (int st = 0; st < NS - 1; ++st) issue_block(st, st);
@@ -397,24 +411,32 @@ __global__ __launch_bounds__(64 * kFlashWaves) void attn_flash_fwd_kernel(int S,
   for (int j = 0; j < TN; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[0][j][r] *= inv;
-  if (half == 0) lse[(size_t)blockIdx.x * S + query] = (mrun + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
+  if (half == 0 && query < S) lse[(size_t)blockIdx.x * S + query] = (mrun + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
   float* wave_lds = reinterpret_cast<float*>(lds_raw) + wave * (wave_epilogue_bytes<1, TN>() / 4);
-  store_tiles_coalesced<1, TN>(oacc, EpiDgrad{nullptr, out, D}, zb * S + qw, zh * DH, lane, wave_lds);
+  if (qw + 32 <= S)
+    store_tiles_coalesced<1, TN>(oacc, EpiDgrad{nullptr, out, D}, zb * S + qw, zh * DH, lane, wave_lds);
+  else
+    store_tiles<1, TN>(oacc, EpiDgrad{nullptr, out, D}, zb * S + qw, zh * DH, zb * S + S, zh * DH + DH, lane);
 }
 
-template <int DH>
+// Waves per workgroup of the fused kernels: eight share every streamed block and cover each other's stalls, where the
+// chip gets a workgroup per CU that way.
+inline int flash_waves(int seqs, int S, int heads) { return S > 128 && (long)seqs * heads * ((S + 255) / 256) >= 256 ? 8 : 4; }
+
+template <int DH, int NW>
 hipError_t launch_flash_fwd(hipStream_t s, int seqs, int S, int heads, const uint16_t* qkv, uint16_t* out, float* lse) {
-  constexpr size_t stage_bytes = (size_t)kFlashStages * ((DH / 64) * RowDma<64, kFlashWaves>::kBytes + ColDma<DH, kFlashWaves>::kBytes);
-  constexpr size_t epi_bytes = (size_t)kFlashWaves * wave_epilogue_bytes<1, DH / 32>();
+  constexpr int kFlashQ = 32 * NW;
+  constexpr size_t stage_bytes = (size_t)kFlashStages * ((DH / 64) * RowDma<64, NW>::kBytes + ColDma<DH, NW>::kBytes);
+  constexpr size_t epi_bytes = (size_t)NW * wave_epilogue_bytes<1, DH / 32>();
   constexpr size_t lds_bytes = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
   static_assert(lds_bytes <= 160 * 1024, "stages do not fit the LDS of a CU");
-  auto kernel = attn_flash_fwd_kernel<DH>;
+  auto kernel = attn_flash_fwd_kernel<DH, NW>;
   static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
   // scores are scaled by 1/sqrt(dh) and exponentiated in base 2
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
-  hipLaunchKernelGGL(kernel, dim3(seqs * heads, (S + kFlashQ - 1) / kFlashQ), dim3(64 * kFlashWaves), lds_bytes, s, S, heads, qkv,
+  hipLaunchKernelGGL(kernel, dim3(seqs * heads, (S + kFlashQ - 1) / kFlashQ), dim3(64 * NW), lds_bytes, s, S, heads, qkv,
                      out, lse, scale_log2);
   return hipGetLastError();
 }
@@ -432,13 +454,16 @@ hipError_t launch_flash_fwd(hipStream_t s, int seqs, int S, int heads, const uin
 // once in the row layout the first products read and once in the layout the transposing reads of the second
 // products want.  The scores are recomputed in both launches (7 matrix products instead of 5), no score-sized
 // tensor reaches memory, nothing is accumulated with atomics: every output element has one owner.
-// 8 waves per workgroup, two per SIMD: the second wave covers the first one's LDS and barrier stalls (25 % faster than
+// Tokens that fill no block: as in the forward kernel, rows past the last token repeat it.  A repeated query among the
+// streamed rows of the dK/dV launch is masked like a key above the diagonal; its (lse, delta) are zeros.
+// 8 waves per workgroup (4 where flash_waves says so), two per SIMD: the second wave covers the first one's LDS and barrier stalls (25 % faster than
 // 4 waves in both launches).  The dK/dV launch fits the 256 registers that leaves because only one half of a streamed
 // block has its score tiles alive at a time.
-constexpr int kBwdWaves = 8;
 constexpr float kLog2e = 1.4426950408889634f;
+__host__ __device__ constexpr int stat_rows(int S) { return (S + 63) / 64 * 64; }
 
-// stat[(z*S + i)*2] = lse_i * log2(e), stat[(z*S + i)*2 + 1] = delta_i = sum_d dO[i][d] * O[i][d];  z = sequence*heads + head.
+// stat[(z*SP + i)*2] = lse_i * log2(e), stat[(z*SP + i)*2 + 1] = delta_i = sum_d dO[i][d] * O[i][d];  z = sequence*heads + head,
+// SP = S rounded up to whole blocks of 64; zeros behind the last token.
 // One wave per token row; a lane takes 8 consecutive columns per step, the dh/8 lanes of a head are added.
 __global__ __launch_bounds__(256) void attn_stat_kernel(int S, int heads, int dh, size_t rows, const uint16_t* __restrict__ dout,
                                                         const uint16_t* __restrict__ out, const float* __restrict__ lse,
@@ -461,19 +486,26 @@ __global__ __launch_bounds__(256) void attn_stat_kernel(int S, int heads, int dh
     }
     for (int off = 1; off < group; off <<= 1) acc += __shfl_xor(acc, off, 64);
     if (col < D && (lane % group) == 0) {
-      const size_t zi = (b * heads + col / dh) * S + i;
-      stat[zi * 2] = lse[zi] * kLog2e;
+      const size_t z = b * heads + col / dh, zi = z * stat_rows(S) + i;
+      stat[zi * 2] = lse[z * S + i] * kLog2e;
       stat[zi * 2 + 1] = acc;
+    }
+  }
+  if ((int)i == S - 1) {
+    const int pad = stat_rows(S) - S;
+    for (int q = lane; q < pad * heads; q += 64) {
+      const size_t zi = (b * heads + q / pad) * stat_rows(S) + S + q % pad;
+      stat[zi * 2] = stat[zi * 2 + 1] = 0.f;
     }
   }
 }
 
-template <int DH, bool OWN_KEYS>
-__global__ __launch_bounds__(64 * kBwdWaves) void attn_flash_bwd_kernel(int S, int heads, const uint16_t* __restrict__ qkv,
-                                                                        const uint16_t* __restrict__ dout,
-                                                                        const float* __restrict__ stat, uint16_t* __restrict__ dqkv,
-                                                                        float scale, float scale_log2) {
-  constexpr int NW = kBwdWaves, kBwdOwn = 32 * NW;
+template <int DH, bool OWN_KEYS, int NW, bool WHOLE>
+__global__ __launch_bounds__(64 * NW) void attn_flash_bwd_kernel(int S, int heads, const uint16_t* __restrict__ qkv,
+                                                                 const uint16_t* __restrict__ dout,
+                                                                 const float* __restrict__ stat, uint16_t* __restrict__ dqkv,
+                                                                 float scale, float scale_log2) {
+  constexpr int kBwdOwn = 32 * NW;
   constexpr int HALVES = DH / 64, TN = DH / 32;
   using RT = RowDma<64, NW>;   // 64 streamed rows x one 64-wide chunk of the head dimension
   using CT = ColDma<DH, NW>;   // [64 streamed rows][DH], read transposed
@@ -507,7 +539,7 @@ __global__ __launch_bounds__(64 * kBwdWaves) void attn_flash_bwd_kernel(int S, i
   bf16x8 f1[DH / 16], f2[DH / 16];
   float own_l2 = 0.f, own_delta = 0.f;
   {
-    const size_t r = active ? oi : 0;
+    const size_t r = WHOLE && !active ? 0 : min(oi, S - 1);
     const uint16_t* p1 = own1 + r * ld3 + 8 * half;
     const uint16_t* p2 = own2 + r * ld_own2 + 8 * half;
 #pragma unroll
@@ -516,7 +548,7 @@ __global__ __launch_bounds__(64 * kBwdWaves) void attn_flash_bwd_kernel(int S, i
       f2[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p2 + kk * 16));
     }
     if (!OWN_KEYS) {
-      const float2 st = *reinterpret_cast<const float2*>(stat + ((size_t)z * S + r) * 2);
+      const float2 st = *reinterpret_cast<const float2*>(stat + ((size_t)z * stat_rows(S) + r) * 2);
       own_l2 = st.x;
       own_delta = st.y;
     }
@@ -526,20 +558,25 @@ __global__ __launch_bounds__(64 * kBwdWaves) void attn_flash_bwd_kernel(int S, i
   for (int kk = 0; kk < DH / 16; ++kk) asm volatile("" : "+v"(f1[kk]), "+v"(f2[kk]));
   asm volatile("" : "+v"(own_l2), "+v"(own_delta));
 
+  const int short_block = S / 64, rows_left = S - 64 * short_block;  // the last block, where it is not whole
   RT rt1, rt2;
   CT ct1, ct2;
-  rt1.init(ld3, 0, 64, wave, lane);
-  rt2.init(ld_str2, 0, 64, wave, lane);
-  ct1.init(ld3, 0, DH, wave, lane);
-  ct2.init(ld_str2, 0, DH, wave, lane);
+  auto offsets = [&](int rows) {  // of a block of `rows` rows, the last one repeated
+    rt1.init(ld3, 0, rows, wave, lane);
+    rt2.init(ld_str2, 0, rows, wave, lane);
+    ct1.init(ld3, 0, DH, wave, lane, rows - 1);
+    if (OWN_KEYS) ct2.init(ld_str2, 0, DH, wave, lane, rows - 1);
+  };
+  offsets(64);
   // streamed blocks of 64 rows: keys 0 .. diagonal of the workgroup | queries diagonal .. end
   const int sb_begin = OWN_KEYS ? o0 / 64 : 0;
-  const int sb_end = OWN_KEYS ? S / 64 : min(S, o0 + kBwdOwn) / 64;
+  const int sb_end = ((OWN_KEYS ? S : min(S, o0 + kBwdOwn)) + 63) / 64;
   auto issue_block = [&](int blk, int st) {
     const int sb = min(blk, sb_end - 1);  // past the end: re-read the last block into a stage nobody reads again
     const uint32_t dst = lds_base + st * kStageBytes;
     const uint16_t* s1 = str1 + (size_t)sb * 64 * ld3;
     const uint16_t* s2 = str2 + (size_t)sb * 64 * ld_str2;
+    if constexpr (!WHOLE) offsets(sb == short_block ? rows_left : 64);  // a dozen instructions a block
 #pragma unroll
     for (int c = 0; c < HALVES; ++c)
 #pragma unroll
@@ -553,7 +590,7 @@ __global__ __launch_bounds__(64 * kBwdWaves) void attn_flash_bwd_kernel(int S, i
       if (OWN_KEYS) ct2.issue_one(t, dst + 2 * kRowBytes + CT::kBytes, s2, wave);
     }
     // (lse*log2e, delta) of the 64 streamed queries: 512 bytes, lanes 32-63 repeat lanes 0-31 into the spare half
-    if (OWN_KEYS) dma16(dst + 2 * kRowBytes + 2 * CT::kBytes, stat + ((size_t)z * S + (size_t)sb * 64) * 2, (uint32_t)(lane & 31) * 16);
+    if (OWN_KEYS) dma16(dst + 2 * kRowBytes + 2 * CT::kBytes, stat + ((size_t)z * stat_rows(S) + (size_t)sb * 64) * 2, (uint32_t)(lane & 31) * 16);
   };
   issue_block(sb_begin, 0);
 
@@ -576,8 +613,8 @@ __global__ __launch_bounds__(64 * kBwdWaves) void attn_flash_bwd_kernel(int S, i
       const uint16_t* lc1 = lr2 + kRowBytes / 2;
       const uint16_t* lc2 = lc1 + CT::kBytes / 2;
       const float* lstat = reinterpret_cast<const float*>(lc1 + kCols * (CT::kBytes / 2));
-      // some pair of this wave and block lies above the diagonal
-      const bool diagonal = OWN_KEYS ? sb * 64 < ow + 31 : sb * 64 + 63 > ow;
+      // some pair of this wave and block lies above the diagonal or has a repeated query
+      const bool diagonal = OWN_KEYS ? sb * 64 < ow + 31 || (!WHOLE && sb == short_block) : sb * 64 + 63 > ow;
       // one half of the block (32 streamed rows) at a time, first products to second products: the score tiles of
       // one half only are alive at any time, which is what lets two waves share a SIMD's registers
 #pragma unroll
@@ -616,7 +653,7 @@ __global__ __launch_bounds__(64 * kBwdWaves) void attn_flash_bwd_kernel(int S, i
               if (diagonal) {
                 const int si = sb * 64 + srow;
                 const int key = OWN_KEYS ? oi : si, query = OWN_KEYS ? si : oi;
-                if (key > query) p = 0.f;
+                if (key > query || (!WHOLE && OWN_KEYS && query >= S)) p = 0.f;
               }
               pe[t] = p;
               de[t] = p * (pacc[r] - dlv[u]) * scale;
@@ -646,25 +683,31 @@ __global__ __launch_bounds__(64 * kBwdWaves) void attn_flash_bwd_kernel(int S, i
   lds_barrier();
   if (!active) return;
   float* wave_lds = reinterpret_cast<float*>(lds_raw) + wave * (wave_epilogue_bytes<1, TN>() / 4);
-  store_tiles_coalesced<1, TN>(acc1, EpiDgrad{nullptr, dqkv + (OWN_KEYS ? D : 0), ld3}, zb * S + ow, zh * DH, lane, wave_lds);
-  if (OWN_KEYS) store_tiles_coalesced<1, TN>(acc2, EpiDgrad{nullptr, dqkv + 2 * D, ld3}, zb * S + ow, zh * DH, lane, wave_lds);
+  const EpiDgrad e1{nullptr, dqkv + (OWN_KEYS ? D : 0), ld3}, e2{nullptr, dqkv + 2 * D, ld3};
+  if (WHOLE || ow + 32 <= S) {
+    store_tiles_coalesced<1, TN>(acc1, e1, zb * S + ow, zh * DH, lane, wave_lds);
+    if (OWN_KEYS) store_tiles_coalesced<1, TN>(acc2, e2, zb * S + ow, zh * DH, lane, wave_lds);
+  } else {
+    store_tiles<1, TN>(acc1, e1, zb * S + ow, zh * DH, zb * S + S, zh * DH + DH, lane);
+    if (OWN_KEYS) store_tiles<1, TN>(acc2, e2, zb * S + ow, zh * DH, zb * S + S, zh * DH + DH, lane);
+  }
 }
 
-template <int DH, bool OWN_KEYS>
+template <int DH, bool OWN_KEYS, int NW, bool WHOLE>
 hipError_t launch_flash_bwd(hipStream_t s, int seqs, int S, int heads, const uint16_t* qkv, const uint16_t* dout, const float* stat,
                             uint16_t* dqkv) {
-  constexpr int kBwdOwn = 32 * kBwdWaves;
-  constexpr size_t row_bytes = (size_t)(DH / 64) * RowDma<64, kBwdWaves>::kBytes, col_bytes = ColDma<DH, kBwdWaves>::kBytes;
+  constexpr int kBwdOwn = 32 * NW;
+  constexpr size_t row_bytes = (size_t)(DH / 64) * RowDma<64, NW>::kBytes, col_bytes = ColDma<DH, NW>::kBytes;
   constexpr size_t stage_bytes = 2 * (2 * row_bytes + (OWN_KEYS ? 2 : 1) * col_bytes + (OWN_KEYS ? 1024 : 0));
-  constexpr size_t epi_bytes = (size_t)kBwdWaves * wave_epilogue_bytes<1, DH / 32>();
+  constexpr size_t epi_bytes = (size_t)NW * wave_epilogue_bytes<1, DH / 32>();
   constexpr size_t lds_bytes = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
   static_assert(lds_bytes <= 160 * 1024, "stages do not fit the LDS of a CU");
-  auto kernel = attn_flash_bwd_kernel<DH, OWN_KEYS>;
+  auto kernel = attn_flash_bwd_kernel<DH, OWN_KEYS, NW, WHOLE>;
   static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
   const float scale = 1.0f / sqrtf((float)DH);
-  hipLaunchKernelGGL(kernel, dim3(seqs * heads, (S + kBwdOwn - 1) / kBwdOwn), dim3(64 * kBwdWaves), lds_bytes, s, S, heads, qkv, dout,
+  hipLaunchKernelGGL(kernel, dim3(seqs * heads, (S + kBwdOwn - 1) / kBwdOwn), dim3(64 * NW), lds_bytes, s, S, heads, qkv, dout,
                      stat, dqkv, scale, scale * kLog2e);
   return hipGetLastError();
 }
@@ -687,16 +730,18 @@ size_t attention_mfma_scratch_bytes(int seqs, int S, int heads) {
 }
 
 bool attention_flash_fwd_supported(int seqs, int S, int heads, int dh) {
-  return (dh == 64 || dh == 128) && S >= 64 && S % 64 == 0 && heads >= 1 && seqs >= 1 && (long)seqs * heads <= 65535 &&
+  return (dh == 64 || dh == 128) && S >= 1 && heads >= 1 && seqs >= 1 && (long)seqs * heads <= 65535 &&
          64ull * 3 * heads * dh * 2 < (1ull << 31);  // 32-bit byte offsets inside one 64-key block
 }
 
 hipError_t attention_flash_fwd(hipStream_t s, int seqs, int S, int heads, int dh, const uint16_t* qkv, uint16_t* out, float* lse) {
   if (!attention_flash_fwd_supported(seqs, S, heads, dh)) return hipErrorNotSupported;
-  return dh == 64 ? launch_flash_fwd<64>(s, seqs, S, heads, qkv, out, lse) : launch_flash_fwd<128>(s, seqs, S, heads, qkv, out, lse);
+  if (flash_waves(seqs, S, heads) == 8)
+    return dh == 64 ? launch_flash_fwd<64, 8>(s, seqs, S, heads, qkv, out, lse) : launch_flash_fwd<128, 8>(s, seqs, S, heads, qkv, out, lse);
+  return dh == 64 ? launch_flash_fwd<64, 4>(s, seqs, S, heads, qkv, out, lse) : launch_flash_fwd<128, 4>(s, seqs, S, heads, qkv, out, lse);
 }
 
-size_t attention_flash_bwd_scratch_bytes(int seqs, int S, int heads) { return (size_t)seqs * heads * S * 2 * sizeof(float); }
+size_t attention_flash_bwd_scratch_bytes(int seqs, int S, int heads) { return (size_t)seqs * heads * stat_rows(S) * 2 * sizeof(float); }
 
 hipError_t attention_flash_bwd(hipStream_t s, int seqs, int S, int heads, int dh, const uint16_t* qkv, const uint16_t* out,
                                const uint16_t* dout, const float* lse, uint16_t* dqkv, void* scratch, size_t scratch_bytes) {
@@ -707,11 +752,24 @@ hipError_t attention_flash_bwd(hipStream_t s, int seqs, int S, int heads, int dh
   hipLaunchKernelGGL(attn_stat_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, S, heads, dh, rows, dout, out, lse, stat);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = dh == 64 ? launch_flash_bwd<64, false>(s, seqs, S, heads, qkv, dout, stat, dqkv)
-               : launch_flash_bwd<128, false>(s, seqs, S, heads, qkv, dout, stat, dqkv);
-  if (e != hipSuccess) return e;
-  return dh == 64 ? launch_flash_bwd<64, true>(s, seqs, S, heads, qkv, dout, stat, dqkv)
-                  : launch_flash_bwd<128, true>(s, seqs, S, heads, qkv, dout, stat, dqkv);
+  auto both = [&](auto dq, auto dkv) {
+    const hipError_t err = dq(s, seqs, S, heads, qkv, dout, stat, dqkv);
+    return err != hipSuccess ? err : dkv(s, seqs, S, heads, qkv, dout, stat, dqkv);
+  };
+  const bool wide = dh == 128;
+  if (flash_waves(seqs, S, heads) == 8) {
+    if (S % 64 == 0)
+      return wide ? both(launch_flash_bwd<128, false, 8, true>, launch_flash_bwd<128, true, 8, true>)
+                  : both(launch_flash_bwd<64, false, 8, true>, launch_flash_bwd<64, true, 8, true>);
+    // (the dK/dV launch of ragged 128-wide heads does not fit the registers of eight waves)
+    return wide ? both(launch_flash_bwd<128, false, 8, false>, launch_flash_bwd<128, true, 4, false>)
+                : both(launch_flash_bwd<64, false, 8, false>, launch_flash_bwd<64, true, 8, false>);
+  }
+  if (S % 64 == 0)
+    return wide ? both(launch_flash_bwd<128, false, 4, true>, launch_flash_bwd<128, true, 4, true>)
+                : both(launch_flash_bwd<64, false, 4, true>, launch_flash_bwd<64, true, 4, true>);
+  return wide ? both(launch_flash_bwd<128, false, 4, false>, launch_flash_bwd<128, true, 4, false>)
+              : both(launch_flash_bwd<64, false, 4, false>, launch_flash_bwd<64, true, 4, false>);
 }
 
 hipError_t attention_mfma_fwd(hipStream_t s, int seqs, int S, int heads, int dh, const uint16_t* qkv, uint16_t* out, float* lse,

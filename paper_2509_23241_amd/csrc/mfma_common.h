@@ -316,14 +316,15 @@ struct ColDma {
 
   static __device__ __forceinline__ int swz(int k) { return R >= 128 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); }
 
-  __device__ __forceinline__ void init(int ld, int r0, int rows, int wave, int lane) {
+  // klast: k rows past it re-read it (a last, shorter k tile whose surplus the caller masks)
+  __device__ __forceinline__ void init(int ld, int r0, int rows, int wave, int lane, int klast = DBK - 1) {
 #pragma unroll
     for (int t = 0; t < kPerWave; ++t) {
       const int flat = 64 * (wave + NW * t) + lane;
       const int k = flat / kPerK;
       const int c = (flat % kPerK) ^ swz(k);
       // chunks past the edge re-read the last valid chunk: those columns are never stored
-      voff[t] = (uint32_t)(((size_t)k * ld + min(r0 + c * 8, rows - 8)) * 2);
+      voff[t] = (uint32_t)(((size_t)min(k, klast) * ld + min(r0 + c * 8, rows - 8)) * 2);
     }
   }
   __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, const uint16_t* base, int wave) const {
