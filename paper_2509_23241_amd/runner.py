@@ -5,6 +5,7 @@ order the library's own schedule generator gives.
 """
 from __future__ import annotations
 
+import threading
 from typing import Callable, Dict, List, Optional, Sequence
 
 import numpy as np
@@ -43,6 +44,30 @@ def _torch_dtype(dtype: str):
     return torch.bfloat16 if dtype == "bf16" else torch.float32
 
 
+# The runtime maps streams onto four hardware queues (its default) in the order they are created.  The default stream
+# has the first; three more streams get the others, and every further one shares a queue, i.e. waits in line, with one
+# of these.  So all stages on a device share three forward streams instead of creating their own: with a second and third
+# stage in the process whose streams shared the default stream's queue, a step of the conv4_x stage took 1.96 ms instead of
+# 1.73 ms on average, one of the last stage 1.20 ms instead of 1.00 ms.
+_forward_streams: Dict[int, List[torch.cuda.Stream]] = {}
+_forward_streams_lock = threading.Lock()
+
+
+def forward_streams(device: torch.device, count: int, besides: int) -> List[torch.cuda.Stream]:
+    """`count` of the device's forward streams, none of them the stream with the handle `besides`."""
+    with _forward_streams_lock:
+        index = device.index if device.index is not None else torch.cuda.current_device()
+        pool = _forward_streams.setdefault(index, [])
+        while len(pool) < B.TP_MAX_FORWARD_STREAMS:
+            pool.append(torch.cuda.Stream(device))
+        chosen = [q for q in pool if q.cuda_stream != besides]
+        while len(chosen) < count:                     # torch hands out its 32 streams again and again
+            q = torch.cuda.Stream(device)
+            if q.cuda_stream != besides and all(q.cuda_stream != c.cuda_stream for c in chosen):
+                chosen.append(q)
+        return chosen[:count]
+
+
 class GpuStage:
     """One pipeline stage on the current device; owns the torch tensors the library works in."""
 
@@ -52,7 +77,7 @@ class GpuStage:
                  needs_dx: Optional[bool] = None, device="cuda:0", stream: Optional[torch.cuda.Stream] = None,
                  forward_stream=False):
         """forward_stream: False / 0, or how many streams (default priority; True = 1) the stage gets for the forward
-        passes; what runs there is ordered on the stage's stream by forward_join() or any later call other than a
+        passes, the same ones for all stages on the device; what runs there is ordered on the stage's stream by forward_join() or any later call other than a
         forward or a backward (a backward waits for the forwards of its own mini-batch only)."""
         self.layers = [tuple(l) for l in layers]
         self.in_elems = B.layer_in_elems(self.layers[0])      # values per sample in / out of the stage
@@ -97,7 +122,7 @@ class GpuStage:
                             self.scratch.data_ptr(), self.diag.data_ptr())
         with torch.cuda.stream(self.stream):
             self.handle = B.stage_init(self.desc, bufs, self.stream.cuda_stream)
-        self.fwd_streams = [torch.cuda.Stream(self.device) for _ in range(int(forward_stream))]
+        self.fwd_streams = forward_streams(self.device, int(forward_stream), self.stream.cuda_stream)
         if self.fwd_streams:
             B.stage_set_forward_streams(self.handle, [q.cuda_stream for q in self.fwd_streams])
 
