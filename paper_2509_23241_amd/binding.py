@@ -268,9 +268,16 @@ def stage_destroy(st):
     _check(lib.stage_destroy(st))
 
 
+# The per-micro-batch and per-mini-batch calls: the argument types are declared above, so integers go in as they are.
+_byref = C.byref
+_stage_forward, _stage_backward, _stage_blend_update = lib.stage_forward, lib.stage_backward, lib.stage_blend_update
+
+
 def stage_forward(st, mb_id: int, ub_idx: int, x_dev: int, y_dev: int) -> int:
     v = _u64()
-    _check(lib.stage_forward(st, mb_id, ub_idx, _vp(x_dev), _vp(y_dev), C.byref(v)))
+    rc = _stage_forward(st, mb_id, ub_idx, x_dev, y_dev, _byref(v))
+    if rc:
+        _check(rc)
     return v.value
 
 
@@ -314,13 +321,17 @@ def stage_loss_softmax_ce(st, mb_id: int, logits_dev: int, labels_dev: int, dlog
 
 def stage_backward(st, mb_id: int, dy_dev: int, dx_dev: int) -> int:
     d = _u32()
-    _check(lib.stage_backward(st, mb_id, _vp(dy_dev), _vp(dx_dev), C.byref(d)))
+    rc = _stage_backward(st, mb_id, dy_dev, dx_dev, _byref(d))
+    if rc:
+        _check(rc)
     return d.value
 
 
 def stage_blend_update(st, mb_id_done: int, mb_id_next_bwd: int = TP_NONE) -> int:
     v = _u64()
-    _check(lib.stage_blend_update(st, mb_id_done, mb_id_next_bwd, C.byref(v)))
+    rc = _stage_blend_update(st, mb_id_done, mb_id_next_bwd, _byref(v))
+    if rc:
+        _check(rc)
     return v.value
 
 

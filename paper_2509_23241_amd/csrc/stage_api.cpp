@@ -418,6 +418,11 @@ struct tp_stage {
   hipEvent_t ev_main = nullptr;                           // "the stage's stream is ready for forwards"
   hipEvent_t ev_fwd[TP_MAX_FORWARD_STREAMS] = {};         // "this forward stream is done"
   bool main_dirty = true;                                 // the stage's stream got work other than forwards since ev_main was recorded
+  bool main_seen[TP_MAX_FORWARD_STREAMS] = {};            // the forward stream waits for ev_main as it was recorded last
+  // Recording an event or waiting for one costs the host and the stream as much as a small launch, so they are kept to
+  // one wait and one record per forward stream and mini-batch: 9 of them in a step of 4 micro-batches on two streams where
+  // one of each per forward makes 15.
+  hipEvent_t fwd_tail[TP_MAX_FORWARD_STREAMS] = {};       // an event recorded behind everything enqueued on the stream, or null
   bool fwd_pending[TP_MAX_FORWARD_STREAMS] = {};          // the stream holds forwards the stage's stream has not waited for yet
   // per activation slot (= mini-batch in flight) and forward stream: the last forward of that mini-batch there, which
   // its backward pass waits for -- and for no other, so that forwards of later mini-batches run beside it
@@ -482,8 +487,11 @@ int join_forwards(tp_stage* st) {
   st->main_dirty = true;
   for (int k = 0; k < TP_MAX_FORWARD_STREAMS; ++k) {
     if (!st->fwd_pending[k]) continue;
-    HIP_TRY(hipEventRecord(st->ev_fwd[k], st->fwd_stream[k]));
-    HIP_TRY(hipStreamWaitEvent(st->stream, st->ev_fwd[k], 0));
+    if (!st->fwd_tail[k]) {
+      HIP_TRY(hipEventRecord(st->ev_fwd[k], st->fwd_stream[k]));
+      st->fwd_tail[k] = st->ev_fwd[k];
+    }
+    HIP_TRY(hipStreamWaitEvent(st->stream, st->fwd_tail[k], 0));
     st->fwd_pending[k] = false;
     for (int q = 0; q < TP_MAX_IN_FLIGHT; ++q) st->slot_fwd[q][k] = false;  // ordered with everything else on the stream
   }
@@ -700,6 +708,7 @@ int stage_set_forward_streams(tp_stage* st, void* const* hip_streams, int32_t co
       if (!st->ev_slot[q][k]) HIP_TRY(hipEventCreateWithFlags(&st->ev_slot[q][k], hipEventDisableTiming));
   }
   for (int k = 0; k < TP_MAX_FORWARD_STREAMS; ++k) st->fwd_stream[k] = k < count ? (hipStream_t)hip_streams[k] : nullptr;
+  for (int k = 0; k < TP_MAX_FORWARD_STREAMS; ++k) st->fwd_tail[k] = nullptr;  // recorded on the streams before
   st->fwd_streams = count;
   st->main_dirty = true;
   return TP_OK;
@@ -846,29 +855,40 @@ int forward_impl(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_de
   // own stream takes a turn too (ub % (S + 1) == 0).  Every stream's forwards start behind everything the stage's
   // stream held before this run of forwards.
   hipStream_t fs = st->stream;
-  int fsk = -1;  // index of the forward stream in use
+  int fsk = -1, streams = 1;  // index of the forward stream in use, number of streams that take turns
   const int act_q = f->act_slot;
   if (st->fwd_streams > 0 && !st->prof_on) {
     if (st->main_dirty) {
       HIP_TRY(hipEventRecord(st->ev_main, st->stream));
       st->main_dirty = false;
+      for (bool& seen : st->main_seen) seen = false;
     }
-    fsk = d.max_in_flight == 1 ? (int)(ub_idx % (uint32_t)(st->fwd_streams + 1)) - 1 : (int)(ub_idx % (uint32_t)st->fwd_streams);
+    streams = d.max_in_flight == 1 ? st->fwd_streams + 1 : st->fwd_streams;
+    fsk = (int)(ub_idx % (uint32_t)streams) - (streams - st->fwd_streams);
     if (fsk >= 0) {
-      HIP_TRY(hipStreamWaitEvent(st->fwd_stream[fsk], st->ev_main, 0));
       fs = st->fwd_stream[fsk];
       st->fwd_pending[fsk] = true;
+      st->fwd_tail[fsk] = nullptr;
+      if (!st->main_seen[fsk]) {
+        HIP_TRY(hipStreamWaitEvent(fs, st->ev_main, 0));
+        st->main_seen[fsk] = true;
+      }
     }
   }
-  // however the call ends, what it enqueued on a forward stream is what the mini-batch's backward pass waits for
+  // The last forward of the mini-batch on its stream is what the mini-batch's backward pass, which needs all n of them,
+  // waits for -- however the call ends.
   struct MarkForward {
-    tp_stage* st; int q, k; hipStream_t s;
+    tp_stage* st; int q, k; hipStream_t s; bool last;
     ~MarkForward() {
-      if (k < 0) return;
-      if (hipEventRecord(st->ev_slot[q][k], s) == hipSuccess) st->slot_fwd[q][k] = true;
-      else st->slot_event_lost = true;
+      if (k < 0 || !last) return;
+      if (hipEventRecord(st->ev_slot[q][k], s) == hipSuccess) {
+        st->slot_fwd[q][k] = true;
+        st->fwd_tail[k] = st->ev_slot[q][k];
+      } else {
+        st->slot_event_lost = true;
+      }
     }
-  } mark_forward{st, act_q, fsk, fs};
+  } mark_forward{st, act_q, fsk, fs, (int)ub_idx + streams >= d.n};
   const uint64_t row0 = (uint64_t)ub_idx * d.mb;
   const int L = d.num_layers;
   for (int l = 0; l < L; ++l) {

@@ -158,11 +158,11 @@ class GpuStage:
     def forward(self, mb_id: int, ub: int, x: torch.Tensor, y: Optional[torch.Tensor] = None):
         if y is None:
             y = torch.empty(self.mb, self.out_elems, dtype=self.tdtype, device=self.device)
-        assert x.is_contiguous() and y.is_contiguous() and x.dtype == self.tdtype and y.dtype == self.tdtype
-        assert x.shape[0] == self.mb and x.numel() == self.mb * self.in_elems
-        assert y.shape[0] == self.mb and y.numel() == self.mb * self.out_elems
-        v = B.stage_forward(self.handle, mb_id, ub, x.data_ptr(), y.data_ptr())
-        return y, v
+        dtype, mb = self.tdtype, self.mb
+        assert x.dtype == dtype and y.dtype == dtype and x.is_contiguous() and y.is_contiguous()
+        assert len(x) == mb and x.numel() == mb * self.in_elems
+        assert len(y) == mb and y.numel() == mb * self.out_elems
+        return y, B.stage_forward(self.handle, mb_id, ub, x.data_ptr(), y.data_ptr())
 
     def forward_join(self):
         B.stage_forward_join(self.handle)
