@@ -220,7 +220,10 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(size_t nvec, const uint4
   for (size_t i = tid; i < tail_bytes; i += stride) tdst[i] = tsrc[i];
 }
 
-// One wave per row.
+// One wave per row.  The first 16 values of a lane (rows of up to 1024 classes: all of them) are loaded together and kept
+// in registers for the three passes over the row; fetched again in every pass, one memory latency per 64 classes, 400 rows
+// of 1000 classes took 12.2 us.
+constexpr int kHeld = 16;
 template <typename T>
 __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(int rows, int classes, const T* __restrict__ logits,
                                                               const int32_t* __restrict__ labels,
@@ -229,22 +232,34 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(int rows, int clas
   const int row = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   if (row >= rows) return;
   const T* lg = logits + (size_t)row * classes;
+  const int label = labels[row];
+  float v[kHeld];
+#pragma unroll
+  for (int i = 0; i < kHeld; ++i) v[i] = lane + 64 * i < classes ? to_float(lg[lane + 64 * i]) : -INFINITY;
   float mx = -INFINITY;
-  for (int c = lane; c < classes; c += 64) mx = fmaxf(mx, to_float(lg[c]));
+#pragma unroll
+  for (int i = 0; i < kHeld; ++i) mx = fmaxf(mx, v[i]);
+  for (int c = lane + 64 * kHeld; c < classes; c += 64) mx = fmaxf(mx, to_float(lg[c]));
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
   float sum = 0.f;
-  for (int c = lane; c < classes; c += 64) sum += expf(to_float(lg[c]) - mx);
+#pragma unroll
+  for (int i = 0; i < kHeld; ++i)
+    if (lane + 64 * i < classes) sum += expf(v[i] - mx);
+  for (int c = lane + 64 * kHeld; c < classes; c += 64) sum += expf(to_float(lg[c]) - mx);
   sum = wave_sum(sum);
   const float lse = logf(sum);
-  const int label = labels[row];
   const float inv_rows = 1.0f / (float)rows;
   T* dl = dlogits + (size_t)row * classes;
-  for (int c = lane; c < classes; c += 64) {
-    const float p = expf(to_float(lg[c]) - mx - lse);
+  auto put = [&](int c, float z) {
+    const float p = expf(z - mx - lse);
     dl[c] = from_float<T>((p - (c == label ? 1.f : 0.f)) * inv_rows);
-  }
-  if (lane == 0) row_loss[row] = -(to_float(lg[label]) - mx - lse);
+    if (c == label) row_loss[row] = -(z - mx - lse);
+  };
+#pragma unroll
+  for (int i = 0; i < kHeld; ++i)
+    if (lane + 64 * i < classes) put(lane + 64 * i, v[i]);
+  for (int c = lane + 64 * kHeld; c < classes; c += 64) put(c, to_float(lg[c]));
 }
 
 __global__ __launch_bounds__(kThreads) void mean_kernel(const float* __restrict__ v, int count, float* __restrict__ out) {
