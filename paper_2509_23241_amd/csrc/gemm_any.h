@@ -9,7 +9,7 @@ namespace tp {
 
 // fp32 dense layers, any shape and alignment; arguments as launch_fprop, launch_dgrad and launch_wgrad.
 hipError_t f32_fprop(hipStream_t s, int M, int N, int K, const float* x, const float* W, const float* bias, int act, float* d_out,
-                     float* a_out);
+                     float* a_out, float* x_copy);
 hipError_t f32_dgrad(hipStream_t s, int M, int N, int K, const float* dz, const float* Wb, const float* d_prev, float* out,
                      int relu_mask);
 // partial: scratch of f32_wgrad_splits(M, N, K) * N * K floats where that is more than one range, or null

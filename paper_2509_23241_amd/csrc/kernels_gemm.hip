@@ -341,15 +341,15 @@ hipError_t launch_fprop(hipStream_t s, int elt, int M, int N, int K, const void*
   if (elt == ELT_BF16 && mfma_fprop_supported(M, N, K) && aligned)
     return mfma_fprop(s, M, N, K, (const uint16_t*)x, (const uint16_t*)W, bias, act, (uint16_t*)d_out, (uint16_t*)a_out,
                       (uint16_t*)x_copy, (const uint16_t*)addend);
+  if (elt == ELT_F32)
+    return f32_fprop(s, M, N, K, (const float*)x, (const float*)W, bias, act, (float*)d_out, (float*)a_out, (float*)x_copy);
   if (x_copy) {
-    hipError_t err = launch_copy(s, x, x_copy, (size_t)M * K * (elt == ELT_BF16 ? 2 : 4));
+    hipError_t err = launch_copy(s, x, x_copy, (size_t)M * K * 2);
     if (err != hipSuccess) return err;
   }
-  if (elt == ELT_BF16 && mfma_fprop_supported(M, N, K))
+  if (mfma_fprop_supported(M, N, K))
     return mfma_fprop(s, M, N, K, (const uint16_t*)x, (const uint16_t*)W, bias, act, (uint16_t*)d_out, (uint16_t*)a_out,
                       nullptr, (const uint16_t*)addend);
-  if (elt == ELT_F32)
-    return f32_fprop(s, M, N, K, (const float*)x, (const float*)W, bias, act, (float*)d_out, (float*)a_out);
   EpiArgs e{};
   e.bias = bias; e.d_out = d_out; e.a_out = a_out; e.act = act;
   return simt<EPI_FPROP>(s, M, N, K, x, K, 1, W, 1, K, e);

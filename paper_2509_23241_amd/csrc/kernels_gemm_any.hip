@@ -491,7 +491,7 @@ struct EpiPartial {
 // multiplied, so that a wave that has its SIMD to itself waits for LDS once per barrier and not once per step.
 template <class T, class Sum, int BM, int BN, int WGM, int WGN, int NS, int U, class AL, class BL, class Epi>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_any_kernel(int M, int N, int KT, int per, typename AL::Desc ad,
-                                                                  typename BL::Desc bd, Epi epi, TileMap map) {
+                                                                  typename BL::Desc bd, Epi epi, TileMap map, SideCopy side) {
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, NW = WGM * WGN;
   constexpr int kABytes = BM * 128, kStage = (BM + BN) * 128;
   constexpr int kLoads = AL::kPerWave + BL::kPerWave;
@@ -501,6 +501,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_any_kernel(int M, int N, 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
+  const int tiles = map.tiles_m * map.tiles_n;
+  if ((int)blockIdx.x >= tiles) {
+    // Workgroups behind the tiles copy.  Shared among the tiles' workgroups the copy added its own latency to theirs: 7.0 to
+    // 8.4 us for 32 rows of 512 by 512, where a launch of its own takes 2.2 us.
+    const size_t step = (size_t)(gridDim.x - tiles) * (64 * NW);
+    for (size_t i = (size_t)(blockIdx.x - tiles) * (64 * NW) + threadIdx.x; i < side.nvec; i += step) side.dst[i] = side.src[i];
+    return;
+  }
   int tile_m, tile_n;
   map.get(blockIdx.x, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
@@ -580,7 +588,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_any_kernel(int M, int N, 
 
 template <class T, class Sum, int BM, int BN, int WGM, int WGN, int NS, int U, class AL, class BL, class Epi>
 hipError_t launch_any(hipStream_t s, int M, int N, int KT, int splits, const typename AL::Desc& ad, const typename BL::Desc& bd,
-                      const Epi& epi) {
+                      const Epi& epi, const SideCopy& side) {
   constexpr size_t lds_bytes = (size_t)NS * U * (BM + BN) * 128;
   static_assert(lds_bytes <= 160 * 1024, "stages do not fit the LDS of a CU");
   auto kernel = gemm_any_kernel<T, Sum, BM, BN, WGM, WGN, NS, U, AL, BL, Epi>;
@@ -593,8 +601,10 @@ hipError_t launch_any(hipStream_t s, int M, int N, int KT, int splits, const typ
   const int per = (KT + splits - 1) / splits;
   const int ranges = (KT + per - 1) / per;  // every one of them has a tile to sum; ranges == splits by any_splits
   if (ranges != splits) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n, ranges), dim3(64 * WGM * WGN), lds_bytes, s, M, N, KT, per, ad, bd, epi,
-                     make_tile_map(tiles_m, tiles_n));
+  constexpr int kThreads = 64 * WGM * WGN;
+  const unsigned copiers = (unsigned)std::min<size_t>((side.nvec + 4 * kThreads - 1) / (4 * kThreads), 64);
+  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n + copiers, ranges), dim3(kThreads), lds_bytes, s, M, N, KT, per, ad, bd, epi,
+                     make_tile_map(tiles_m, tiles_n), side);
   return hipGetLastError();
 }
 
@@ -692,13 +702,14 @@ template <class T, class Sum, int VEC> struct WgradConv {
 };
 
 template <class T, class Sum, template <class, class, int> class Product, int VEC, class AD, class BD, class Epi>
-hipError_t run(hipStream_t s, int M, int N, int K, const AD& ad, const BD& bd, const Epi& epi, bool split = false) {
+hipError_t run(hipStream_t s, int M, int N, int K, const AD& ad, const BD& bd, const Epi& epi, bool split = false,
+               const SideCopy& side = SideCopy{nullptr, nullptr, 0}) {
   using P = Product<T, Sum, VEC>;
   const int KT = (K + kTileK<T> - 1) / kTileK<T>;
   int ranges = 1;
 #define TP_ANY(E, WGM, WGN, NS, U)                                                                                           \
   launch_any<T, Sum, E, E, WGM, WGN, NS, U, typename P::template A<E, WGM * WGN>, typename P::template B<E, WGM * WGN>>( \
-      s, M, N, KT, ranges, ad, bd, epi)
+      s, M, N, KT, ranges, ad, bd, epi, side)
   switch (pick_tile<T, Sum>(M, N, KT, split, &ranges)) {
     case Tile::k128:
       if constexpr (!(sizeof(T) == 2 && __is_same(Sum, Chain))) return TP_ANY(128, 4, 2, 3, 1);
@@ -722,11 +733,22 @@ int ranges_of(int M, int N, int K) {
 
 // ---- dense, fp32 -------------------------------------------------------------------------------
 hipError_t f32_fprop(hipStream_t s, int M, int N, int K, const float* x, const float* W, const float* bias, int act, float* d_out,
-                     float* a_out) {
+                     float* a_out, float* x_copy) {
+  SideCopy side{nullptr, nullptr, 0};
+  if (x_copy) {
+    // Behind the tiles a copy of 64 KB is hidden (pipeline of 256-512-512-10, batches of 32: 1268 us to 1140 us); one of 512 KB
+    // takes slots from products on other streams (stage of 1024, micro-batches of 128: 151 us, 145 us with a launch of its own).
+    if (aligned16(x, x_copy) && (size_t)M * K % 4 == 0 && (size_t)M * K <= 65536) {
+      side = SideCopy{(const uint4*)x, (uint4*)x_copy, (size_t)M * K / 4};
+    } else {
+      const hipError_t e = launch_copy(s, x, x_copy, (size_t)M * K * 4);
+      if (e != hipSuccess) return e;
+    }
+  }
   const DenseDesc a{x, K, M, K}, b{W, K, N, K};
   const EpiForward<float> e{bias, d_out, a_out, act, N, N % 4 == 0 && aligned16(d_out, a_out)};
-  if (K % 4 == 0 && aligned16(x, W)) return run<float, Chain, FpropDense, 4>(s, M, N, K, a, b, e);
-  return run<float, Chain, FpropDense, 1>(s, M, N, K, a, b, e);
+  if (K % 4 == 0 && aligned16(x, W)) return run<float, Chain, FpropDense, 4>(s, M, N, K, a, b, e, false, side);
+  return run<float, Chain, FpropDense, 1>(s, M, N, K, a, b, e, false, side);
 }
 
 hipError_t f32_dgrad(hipStream_t s, int M, int N, int K, const float* dz, const float* Wb, const float* d_prev, float* out,

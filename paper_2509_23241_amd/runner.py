@@ -160,8 +160,8 @@ class GpuStage:
             y = torch.empty(self.mb, self.out_elems, dtype=self.tdtype, device=self.device)
         dtype, mb = self.tdtype, self.mb
         assert x.dtype == dtype and y.dtype == dtype and x.is_contiguous() and y.is_contiguous()
-        assert len(x) == mb and x.numel() == mb * self.in_elems
-        assert len(y) == mb and y.numel() == mb * self.out_elems
+        assert x.size(0) == mb and x.numel() == mb * self.in_elems
+        assert y.size(0) == mb and y.numel() == mb * self.out_elems
         return y, B.stage_forward(self.handle, mb_id, ub, x.data_ptr(), y.data_ptr())
 
     def forward_join(self):
