@@ -1,8 +1,7 @@
 // GEMM launchers of a stage: fprop (z = x W^T + b, a = act(z)), dgrad (dx = dz W_b, fused with
 // the previous layer's activation derivative) and wgrad (dW = dz^T x, db = column sums of dz).
 //
-// This file holds the shape-generic, bounds-checked SIMT kernel (fp32 FMA, LDS-tiled) that serves bf16
-// shapes the MFMA kernels do not take, and the dispatch.
+// This file holds the dispatch by element type and the column sums and sums of partial results.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -17,96 +16,7 @@ namespace tp {
 
 namespace {
 
-constexpr int BM = 64, BN = 64, BK = 16, kThreads = 256;
-
-enum Epi : int { EPI_STORE_F32 = 0, EPI_FPROP = 1, EPI_DGRAD = 2 };
-
-struct EpiArgs {
-  float* c_f32;        // EPI_STORE_F32: [M x N] fp32
-  const float* bias;   // EPI_FPROP
-  void* d_out;         // EPI_FPROP: optional act'(z)
-  void* a_out;         // EPI_FPROP: activation; EPI_DGRAD: output
-  const void* d_prev;  // EPI_DGRAD: optional saved act'(z) of the previous layer
-  int act;
-  int relu_mask;       // EPI_DGRAD: d_prev holds the ReLU output, the factor is (output > 0)
-};
-
-// C(m,n) = sum_k A[m*sam + k*sak] * B[k*sbk + n*sbn], 64x64 tile per block, 4x4 per thread.
-template <typename T, int EPI>
-__global__ __launch_bounds__(kThreads) void gemm_simt_kernel(int M, int N, int K, const T* __restrict__ A, long sam,
-                                                             long sak, const T* __restrict__ B, long sbk, long sbn,
-                                                             EpiArgs e) {
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  const int t = threadIdx.x;
-  const int tx = t & 15, ty = t >> 4;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  float acc[4][4] = {};
-  const bool a_kfast = sak == 1, b_kfast = sbk == 1;
-  for (int k0 = 0; k0 < K; k0 += BK) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int el = t + i * kThreads;
-      int m, k;
-      if (a_kfast) { k = el & (BK - 1); m = el >> 4; } else { m = el & (BM - 1); k = el >> 6; }
-      float v = 0.f;
-      if (m0 + m < M && k0 + k < K) v = to_float(A[(long)(m0 + m) * sam + (long)(k0 + k) * sak]);
-      As[k][m] = v;
-      int n, kb;
-      if (b_kfast) { kb = el & (BK - 1); n = el >> 4; } else { n = el & (BN - 1); kb = el >> 6; }
-      float w = 0.f;
-      if (n0 + n < N && k0 + kb < K) w = to_float(B[(long)(k0 + kb) * sbk + (long)(n0 + n) * sbn]);
-      Bs[kb][n] = w;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < BK; ++k) {
-      const float4 a = *reinterpret_cast<const float4*>(&As[k][ty * 4]);
-      const float4 b = *reinterpret_cast<const float4*>(&Bs[k][tx * 4]);
-      const float av[4] = {a.x, a.y, a.z, a.w};
-      const float bv[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      const size_t idx = (size_t)m * N + n;
-      float v = acc[i][j];
-      if (EPI == EPI_STORE_F32) {
-        e.c_f32[idx] = v;
-      } else if (EPI == EPI_FPROP) {
-        v += e.bias[n];
-        if (e.d_out) ((T*)e.d_out)[idx] = from_float<T>(act_derivative(v, e.act));
-        ((T*)e.a_out)[idx] = from_float<T>(act_forward(v, e.act));
-      } else {
-        if (e.d_prev) {
-          const float dp = to_float(((const T*)e.d_prev)[idx]);
-          v = e.relu_mask ? (dp > 0.f ? v : 0.f) : v * dp;
-        }
-        ((T*)e.a_out)[idx] = from_float<T>(v);
-      }
-    }
-  }
-}
-
-template <int EPI>
-hipError_t simt(hipStream_t s, int M, int N, int K, const void* A, long sam, long sak, const void* B, long sbk, long sbn,
-                const EpiArgs& e) {
-  dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM);
-  hipLaunchKernelGGL((gemm_simt_kernel<uint16_t, EPI>), grid, dim3(kThreads), 0, s, M, N, K, (const uint16_t*)A, sam, sak,
-                     (const uint16_t*)B, sbk, sbn, e);
-  return hipGetLastError();
-}
+constexpr int kThreads = 256;
 
 // Column sums of dz[M x N] in two fixed-order steps: row chunks -> partials[chunk][N] -> gb[N].
 // A lane owns V = 16/sizeof(T) adjacent columns (one 16-byte load per row).  A block covers up
@@ -332,39 +242,22 @@ size_t colsum_scratch_floats(int M, int N) {
   return (size_t)std::max(colsum_shape(M, N, 4).chunks, colsum_shape(M, N, 8).chunks) * (size_t)N;
 }
 
-bool fprop_add_supported(int elt, int M, int N, int K) { return elt == ELT_BF16 && mfma_fprop_supported(M, N, K) && N % 8 == 0; }
+bool fprop_add_supported(int elt, int M, int N, int K) { return elt == ELT_BF16 && M >= 1 && N % 8 == 0 && K % 8 == 0; }
 
 hipError_t launch_fprop(hipStream_t s, int elt, int M, int N, int K, const void* x, const void* W, const float* bias,
                         int act, void* d_out, void* a_out, void* x_copy, const void* addend) {
   if (addend && (!fprop_add_supported(elt, M, N, K) || ((uintptr_t)addend & 15))) return hipErrorNotSupported;
-  const bool aligned = (((uintptr_t)x | (uintptr_t)x_copy) & 15) == 0;
-  if (elt == ELT_BF16 && mfma_fprop_supported(M, N, K) && aligned)
-    return mfma_fprop(s, M, N, K, (const uint16_t*)x, (const uint16_t*)W, bias, act, (uint16_t*)d_out, (uint16_t*)a_out,
-                      (uint16_t*)x_copy, (const uint16_t*)addend);
   if (elt == ELT_F32)
     return f32_fprop(s, M, N, K, (const float*)x, (const float*)W, bias, act, (float*)d_out, (float*)a_out, (float*)x_copy);
-  if (x_copy) {
-    hipError_t err = launch_copy(s, x, x_copy, (size_t)M * K * 2);
-    if (err != hipSuccess) return err;
-  }
-  if (mfma_fprop_supported(M, N, K))
-    return mfma_fprop(s, M, N, K, (const uint16_t*)x, (const uint16_t*)W, bias, act, (uint16_t*)d_out, (uint16_t*)a_out,
-                      nullptr, (const uint16_t*)addend);
-  EpiArgs e{};
-  e.bias = bias; e.d_out = d_out; e.a_out = a_out; e.act = act;
-  return simt<EPI_FPROP>(s, M, N, K, x, K, 1, W, 1, K, e);
+  return mfma_fprop(s, M, N, K, (const uint16_t*)x, (const uint16_t*)W, bias, act, (uint16_t*)d_out, (uint16_t*)a_out,
+                    (uint16_t*)x_copy, (const uint16_t*)addend);
 }
 
 hipError_t launch_dgrad(hipStream_t s, int elt, int M, int N, int K, const void* dz, const void* Wb, const void* d_prev,
                         void* out, int relu_mask) {
-  if (elt == ELT_BF16 && mfma_dgrad_supported(M, N, K))
-    return mfma_dgrad(s, M, N, K, (const uint16_t*)dz, (const uint16_t*)Wb, (const uint16_t*)d_prev, (uint16_t*)out, relu_mask);
   if (elt == ELT_F32)
     return f32_dgrad(s, M, N, K, (const float*)dz, (const float*)Wb, (const float*)d_prev, (float*)out, relu_mask);
-  EpiArgs e{};
-  e.a_out = out; e.d_prev = d_prev; e.relu_mask = relu_mask;
-  // out[M x K] = dz[M x N] . Wb[N x K]: contraction over N
-  return simt<EPI_DGRAD>(s, M, K, N, dz, N, 1, Wb, K, 1, e);
+  return mfma_dgrad(s, M, N, K, (const uint16_t*)dz, (const uint16_t*)Wb, (const uint16_t*)d_prev, (uint16_t*)out, relu_mask);
 }
 
 void set_sum_sink(std::vector<SumJob>* sink) { g_sum_sink = sink; }
@@ -451,21 +344,14 @@ hipError_t launch_act_backward_colsum(hipStream_t s, int elt, int M, int N, cons
 }
 
 size_t wgrad_scratch_floats(int elt, int M, int N, int K) {
-  if (elt == ELT_F32) {
-    const int splits = f32_wgrad_splits(M, N, K);
-    return splits > 1 ? (size_t)splits * N * K : 0;
-  }
-  return mfma_wgrad_supported(M, N, K) ? mfma_wgrad_scratch_floats(M, N, K) : 0;
+  if (elt == ELT_BF16) return mfma_wgrad_scratch_floats(M, N, K);
+  const int splits = f32_wgrad_splits(M, N, K);
+  return splits > 1 ? (size_t)splits * N * K : 0;
 }
 
 hipError_t launch_wgrad(hipStream_t s, int elt, int M, int N, int K, const void* dz, const void* x, float* gW, float* partial) {
-  if (elt == ELT_BF16 && mfma_wgrad_supported(M, N, K))
-    return mfma_wgrad(s, M, N, K, (const uint16_t*)dz, (const uint16_t*)x, gW, partial);
   if (elt == ELT_F32) return f32_wgrad(s, M, N, K, (const float*)dz, (const float*)x, gW, partial);
-  EpiArgs e{};
-  e.c_f32 = gW;
-  // gW[N x K] = dz^T[N x M] . x[M x K]: contraction over M
-  return simt<EPI_STORE_F32>(s, N, K, M, dz, 1, N, x, K, 1, e);
+  return mfma_wgrad(s, M, N, K, (const uint16_t*)dz, (const uint16_t*)x, gW, partial);
 }
 
 }  // namespace tp

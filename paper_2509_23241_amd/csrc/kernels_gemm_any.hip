@@ -31,20 +31,6 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-__device__ uint4 g_zero_chunk;  // what copies of nothing read
-
-__device__ __forceinline__ const char* zero_chunk() { return reinterpret_cast<const char*>(&g_zero_chunk); }
-
-// 16 or 4 bytes per lane, global -> LDS address + lane * (16 or 4)
-template <int BYTES>
-__device__ __forceinline__ void dma_addr(uint32_t lds_byte_addr, const void* lane_ptr) {
-  static_assert(BYTES == 16 || BYTES == 4, "copies of one chunk or one word per lane");
-  if constexpr (BYTES == 16)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_byte_addr), "v"(lane_ptr) : "memory");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(lds_byte_addr), "v"(lane_ptr) : "memory");
-}
-
 // ---- LDS stages --------------------------------------------------------------------------------
 // k-contiguous operand: [R rows][8 chunks of 16 bytes], chunk c of row r in slot c ^ ((r / 2) % 8): the 16 rows of a
 // fragment read fall into different banks.

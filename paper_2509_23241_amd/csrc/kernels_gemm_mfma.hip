@@ -10,12 +10,12 @@
 // lane gets its 8 k values through two LDS transpose reads.
 //
 // Two kernels share the tile and epilogue code:
-//   gemm_bf16_mfma_kernel  any shape whose extents are multiples of 8: global loads go through
-//                          registers, one k tile ahead, LDS double buffered and padded.
-//   gemm_bf16_dma_kernel   contraction extent a multiple of 64: global loads write LDS directly
-//                          (global_load_lds_dwordx4), NS stages deep, no staging registers; LDS is
-//                          unpadded, bank conflicts are avoided by an XOR swizzle of the 16-byte
+//   gemm_bf16_dma_kernel   16-byte aligned operands whose rows are whole 16-byte chunks: global loads write
+//                          LDS directly (global_load_lds_dwordx4), NS stages deep, no staging registers;
+//                          LDS is unpadded, bank conflicts are avoided by an XOR swizzle of the 16-byte
 //                          chunks, applied on the global side of the copy.
+//   gemm_bf16_any_kernel   any extents and alignment: global loads go through registers, three k tiles
+//                          ahead, LDS double buffered and padded.
 // Workgroup ids are remapped so that the workgroups of one XCD (ids equal mod 8) cover a
 // compact 2-D patch of output tiles and share their operand panels in that XCD's L2.
 #include <hip/hip_runtime.h>
@@ -33,6 +33,23 @@ namespace tp {
 namespace {
 
 
+inline int k_tiles(int K) { return (K + DBK - 1) / DBK; }
+
+// 8 consecutive values from an address of any (2-byte) alignment, those from `valid` on zero and not read
+__device__ __forceinline__ uint4 load8(const uint16_t* p, int valid) {
+  uint4 v = make_uint4(0, 0, 0, 0);
+  if (valid >= 8) {
+    __builtin_memcpy(&v, p, 16);
+  } else if (valid > 0) {
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < 7; ++j)
+      if (j < valid) w[j >> 1] |= (uint32_t)p[j] << (16 * (j & 1));
+    v = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+  return v;
+}
+
 // ---- staging of one operand tile -------------------------------------------------------------
 // k-contiguous operand: tile [R rows][BKT k]; memory element (r, k) at base[r*ld + k].
 template <int R, int BKT, int NT>
@@ -46,13 +63,12 @@ struct RowTile {
 
   static __device__ __forceinline__ void load(uint4 (&regs)[kChunks], const uint16_t* __restrict__ base, int ld, int r0,
                                               int rows, int k0, int K) {
-    const int c = threadIdx.x % kPerRow;
-    const int k = k0 + c * 8;
+    const int k = k0 + (threadIdx.x % kPerRow) * 8;
 #pragma unroll
     for (int i = 0; i < kChunks; ++i) {
       const int r = threadIdx.x / kPerRow + kRowStep * i;
-      const int gr = min(r0 + r, rows - 1);  // clamp: rows past the edge are computed but never stored
-      regs[i] = k < K ? *reinterpret_cast<const uint4*>(base + (size_t)gr * ld + k) : make_uint4(0, 0, 0, 0);
+      // clamp: rows past the edge are computed but never stored
+      regs[i] = load8(base + (size_t)min(r0 + r, rows - 1) * ld + k, K - k);
     }
   }
   static __device__ __forceinline__ void store(const uint4 (&regs)[kChunks], uint16_t* lds) {
@@ -89,10 +105,8 @@ struct ColTile {
 #pragma unroll
     for (int i = 0; i < kChunks; ++i) {
       const int id = threadIdx.x + NT * i;
-      const int c = id % kPerK, k = id / kPerK;
-      const int r = r0 + c * 8;
-      const bool ok = (k0 + k < K) && (r + 8 <= rows);
-      regs[i] = ok ? *reinterpret_cast<const uint4*>(base + (size_t)(k0 + k) * ld + r) : make_uint4(0, 0, 0, 0);
+      const int r = r0 + (id % kPerK) * 8, k = k0 + id / kPerK;
+      regs[i] = load8(base + (size_t)k * ld + r, k < K ? rows - r : 0);
     }
   }
   static __device__ __forceinline__ void store(const uint4 (&regs)[kChunks], uint16_t* lds) {
@@ -122,12 +136,26 @@ template <int R, int BKT, int NT>
 struct TileSel<R, BKT, NT, true> { using type = ColTile<R, BKT, NT>; };
 
 
-// ---- the kernel --------------------------------------------------------------------------------
-template <int BM, int BN, int WGM, int WGN, int BKT, bool A_COL, bool B_COL, class Epi>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_mfma_kernel(int M, int N, int K,
-                                                                         const uint16_t* __restrict__ A, int lda,
-                                                                         const uint16_t* __restrict__ B, int ldb,
-                                                                         Epi epi, TileMap map) {
+// output of contraction range `split`: only the fp32 weight-gradient product is ever split
+template <class E>
+__device__ __forceinline__ const E& epi_of_split(const E& e, int) { return e; }
+struct EpiWgradSplit {
+  float* out; int ldc; size_t split_stride;
+  static constexpr bool kSwap = false;
+};
+__device__ __forceinline__ EpiWgrad epi_of_split(const EpiWgradSplit& e, int split) {
+  return EpiWgrad{e.out + (size_t)split * e.split_stride, e.ldc};
+}
+
+// ---- any extents and alignment ------------------------------------------------------------------
+// Bound by the latency of its loads at the few workgroups it mostly has.  PF: k tiles in flight in registers (with one,
+// every k tile cost a memory latency: 0.7 us at 100 x 2000 x 2000).  Against bounds-checked fp32 FMAs: stage of width 2315
+// 1039 -> 267 us, 783 491 -> 150 us, of width 70 with 200 classes 1095 -> 216 us.
+template <int BM, int BN, int WGM, int WGN, int BKT, int PF, bool A_COL, bool B_COL, class Epi>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_any_kernel(int M, int N, int K, int per,
+                                                                        const uint16_t* __restrict__ A, int lda,
+                                                                        const uint16_t* __restrict__ B, int ldb,
+                                                                        Epi epi, TileMap map) {
   constexpr int NT = 64 * WGM * WGN;
   using ATile = typename TileSel<BM, BKT, NT, A_COL>::type;
   using BTile = typename TileSel<BN, BKT, NT, B_COL>::type;
@@ -169,64 +197,47 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_mfma_kernel(int M, i
     }
   };
 
-  uint4 ra[ATile::kChunks], rb[BTile::kChunks];
-  const int KT = (K + BKT - 1) / BKT;
-  ATile::load(ra, A, lda, m0, M, 0, K);
-  BTile::load(rb, B, ldb, n0, N, 0, K);
-  ATile::store(ra, lds_a(0));
-  BTile::store(rb, lds_b(0));
-  __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < KT) {
-      ATile::load(ra, A, lda, m0, M, (kt + 1) * BKT, K);
-      BTile::load(rb, B, ldb, n0, N, (kt + 1) * BKT, K);
+  // k tiles first .. end - 1: the contraction range blockIdx.y, `per` tiles long
+  const int first = blockIdx.y * per, end = min(first + per, (K + BKT - 1) / BKT);
+  uint4 ra[PF][ATile::kChunks], rb[PF][BTile::kChunks];
+#pragma unroll
+  for (int u = 0; u < PF; ++u)
+    if (first + u < end) {
+      ATile::load(ra[u], A, lda, m0, M, (first + u) * BKT, K);
+      BTile::load(rb[u], B, ldb, n0, N, (first + u) * BKT, K);
     }
-    compute(cur);
-    if (kt + 1 < KT) {
-      ATile::store(ra, lds_a(cur ^ 1));
-      BTile::store(rb, lds_b(cur ^ 1));
+  static_assert(PF % 2 == 0, "LDS buffers alternate with the k tiles of a run");
+  for (int kt = first; kt < end; kt += PF) {
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      if (kt + u >= end) break;  // uniform
+      ATile::store(ra[u], lds_a(u & 1));
+      BTile::store(rb[u], lds_b(u & 1));
+      // tile kt + u visible; the other buffer is free once every wave is here, behind its reads of the tile before
+      lds_barrier();
+      if (kt + u + PF < end) {
+        ATile::load(ra[u], A, lda, m0, M, (kt + u + PF) * BKT, K);
+        BTile::load(rb[u], B, ldb, n0, N, (kt + u + PF) * BKT, K);
+      }
+      compute(u & 1);
     }
-    __syncthreads();
   }
-
-  store_tiles<TM, TN>(acc, epi, m0 + wm, n0 + wn, M, N, lane);
+  store_tiles<TM, TN>(acc, epi_of_split(epi, blockIdx.y), m0 + wm, n0 + wn, M, N, lane);
 }
 
-template <int BM, int BN, int WGM, int WGN, int BKT, bool A_COL, bool B_COL, class Epi>
-hipError_t launch(hipStream_t s, int M, int N, int K, const uint16_t* A, int lda, const uint16_t* B, int ldb,
-                  const Epi& epi, SideCopy side = SideCopy{nullptr, nullptr, 0}) {
-  if (side.nvec) {  // this kernel has no side job: a plain copy first
-    hipError_t e = hipMemcpyAsync(side.dst, side.src, side.nvec * 16, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-  }
-  constexpr int NT = 64 * WGM * WGN;
-  using ATile = typename TileSel<BM, BKT, NT, A_COL>::type;
-  using BTile = typename TileSel<BN, BKT, NT, B_COL>::type;
+template <int BM, int BN, int WGM, int WGN, bool A_COL, bool B_COL, class Epi>
+hipError_t launch_any(hipStream_t s, int M, int N, int K, const uint16_t* A, int lda, const uint16_t* B, int ldb, const Epi& epi,
+                      int per) {
+  constexpr int NT = 64 * WGM * WGN, PF = 4;
+  using ATile = typename TileSel<BM, DBK, NT, A_COL>::type;
+  using BTile = typename TileSel<BN, DBK, NT, B_COL>::type;
   constexpr size_t lds_bytes = 2 * (ATile::kLdsElems + BTile::kLdsElems) * sizeof(uint16_t);
-  static_assert(lds_bytes <= 160 * 1024, "tile does not fit the LDS of a CU");
-  auto kernel = gemm_bf16_mfma_kernel<BM, BN, WGM, WGN, BKT, A_COL, B_COL, Epi>;
-  if (lds_bytes > 64 * 1024) {
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (attr != hipSuccess) return attr;
-  }
+  static_assert(lds_bytes <= 64 * 1024, "more LDS than a launch has without asking for it");
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  const TileMap map = make_tile_map(tiles_m, tiles_n);
-  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(NT), lds_bytes, s, M, N, K, A, lda, B, ldb, epi, map);
+  hipLaunchKernelGGL((gemm_bf16_any_kernel<BM, BN, WGM, WGN, DBK, PF, A_COL, B_COL, Epi>),
+                     dim3(tiles_m * tiles_n, (k_tiles(K) + per - 1) / per), dim3(NT), lds_bytes, s, M, N, K, per, A, lda, B, ldb,
+                     epi, make_tile_map(tiles_m, tiles_n));
   return hipGetLastError();
-}
-
-
-// output of contraction range `split`: only the fp32 weight-gradient product is ever split
-template <class E>
-__device__ __forceinline__ const E& epi_of_split(const E& e, int) { return e; }
-struct EpiWgradSplit {
-  float* out; int ldc; size_t split_stride;
-  static constexpr bool kSwap = false;
-};
-__device__ __forceinline__ EpiWgrad epi_of_split(const EpiWgradSplit& e, int split) {
-  return EpiWgrad{e.out + (size_t)split * e.split_stride, e.ldc};
 }
 
 // LEAN: small wave tiles (one or two 32x32 blocks) have so few MFMAs per k tile that the address and stage
@@ -237,9 +248,11 @@ __device__ __forceinline__ EpiWgrad epi_of_split(const EpiWgradSplit& e, int spl
 // ROT: the barrier that makes a k tile visible sits one k step early, before the last MFMA group of the tile
 // before it, so that the first fragment reads of the new tile run under that group instead of stalling the wave
 // (with one wave per SIMD nothing else would cover them).
-template <int BM, int BN, int WGM, int WGN, int NS, bool A_COL, bool B_COL, class Epi, bool LEAN = false,
-          bool ROT = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, int N, int K,
+// TAIL: the contraction is no whole number of k tiles; what the last tile lacks is copied from a block of zeros, for
+// both operands.  A kernel of its own, so that whole ones carry no second form of the copies.  Through registers, as in
+// the kernel above with one k tile in flight, 100 x 2000 x 2000 took 23 us; a last stage of width 2000 235 -> 192 us a step.
+template <int BM, int BN, int WGM, int WGN, int NS, bool A_COL, bool B_COL, class Epi, bool LEAN, bool ROT, bool TAIL>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, int N, int K, int per,
                                                                         const uint16_t* __restrict__ A, int lda,
                                                                         const uint16_t* __restrict__ B, int ldb,
                                                                         Epi epi, TileMap map, SideCopy side) {
@@ -260,11 +273,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
   map.get(blockIdx.x, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const uint32_t lds_base = lds_addr_of(lds_raw);
-  // blockIdx.y: range of the contraction this workgroup sums over (K is the length of one range); each range
-  // writes its own output (fp32 partial results that a second kernel adds in a fixed order)
-  const int split = blockIdx.y;
-  A += (size_t)split * K * (A_COL ? lda : 1);
-  B += (size_t)split * K * (B_COL ? ldb : 1);
+  // blockIdx.y: range of the contraction this workgroup sums over, `per` k tiles long (the last one may be shorter);
+  // each range writes its own output (fp32 partial results that a second kernel adds in a fixed order)
+  const int split = blockIdx.y, first = split * per;
+  const int KT = min(per, (TAIL ? (K + DBK - 1) / DBK : K / DBK) - first);
+  const int last_k = K - (first + KT - 1) * DBK;  // k values of the last tile, if it holds fewer than DBK
+  A += first * AT::tile_step(lda);
+  B += first * BT::tile_step(ldb);
 
   floatx16 acc[TM][TN];
 #pragma unroll
@@ -281,7 +296,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
   BT tb;
   ta.init(lda, m0, M, wave, lane);
   tb.init(ldb, n0, N, wave, lane);
-  const int KT = K / DBK;
   const size_t step_a = AT::tile_step(lda), step_b = BT::tile_step(ldb);
   constexpr int NM = (DBK / 16) * TM * TN;  // MFMAs of one wave per k tile
   // MFMA after which copy t of the next tile is issued.  With three or more stages a copy has a whole tile of slack
@@ -295,6 +309,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
   auto issue_copy = [&](int t, int tile, int st) {
     const int tc = min(tile, KT - 1);
     const uint32_t dst = lds_base + st * kStageBytes;
+    if (TAIL && tc == KT - 1) {  // uniform
+      if (t < AT::kPerWave) ta.issue_one_of(last_k, t, dst, A + tc * step_a, wave, lane);
+      else tb.issue_one_of(last_k, t - AT::kPerWave, dst + AT::kBytes, B + tc * step_b, wave, lane);
+      return;
+    }
     if (t < AT::kPerWave) ta.issue_one(t, dst, A + tc * step_a, wave);
     else tb.issue_one(t - AT::kPerWave, dst + AT::kBytes, B + tc * step_b, wave);
   };
@@ -309,7 +328,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
   if constexpr (LEAN) {
     const uint16_t* pa = A + (size_t)(NS - 1) * step_a;  // source of the next tile to copy
     const uint16_t* pb = B + (size_t)(NS - 1) * step_b;
-    for (; kt0 + NS <= KT - (NS - 1); kt0 += NS) {
+    for (; kt0 + NS <= KT - (NS - 1) - TAIL; kt0 += NS) {  // all copies of whole tiles
 #pragma unroll
       for (int u = 0; u < NS; ++u) {  // tile kt0 + u lives in buffer u, tile kt0 + u + NS - 1 goes to buffer (u + NS - 1) % NS
         wait_vmcnt<(NS - 2) * kLoads>();
@@ -477,20 +496,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
   store_tiles<TM, TN>(acc, epi_of_split(epi, split), m0 + wm, n0 + wn, M, N, lane);
 }
 
-// Shapes the direct-to-LDS kernel takes: whole 64-wide k tiles, 32-bit byte offsets inside each
-// operand, and at least one 8-wide chunk along the rows of an operand staged [k][row].
+// Operands the direct-to-LDS kernel takes: 16-byte aligned with rows of whole 16-byte chunks (of at least one, along the
+// rows of an operand staged [k][row]), 32-bit byte offsets inside each.
 inline bool dma_ok(int M, int N, int K, int lda, int ldb, bool a_col, bool b_col) {
-  if (K < DBK || K % DBK) return false;
+  if (((a_col ? M : K) | (b_col ? N : K) | lda | ldb) & 7) return false;
   const size_t a_bytes = (size_t)(a_col ? K : M) * lda * 2, b_bytes = (size_t)(b_col ? K : N) * ldb * 2;
-  if (a_bytes >= (1ull << 31) || b_bytes >= (1ull << 31)) return false;
-  if ((a_col && M < 8) || (b_col && N < 8)) return false;
-  return true;
+  return a_bytes < (1ull << 31) && b_bytes < (1ull << 31);
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, bool A_COL, bool B_COL, class Epi, bool LEAN = false,
-          bool ROT = false>
+template <int BM, int BN, int WGM, int WGN, int NS, bool A_COL, bool B_COL, bool LEAN, bool ROT, bool TAIL, class Epi>
 hipError_t launch_dma(hipStream_t s, int M, int N, int K, const uint16_t* A, int lda, const uint16_t* B, int ldb,
-                      const Epi& epi, SideCopy side = SideCopy{nullptr, nullptr, 0}, int splits = 1) {
+                      const Epi& epi, SideCopy side, int per) {
   constexpr int NW = WGM * WGN;
   using AT = typename DmaSel<BM, NW, A_COL>::type;
   using BT = typename DmaSel<BN, NW, B_COL>::type;
@@ -501,7 +517,7 @@ hipError_t launch_dma(hipStream_t s, int M, int N, int K, const uint16_t* A, int
   constexpr size_t epi_bytes = !epi_lds ? 0 : epi_whole <= 160 * 1024 ? epi_whole : epi_rows;  // tiles turned through LDS
   constexpr size_t lds_bytes = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
   static_assert(lds_bytes <= 160 * 1024, "stages do not fit the LDS of a CU");
-  auto kernel = gemm_bf16_dma_kernel<BM, BN, WGM, WGN, NS, A_COL, B_COL, Epi, LEAN, ROT>;
+  auto kernel = gemm_bf16_dma_kernel<BM, BN, WGM, WGN, NS, A_COL, B_COL, Epi, LEAN, ROT, TAIL>;
   if (lds_bytes > 64 * 1024) {
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
@@ -509,122 +525,133 @@ hipError_t launch_dma(hipStream_t s, int M, int N, int K, const uint16_t* A, int
   }
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const TileMap map = make_tile_map(tiles_m, tiles_n);
-  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n, splits), dim3(64 * NW), lds_bytes, s, M, N, K / splits, A, lda, B, ldb,
-                     epi, map, side);
+  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n, (k_tiles(K) + per - 1) / per), dim3(64 * NW), lds_bytes, s, M, N, K, per, A,
+                     lda, B, ldb, epi, map, side);
   return hipGetLastError();
 }
 
-int g_cfg[3] = {-1, -1, -1};  // tuning override per product (fprop, dgrad, wgrad); -1 = heuristic
+// Tile choice: the tile that needs the least time on 256 CUs, taken as (rounds of 256 workgroups) x (tile area) x (k tiles
+// of a range) / (rate the tile sustains relative to the largest one): large tiles move less data per flop, but a last round
+// that fills a fraction of the chip costs a whole round -- the 6144 x 2048 weight gradient of a fused QKV projection is 1.5
+// rounds of 256x128 tiles, 192 tiles of 256x256 and exactly 256 tiles of 384x128 (51 us against 65 us and 57 us at 2048
+// rows).  The 384-wide tiles serve the fp32-output product only (three 32-wide blocks per wave row do not fit the 16-byte
+// row stores of the bf16 epilogues) and only shapes they divide.
+enum Tile { T256x256, T384x128, T128x384, T256x128, T128x128, T128x64, T64x64 };
+struct TileCost {
+  Tile t;
+  int bm, bn, rate;  // rate in per cent of the 256x256 tile's
+  bool wgrad_only;
+};
+constexpr TileCost kTiles[] = {{T256x256, 256, 256, 100, false}, {T384x128, 384, 128, 88, true},  {T128x384, 128, 384, 88, true},
+                               {T256x128, 256, 128, 88, false},  {T128x128, 128, 128, 78, false}, {T128x64, 128, 64, 62, false},
+                               {T64x64, 64, 64, 45, false}};
 
-// Tile choice.  The direct-to-LDS kernel is taken whenever the shape allows it: the largest of
-// its tiles that still gives every CU a workgroup (large tiles cut the L2->LDS traffic, which
-// together with the LDS reads is what bounds these kernels).  Ragged shapes go to the
-// register-staged kernel.
-int pick(int rows, int cols, int contraction, int lda, int ldb, bool a_col, bool b_col, int override_cfg) {
-  const bool dma = dma_ok(rows, cols, contraction, lda, ldb, a_col, b_col);
-  if (override_cfg >= 0 && (override_cfg < 10 || dma)) return override_cfg;  // a direct-to-LDS tile only where it is valid
-  auto blocks = [&](int bm, int bn) { return (long)((rows + bm - 1) / bm) * ((cols + bn - 1) / bn); };
-  if (dma) {
-    // The tile that needs the least time on 256 CUs, taken as (rounds of 256 workgroups) x (tile area) / (rate the
-    // tile sustains relative to the largest one): large tiles move less data per flop, but a last round that fills
-    // a fraction of the chip costs a whole round -- the 6144 x 2048 weight gradient of a fused QKV projection is 1.5
-    // rounds of 256x128 tiles, 192 tiles of 256x256 and exactly 256 tiles of 384x128 (51 us against 65 us and 57 us
-    // at 2048 rows).  The 384-wide tiles serve the fp32-output product only (three 32-wide blocks per wave row do
-    // not fit the 16-byte row stores of the bf16 epilogues) and only shapes they divide.
-    struct Tile { int cfg, bm, bn, rate; bool wgrad_only; };  // rate in per cent of the 256x256 tile's
-    static const Tile tiles[] = {{18, 256, 256, 100, false}, {25, 384, 128, 88, true}, {24, 128, 384, 88, true},
-                                 {19, 256, 128, 88, false},  {12, 128, 128, 78, false}, {11, 128, 64, 62, false},
-                                 {10, 64, 64, 45, false}};
-    int best = 10;
-    long best_cost = -1;
-    for (const Tile& t : tiles) {
-      if (t.wgrad_only && !(a_col && b_col && rows % t.bm == 0 && cols % t.bn == 0)) continue;
-      const long cost = ((blocks(t.bm, t.bn) + 255) / 256) * t.bm * t.bn * 100 / t.rate;
-      if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = t.cfg; }
-    }
-    return best;
+inline long blocks_of(const TileCost& t, int M, int N) { return (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
+
+Tile pick(int M, int N, bool wgrad) {
+  Tile best = T64x64;
+  long best_cost = -1;
+  for (const TileCost& t : kTiles) {
+    if (t.wgrad_only && !(wgrad && M % t.bm == 0 && N % t.bn == 0)) continue;
+    const long cost = (blocks_of(t, M, N) + 255) / 256 * t.bm * t.bn * 100 / t.rate;
+    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = t.t; }
   }
-  if (blocks(128, 128) >= 256) return 2;
-  if (blocks(128, 64) >= 128) return 1;
-  return 0;
+  return best;
+}
+
+// k tiles per range of a weight gradient's contraction (the rows of the mini-batch): where its output has too few 64x64
+// tiles to fill the chip, as many ranges as give every CU a workgroup, at least 8 k tiles each (a 64 x 64 gradient over the
+// 131072 pixels of 16x16 maps is one tile and 2048 k tiles).  Larger tiles are only chosen when they already give 256
+// workgroups.
+int wgrad_range(int M, int N, int K, bool dma) {
+  const int kt = k_tiles(M);
+  if (dma && pick(N, K, true) != T64x64) return kt;
+  const long blocks = (long)((N + 63) / 64) * ((K + 63) / 64);
+  const int ranges = (int)std::min<long>(256 / blocks, kt / 8);
+  return ranges > 1 ? (kt + ranges - 1) / ranges : kt;
+}
+inline int wgrad_ranges(int M, int N, int K) {
+  const int per = wgrad_range(M, N, K, dma_ok(N, K, M, N, K, true, true));
+  return (k_tiles(M) + per - 1) / per;
+}
+
+inline bool aligned(int bytes, const void* a, const void* b = nullptr, const void* c = nullptr) {
+  return (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & (bytes - 1)) == 0;
+}
+
+// per: k tiles per contraction range
+template <bool A_COL, bool B_COL, bool TAIL, class Epi>
+hipError_t run_dma(Tile tile, hipStream_t s, int M, int N, int K, const uint16_t* A, int lda, const uint16_t* B, int ldb,
+                   const Epi& e, SideCopy side, int per) {
+  switch (tile) {
+    case T256x256: return launch_dma<256, 256, 2, 4, 2, A_COL, B_COL, false, true, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
+    case T256x128: return launch_dma<256, 128, 2, 4, 3, A_COL, B_COL, false, true, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
+    case T384x128:
+      if constexpr (A_COL) return launch_dma<384, 128, 4, 2, 2, A_COL, B_COL, false, true, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
+      break;
+    case T128x384:
+      if constexpr (A_COL) return launch_dma<128, 384, 2, 4, 2, A_COL, B_COL, false, true, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
+      break;
+    case T128x128: return launch_dma<128, 128, 2, 2, 3, A_COL, B_COL, false, true, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
+    case T128x64: return launch_dma<128, 64, 2, 2, 4, A_COL, B_COL, true, false, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
+    case T64x64: return launch_dma<64, 64, 2, 2, 4, A_COL, B_COL, true, false, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
+  }
+  return hipErrorInvalidValue;
+}
+
+// dma: the operands suit the direct-to-LDS kernel.  Otherwise 64x64 tiles, or 128x64 ones where those still fill the chip
+// half.
+template <bool A_COL, bool B_COL, class Epi>
+hipError_t run(bool dma, hipStream_t s, int M, int N, int K, const uint16_t* A, int lda, const uint16_t* B, int ldb, const Epi& e,
+               SideCopy side = SideCopy{nullptr, nullptr, 0}) {
+  const int per = k_tiles(K);
+  if (dma && K % DBK) return run_dma<A_COL, B_COL, true>(pick(M, N, A_COL), s, M, N, K, A, lda, B, ldb, e, side, per);
+  if (dma) return run_dma<A_COL, B_COL, false>(pick(M, N, A_COL), s, M, N, K, A, lda, B, ldb, e, side, per);
+  if ((long)((M + 127) / 128) * ((N + 63) / 64) >= 128)
+    return launch_any<128, 64, 2, 2, A_COL, B_COL>(s, M, N, K, A, lda, B, ldb, e, per);
+  return launch_any<64, 64, 2, 2, A_COL, B_COL>(s, M, N, K, A, lda, B, ldb, e, per);
 }
 
 }  // namespace
 
-void mfma_set_config(int product, int cfg) {
-  if (product >= 0 && product < 3) g_cfg[product] = cfg;
-}
-
-// Contraction extents must be a multiple of 8 (16-byte chunks along k); operands that are staged
-// [k][row] also need their row extent to be a multiple of 8.
-bool mfma_fprop_supported(int M, int N, int K) { return M >= 1 && N >= 1 && K % 8 == 0; }
-bool mfma_dgrad_supported(int M, int N, int K) { return M >= 1 && N % 8 == 0 && K % 8 == 0; }
-bool mfma_wgrad_supported(int M, int N, int K) { return M >= 1 && N % 8 == 0 && K % 8 == 0; }
-
-#define TP_GEMM_DISPATCH(cfg, ACOL, BCOL, ...)                                  \
-  switch (cfg) {                                                                \
-    case 10: return launch_dma<64, 64, 2, 2, 4, ACOL, BCOL, decltype(e), true>(__VA_ARGS__);  \
-    case 11: return launch_dma<128, 64, 2, 2, 4, ACOL, BCOL, decltype(e), true>(__VA_ARGS__); \
-    case 30: return launch_dma<64, 64, 2, 2, 8, ACOL, BCOL, decltype(e), true>(__VA_ARGS__);  \
-    case 31: return launch_dma<64, 64, 2, 2, 6, ACOL, BCOL, decltype(e), true>(__VA_ARGS__);  \
-    case 12: return launch_dma<128, 128, 2, 2, 3, ACOL, BCOL, decltype(e), false, true>(__VA_ARGS__); \
-    case 18: return launch_dma<256, 256, 2, 4, 2, ACOL, BCOL, decltype(e), false, true>(__VA_ARGS__); \
-    case 19: return launch_dma<256, 128, 2, 4, 3, ACOL, BCOL, decltype(e), false, true>(__VA_ARGS__); \
-    case 24: return launch_dma<128, 384, 2, 4, 2, ACOL, BCOL, decltype(e), false, true>(__VA_ARGS__); \
-    case 25: return launch_dma<384, 128, 4, 2, 2, ACOL, BCOL, decltype(e), false, true>(__VA_ARGS__); \
-    case 2: return launch<128, 128, 2, 2, 64, ACOL, BCOL>(__VA_ARGS__);         \
-    case 1: return launch<128, 64, 2, 2, 64, ACOL, BCOL>(__VA_ARGS__);          \
-    default: return launch<64, 64, 2, 2, 64, ACOL, BCOL>(__VA_ARGS__);          \
-  }
-
 hipError_t mfma_fprop(hipStream_t s, int M, int N, int K, const uint16_t* x, const uint16_t* W, const float* bias,
                       int act, uint16_t* d_out, uint16_t* a_out, uint16_t* x_copy, const uint16_t* addend) {
-  // x is [M x K] with K % 8 == 0 and 16-byte aligned rows, so it is a whole number of 16-byte units
-  SideCopy side{(const uint4*)x, (uint4*)x_copy, x_copy ? (size_t)M * K / 8 : 0};
-  if (addend) {
-    EpiFpropAdd e{bias, d_out, a_out, act, N, addend};
-    TP_GEMM_DISPATCH(pick(M, N, K, K, K, false, false, g_cfg[0]), false, false, s, M, N, K, x, K, W, K, e, side)
+  const bool dma = dma_ok(M, N, K, K, K, false, false) && aligned(16, x, W, x_copy);
+  SideCopy side{(const uint4*)x, (uint4*)x_copy, x_copy ? (size_t)M * K / 8 : 0};  // whole 16-byte units with dma
+  if (x_copy && !dma) {
+    const hipError_t err = launch_copy(s, x, x_copy, (size_t)M * K * 2);
+    if (err != hipSuccess) return err;
   }
-  EpiFprop e{bias, d_out, a_out, act, N};
-  TP_GEMM_DISPATCH(pick(M, N, K, K, K, false, false, g_cfg[0]), false, false, s, M, N, K, x, K, W, K, e, side)
+  const int wide = aligned(8, d_out, a_out);
+  if (addend) return run<false, false>(dma, s, M, N, K, x, K, W, K, EpiFpropAdd{bias, d_out, a_out, act, N, addend, wide}, side);
+  return run<false, false>(dma, s, M, N, K, x, K, W, K, EpiFprop{bias, d_out, a_out, act, N, nullptr, wide}, side);
 }
 
 hipError_t mfma_dgrad(hipStream_t s, int M, int N, int K, const uint16_t* dz, const uint16_t* Wb,
                       const uint16_t* d_prev, uint16_t* out, int relu_mask) {
   // out[M x K] = dz[M x N] . Wb[N x K]: GEMM (M, K, contraction N)
-  EpiDgrad e{d_prev, out, K, relu_mask};
-  TP_GEMM_DISPATCH(pick(M, K, N, N, K, false, true, g_cfg[1]), false, true, s, M, K, N, dz, N, Wb, K, e)
-}
-
-// Ranges of the contraction (the rows of the mini-batch) a weight gradient is split into when its output has too
-// few tiles to fill the chip: whole 64-row k tiles, at least 8 per range, as many ranges as give every CU a
-// workgroup (a 64 x 64 gradient over the 131072 pixels of 16x16 maps is one tile and 2048 k tiles).
-int mfma_wgrad_splits(int M, int N, int K) {
-  if (!dma_ok(N, K, M, N, K, true, true)) return 1;
-  const int cfg = pick(N, K, M, N, K, true, true, g_cfg[2]);
-  if (cfg != 10) return 1;  // larger tiles are only chosen when they already give 256 workgroups
-  const long blocks = (long)((N + 63) / 64) * ((K + 63) / 64);
-  int s = (int)std::min<long>(256, 256 / std::max<long>(blocks, 1));
-  while (s > 1 && (M % (DBK * s) != 0 || M / (DBK * s) < 8)) --s;
-  return std::max(s, 1);
+  const bool dma = dma_ok(M, K, N, N, K, false, true) && aligned(16, dz, Wb);
+  return run<false, true>(dma, s, M, K, N, dz, N, Wb, K, EpiDgrad{d_prev, out, K, relu_mask, aligned(8, d_prev, out)});
 }
 
 size_t mfma_wgrad_scratch_floats(int M, int N, int K) {
-  const int s = mfma_wgrad_splits(M, N, K);
-  return s > 1 ? (size_t)s * N * K : 0;
+  const int ranges = wgrad_ranges(M, N, K);
+  return ranges > 1 ? (size_t)ranges * N * K : 0;
 }
 
 hipError_t mfma_wgrad(hipStream_t s, int M, int N, int K, const uint16_t* dz, const uint16_t* x, float* gW, float* partial) {
   // gW[N x K] = dz^T[N x M] . x[M x K]: GEMM (N, K, contraction M)
-  const int splits = partial ? mfma_wgrad_splits(M, N, K) : 1;
-  if (splits > 1) {
-    EpiWgradSplit e{partial, K, (size_t)N * K};
-    const hipError_t err = launch_dma<64, 64, 2, 2, 4, true, true>(s, N, K, M, dz, N, x, K, e, SideCopy{nullptr, nullptr, 0}, splits);
-    if (err != hipSuccess) return err;
-    return launch_sum_partials(s, (size_t)N * K, splits, partial, gW);
-  }
-  EpiWgrad e{gW, K};
-  TP_GEMM_DISPATCH(pick(N, K, M, N, K, true, true, g_cfg[2]), true, true, s, N, K, M, dz, N, x, K, e)
+  const bool fits = dma_ok(N, K, M, N, K, true, true);
+  const bool dma = fits && aligned(16, dz, x);
+  const int per = wgrad_range(M, N, K, fits), ranges = (k_tiles(M) + per - 1) / per;
+  if (!partial || ranges == 1) return run<true, true>(dma, s, N, K, M, dz, N, x, K, EpiWgrad{gW, K});
+  const EpiWgradSplit e{partial, K, (size_t)N * K};
+  const hipError_t err =
+      !dma ? launch_any<64, 64, 2, 2, true, true>(s, N, K, M, dz, N, x, K, e, per)
+      : M % DBK ? launch_dma<64, 64, 2, 2, 4, true, true, true, false, true>(s, N, K, M, dz, N, x, K, e, SideCopy{nullptr, nullptr, 0}, per)
+                : launch_dma<64, 64, 2, 2, 4, true, true, true, false, false>(s, N, K, M, dz, N, x, K, e, SideCopy{nullptr, nullptr, 0}, per);
+  if (err != hipSuccess) return err;
+  return launch_sum_partials(s, (size_t)N * K, ranges, partial, gW);
 }
 
 }  // namespace tp

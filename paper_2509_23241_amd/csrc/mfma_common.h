@@ -28,6 +28,7 @@ template <bool ADD>
 struct EpiFpropT {
   const float* bias; uint16_t* d_out; uint16_t* a_out; int act; int ldc;  // d_out: act'(z) for the backward, or null
   const uint16_t* addend = nullptr;
+  int wide = 1;  // 0: the outputs are not 8-byte aligned
   static constexpr bool kSwap = true;
   // 8 consecutive columns n..n+7 of row m (n and ldc multiples of 8)
   __device__ __forceinline__ void row8(int m, int n, float (&v)[8]) const {
@@ -58,7 +59,7 @@ struct EpiFpropT {
   }
   __device__ __forceinline__ void quad(int m, int n, int count, float v0, float v1, float v2, float v3) const {
     const size_t i = (size_t)m * ldc + n;
-    if (count == 4 && (ldc & 3) == 0 && !ADD) {
+    if (count == 4 && (ldc & 3) == 0 && wide && !ADD) {
       const float4 b = *reinterpret_cast<const float4*>(bias + n);
       const ActPair p0 = act_pair_fast(v0 + b.x, act), p1 = act_pair_fast(v1 + b.y, act);
       const ActPair p2 = act_pair_fast(v2 + b.z, act), p3 = act_pair_fast(v3 + b.w, act);
@@ -79,6 +80,7 @@ using EpiFpropAdd = EpiFpropT<true>;
 struct EpiDgrad {
   const uint16_t* d_prev; uint16_t* out; int ldc;  // d_prev: saved act'(z) of the previous layer, or null
   int relu_mask = 0;  // 1: d_prev holds the previous layer's ReLU OUTPUT instead; its derivative is (output > 0)
+  int wide = 1;       // 0: the output is not 8-byte aligned
   static constexpr bool kSwap = true;
   __device__ __forceinline__ float through(float v, float d) const { return relu_mask ? (d > 0.f ? v : 0.f) : v * d; }
   // 8 consecutive columns n..n+7 of row m (n and ldc multiples of 8)
@@ -98,7 +100,7 @@ struct EpiDgrad {
   }
   __device__ __forceinline__ void quad(int m, int n, int count, float v0, float v1, float v2, float v3) const {
     const size_t i = (size_t)m * ldc + n;
-    if (count == 4 && (ldc & 3) == 0) {
+    if (count == 4 && (ldc & 3) == 0 && wide) {
       if (d_prev) {
         const uint2 d = *reinterpret_cast<const uint2*>(d_prev + i);
         v0 = through(v0, __uint_as_float(d.x << 16));
@@ -254,6 +256,19 @@ __device__ __forceinline__ void dma16(uint32_t lds_byte_addr, const void* sbase,
                : "memory");
 }
 
+__device__ uint4 g_zero_chunk;  // what copies of nothing read
+__device__ __forceinline__ const char* zero_chunk() { return reinterpret_cast<const char*>(&g_zero_chunk); }
+
+// 16 or 4 bytes per lane from an address of the lane's own, global -> LDS address + lane * (16 or 4)
+template <int BYTES>
+__device__ __forceinline__ void dma_addr(uint32_t lds_byte_addr, const void* lane_ptr) {
+  static_assert(BYTES == 16 || BYTES == 4, "copies of one chunk or one word per lane");
+  if constexpr (BYTES == 16)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_byte_addr), "v"(lane_ptr) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(lds_byte_addr), "v"(lane_ptr) : "memory");
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
@@ -293,6 +308,12 @@ struct RowDma {
   __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, const uint16_t* base, int wave) const {
     dma16(lds_stage + (wave + NW * t) * 1024, base, voff[t]);
   }
+  // of a tile that holds `kin` k values (a multiple of 8): chunks past them are zeros
+  __device__ __forceinline__ void issue_one_of(int kin, int t, uint32_t lds_stage, const uint16_t* base, int wave, int lane) const {
+    const int r = 8 * (wave + NW * t) + (lane >> 3);
+    const int c = (lane & 7) ^ ((r >> 1) & 7);
+    dma_addr<16>(lds_stage + (wave + NW * t) * 1024, c * 8 < kin ? (const char*)base + voff[t] : zero_chunk());
+  }
   static __device__ __forceinline__ size_t tile_step(int) { return DBK; }  // elements between k tiles
   static __device__ __forceinline__ bf16x8 frag(const uint16_t* lds, int rbase, int kk, int lane) {
     const int r = rbase + (lane & 31);
@@ -329,6 +350,11 @@ struct ColDma {
   }
   __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, const uint16_t* base, int wave) const {
     dma16(lds_stage + (wave + NW * t) * 1024, base, voff[t]);
+  }
+  // of a tile that holds `kin` k rows: rows past them are zeros
+  __device__ __forceinline__ void issue_one_of(int kin, int t, uint32_t lds_stage, const uint16_t* base, int wave, int lane) const {
+    const int k = (64 * (wave + NW * t) + lane) / kPerK;
+    dma_addr<16>(lds_stage + (wave + NW * t) * 1024, k < kin ? (const char*)base + voff[t] : zero_chunk());
   }
   static __device__ __forceinline__ size_t tile_step(int ld) { return (size_t)DBK * ld; }
   static __device__ __forceinline__ bf16x8 frag(const uint16_t* lds, int rbase, int kk, int lane) {

@@ -1,5 +1,5 @@
-"""The matrix-core kernels for shapes outside the tuned bf16 ones (kernels_gemm_any.hip), at the edges of their tiles:
-one layer's forward, input gradient and weight gradient against fp64."""
+"""The matrix-core kernels for shapes that fill no tile (kernels_gemm_any.hip, kernels_gemm_mfma.hip), at the edges of
+their tiles: one layer's forward, input gradient and weight gradient against fp64."""
 import numpy as np
 import pytest
 
@@ -50,6 +50,58 @@ def test_dense_fp32(rows, fin, fout):
     assert _rel(dx, dy64 @ W64) <= _sum_tol(fout)
     assert _rel(gw, dy64.T @ x64) <= _sum_tol(rows)
     assert _rel(gb, dy64.sum(0)) <= _sum_tol(rows)
+
+
+@pytest.mark.parametrize("rows,fin,fout", [
+    (1, 1, 1), (3, 7, 9), (63, 65, 66), (129, 70, 10),        # values copied one by one at the edges, 64 x 64 tiles
+    (1001, 1003, 1002),                                       # the same, 128 x 64 tiles
+    (3001, 41, 39), (3001, 39, 40),                           # ... weight gradient over several row ranges
+    (1, 8, 8), (130, 56, 16), (100, 200, 104),                # 16-byte chunks, 64 x 64 tiles: less than one k tile, a remainder
+    (70, 72, 10),                                             # chunks forward, single values backward
+    (3000, 40, 72),                                           # weight gradient over several row ranges, the last one shorter
+    (1000, 136, 2040), (2040, 136, 2040), (2040, 136, 4088), (4000, 136, 4088),   # 128 x 64, 128 x 128, 256 x 128, 256 x 256
+    (72, 2048, 6144), (72, 6144, 2048),                       # weight gradients on 384 x 128 and 128 x 384 tiles
+])
+@pytest.mark.parametrize("shift", [0, 1])                     # 1: the input starts at an odd element
+def test_dense_bf16(rows, fin, fout, shift):
+    import torch
+    from synth_inputs import round_bf16
+    if shift and rows > 1001:
+        pytest.skip("alignment decides the kernel, which the smaller shapes run")
+    rng = np.random.default_rng(rows + fin)
+    cast = lambda t: round_bf16(t).astype(np.float32)
+    W = cast(rng.standard_normal((fout, fin)) / np.sqrt(fin))
+    b = rng.standard_normal(fout).astype(np.float32)
+    x, dy = cast(rng.standard_normal((rows, fin))), cast(rng.standard_normal((rows, fout)))
+    st = _stage((fin, fout, "none"), [W, b], rows, "bf16")
+    xs = torch.zeros(rows * fin + shift, dtype=torch.bfloat16, device="cuda")
+    ys = torch.zeros(rows * fout + shift, dtype=torch.bfloat16, device="cuda")
+    xt, yt = xs[shift:].view(rows, fin), ys[shift:].view(rows, fout)
+    xt.copy_(torch.from_numpy(x))
+    st.forward(0, 0, xt, yt)
+    dx, _ = st.backward(0, torch.from_numpy(dy).cuda().to(st.tdtype))
+    gw, gb = st.unpack(st.grad.cpu().numpy())
+    x64, W64, dy64 = x.astype(np.float64), W.astype(np.float64), dy.astype(np.float64)
+    store = 2.0 ** -9                                         # the stored result is rounded once
+    assert _rel(yt.float().cpu().numpy(), x64 @ W64.T + b) <= _sum_tol(fin) + store
+    assert _rel(dx.float().cpu().numpy(), dy64 @ W64) <= _sum_tol(fout) + store
+    assert _rel(gw, dy64.T @ x64) <= _sum_tol(rows)
+    assert _rel(gb, dy64.sum(0)) <= _sum_tol(rows)
+    st.close()
+
+
+def test_dense_bf16_keeps_nonfinite_values_in_their_row():
+    """Remainders of a k tile are zeros in both operands: an infinity reaches its own row only."""
+    import torch
+    rows, fin, fout = 70, 72, 80
+    st = _stage((fin, fout, "none"), [np.ones((fout, fin), np.float32), np.zeros(fout, np.float32)], rows, "bf16")
+    x = torch.ones(rows, fin, dtype=torch.bfloat16, device="cuda")
+    x[5, fin - 1] = float("inf")
+    y, _ = st.forward(0, 0, x)
+    want = torch.full((rows, fout), float(fin), device="cuda")
+    want[5] = float("inf")
+    assert torch.equal(y.float(), want)
+    st.close()
 
 
 def _conv_reference(x, W, b, dy, stride):
