@@ -295,7 +295,13 @@ struct EpiDgradClass {
     const int w2 = m & ((W >> 1) - 1), h2 = (m >> lw2) & ((H >> 1) - 1), img = m >> (lw2 + lh2);
     return (img * H + 2 * h2 + ph) * W + 2 * w2 + pw;
   }
-  __device__ __forceinline__ void row8(int m, int n, float (&v)[8]) const { e.row8(pixel(m), n, v); }
+  using Cols = EpiDgrad::Cols;
+  __device__ __forceinline__ Cols cols(int n) const { return e.cols(n); }
+  __device__ __forceinline__ bool has_rows() const { return e.has_rows(); }
+  __device__ __forceinline__ uint4 row_in(int m, int n) const { return e.row_in(pixel(m), n); }
+  __device__ __forceinline__ void row8(int m, int n, float (&v)[8], const Cols& c, const uint4& u) const {
+    e.row8(pixel(m), n, v, c, u);
+  }
   __device__ __forceinline__ void quad(int m, int n, int count, float v0, float v1, float v2, float v3) const {
     e.quad(pixel(m), n, count, v0, v1, v2, v3);
   }

@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <stdint.h>
 
 #include "device_utils.h"
@@ -240,6 +241,22 @@ hipError_t launch_any(hipStream_t s, int M, int N, int K, const uint16_t* A, int
   return hipGetLastError();
 }
 
+// a pointer that is the same in every lane, where the compiler would form it in vector registers
+__device__ __forceinline__ const uint16_t* in_sgprs(const uint16_t* p) {
+  const uint64_t a = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+  return reinterpret_cast<const uint16_t*>((uint64_t)hi << 32 | lo);
+}
+
+struct NoInputs {
+  template <class Epi>
+  __device__ __forceinline__ void load(const Epi&, int, int, int) {}
+};
+template <int TM, int TN, class Epi, bool ROWS>
+struct EpiInputs { using type = NoInputs; };
+template <int TM, int TN, class Epi>
+struct EpiInputs<TM, TN, Epi, true> { using type = RowInputs<TM, TN, Epi>; };
+
 // LEAN: small wave tiles (one or two 32x32 blocks) have so few MFMAs per k tile that the address and stage
 // bookkeeping is a third of the instructions of the loop.  The k loop is then unrolled over the NS stage buffers,
 // so that every LDS address is a loop-invariant register plus an immediate and the stage indices are constants;
@@ -247,7 +264,11 @@ hipError_t launch_any(hipStream_t s, int M, int N, int K, const uint16_t* A, int
 // in step with them) run through the generic loop.  Worth about 5 % on the 64x64 and 128x64 tiles.
 // ROT: the barrier that makes a k tile visible sits one k step early, before the last MFMA group of the tile
 // before it, so that the first fragment reads of the new tile run under that group instead of stalling the wave
-// (with one wave per SIMD nothing else would cover them).
+// (with one wave per SIMD nothing else would cover them).  The fragment reads of the next k step go out one by one
+// between the MFMAs of the current one, as the copies do: bunched in front of them, all eight waves queued for the LDS
+// at once.  Eight waves split 256x128 as 64x64 (4 fragments for 4 MFMAs; 128x32 takes 5).  The last NS - 1 tiles run
+// without copies.  Together, weight gradient 8192 x 2048 over 32768 rows 870 -> 850 us, 6144 x 2048 794 -> 765, input
+// gradient 2048 x 4096 x 4096 64.6 -> 62.5.
 // TAIL: the contraction is no whole number of k tiles; what the last tile lacks is copied from a block of zeros, for
 // both operands.  A kernel of its own, so that whole ones carry no second form of the copies.  Through registers, as in
 // the kernel above with one k tile in flight, 100 x 2000 x 2000 took 23 us; a last stage of width 2000 235 -> 192 us a step.
@@ -314,8 +335,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
       else tb.issue_one_of(last_k, t - AT::kPerWave, dst + AT::kBytes, B + tc * step_b, wave, lane);
       return;
     }
-    if (t < AT::kPerWave) ta.issue_one(t, dst, A + tc * step_a, wave);
-    else tb.issue_one(t - AT::kPerWave, dst + AT::kBytes, B + tc * step_b, wave);
+    if (t < AT::kPerWave) ta.issue_one(t, dst, in_sgprs(A + tc * step_a), wave);
+    else tb.issue_one(t - AT::kPerWave, dst + AT::kBytes, in_sgprs(B + tc * step_b), wave);
   };
 
   // prologue: stages 0 .. NS-2
@@ -323,6 +344,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
   for (int st = 0; st < NS - 1; ++st)
 #pragma unroll
     for (int t = 0; t < kLoads; ++t) issue_copy(t, st, st);
+
+  // rows of the wave tile stored whole, by 4 * TN lanes each
+  constexpr bool kRowStores = Epi::kSwap && 64 % (4 * TN) == 0;
+  const bool whole = kRowStores && m0 + wm + WM <= M && n0 + wn + WN <= N && (N & 7) == 0;
+  typename EpiInputs<TM, TN, Epi, kRowStores>::type row_inputs;
 
   int kt0 = 0;
   if constexpr (LEAN) {
@@ -391,8 +417,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int e = 0; e < 8; ++e) bfr[1][j][e] = 0;
-    for (int kt = 0; kt < KT; ++kt) {
-      wait_vmcnt<(NS - 2) * kLoads>();
+    static_assert(NS <= 3, "the wait below knows of one newer tile in flight");
+    // copies: issue those of tile kt + NS - 1
+    auto tile = [&](int kt, auto copies) {
+      if (NS == 2 || kt + 1 >= KT) wait_vmcnt<0>();
+      else wait_vmcnt<(NS - 2) * kLoads>();
       lds_barrier();  // tile kt visible; every wave holds its last fragments of tile kt-1 in registers
       const uint16_t* la = lds_raw + rd * (kStageBytes / 2);
       const uint16_t* lb = la + AT::kBytes / 2;
@@ -400,29 +429,37 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
       for (int st = 0; st < KS; ++st) {
         const int nx = st & 1, c = nx ^ 1;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) af[nx][i] = AT::frag(la, wm + i * 32, st, lane);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) bfr[nx][j] = BT::frag(lb, wn + j * 32, st, lane);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
             acc[i][j] = mma<Epi::kSwap>(af[c][i], bfr[c][j], acc[i][j]);
-            const int q = (st * TM + i) * TN + j;
+            const int q = i * TN + j;
 #pragma unroll
-            for (int t = 0; t < kLoads; ++t)
-              if (copy_slot(t) == q) {
+            for (int r = 0; r < TM + TN; ++r)
+              if (r * TM * TN / (TM + TN) == q) {
                 __builtin_amdgcn_sched_barrier(0);
-                issue_copy(t, kt + NS - 1, wr);
+                if (r < TN) bfr[nx][r] = BT::frag(lb, wn + r * 32, st, lane);
+                else af[nx][r - TN] = AT::frag(la, wm + (r - TN) * 32, st, lane);
                 __builtin_amdgcn_sched_barrier(0);
               }
+            if constexpr (decltype(copies)::value) {
+#pragma unroll
+              for (int t = 0; t < kLoads; ++t)
+                if (copy_slot(t) == st * TM * TN + q) {
+                  __builtin_amdgcn_sched_barrier(0);
+                  issue_copy(t, kt + NS - 1, wr);
+                  __builtin_amdgcn_sched_barrier(0);
+                }
+            }
           }
         __builtin_amdgcn_sched_barrier(0);
       }
       rd = rd + 1 == NS ? 0 : rd + 1;
       wr = wr + 1 == NS ? 0 : wr + 1;
-    }
+    };
+    for (int kt = 0; kt < KT - (NS - 1); ++kt) tile(kt, std::true_type{});
+    for (int kt = max(0, KT - (NS - 1)); kt < KT; ++kt) tile(kt, std::false_type{});
+    if (whole) row_inputs.load(epi, m0 + wm, n0 + wn, lane);  // under the last products
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -475,21 +512,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
     rd = rd + 1 == NS ? 0 : rd + 1;
     wr = wr + 1 == NS ? 0 : wr + 1;
   }
-  wait_vmcnt<0>();  // the trailing dummy copies must have landed before LDS is reused
-  lds_barrier();    // all waves are done with the last stage
-  if constexpr (Epi::kSwap && 64 % (4 * TN) == 0) {  // a row of the wave tile is stored by 4 * TN lanes
-    if (m0 + wm + WM <= M && n0 + wn + WN <= N && (N & 7) == 0) {
-      if constexpr (NW * wave_epilogue_bytes<TM, TN>() <= 160 * 1024) {
-        float* wave_lds = reinterpret_cast<float*>(lds_raw) + wave * (wave_epilogue_bytes<TM, TN>() / 4);
-        store_tiles_coalesced<TM, TN>(acc, epi, m0 + wm, n0 + wn, lane, wave_lds);
-      } else {
-        // the whole wave tiles do not fit the LDS together (256x256): one 32-row block of every wave at a time
-        float* wave_lds = reinterpret_cast<float*>(lds_raw) + wave * (wave_epilogue_bytes<1, TN>() / 4);
+  if constexpr (!ROT) wait_vmcnt<0>();  // the trailing dummy copies must have landed before LDS is reused
+  lds_barrier();                        // all waves are done with the last stage
+  if constexpr (kRowStores) {
+    if (whole) {
+      if constexpr (!ROT) row_inputs.load(epi, m0 + wm, n0 + wn, lane);
+      // where the whole wave tiles do not fit the LDS together (256x256): one 32-row block of every wave at a time
+      constexpr int TB = NW * wave_epilogue_bytes<TM, TN>() <= 160 * 1024 ? TM : 1;
+      float* wave_lds = reinterpret_cast<float*>(lds_raw) + wave * (wave_epilogue_bytes<TB, TN>() / 4);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-          store_tiles_coalesced<1, TN>(reinterpret_cast<const floatx16(&)[1][TN]>(acc[i]), epi, m0 + wm + 32 * i, n0 + wn,
-                                       lane, wave_lds);
-      }
+      for (int i = 0; i < TM; i += TB)
+        store_blocks_coalesced<TB>(acc, i, epi, row_inputs, m0 + wm, n0 + wn, lane, wave_lds);
       return;
     }
   }
@@ -585,7 +618,7 @@ hipError_t run_dma(Tile tile, hipStream_t s, int M, int N, int K, const uint16_t
                    const Epi& e, SideCopy side, int per) {
   switch (tile) {
     case T256x256: return launch_dma<256, 256, 2, 4, 2, A_COL, B_COL, false, true, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
-    case T256x128: return launch_dma<256, 128, 2, 4, 3, A_COL, B_COL, false, true, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
+    case T256x128: return launch_dma<256, 128, 4, 2, 3, A_COL, B_COL, false, true, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
     case T384x128:
       if constexpr (A_COL) return launch_dma<384, 128, 4, 2, 2, A_COL, B_COL, false, true, TAIL>(s, M, N, K, A, lda, B, ldb, e, side, per);
       break;

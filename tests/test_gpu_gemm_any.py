@@ -60,6 +60,7 @@ def test_dense_fp32(rows, fin, fout):
     (70, 72, 10),                                             # chunks forward, single values backward
     (3000, 40, 72),                                           # weight gradient over several row ranges, the last one shorter
     (1000, 136, 2040), (2040, 136, 2040), (2040, 136, 4088), (4000, 136, 4088),   # 128 x 64, 128 x 128, 256 x 128, 256 x 256
+    (2040, 64, 4088), (2040, 128, 4088), (4000, 64, 4088), (4000, 128, 4088),     # fewer k tiles than the last two have stages
     (72, 2048, 6144), (72, 6144, 2048),                       # weight gradients on 384 x 128 and 128 x 384 tiles
 ])
 @pytest.mark.parametrize("shift", [0, 1])                     # 1: the input starts at an odd element
