@@ -9,8 +9,8 @@
 // backward  S = Q K^T, dP = dO V^T (fp32)  ->  P, dS = scale P (dP - rowsum(P dP)) (bf16)
 //           ->  dQ = dS K, dK = dS^T Q, dV = P^T dO
 // The score matrices are transient: a call works through the sequences in chunks that fit the
-// scratch the caller provides.  Needs tokens % 64 == 0 and head width % 64 == 0; other shapes
-// stay on the wavefront kernels of kernels_transformer.hip.
+// scratch the caller provides.  The fused kernels take any number of tokens at head widths 64 and 128, the batched ones
+// tokens % 64 == 0 and head width % 64 == 0; other shapes stay on the wavefront kernels of kernels_transformer.hip.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -4,8 +4,8 @@
 // Forward products and input gradients keep the arithmetic of a plain fp32 loop: every output is ONE chain of fused
 // multiply-adds over the contraction index in ascending order (v_mfma_f32_16x16x4_f32 adds its four products one after
 // the other, lowest k first, rounding each time -- checked against fmaf bit for bit).  What feeds a ReLU or a pooling is
-// therefore the same to the last bit whatever tile it was formed in, and the same as the bounds-checked FMA kernels of
-// kernels_gemm.hip and kernels_conv.hip give.  bf16 operands are widened on their way out of LDS.  Weight gradients are
+// therefore the same to the last bit whatever tile it was formed in, and the same as the bounds-checked FMA kernel of
+// kernels_conv.hip gives.  bf16 operands are widened on their way out of LDS.  Weight gradients are
 // sums over thousands of rows and feed no decision: they may be formed over several row ranges, in bf16 with
 // v_mfma_f32_16x16x32_bf16.
 //
