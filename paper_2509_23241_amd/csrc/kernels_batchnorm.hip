@@ -21,7 +21,8 @@ namespace {
 constexpr int kThreads = 256;
 constexpr float kBnEps = 1e-5f;
 
-inline int bn_chunk_rows(size_t rows) { return (int)std::max<size_t>(16, (rows + 255) / 256); }
+constexpr int kMaxChunks = 256;
+inline int bn_chunk_rows(size_t rows) { return (int)std::max<size_t>(16, (rows + kMaxChunks - 1) / kMaxChunks); }
 inline int bn_chunks(size_t rows) { return (int)((rows + bn_chunk_rows(rows) - 1) / bn_chunk_rows(rows)); }
 
 // MODE 0: sum d and sum d^2 with d = x - x[0][c] (out[0..C), out[C..2C)): mean and variance from ONE pass; the shift by the
@@ -69,73 +70,118 @@ __global__ __launch_bounds__(kThreads) void bn_colsum_kernel(size_t rows, int C,
   }
 }
 
-// The same for bf16 with C % 8 == 0 in 16-byte units: a workgroup covers 128 channels (16 lanes of 8) x 16 rows per
-// step; the sixteen row lanes of a channel meet in LDS in a fixed order.  Same partial layout.
-__device__ __forceinline__ void bn_unpack8(const uint4& u, float (&f)[8]) {
-  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+// Values in 16-byte units
+template <typename T>
+struct Unit;
+template <>
+struct Unit<uint16_t> {
+  static constexpr int N = 8;
+  static __device__ __forceinline__ void unpack(const uint4& u, float (&f)[N]) {
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    f[2 * j] = __uint_as_float(w[j] << 16);
-    f[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+    for (int j = 0; j < 4; ++j) {
+      f[2 * j] = __uint_as_float(w[j] << 16);
+      f[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+    }
   }
-}
-template <int MODE>
-__global__ __launch_bounds__(kThreads) void bn_colsum_vec_kernel(size_t rows, int C, int chunk_rows, const uint16_t* __restrict__ x,
-                                                                 const uint16_t* __restrict__ dy, const float* __restrict__ aux,
+  static __device__ __forceinline__ uint4 pack(const float (&f)[N]) {
+    return make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
+  }
+};
+template <>
+struct Unit<float> {
+  static constexpr int N = 4;
+  static __device__ __forceinline__ void unpack(const uint4& u, float (&f)[N]) {
+    f[0] = __uint_as_float(u.x); f[1] = __uint_as_float(u.y); f[2] = __uint_as_float(u.z); f[3] = __uint_as_float(u.w);
+  }
+  static __device__ __forceinline__ uint4 pack(const float (&f)[N]) {
+    return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
+  }
+};
+
+// The same in 16-byte units, for rows of whole units: a workgroup covers 16 units of a row x 16 rows per step; the sixteen
+// row lanes of a channel meet in LDS in a fixed order.  Same partial layout.  Bound by the loads a lane has in flight: eight
+// rows of x, or four of x and dy (two before; with the partial sums of bn_finalize_sum_kernel in flight at once, first stage
+// of a bottleneck net on 64-pixel images 1.81 -> 1.76 ms; fp32, one value per lane before, on 128-pixel images 1.04 -> 0.89).
+// Fewer units and more rows per step for narrow layers change the order of the sums, and with it ReLU masks: not done.
+template <typename T, int MODE>
+__global__ __launch_bounds__(kThreads) void bn_colsum_vec_kernel(size_t rows, int C, int chunk_rows, const T* __restrict__ x,
+                                                                 const T* __restrict__ dy, const float* __restrict__ aux,
                                                                  float* __restrict__ partial) {
-  __shared__ float sm[2][16][128 + 4];
-  const int cl = threadIdx.x & 15, rl = threadIdx.x >> 4;
-  const int c = blockIdx.x * 128 + cl * 8;
+  constexpr int N = Unit<T>::N, kLanes = 16, kCols = kLanes * N;
+  __shared__ float sm[2][kLanes][kCols + 4];
+  const int cl = threadIdx.x % kLanes, rl = threadIdx.x / kLanes;
+  const int c = blockIdx.x * kCols + cl * N;
   const size_t seg = blockIdx.z, nseg = gridDim.z;
   x += seg * rows * C;
   if (MODE == 2) { dy += seg * rows * C; aux += seg * 2 * C; }
   const size_t r0 = (size_t)blockIdx.y * chunk_rows;
   const size_t r1 = std::min(rows, r0 + chunk_rows);
-  float s0[8], s1[8];
+  float s0[N], s1[N];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) s0[j] = s1[j] = 0.f;
+  for (int j = 0; j < N; ++j) s0[j] = s1[j] = 0.f;
   if (c < C) {
-    float mean[8], rstd[8];
+    float mean[N], rstd[N];
     if (MODE == 0) {
-      bn_unpack8(*reinterpret_cast<const uint4*>(x + c), mean);
+      Unit<T>::unpack(*reinterpret_cast<const uint4*>(x + c), mean);
     } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) { mean[j] = aux[2 * (c + j)]; rstd[j] = aux[2 * (c + j) + 1]; }
+      for (int j = 0; j < N; ++j) { mean[j] = aux[2 * (c + j)]; rstd[j] = aux[2 * (c + j) + 1]; }
     }
-#pragma unroll 2
-    for (size_t r = r0 + rl; r < r1; r += 16) {
-      float v[8], g[8];
-      bn_unpack8(*reinterpret_cast<const uint4*>(x + r * C + c), v);
-      if (MODE == 2) bn_unpack8(*reinterpret_cast<const uint4*>(dy + r * C + c), g);
+    constexpr int kFlight = MODE == 0 ? 8 : 4;
+    for (size_t rb = r0 + rl; rb < r1; rb += kFlight * kLanes) {
+      uint4 ux[kFlight], ud[kFlight];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (MODE == 0) {
-          s0[j] += v[j] - mean[j];
-          s1[j] = fmaf(v[j] - mean[j], v[j] - mean[j], s1[j]);
-        } else {
-          s0[j] += g[j] * (v[j] - mean[j]) * rstd[j];
-          s1[j] += g[j];
+      for (int u = 0; u < kFlight; ++u) {
+        const size_t r = rb + u * kLanes;
+        if (r < r1) {
+          ux[u] = *reinterpret_cast<const uint4*>(x + r * C + c);
+          if (MODE == 2) ud[u] = *reinterpret_cast<const uint4*>(dy + r * C + c);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        if (rb + u * kLanes >= r1) break;
+        float v[N], g[N];
+        Unit<T>::unpack(ux[u], v);
+        if (MODE == 2) Unit<T>::unpack(ud[u], g);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+          if (MODE == 0) {
+            s0[j] += v[j] - mean[j];
+            s1[j] = fmaf(v[j] - mean[j], v[j] - mean[j], s1[j]);
+          } else {
+            s0[j] += g[j] * (v[j] - mean[j]) * rstd[j];
+            s1[j] += g[j];
+          }
         }
       }
     }
   }
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    sm[0][rl][cl * 8 + j] = s0[j];
-    sm[1][rl][cl * 8 + j] = s1[j];
+  for (int j = 0; j < N; ++j) {
+    sm[0][rl][cl * N + j] = s0[j];
+    sm[1][rl][cl * N + j] = s1[j];
   }
   __syncthreads();
-  if (threadIdx.x < 128 && blockIdx.x * 128 + threadIdx.x < C) {
+  if (threadIdx.x < kCols && blockIdx.x * kCols + threadIdx.x < C) {
     float a = 0.f, b = 0.f;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    for (int k = 0; k < kLanes; ++k) {
       a += sm[0][k][threadIdx.x];
       b += sm[1][k][threadIdx.x];
     }
     float* out = partial + ((size_t)blockIdx.y * nseg + seg) * 2 * C;
-    out[blockIdx.x * 128 + threadIdx.x] = a;
-    out[C + blockIdx.x * 128 + threadIdx.x] = b;
+    out[blockIdx.x * kCols + threadIdx.x] = a;
+    out[C + blockIdx.x * kCols + threadIdx.x] = b;
   }
+}
+
+template <typename T, int MODE>
+void launch_colsum_vec(hipStream_t s, size_t rows, int C, int nseg, const T* x, const T* dy, const float* aux, float* partial) {
+  const int units = C / Unit<T>::N;
+  hipLaunchKernelGGL((bn_colsum_vec_kernel<T, MODE>), dim3((units + 15) / 16, bn_chunks(rows), nseg), dim3(kThreads), 0, s, rows, C,
+                     bn_chunk_rows(rows), x, dy, aux, partial);
 }
 
 // partial[chunk][0..C) = sum d, [C..2C) = sum d^2 over the chunk's rows (d = x - x[0][c])  ->  stats[2c] = mean,
@@ -149,11 +195,21 @@ __global__ __launch_bounds__(kThreads) void bn_finalize_sum_kernel(size_t rows, 
   const int c = blockIdx.x * 16 + cl;
   float s0 = 0.f, s1 = 0.f;
   if (c < C) {
-#pragma unroll 4
-    for (int k = g; k < chunks; k += 16) {
-      s0 += partial[(size_t)k * 2 * C + c];
-      s1 += partial[(size_t)k * 2 * C + C + c];
+    float p0[kMaxChunks / 16], p1[kMaxChunks / 16];  // all in flight at once
+#pragma unroll
+    for (int u = 0; u < kMaxChunks / 16; ++u) {
+      const int k = g + 16 * u;
+      if (k < chunks) {
+        p0[u] = partial[(size_t)k * 2 * C + c];
+        p1[u] = partial[(size_t)k * 2 * C + C + c];
+      }
     }
+#pragma unroll
+    for (int u = 0; u < kMaxChunks / 16; ++u)
+      if (g + 16 * u < chunks) {
+        s0 += p0[u];
+        s1 += p1[u];
+      }
   }
   sm[0][g][cl] = s0;
   sm[1][g][cl] = s1;
@@ -209,18 +265,6 @@ __global__ __launch_bounds__(kThreads) void bn_dx_kernel(size_t rows, int C, siz
   }
 }
 
-// bf16, C a multiple of 8: the two elementwise kernels with 16 bytes per lane
-__global__ __launch_bounds__(kThreads) void bn_normalize_vec_kernel(size_t rows, int C, const uint16_t* __restrict__ x,
-                                                                    const float* __restrict__ stats,
-                                                                    const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                                    int act, const uint16_t* __restrict__ addend,
-                                                                    uint16_t* __restrict__ a_out, uint16_t* __restrict__ d_out);
-__global__ __launch_bounds__(kThreads) void bn_dx_vec_kernel(size_t rows, int C, size_t nseg, const uint16_t* __restrict__ dy,
-                                                             const uint16_t* __restrict__ x, const float* __restrict__ stats,
-                                                             const float* __restrict__ sums, const float* __restrict__ gamma_s,
-                                                             const float* __restrict__ gamma_l, float alpha, float beta_c,
-                                                             uint16_t* __restrict__ dx);
-
 // ---- slab kernels (bf16, small layers) -----------------------------------------------------------------
 // One workgroup of 1024 lanes owns W adjacent 16-byte units of every row (8 * W channels) for ALL rows the
 // statistics run over: lane t takes unit t % W of rows t / W, t / W + 1024 / W, ... and keeps them in registers.
@@ -269,36 +313,29 @@ __device__ __forceinline__ void slab_sum(float (&v)[NV], float* red /* [NV][kSla
   for (int i = 0; i < NV; ++i) v[i] = red[NV * kSlabThreads + i * W + t % W];
 }
 
-__device__ __forceinline__ void unpack8(const uint4& u, float (&f)[8]) {
-  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    f[2 * j] = __uint_as_float(w[j] << 16);
-    f[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
-  }
-}
-__device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
-  return make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
-}
+__device__ __forceinline__ void unpack8(const uint4& u, float (&f)[8]) { Unit<uint16_t>::unpack(u, f); }
+__device__ __forceinline__ uint4 pack8(const float (&f)[8]) { return Unit<uint16_t>::pack(f); }
 
 // The launchers give these two kernels a grid whose stride (threads of the grid, in 16-byte units) is a multiple of
-// the units per row, so a lane stays on the same 8 channels for all its rows and reads their statistics and affine
+// the units per row, so a lane stays on the same channels for all its rows and reads their statistics and affine
 // parameters once (fetched per element they were 32-48 extra loads for every 16 bytes of x: 14 us for a layer the
 // kernel now streams in a few).  addend (or null): the kept tensor of a residual add that follows a normalisation
 // without activation -- the result is act(bf16(bn(x)) + addend), as the slab kernel forms it.
-__global__ __launch_bounds__(kThreads) void bn_normalize_vec_kernel(size_t rows, int C, const uint16_t* __restrict__ x,
+template <typename T>
+__global__ __launch_bounds__(kThreads) void bn_normalize_vec_kernel(size_t rows, int C, const T* __restrict__ x,
                                                                     const float* __restrict__ stats,
                                                                     const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                                    int act, const uint16_t* __restrict__ addend,
-                                                                    uint16_t* __restrict__ a_out, uint16_t* __restrict__ d_out) {
-  const size_t nvec = rows * C / 8;
-  const int cv = C / 8;
+                                                                    int act, const T* __restrict__ addend,
+                                                                    T* __restrict__ a_out, T* __restrict__ d_out) {
+  constexpr int N = Unit<T>::N;
+  const size_t nvec = rows * C / N;
+  const int cv = C / N;
   const size_t stride = (size_t)gridDim.x * kThreads;  // a multiple of cv
   const size_t first = (size_t)blockIdx.x * kThreads + threadIdx.x;
-  const int c0 = (int)(first % cv) * 8;
-  float mean[8], rstd[8], ga[8], be[8];
+  const int c0 = (int)(first % cv) * N;
+  float mean[N], rstd[N], ga[N], be[N];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
+  for (int j = 0; j < N; ++j) {
     mean[j] = stats[2 * (c0 + j)];
     rstd[j] = stats[2 * (c0 + j) + 1];
     ga[j] = gamma[c0 + j];
@@ -306,39 +343,41 @@ __global__ __launch_bounds__(kThreads) void bn_normalize_vec_kernel(size_t rows,
   }
 #pragma unroll 2
   for (size_t i = first; i < nvec; i += stride) {
-    float f[8], a[8], d[8], sk[8];
-    unpack8(reinterpret_cast<const uint4*>(x)[i], f);
-    if (addend) unpack8(reinterpret_cast<const uint4*>(addend)[i], sk);
+    float f[N], a[N], d[N], sk[N];
+    Unit<T>::unpack(reinterpret_cast<const uint4*>(x)[i], f);
+    if (addend) Unit<T>::unpack(reinterpret_cast<const uint4*>(addend)[i], sk);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < N; ++j) {
       float z = fmaf((f[j] - mean[j]) * rstd[j], ga[j], be[j]);
-      if (addend) z = bf16_to_float(float_to_bf16(z)) + sk[j];
+      if (addend) z = to_float(from_float<T>(z)) + sk[j];
       a[j] = act_forward(z, act);
       d[j] = act_derivative(z, act);
     }
-    reinterpret_cast<uint4*>(a_out)[i] = pack8(a);
-    if (d_out) reinterpret_cast<uint4*>(d_out)[i] = pack8(d);
+    reinterpret_cast<uint4*>(a_out)[i] = Unit<T>::pack(a);
+    if (d_out) reinterpret_cast<uint4*>(d_out)[i] = Unit<T>::pack(d);
   }
 }
 
 // grid.y = segment (micro-batch)
-__global__ __launch_bounds__(kThreads) void bn_dx_vec_kernel(size_t rows, int C, size_t nseg, const uint16_t* __restrict__ dy,
-                                                             const uint16_t* __restrict__ x, const float* __restrict__ stats,
+template <typename T>
+__global__ __launch_bounds__(kThreads) void bn_dx_vec_kernel(size_t rows, int C, size_t nseg, const T* __restrict__ dy,
+                                                             const T* __restrict__ x, const float* __restrict__ stats,
                                                              const float* __restrict__ sums, const float* __restrict__ gamma_s,
                                                              const float* __restrict__ gamma_l, float alpha, float beta_c,
-                                                             uint16_t* __restrict__ dx) {
-  const size_t per = rows * C / 8;
-  const int cv = C / 8;
+                                                             T* __restrict__ dx) {
+  constexpr int N = Unit<T>::N;
+  const size_t per = rows * C / N;
+  const int cv = C / N;
   const size_t q = blockIdx.y;
   const size_t stride = (size_t)gridDim.x * kThreads;  // a multiple of cv
   const size_t first = (size_t)blockIdx.x * kThreads + threadIdx.x;
-  const int c0 = (int)(first % cv) * 8;
+  const int c0 = (int)(first % cv) * N;
   const float inv_rows = 1.f / (float)rows;
   const float* st = stats + q * 2 * C;
   const float* sq = sums + q * 2 * C;
-  float mean[8], rstd[8], gr[8], s_xh[8], s_dy[8];
+  float mean[N], rstd[N], gr[N], s_xh[N], s_dy[N];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
+  for (int j = 0; j < N; ++j) {
     const int c = c0 + j;
     mean[j] = st[2 * c];
     rstd[j] = st[2 * c + 1];
@@ -351,15 +390,15 @@ __global__ __launch_bounds__(kThreads) void bn_dx_vec_kernel(size_t rows, int C,
   uint4* os = reinterpret_cast<uint4*>(dx) + q * per;
 #pragma unroll 2
   for (size_t i = first; i < per; i += stride) {
-    float fx[8], fd[8], o[8];
-    unpack8(xs[i], fx);
-    unpack8(ds[i], fd);
+    float fx[N], fd[N], o[N];
+    Unit<T>::unpack(xs[i], fx);
+    Unit<T>::unpack(ds[i], fd);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < N; ++j) {
       const float xh = (fx[j] - mean[j]) * rstd[j];
       o[j] = gr[j] * (fd[j] - (s_dy[j] + xh * s_xh[j]) * inv_rows);
     }
-    os[i] = pack8(o);
+    os[i] = Unit<T>::pack(o);
   }
 }
 
@@ -543,21 +582,22 @@ inline unsigned vec_grid(size_t units, int units_per_row) {
   return (unsigned)g;
 }
 
-inline bool vec_ok(int es, int C, const void* p0, const void* p1, const void* p2) {
-  return es == 2 && C % 8 == 0 && ((((uintptr_t)p0 | (uintptr_t)p1 | (uintptr_t)p2) & 15) == 0);
+// rows of whole 16-byte units
+template <typename T>
+inline bool vec_ok(int C, const void* p0, const void* p1 = nullptr, const void* p2 = nullptr) {
+  return C % Unit<T>::N == 0 && ((((uintptr_t)p0 | (uintptr_t)p1 | (uintptr_t)p2) & 15) == 0);
 }
 
 // scratch: [chunks][2C] partial sums
 template <typename T>
 hipError_t bn_fwd_typed(hipStream_t s, size_t rows, int C, const T* x, const float* gamma, const float* beta, int act, T* a_out,
                         T* d_out, float* stats, float* scratch, const T* addend) {
-  const bool vec = vec_ok(sizeof(T), C, x, a_out, d_out) && (((uintptr_t)addend) & 15) == 0;
+  const bool vec = vec_ok<T>(C, x, a_out, d_out) && (((uintptr_t)addend) & 15) == 0;
   if (addend && !vec) return hipErrorNotSupported;
   const int cr = bn_chunk_rows(rows), chunks = bn_chunks(rows);
   float* partial = scratch;
-  if (sizeof(T) == 2 && C % 8 == 0 && (((uintptr_t)x) & 15) == 0)
-    hipLaunchKernelGGL(bn_colsum_vec_kernel<0>, dim3((C + 127) / 128, chunks, 1), dim3(kThreads), 0, s, rows, C, cr, (const uint16_t*)x,
-                       (const uint16_t*)nullptr, (const float*)nullptr, partial);
+  if (vec_ok<T>(C, x))
+    launch_colsum_vec<T, 0>(s, rows, C, 1, x, nullptr, nullptr, partial);
   else
     hipLaunchKernelGGL((bn_colsum_kernel<T, 0>), dim3((C + 63) / 64, chunks, 1), dim3(kThreads), 0, s, rows, C, cr, x, (const T*)nullptr,
                        (const float*)nullptr, partial);
@@ -567,8 +607,8 @@ hipError_t bn_fwd_typed(hipStream_t s, size_t rows, int C, const T* x, const flo
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (vec)
-    hipLaunchKernelGGL(bn_normalize_vec_kernel, dim3(vec_grid(rows * C / 8, C / 8)), dim3(kThreads), 0, s, rows, C, (const uint16_t*)x,
-                       stats, gamma, beta, act, (const uint16_t*)addend, (uint16_t*)a_out, (uint16_t*)d_out);
+    hipLaunchKernelGGL(bn_normalize_vec_kernel<T>, dim3(vec_grid(rows * C / Unit<T>::N, C / Unit<T>::N)), dim3(kThreads), 0, s, rows, C, x,
+                       stats, gamma, beta, act, addend, a_out, d_out);
   else
     hipLaunchKernelGGL(bn_normalize_kernel<T>, dim3(stream_grid(rows * C)), dim3(kThreads), 0, s, rows, C, x, stats, gamma, beta, act,
                        a_out, d_out);
@@ -580,18 +620,17 @@ template <typename T>
 hipError_t bn_bwd_typed(hipStream_t s, size_t rows, int C, int nseg, const T* dy, const T* x, const float* stats, const float* gamma_s,
                         const float* gamma_l, float alpha, float beta_c, T* dx, float* sums, float* scratch) {
   const int cr = bn_chunk_rows(rows), chunks = bn_chunks(rows);
-  if (sizeof(T) == 2 && C % 8 == 0 && ((((uintptr_t)x | (uintptr_t)dy)) & 15) == 0)
-    hipLaunchKernelGGL(bn_colsum_vec_kernel<2>, dim3((C + 127) / 128, chunks, nseg), dim3(kThreads), 0, s, rows, C, cr, (const uint16_t*)x,
-                       (const uint16_t*)dy, stats, scratch);
+  if (vec_ok<T>(C, x, dy))
+    launch_colsum_vec<T, 2>(s, rows, C, nseg, x, dy, stats, scratch);
   else
     hipLaunchKernelGGL((bn_colsum_kernel<T, 2>), dim3((C + 63) / 64, chunks, nseg), dim3(kThreads), 0, s, rows, C, cr, x, dy, stats, scratch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = launch_sum_partials(s, (size_t)nseg * 2 * C, chunks, scratch, sums);
   if (e != hipSuccess) return e;
-  if (vec_ok(sizeof(T), C, x, dy, dx))
-    hipLaunchKernelGGL(bn_dx_vec_kernel, dim3(vec_grid(rows * C / 8, C / 8), nseg), dim3(kThreads), 0, s, rows, C, (size_t)nseg,
-                       (const uint16_t*)dy, (const uint16_t*)x, stats, sums, gamma_s, gamma_l, alpha, beta_c, (uint16_t*)dx);
+  if (vec_ok<T>(C, x, dy, dx))
+    hipLaunchKernelGGL(bn_dx_vec_kernel<T>, dim3(vec_grid(rows * C / Unit<T>::N, C / Unit<T>::N), nseg), dim3(kThreads), 0, s, rows, C,
+                       (size_t)nseg, dy, x, stats, sums, gamma_s, gamma_l, alpha, beta_c, dx);
   else
     hipLaunchKernelGGL(bn_dx_kernel<T>, dim3(stream_grid(rows * C * nseg)), dim3(kThreads), 0, s, rows, C, (size_t)nseg, dy, x, stats, sums,
                        gamma_s, gamma_l, alpha, beta_c, dx);
