@@ -592,19 +592,39 @@ Tile pick(int M, int N, bool wgrad) {
   return best;
 }
 
-// k tiles per range of a weight gradient's contraction (the rows of the mini-batch): where its output has too few 64x64
-// tiles to fill the chip, as many ranges as give every CU a workgroup, at least 8 k tiles each (a 64 x 64 gradient over the
-// 131072 pixels of 16x16 maps is one tile and 2048 k tiles).  Larger tiles are only chosen when they already give 256
-// workgroups.
-int wgrad_range(int M, int N, int K, bool dma) {
+// Tile of a weight gradient and k tiles per range of its contraction (the rows of the mini-batch).  Where the output has too
+// few tiles to fill the chip, it is formed over as many ranges as give every CU a workgroup, at least 8 k tiles each (a
+// 64 x 64 gradient over the 131072 pixels of 16x16 maps is one tile and 2048 k tiles), and small tiles that fill it
+// unsplit give way to ranges of larger ones where that takes less time: a k tile of a 256x256 tile takes 1.66 us (32768
+// rows), of the others by their rates, and the ranges cost a launch (3 us) and their fp32 partial sums at 4 TB/s.
+// 2048 x 512 and 1536 x 512 over 6400 rows: 64x64 tiles fill the chip but wait for memory (34 us), 128x128 ones over four and
+// five ranges do less of it: two decoder blocks of width 512 1.087 -> 1.039 ms; 2048 x 2048 over 32768 rows, 128x128 tiles
+// before, 256x256 over four ranges now: decoder block of width 2048 10.52 -> 10.45 ms.
+struct WgradPlan { Tile tile; int per; };
+WgradPlan wgrad_plan(int M, int N, int K, bool dma) {
   const int kt = k_tiles(M);
-  if (dma && pick(N, K, true) != T64x64) return kt;
-  const long blocks = (long)((N + 63) / 64) * ((K + 63) / 64);
-  const int ranges = (int)std::min<long>(256 / blocks, kt / 8);
-  return ranges > 1 ? (kt + ranges - 1) / ranges : kt;
+  if (!dma) {
+    const long blocks = (long)((N + 63) / 64) * ((K + 63) / 64);
+    const int ranges = (int)std::min<long>(256 / blocks, kt / 8);
+    return {T64x64, ranges > 1 ? (kt + ranges - 1) / ranges : kt};
+  }
+  auto k_tile_us = [](const TileCost& t) { return 1.66 * t.bm * t.bn / 65536 * 100 / t.rate; };
+  WgradPlan best{pick(N, K, true), kt};
+  double best_us = -1;
+  for (const TileCost& t : kTiles)
+    if (t.t == best.tile) best_us = (double)((blocks_of(t, N, K) + 255) / 256) * k_tile_us(t) * kt;
+  for (const TileCost& t : kTiles) {
+    if (t.t != T256x256 && t.t != T128x128 && t.t != T64x64) continue;
+    const int ranges = (int)std::min<long>(256 / blocks_of(t, N, K), kt / 8);
+    if (ranges < 2) continue;
+    const int per = (kt + ranges - 1) / ranges;
+    const double us = k_tile_us(t) * per + 3 + (double)(ranges + 1) * N * K * 4 / 4e6;
+    if (us < best_us) { best_us = us; best = {t.t, per}; }
+  }
+  return best;
 }
 inline int wgrad_ranges(int M, int N, int K) {
-  const int per = wgrad_range(M, N, K, dma_ok(N, K, M, N, K, true, true));
+  const int per = wgrad_plan(M, N, K, dma_ok(N, K, M, N, K, true, true)).per;
   return (k_tiles(M) + per - 1) / per;
 }
 
@@ -676,13 +696,22 @@ hipError_t mfma_wgrad(hipStream_t s, int M, int N, int K, const uint16_t* dz, co
   // gW[N x K] = dz^T[N x M] . x[M x K]: GEMM (N, K, contraction M)
   const bool fits = dma_ok(N, K, M, N, K, true, true);
   const bool dma = fits && aligned(16, dz, x);
-  const int per = wgrad_range(M, N, K, fits), ranges = (k_tiles(M) + per - 1) / per;
+  const WgradPlan plan = wgrad_plan(M, N, K, fits);
+  const int per = plan.per, ranges = (k_tiles(M) + per - 1) / per;
   if (!partial || ranges == 1) return run<true, true>(dma, s, N, K, M, dz, N, x, K, EpiWgrad{gW, K});
   const EpiWgradSplit e{partial, K, (size_t)N * K};
-  const hipError_t err =
-      !dma ? launch_any<64, 64, 2, 2, true, true>(s, N, K, M, dz, N, x, K, e, per)
-      : M % DBK ? launch_dma<64, 64, 2, 2, 4, true, true, true, false, true>(s, N, K, M, dz, N, x, K, e, SideCopy{nullptr, nullptr, 0}, per)
-                : launch_dma<64, 64, 2, 2, 4, true, true, true, false, false>(s, N, K, M, dz, N, x, K, e, SideCopy{nullptr, nullptr, 0}, per);
+  const SideCopy none{nullptr, nullptr, 0};
+  auto split = [&](auto tail) {
+    constexpr bool T = decltype(tail)::value;
+    switch (plan.tile) {
+      case T256x256: return launch_dma<256, 256, 2, 4, 2, true, true, false, true, T>(s, N, K, M, dz, N, x, K, e, none, per);
+      case T128x128: return launch_dma<128, 128, 2, 2, 3, true, true, false, true, T>(s, N, K, M, dz, N, x, K, e, none, per);
+      default: return launch_dma<64, 64, 2, 2, 4, true, true, true, false, T>(s, N, K, M, dz, N, x, K, e, none, per);
+    }
+  };
+  const hipError_t err = !dma        ? launch_any<64, 64, 2, 2, true, true>(s, N, K, M, dz, N, x, K, e, per)
+                         : M % DBK ? split(std::true_type{})
+                                   : split(std::false_type{});
   if (err != hipSuccess) return err;
   return launch_sum_partials(s, (size_t)N * K, ranges, partial, gW);
 }

@@ -62,6 +62,8 @@ def test_dense_fp32(rows, fin, fout):
     (1000, 136, 2040), (2040, 136, 2040), (2040, 136, 4088), (4000, 136, 4088),   # 128 x 64, 128 x 128, 256 x 128, 256 x 256
     (2040, 64, 4088), (2040, 128, 4088), (4000, 64, 4088), (4000, 128, 4088),     # fewer k tiles than the last two have stages
     (72, 2048, 6144), (72, 6144, 2048),                       # weight gradients on 384 x 128 and 128 x 384 tiles
+    (6400, 768, 776), (6401, 520, 1032),                      # ... over several row ranges on 128 x 128 tiles
+    (16384, 1024, 1024), (16389, 1032, 1032),                 # ... and on 256 x 256 tiles, or 128 x 128 ones
 ])
 @pytest.mark.parametrize("shift", [0, 1])                     # 1: the input starts at an odd element
 def test_dense_bf16(rows, fin, fout, shift):
