@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device_utils.h"
 #include "mfma_common.h"
@@ -236,8 +237,9 @@ __global__ __launch_bounds__(256) void attn_softmax_bwd_kernel(int S, size_t row
 // divided by the row sums and turned through LDS for 16-byte row stores; lse = max + log(sum) (natural
 // logarithm of the scaled scores) is what the backward pass recomputes the probabilities from.
 // No score matrix reaches memory.
-// Any number of tokens: rows past the last token repeat it, in the last key block as among the queries.  A repeated key
-// comes after every real query, so the causal mask removes it; a repeated query is not stored.
+// WHOLE: the tokens are whole blocks of 64.  Otherwise rows past the last token repeat it, in the last key block as among
+// the queries: a repeated key comes after every real query, so the causal mask removes it; a repeated query is not
+// stored.  There P also keeps its 32 bits into the second product (Split below).
 // Four waves per workgroup instead of eight where that many workgroups would not fill the chip, and on short
 // sequences, whose last waves would have no queries (see flash_waves).
 constexpr int kFlashStages = 3;
@@ -257,7 +259,37 @@ __device__ __forceinline__ bf16x8 flash_v_frag(const uint16_t* lds, int dbase, i
   return __builtin_bit_cast(bf16x8, v);
 }
 
-template <int DH, int NW>
+// Eight fp32 values as the sum of bf16 fragments.  WHOLE: one, the values rounded to bf16.  Otherwise three, which hold
+// the 24 bits of each value: bf16 products are exact in fp32, so three matrix instructions on the parts are one product
+// with the fp32 value.  Sequences that are no whole blocks were computed with fp32 probabilities throughout before these
+// kernels took them, and rounding P and dS to bf16 moves the results off by more than the rounding of the stored result
+// does (relative to fp64, 32 sequences of 200 tokens, 8 heads of 64: output 1.58e-3 -> 1.92e-3, dQ 1.88e-3 -> 2.57e-3, dV
+// 1.66e-3 -> 2.29e-3).
+template <bool WHOLE>
+struct Split {
+  static constexpr int N = WHOLE ? 1 : 3;
+  bf16x8 part[N];
+  __device__ __forceinline__ void set(float (&e)[8]) {
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const uint32_t u[4] = {pack_bf16x2(e[0], e[1]), pack_bf16x2(e[2], e[3]), pack_bf16x2(e[4], e[5]), pack_bf16x2(e[6], e[7])};
+      part[n] = __builtin_bit_cast(bf16x8, make_uint4(u[0], u[1], u[2], u[3]));
+      if (n + 1 < N)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {  // exact
+          e[2 * t] -= __uint_as_float(u[t] << 16);
+          e[2 * t + 1] -= __uint_as_float(u[t] & 0xffff0000u);
+        }
+    }
+  }
+  // c += a . (the values)^T, the smallest parts first
+  __device__ __forceinline__ void multiply(const bf16x8& a, floatx16& c) const {
+#pragma unroll
+    for (int n = N - 1; n >= 0; --n) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, part[n], c, 0, 0, 0);
+  }
+};
+
+template <int DH, int NW, bool WHOLE>
 __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int heads, const uint16_t* __restrict__ qkv,
                                                                  uint16_t* __restrict__ out, float* __restrict__ lse,
                                                                  float scale_log2) {
@@ -289,7 +321,8 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int head
   // Q fragments (B operand: column = query lane % 32, 8 consecutive head-dimension values)
   bf16x8 qf[DH / 16];
   {
-    const uint16_t* qrow = qbase + (size_t)min(qw + (lane & 31), S - 1) * ld + 8 * half;
+    const int q = WHOLE ? (active ? qw + (lane & 31) : 0) : min(qw + (lane & 31), S - 1);
+    const uint16_t* qrow = qbase + (size_t)q * ld + 8 * half;
 #pragma unroll
     for (int kk = 0; kk < DH / 16; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qrow + kk * 16));
   }
@@ -302,15 +335,17 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int head
   const int short_block = S / 64, keys_left = S - 64 * short_block;  // the last block, where it is not whole
   kt.init(ld, 0, 64, wave, lane);
   vt.init(ld, 0, DH, wave, lane);
-  kt_last.init(ld, 0, max(keys_left, 1), wave, lane);
-  vt_last.init(ld, 0, DH, wave, lane, max(keys_left, 1) - 1);
+  if constexpr (!WHOLE) {
+    kt_last.init(ld, 0, keys_left, wave, lane);
+    vt_last.init(ld, 0, DH, wave, lane, keys_left - 1);
+  }
   const int nkb = (min(S, q0 + kFlashQ) + 63) / 64;  // key blocks any query of the workgroup can see
   auto issue_block = [&](int blk, int st) {
     const int kb = min(blk, nkb - 1);  // blocks past the end re-read the last one into a stage nobody reads again
     const uint32_t dst = lds_base + st * kStageBytes;
     const uint16_t* ksrc = kbase + (size_t)kb * 64 * ld;
     const uint16_t* vsrc = vbase + (size_t)kb * 64 * ld;
-    const bool whole = kb != short_block;  // wave uniform
+    const bool whole = WHOLE || kb != short_block;  // wave uniform
     KT k = kt;
     VT v = vt;
 #pragma unroll
@@ -374,7 +409,7 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int head
       const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);
       mrun = mnew;
       float psum = 0.f;
-      bf16x8 pf[4];
+      Split<WHOLE> pf[4];
 #pragma unroll
       for (int g16 = 0; g16 < 4; ++g16) {
         float e[8];
@@ -383,8 +418,7 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int head
           e[t] = __builtin_amdgcn_exp2f(sacc[g16 >> 1][8 * (g16 & 1) + t] - mnew);
           psum += e[t];
         }
-        const uint4 u = make_uint4(pack_bf16x2(e[0], e[1]), pack_bf16x2(e[2], e[3]), pack_bf16x2(e[4], e[5]), pack_bf16x2(e[6], e[7]));
-        pf[g16] = __builtin_bit_cast(bf16x8, u);
+        pf[g16].set(e);
       }
       lsum = fmaf(lsum, alpha, psum);
       if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {  // some row's maximum moved: rescale what is accumulated
@@ -396,8 +430,7 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int head
 #pragma unroll
       for (int g16 = 0; g16 < 4; ++g16)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          oacc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(flash_v_frag<DH>(lv, 32 * j, g16, lane), pf[g16], oacc[0][j], 0, 0, 0);
+        for (int j = 0; j < TN; ++j) pf[g16].multiply(flash_v_frag<DH>(lv, 32 * j, g16, lane), oacc[0][j]);
     }
     rd = rd + 1 == NS ? 0 : rd + 1;
     wr = wr + 1 == NS ? 0 : wr + 1;
@@ -411,9 +444,9 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int head
   for (int j = 0; j < TN; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[0][j][r] *= inv;
-  if (half == 0 && query < S) lse[(size_t)blockIdx.x * S + query] = (mrun + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
+  if (half == 0 && (WHOLE || query < S)) lse[(size_t)blockIdx.x * S + query] = (mrun + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
   float* wave_lds = reinterpret_cast<float*>(lds_raw) + wave * (wave_epilogue_bytes<1, TN>() / 4);
-  if (qw + 32 <= S)
+  if (WHOLE || qw + 32 <= S)
     store_tiles_coalesced<1, TN>(oacc, EpiDgrad{nullptr, out, D}, zb * S + qw, zh * DH, lane, wave_lds);
   else
     store_tiles<1, TN>(oacc, EpiDgrad{nullptr, out, D}, zb * S + qw, zh * DH, zb * S + S, zh * DH + DH, lane);
@@ -423,14 +456,14 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int head
 // chip gets a workgroup per CU that way.
 inline int flash_waves(int seqs, int S, int heads) { return S > 128 && (long)seqs * heads * ((S + 255) / 256) >= 256 ? 8 : 4; }
 
-template <int DH, int NW>
+template <int DH, int NW, bool WHOLE>
 hipError_t launch_flash_fwd(hipStream_t s, int seqs, int S, int heads, const uint16_t* qkv, uint16_t* out, float* lse) {
   constexpr int kFlashQ = 32 * NW;
   constexpr size_t stage_bytes = (size_t)kFlashStages * ((DH / 64) * RowDma<64, NW>::kBytes + ColDma<DH, NW>::kBytes);
   constexpr size_t epi_bytes = (size_t)NW * wave_epilogue_bytes<1, DH / 32>();
   constexpr size_t lds_bytes = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
   static_assert(lds_bytes <= 160 * 1024, "stages do not fit the LDS of a CU");
-  auto kernel = attn_flash_fwd_kernel<DH, NW>;
+  auto kernel = attn_flash_fwd_kernel<DH, NW, WHOLE>;
   static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
@@ -449,8 +482,8 @@ hipError_t launch_flash_fwd(hipStream_t s, int seqs, int S, int heads, const uin
 //   dK, dV  a workgroup owns 256 keys and walks over the query blocks from its diagonal to the end:
 //           S = Q K^T and dP = dO V^T with K, V fragments in registers, Q and dO streamed; lse, delta of the 64
 //           streamed queries come through LDS with the block; dV^T += dO^T P, dK^T += Q^T dS.
-// P = exp(scale S - lse) and dS = scale P (dP - delta) are formed in registers and packed to bf16 as the B
-// fragments of the second products, exactly like P in the forward kernel; the streamed operand is staged twice,
+// P = exp(scale S - lse) and dS = scale P (dP - delta) are formed in registers and packed to bf16 (WHOLE; three bf16
+// parts otherwise) as the B fragments of the second products, exactly like P in the forward kernel; the streamed operand is staged twice,
 // once in the row layout the first products read and once in the layout the transposing reads of the second
 // products want.  The scores are recomputed in both launches (7 matrix products instead of 5), no score-sized
 // tensor reaches memory, nothing is accumulated with atomics: every output element has one owner.
@@ -631,7 +664,14 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_bwd_kernel(int S, int head
             pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(RT::frag(lr2 + c * (RT::kBytes / 2), 32 * j, kk, lane),
                                                            f2[c * 4 + kk], pacc, 0, 0, 0);
           }
-        bf16x8 pf[2], dsf[2];
+        auto second_products = [&](int h, const Split<WHOLE>& p, const Split<WHOLE>& ds) {
+#pragma unroll
+          for (int jj = 0; jj < TN; ++jj) {
+            ds.multiply(flash_v_frag<DH>(lc1, 32 * jj, 2 * j + h, lane), acc1[0][jj]);
+            if (OWN_KEYS) p.multiply(flash_v_frag<DH>(lc2, 32 * jj, 2 * j + h, lane), acc2[0][jj]);
+          }
+        };
+        Split<WHOLE> pf[2], dsf[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           float pe[8], de[8];
@@ -659,21 +699,14 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_bwd_kernel(int S, int head
               de[t] = p * (pacc[r] - dlv[u]) * scale;
             }
           }
-          pf[h] = __builtin_bit_cast(bf16x8, make_uint4(pack_bf16x2(pe[0], pe[1]), pack_bf16x2(pe[2], pe[3]),
-                                                         pack_bf16x2(pe[4], pe[5]), pack_bf16x2(pe[6], pe[7])));
-          dsf[h] = __builtin_bit_cast(bf16x8, make_uint4(pack_bf16x2(de[0], de[1]), pack_bf16x2(de[2], de[3]),
-                                                          pack_bf16x2(de[4], de[5]), pack_bf16x2(de[6], de[7])));
+          pf[h].set(pe);
+          dsf[h].set(de);
+          if (!WHOLE) second_products(h, pf[h], dsf[h]);  // three parts: of one half at a time
         }
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int jj = 0; jj < TN; ++jj) {
-            acc1[0][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(flash_v_frag<DH>(lc1, 32 * jj, 2 * j + h, lane), dsf[h],
-                                                                  acc1[0][jj], 0, 0, 0);
-            if (OWN_KEYS)
-              acc2[0][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(flash_v_frag<DH>(lc2, 32 * jj, 2 * j + h, lane), pf[h],
-                                                                    acc2[0][jj], 0, 0, 0);
-          }
+        if (WHOLE) {
+          second_products(0, pf[0], dsf[0]);
+          second_products(1, pf[1], dsf[1]);
+        }
         if (OWN_KEYS) __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -736,9 +769,15 @@ bool attention_flash_fwd_supported(int seqs, int S, int heads, int dh) {
 
 hipError_t attention_flash_fwd(hipStream_t s, int seqs, int S, int heads, int dh, const uint16_t* qkv, uint16_t* out, float* lse) {
   if (!attention_flash_fwd_supported(seqs, S, heads, dh)) return hipErrorNotSupported;
-  if (flash_waves(seqs, S, heads) == 8)
-    return dh == 64 ? launch_flash_fwd<64, 8>(s, seqs, S, heads, qkv, out, lse) : launch_flash_fwd<128, 8>(s, seqs, S, heads, qkv, out, lse);
-  return dh == 64 ? launch_flash_fwd<64, 4>(s, seqs, S, heads, qkv, out, lse) : launch_flash_fwd<128, 4>(s, seqs, S, heads, qkv, out, lse);
+  auto run = [&](auto whole) {
+    constexpr bool W = decltype(whole)::value;
+    if (flash_waves(seqs, S, heads) == 8)
+      return dh == 64 ? launch_flash_fwd<64, 8, W>(s, seqs, S, heads, qkv, out, lse)
+                      : launch_flash_fwd<128, 8, W>(s, seqs, S, heads, qkv, out, lse);
+    return dh == 64 ? launch_flash_fwd<64, 4, W>(s, seqs, S, heads, qkv, out, lse)
+                    : launch_flash_fwd<128, 4, W>(s, seqs, S, heads, qkv, out, lse);
+  };
+  return S % 64 == 0 ? run(std::true_type{}) : run(std::false_type{});
 }
 
 size_t attention_flash_bwd_scratch_bytes(int seqs, int S, int heads) { return (size_t)seqs * heads * stat_rows(S) * 2 * sizeof(float); }

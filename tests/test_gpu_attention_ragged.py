@@ -16,3 +16,62 @@ def test_ragged_attention_bf16(tokens, heads, dh, mb):
     d = heads * dh
     specs = (W.Dense(32, 3 * d, "none", tokens=tokens), W.Attention(d, heads, tokens), W.Dense(d, 32, "none", tokens=tokens))
     print(tokens, heads, dh, run_stage(specs, f"attn_ragged_{tokens}_{heads}_{dh}", "bf16", mb=mb, n=2, minibatches=2))
+
+
+def _attention_stage(tokens, heads, dh, mb):
+    """Attention behind which a dense layer passes everything on unchanged (unit matrix: bf16 values times one)."""
+    import numpy as np
+    from paper_2509_23241_amd.runner import GpuStage
+    d = heads * dh
+    return GpuStage([("attn", d, heads, tokens), (d, d, "none", tokens)], [np.eye(d, dtype=np.float32), np.zeros(d, np.float32)],
+                    dtype="bf16", mb=mb, n=1, stage_index=1, num_stages=2, policy="latest", lam=0.1, lr=0.0, momentum=0.0,
+                    ring_capacity=1, max_in_flight=1)
+
+
+def _run_attention(qkv, dy, heads):
+    """Outputs of one pass: y [mb][tokens][d] and the gradients of q, k, v."""
+    mb, tokens, d3 = qkv.shape
+    st = _attention_stage(tokens, heads, d3 // 3 // heads, mb)
+    y, _ = st.forward(0, 0, qkv.reshape(mb, -1))
+    dx, _ = st.backward(0, dy.reshape(mb, -1))
+    st.close()
+    return (y.reshape(mb, tokens, d3 // 3),) + dx.reshape(mb, tokens, d3).split(d3 // 3, -1)
+
+
+def _attention64(qkv, dy, heads, stored=None):
+    """The same in fp64; `stored`: the output the backward pass forms delta = rowsum(dO . O) from (its own, rounded)."""
+    import torch
+    mb, S, d3 = qkv.shape
+    dh = d3 // 3 // heads
+    rows = lambda t: t.double().reshape(mb, S, heads, dh).permute(0, 2, 1, 3).contiguous()
+    flat = lambda t: t.permute(0, 2, 1, 3).reshape(mb, S, heads * dh)
+    turned = lambda t: t.transpose(-1, -2).contiguous()
+    q, k, v = [rows(t) for t in qkv.split(d3 // 3, -1)]
+    do = rows(dy)
+    s = torch.matmul(q, turned(k)) / dh ** 0.5
+    p = s.masked_fill(torch.ones(S, S, dtype=torch.bool, device=s.device).triu(1), -float("inf")).softmax(-1)
+    o = torch.matmul(p, v)
+    delta = (do * (o if stored is None else rows(stored))).sum(-1, keepdim=True)
+    ds = p * (torch.matmul(do, turned(v)) - delta) / dh ** 0.5
+    return flat(o), flat(torch.matmul(ds, k)), flat(torch.matmul(turned(ds), q)), flat(torch.matmul(turned(p), do))
+
+
+@pytest.mark.parametrize("tokens,heads,dh,mb", [
+    (5, 8, 64, 4), (17, 8, 64, 4), (31, 4, 128, 4), (65, 8, 64, 4), (100, 4, 128, 2), (287, 4, 128, 2),   # four waves
+    (200, 8, 64, 32), (191, 16, 128, 16),                                                                 # eight waves
+])
+def test_probabilities_and_their_gradients_keep_32_bits(tokens, heads, dh, mb):
+    """Only the rounding of a stored result separates it from fp64: probabilities or dS held in bf16 would add errors of
+    2^-9 each to the sums, 1.2 to 1.4 times the rounding alone in the norm (fp32 sums: 1e-6, nothing next to 1.6e-3)."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tokens)
+    d = heads * dh
+    qkv = torch.randn(mb, tokens, 3 * d, generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn(mb, tokens, d, generator=g, device="cuda").to(torch.bfloat16)
+    got = _run_attention(qkv, dy, heads)
+    for name, a, ref in zip(("y", "dq", "dk", "dv"), got, _attention64(qkv, dy, heads, got[0])):
+        off = float((a.double() - ref).norm() / ref.norm())
+        rounding = float((ref.to(torch.bfloat16).double() - ref).norm() / ref.norm())
+        print(name, off / rounding)
+        assert off <= 1.05 * rounding, name
