@@ -289,6 +289,116 @@ struct Split {
   }
 };
 
+// ---- rows one by one ------------------------------------------------------------------------------
+// The matrix instructions multiply the zero probability of a masked pair with whatever the other operand holds: an
+// infinity or NaN in a later token of the block makes NaN of rows that do not see it.  Sequences that are no whole blocks
+// were computed pair by pair before the fused kernels took them, and a row depended on nothing but the pairs it sees.  So
+// that it still does, a wave whose result holds something that is not finite forms those rows again, one after the other,
+// from the visible pairs alone: lane = pair for the dot products, lane = column for the sums.  Finite results cost the look
+// at the accumulators.
+template <int TN>
+__device__ __forceinline__ bool all_finite(const floatx16 (&acc)[1][TN]) {
+  float s = 0.f;
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s = fmaf(acc[0][j][r], 0.f, s);  // 0, or NaN
+  return s == 0.f;
+}
+// bit i: row i of the wave (lanes i and i + 32) lies inside the sequence and is not finite
+__device__ __forceinline__ uint32_t rows_to_redo(bool finite, int row, int S) {
+  const uint64_t m = __builtin_amdgcn_ballot_w64(!finite && row < S);
+  return (uint32_t)m | (uint32_t)(m >> 32);
+}
+__device__ __forceinline__ float lane_of(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+__device__ __forceinline__ float sum_of_wave(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+template <int DH>
+__device__ __forceinline__ float row_dot(const uint16_t* a, const uint16_t* b) {
+  float acc = 0.f;
+  for (int d = 0; d < DH; ++d) acc = fmaf(bf16_to_float(a[d]), bf16_to_float(b[d]), acc);
+  return acc;
+}
+// acc[c] += sum over lanes first .. count - 1 of w (of lane) * rows[lane * ld + column of this lane]
+template <int DH>
+__device__ __forceinline__ void add_rows(float (&acc)[DH / 64], float w, const uint16_t* rows, size_t ld, int first, int count, int lane) {
+  for (int t = first; t < count; ++t) {
+    const float wt = lane_of(w, t);
+#pragma unroll
+    for (int c = 0; c < DH / 64; ++c) acc[c] = fmaf(wt, bf16_to_float(rows[t * ld + lane + 64 * c]), acc[c]);
+  }
+}
+
+// Output row i; q, k, v: row 0 of each (row stride ld), scale_log2 as in the kernel
+template <int DH>
+__device__ __forceinline__ void redo_output_row(int i, const uint16_t* q, const uint16_t* k, const uint16_t* v, size_t ld, uint16_t* out,
+                                             float* lse, float scale_log2, int lane) {
+  float m = -INFINITY, l = 0.f, o[DH / 64] = {};
+  for (int k0 = 0; k0 <= i; k0 += 64) {
+    const int j = k0 + lane;
+    const float sc = j <= i ? row_dot<DH>(q + (size_t)i * ld, k + (size_t)j * ld) * scale_log2 : -INFINITY;
+    float mx = sc;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    const float mn = fmaxf(m, mx);
+    const float p = sc == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc - mn);
+    const float corr = __builtin_amdgcn_exp2f(m - mn);
+    l = l * corr + sum_of_wave(p);
+    m = mn;
+#pragma unroll
+    for (int c = 0; c < DH / 64; ++c) o[c] *= corr;
+    add_rows<DH>(o, p, v + (size_t)k0 * ld, ld, 0, min(64, i - k0 + 1), lane);
+  }
+  const float inv = 1.f / l;
+#pragma unroll
+  for (int c = 0; c < DH / 64; ++c) out[lane + 64 * c] = float_to_bf16(o[c] * inv);
+  if (lane == 0) *lse = (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+}
+// dQ row i; stat: (lse * log2(e), delta) of query 0
+template <int DH>
+__device__ __forceinline__ void redo_dq_row(int i, const uint16_t* q, const uint16_t* k, const uint16_t* v, size_t ld, const uint16_t* dout,
+                                         size_t ldo, const float* stat, uint16_t* dq, float scale, float scale_log2, int lane) {
+  const float l2 = stat[2 * i], delta = stat[2 * i + 1];
+  float acc[DH / 64] = {};
+  for (int k0 = 0; k0 <= i; k0 += 64) {
+    const int j = k0 + lane;
+    float ds = 0.f;
+    if (j <= i) {
+      const float p = __builtin_amdgcn_exp2f(row_dot<DH>(q + (size_t)i * ld, k + (size_t)j * ld) * scale_log2 - l2);
+      ds = p * (row_dot<DH>(dout + (size_t)i * ldo, v + (size_t)j * ld) - delta);
+    }
+    add_rows<DH>(acc, ds, k + (size_t)k0 * ld, ld, 0, min(64, i - k0 + 1), lane);
+  }
+#pragma unroll
+  for (int c = 0; c < DH / 64; ++c) dq[lane + 64 * c] = float_to_bf16(acc[c] * scale);
+}
+// dK and dV row j of S
+template <int DH>
+__device__ __forceinline__ void redo_dkv_row(int j, int S, const uint16_t* q, const uint16_t* k, const uint16_t* v, size_t ld,
+                                          const uint16_t* dout, size_t ldo, const float* stat, uint16_t* dk, uint16_t* dv, float scale,
+                                          float scale_log2, int lane) {
+  float ak[DH / 64] = {}, av[DH / 64] = {};
+  for (int i0 = j / 64 * 64; i0 < S; i0 += 64) {
+    const int i = i0 + lane;
+    float p = 0.f, ds = 0.f;
+    if (i >= j && i < S) {
+      p = __builtin_amdgcn_exp2f(row_dot<DH>(q + (size_t)i * ld, k + (size_t)j * ld) * scale_log2 - stat[2 * i]);
+      ds = p * (row_dot<DH>(dout + (size_t)i * ldo, v + (size_t)j * ld) - stat[2 * i + 1]);
+    }
+    const int first = max(0, j - i0), count = min(64, S - i0);
+    add_rows<DH>(ak, ds, q + (size_t)i0 * ld, ld, first, count, lane);
+    add_rows<DH>(av, p, dout + (size_t)i0 * ldo, ldo, first, count, lane);
+  }
+#pragma unroll
+  for (int c = 0; c < DH / 64; ++c) {
+    dk[lane + 64 * c] = float_to_bf16(ak[c] * scale);
+    dv[lane + 64 * c] = float_to_bf16(av[c]);
+  }
+}
+
 template <int DH, int NW, bool WHOLE>
 __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int heads, const uint16_t* __restrict__ qkv,
                                                                  uint16_t* __restrict__ out, float* __restrict__ lse,
@@ -450,6 +560,15 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int head
     store_tiles_coalesced<1, TN>(oacc, EpiDgrad{nullptr, out, D}, zb * S + qw, zh * DH, lane, wave_lds);
   else
     store_tiles<1, TN>(oacc, EpiDgrad{nullptr, out, D}, zb * S + qw, zh * DH, zb * S + S, zh * DH + DH, lane);
+  if constexpr (!WHOLE) {
+    uint32_t redo = rows_to_redo(all_finite(oacc), query, S);
+    if (redo) wait_vmcnt<0>();  // what they replace is stored
+    for (; redo; redo &= redo - 1) {
+      const int i = qw + __builtin_ctz(redo);
+      redo_output_row<DH>(i, qbase, kbase, vbase, ld, out + ((size_t)zb * S + i) * D + zh * DH, lse + (size_t)blockIdx.x * S + i,
+                          scale_log2, lane);
+    }
+  }
 }
 
 // Waves per workgroup of the fused kernels: eight share every streamed block and cover each other's stalls, where the
@@ -723,6 +842,17 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_bwd_kernel(int S, int head
   } else {
     store_tiles<1, TN>(acc1, e1, zb * S + ow, zh * DH, zb * S + S, zh * DH + DH, lane);
     if (OWN_KEYS) store_tiles<1, TN>(acc2, e2, zb * S + ow, zh * DH, zb * S + S, zh * DH + DH, lane);
+  }
+  if constexpr (!WHOLE) {
+    uint32_t redo = rows_to_redo(all_finite(acc1) && (!OWN_KEYS || all_finite(acc2)), oi, S);
+    if (redo) wait_vmcnt<0>();  // what they replace is stored
+    for (; redo; redo &= redo - 1) {
+      const int i = ow + __builtin_ctz(redo);
+      const float* zstat = stat + (size_t)z * stat_rows(S) * 2;
+      uint16_t* row = dqkv + ((size_t)zb * S + i) * ld3 + zh * DH;
+      if (OWN_KEYS) redo_dkv_row<DH>(i, S, qp, qp + D, qp + 2 * D, ld3, dop, D, zstat, row + D, row + 2 * D, scale, scale_log2, lane);
+      else redo_dq_row<DH>(i, qp, qp + D, qp + 2 * D, ld3, dop, D, zstat, row, scale, scale_log2, lane);
+    }
   }
 }
 

@@ -75,3 +75,37 @@ def test_probabilities_and_their_gradients_keep_32_bits(tokens, heads, dh, mb):
         rounding = float((ref.to(torch.bfloat16).double() - ref).norm() / ref.norm())
         print(name, off / rounding)
         assert off <= 1.05 * rounding, name
+
+
+@pytest.mark.parametrize("tokens,heads,dh,mb", [(40, 2, 64, 2), (70, 2, 128, 2), (130, 2, 64, 1),     # four waves
+                                                (150, 16, 64, 16), (150, 16, 128, 16)])                # eight waves
+def test_non_finite_values_stay_in_the_rows_that_see_them(tokens, heads, dh, mb):
+    """An infinity in a token's value, key or upstream gradient: rows that do not depend on it are what they are without
+    (up to the order of the sums: one rounding of the stored result)."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tokens)
+    d = heads * dh
+    qkv = torch.randn(mb, tokens, 3 * d, generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn(mb, tokens, d, generator=g, device="cuda").to(torch.bfloat16)
+    clean = dict(zip(("y", "dq", "dk", "dv"), _run_attention(qkv, dy, heads)))
+    assert all(bool(torch.isfinite(t.float()).all()) for t in clean.values())
+
+    def check(got, rows):
+        for name, sel in rows.items():
+            a, b = got[name][:, sel].double(), clean[name][:, sel].double()
+            assert bool(torch.isfinite(a).all()), name
+            assert float((a - b).norm()) <= 2.0 ** -8 * float(b.norm()), name
+
+    t = tokens // 2 + 3
+    before, after, others = slice(0, t), slice(t + 1, None), [i for i in range(tokens) if i != t]
+    for where, unaffected in (
+            ("v", {"y": before, "dq": before, "dv": slice(None)}),     # dV holds no value
+            ("k", {"y": before, "dq": before}),
+            ("dy", {"y": slice(None), "dq": others, "dk": after, "dv": after})):
+        x, u = qkv.clone(), dy.clone()
+        part = {"k": x[:, t, d:2 * d], "v": x[:, t, 2 * d:], "dy": u[:, t]}[where]
+        part[:, ::3] = float("inf")
+        got = dict(zip(("y", "dq", "dk", "dv"), _run_attention(x, u, heads)))
+        check(got, unaffected)
+        assert not bool(torch.isfinite(got["dq" if where == "dy" else "y"][:, t].float()).all())   # and it does arrive
