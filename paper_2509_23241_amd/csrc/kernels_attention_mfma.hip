@@ -892,8 +892,11 @@ size_t attention_mfma_scratch_bytes(int seqs, int S, int heads) {
   return chunk * per;
 }
 
+// Sequences of one to three tokens (one, with 128-wide heads) stay on the wavefront kernels: forward and backward with 2048
+// heads 73 us there and 118 here for one token, 93 and 120 for two, 130 and 124 for four (64 wide); 177 and 233 for one,
+// 260 and 236 for two (128 wide).
 bool attention_flash_fwd_supported(int seqs, int S, int heads, int dh) {
-  return (dh == 64 || dh == 128) && S >= 1 && heads >= 1 && seqs >= 1 && (long)seqs * heads <= 65535 &&
+  return (dh == 64 || dh == 128) && S >= 1 && S * dh >= 256 && heads >= 1 && seqs >= 1 && (long)seqs * heads <= 65535 &&
          64ull * 3 * heads * dh * 2 < (1ull << 31);  // 32-bit byte offsets inside one 64-key block
 }
 
