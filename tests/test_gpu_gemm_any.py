@@ -148,3 +148,30 @@ def test_convolution(dtype, imgs, H, W, cin, cout, k, stride):
     assert _rel(dx.reshape(rdx.shape), rdx) <= _sum_tol(k * k * cout) + store
     assert _rel(gw, rgw) <= _sum_tol(pixels)
     assert _rel(gb, dy.astype(np.float64).sum((0, 1, 2))) <= _sum_tol(pixels)
+
+
+@pytest.mark.parametrize("dtype,imgs,size,cin,cout,k,stride", [
+    ("f32", 16, 32, 64, 64, 3, 1), ("f32", 16, 16, 128, 128, 3, 1),   # ranges longer than a part, 64 x 64 and 128 x 128 tiles
+    ("f32", 9, 20, 3, 12, 5, 2),                                      # the last part not whole, words
+    ("bf16", 16, 20, 96, 128, 3, 1), ("bf16", 8, 64, 48, 48, 3, 1),
+])
+def test_convolution_weight_gradient_is_summed_in_parts(dtype, imgs, size, cin, cout, k, stride):
+    """Products of 256 pixels are added up apart.  A rounding of a partial sum s is off by 0.39 * 2^-24 |s| (root mean square over
+    a binade); the squares of n partial sums of random terms add up to n / 2 times that of the last one, so a sum of P
+    products in parts of n roundings each is off by 0.39 * 2^-24 * sqrt(n / 2 + P / 512): n = 256 in fp32, 8 in bf16, where
+    a matrix instruction adds 32 products.  One chain over a range of 512 would exceed it by 1.4; 15 % are allowed for."""
+    from synth_inputs import round_bf16
+    rng = np.random.default_rng(imgs * size + k)
+    cast = round_bf16 if dtype == "bf16" else (lambda t: t.astype(np.float32))
+    wgt = cast(rng.standard_normal((cout, k, k, cin))).astype(np.float32)
+    x = cast(rng.standard_normal((imgs, size, size, cin))).astype(np.float32)
+    dy = cast(rng.standard_normal((imgs, size // stride, size // stride, cout))).astype(np.float32)
+    b = np.zeros(cout, np.float32)
+    _, _, (gw, _) = _run(_stage(("conv", cin, cout, size, size, "none", stride, k), [wgt, b], imgs, dtype),
+                         x.reshape(imgs, -1), dy.reshape(imgs, -1))
+    off = _rel(gw, _conv_reference(x, wgt, b, dy, stride)[2])
+    pixels = imgs * (size // stride) ** 2
+    roundings = min(pixels, 256) / (32 if dtype == "bf16" else 1)
+    bound = 1.15 * 0.39 * 2.0 ** -24 * np.sqrt(roundings / 2 + pixels / 512)
+    print(off, bound)
+    assert off <= bound
