@@ -50,3 +50,22 @@ def test_stream_batchnorm(dtype, rows, C):
         rg += (d64 * xh).sum(0)
         rb += d64.sum(0)
     assert _rel(gg, rg) <= TOL and _rel(gb, rb) <= TOL
+
+
+def test_row_lanes_are_added_by_pairs_in_fp32():
+    """Shift gradient of 64 rows.  A rounding of a partial sum s is off by 0.39 * 2^-24 |s| (root mean square over a binade).
+    Sixteen row lanes by pairs: four levels, each off by one such rounding of the whole; the four chunks one after the
+    other: partial sums of 2, 3 and 4 quarters.  A quarter is allowed for; sixteen lanes in a chain are 1.3 times off."""
+    import torch
+    from paper_2509_23241_amd.runner import GpuStage
+    rows, C = 64, 1024
+    rng = np.random.default_rng(5)
+    dy = rng.standard_normal((1, rows * C)).astype(np.float32)
+    st = GpuStage([("bn", C, rows, "none")], [np.ones(C, np.float32), np.zeros(C, np.float32)], dtype="f32", mb=1, n=1,
+                  stage_index=1, num_stages=2, policy="latest", lam=0.1, lr=0.0, momentum=0.0, ring_capacity=1, max_in_flight=1)
+    st.forward(0, 0, torch.from_numpy(rng.standard_normal((1, rows * C)).astype(np.float32)).cuda())
+    st.backward(0, torch.from_numpy(dy).cuda())
+    _, gb = st.unpack(st.grad.cpu().numpy())
+    st.close()
+    off = _rel(gb, dy.reshape(rows, C).astype(np.float64).sum(0))
+    assert off <= 1.25 * 0.39 * 2.0 ** -24 * np.sqrt(4 + (2 + 3 + 4) / 4), off
