@@ -652,17 +652,23 @@ hipError_t run_dma(Tile tile, hipStream_t s, int M, int N, int K, const uint16_t
   return hipErrorInvalidValue;
 }
 
-// dma: the operands suit the direct-to-LDS kernel.  Otherwise 64x64 tiles, or 128x64 ones where those still fill the chip
-// half.
+// 64x64 tiles, or 128x64 ones where those still fill the chip half
+template <bool A_COL, bool B_COL, class Epi>
+hipError_t run_any(hipStream_t s, int M, int N, int K, const uint16_t* A, int lda, const uint16_t* B, int ldb, const Epi& e) {
+  const int per = k_tiles(K);
+  if ((long)((M + 127) / 128) * ((N + 63) / 64) >= 128)
+    return launch_any<128, 64, 2, 2, A_COL, B_COL>(s, M, N, K, A, lda, B, ldb, e, per);
+  return launch_any<64, 64, 2, 2, A_COL, B_COL>(s, M, N, K, A, lda, B, ldb, e, per);
+}
+
+// dma: the operands suit the direct-to-LDS kernel
 template <bool A_COL, bool B_COL, class Epi>
 hipError_t run(bool dma, hipStream_t s, int M, int N, int K, const uint16_t* A, int lda, const uint16_t* B, int ldb, const Epi& e,
                SideCopy side = SideCopy{nullptr, nullptr, 0}) {
   const int per = k_tiles(K);
   if (dma && K % DBK) return run_dma<A_COL, B_COL, true>(pick(M, N, A_COL), s, M, N, K, A, lda, B, ldb, e, side, per);
   if (dma) return run_dma<A_COL, B_COL, false>(pick(M, N, A_COL), s, M, N, K, A, lda, B, ldb, e, side, per);
-  if ((long)((M + 127) / 128) * ((N + 63) / 64) >= 128)
-    return launch_any<128, 64, 2, 2, A_COL, B_COL>(s, M, N, K, A, lda, B, ldb, e, per);
-  return launch_any<64, 64, 2, 2, A_COL, B_COL>(s, M, N, K, A, lda, B, ldb, e, per);
+  return run_any<A_COL, B_COL>(s, M, N, K, A, lda, B, ldb, e);
 }
 
 }  // namespace
@@ -676,6 +682,8 @@ hipError_t mfma_fprop(hipStream_t s, int M, int N, int K, const uint16_t* x, con
     if (err != hipSuccess) return err;
   }
   const int wide = aligned(8, d_out, a_out);
+  // contractions that are no multiple of 8 ran on fp32 FMAs with GELU from erff, and keep it
+  if (K % 8) return run_any<false, false>(s, M, N, K, x, K, W, K, EpiFpropExact{bias, d_out, a_out, act, N, nullptr, wide});
   if (addend) return run<false, false>(dma, s, M, N, K, x, K, W, K, EpiFpropAdd{bias, d_out, a_out, act, N, addend, wide}, side);
   return run<false, false>(dma, s, M, N, K, x, K, W, K, EpiFprop{bias, d_out, a_out, act, N, nullptr, wide}, side);
 }

@@ -24,7 +24,9 @@ typedef short shortx8 __attribute__((ext_vector_type(8)));
 // orientation, where the 32 lanes of a half wave already cover 128 contiguous bytes.
 // ADD: the epilogue also adds `addend` (an [M x ldc] tensor: the residual add that follows the layer) to the rounded
 // activation; a type of its own so that the plain forward GEMM carries none of it.
-template <bool ADD>
+// EXACT: GELU from erff instead of the polynomial of act_pair_fast (for z in -4 .. -2 five times further off fp64, which
+// rounds one value in 50 to the other bf16 neighbour there instead of one in 190); the stores of whole rows know only the latter.
+template <bool ADD, bool EXACT = false>
 struct EpiFpropT {
   const float* bias; uint16_t* d_out; uint16_t* a_out; int act; int ldc;  // d_out: act'(z) for the backward, or null
   const uint16_t* addend = nullptr;
@@ -40,8 +42,13 @@ struct EpiFpropT {
   __device__ __forceinline__ uint4 row_in(int m, int n) const {
     return *reinterpret_cast<const uint4*>(addend + (size_t)m * ldc + n);
   }
+  static __device__ __forceinline__ ActPair act_pair(float z, int act) {
+    if constexpr (EXACT) return ActPair{act_forward(z, act), act_derivative(z, act)};
+    else return act_pair_fast(z, act);
+  }
   // 8 consecutive columns n..n+7 of row m (n and ldc multiples of 8)
   __device__ __forceinline__ void row8(int m, int n, float (&v)[8], const Cols& c, const uint4& u) const {
+    static_assert(!EXACT, "rows are stored whole by kernels that use act_pair_fast");
     const size_t i = (size_t)m * ldc + n;
     const float b[8] = {c.b0.x, c.b0.y, c.b0.z, c.b0.w, c.b1.x, c.b1.y, c.b1.z, c.b1.w};
     float a[8], d[8];
@@ -69,14 +76,14 @@ struct EpiFpropT {
     const size_t i = (size_t)m * ldc + n;
     if (count == 4 && (ldc & 3) == 0 && wide && !ADD) {
       const float4 b = *reinterpret_cast<const float4*>(bias + n);
-      const ActPair p0 = act_pair_fast(v0 + b.x, act), p1 = act_pair_fast(v1 + b.y, act);
-      const ActPair p2 = act_pair_fast(v2 + b.z, act), p3 = act_pair_fast(v3 + b.w, act);
+      const ActPair p0 = act_pair(v0 + b.x, act), p1 = act_pair(v1 + b.y, act);
+      const ActPair p2 = act_pair(v2 + b.z, act), p3 = act_pair(v3 + b.w, act);
       if (d_out) *reinterpret_cast<uint2*>(d_out + i) = make_uint2(pack_bf16x2(p0.d, p1.d), pack_bf16x2(p2.d, p3.d));
       *reinterpret_cast<uint2*>(a_out + i) = make_uint2(pack_bf16x2(p0.a, p1.a), pack_bf16x2(p2.a, p3.a));
     } else {
       const float v[4] = {v0, v1, v2, v3};
       for (int j = 0; j < count; ++j) {
-        const ActPair p = act_pair_fast(v[j] + bias[n + j], act);
+        const ActPair p = act_pair(v[j] + bias[n + j], act);
         if (d_out) d_out[i + j] = float_to_bf16(p.d);
         a_out[i + j] = ADD ? float_to_bf16(bf16_to_float(float_to_bf16(p.a)) + bf16_to_float(addend[i + j])) : float_to_bf16(p.a);
       }
@@ -85,6 +92,7 @@ struct EpiFpropT {
 };
 using EpiFprop = EpiFpropT<false>;
 using EpiFpropAdd = EpiFpropT<true>;
+using EpiFpropExact = EpiFpropT<false, true>;
 struct EpiDgrad {
   const uint16_t* d_prev; uint16_t* out; int ldc;  // d_prev: saved act'(z) of the previous layer, or null
   int relu_mask = 0;  // 1: d_prev holds the previous layer's ReLU OUTPUT instead; its derivative is (output > 0)

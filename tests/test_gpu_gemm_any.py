@@ -93,6 +93,25 @@ def test_dense_bf16(rows, fin, fout, shift):
     st.close()
 
 
+def test_gelu_of_odd_widths_is_the_erf_form():
+    """The bias alone as pre-activation, z in -4 .. -2: an fp32 error e of 0.5 z (1 + erf(z / sqrt 2)) makes the stored bf16
+    value another one than fp64 gives with probability |e| / (spacing of bf16 there).  erf near -1, rounded correctly, is off
+    by 2^-26 on average: 0.5 |z| 2^-26 over the spacing, 0.53 % on average over the range.  Twice that is allowed; the
+    polynomial form, off by up to 1.5e-7, has 2 %."""
+    import math
+    import torch
+    n = 100001
+    z = np.linspace(-4.0, -2.0, n).astype(np.float32)
+    st = _stage((1, n, "gelu"), [np.ones((n, 1), np.float32), z], 1, "bf16")
+    y, _ = st.forward(0, 0, torch.zeros(1, 1, dtype=torch.bfloat16, device="cuda"))
+    z64 = torch.from_numpy(z.astype(np.float64))
+    want = (0.5 * z64 * torch.erfc(-z64 / math.sqrt(2.0))).float().to(torch.bfloat16)
+    differ = float((y.cpu()[0] != want).double().mean())
+    print(differ)
+    st.close()
+    assert differ <= 2 * 0.0053
+
+
 def test_dense_bf16_keeps_nonfinite_values_in_their_row():
     """Remainders of a k tile are zeros in both operands: an infinity reaches its own row only."""
     import torch
