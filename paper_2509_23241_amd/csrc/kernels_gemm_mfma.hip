@@ -347,7 +347,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
 
   // rows of the wave tile stored whole, by 4 * TN lanes each
   constexpr bool kRowStores = Epi::kSwap && 64 % (4 * TN) == 0;
-  const bool whole = kRowStores && m0 + wm + WM <= M && n0 + wn + WN <= N && (N & 7) == 0;
+  bool whole = false;
+  if constexpr (kRowStores) whole = m0 + wm + WM <= M && n0 + wn + WN <= N && (N & 7) == 0 && epi.wide == 2;
   typename EpiInputs<TM, TN, Epi, kRowStores>::type row_inputs;
 
   int kt0 = 0;
@@ -673,6 +674,8 @@ hipError_t run(bool dma, hipStream_t s, int M, int N, int K, const uint16_t* A, 
 
 }  // namespace
 
+inline int store_width(const void* a, const void* b) { return aligned(16, a, b) ? 2 : aligned(8, a, b) ? 1 : 0; }
+
 hipError_t mfma_fprop(hipStream_t s, int M, int N, int K, const uint16_t* x, const uint16_t* W, const float* bias,
                       int act, uint16_t* d_out, uint16_t* a_out, uint16_t* x_copy, const uint16_t* addend) {
   const bool dma = dma_ok(M, N, K, K, K, false, false) && aligned(16, x, W, x_copy);
@@ -681,7 +684,7 @@ hipError_t mfma_fprop(hipStream_t s, int M, int N, int K, const uint16_t* x, con
     const hipError_t err = launch_copy(s, x, x_copy, (size_t)M * K * 2);
     if (err != hipSuccess) return err;
   }
-  const int wide = aligned(8, d_out, a_out);
+  const int wide = store_width(d_out, a_out);
   // contractions that are no multiple of 8 ran on fp32 FMAs with GELU from erff, and keep it
   if (K % 8) return run_any<false, false>(s, M, N, K, x, K, W, K, EpiFpropExact{bias, d_out, a_out, act, N, nullptr, wide});
   if (addend) return run<false, false>(dma, s, M, N, K, x, K, W, K, EpiFpropAdd{bias, d_out, a_out, act, N, addend, wide}, side);
@@ -692,7 +695,7 @@ hipError_t mfma_dgrad(hipStream_t s, int M, int N, int K, const uint16_t* dz, co
                       const uint16_t* d_prev, uint16_t* out, int relu_mask) {
   // out[M x K] = dz[M x N] . Wb[N x K]: GEMM (M, K, contraction N)
   const bool dma = dma_ok(M, K, N, N, K, false, true) && aligned(16, dz, Wb);
-  return run<false, true>(dma, s, M, K, N, dz, N, Wb, K, EpiDgrad{d_prev, out, K, relu_mask, aligned(8, d_prev, out)});
+  return run<false, true>(dma, s, M, K, N, dz, N, Wb, K, EpiDgrad{d_prev, out, K, relu_mask, store_width(d_prev, out)});
 }
 
 size_t mfma_wgrad_scratch_floats(int M, int N, int K) {

@@ -30,7 +30,7 @@ template <bool ADD, bool EXACT = false>
 struct EpiFpropT {
   const float* bias; uint16_t* d_out; uint16_t* a_out; int act; int ldc;  // d_out: act'(z) for the backward, or null
   const uint16_t* addend = nullptr;
-  int wide = 1;  // 0: the outputs are not 8-byte aligned
+  int wide = 2;  // 2: the outputs are 16-byte aligned (row8 may be used), 1: 8-byte, 0: not even that
   static constexpr bool kSwap = true;
   // what row8 below reads, as its own steps so that a wave can have all of it in flight before it needs any: the values
   // of columns n..n+7, and the 16 bytes that belong to row m there
@@ -96,7 +96,7 @@ using EpiFpropExact = EpiFpropT<false, true>;
 struct EpiDgrad {
   const uint16_t* d_prev; uint16_t* out; int ldc;  // d_prev: saved act'(z) of the previous layer, or null
   int relu_mask = 0;  // 1: d_prev holds the previous layer's ReLU OUTPUT instead; its derivative is (output > 0)
-  int wide = 1;       // 0: the output is not 8-byte aligned
+  int wide = 2;       // alignment of d_prev and out, as above
   static constexpr bool kSwap = true;
   __device__ __forceinline__ float through(float v, float d) const { return relu_mask ? (d > 0.f ? v : 0.f) : v * d; }
   struct Cols {};

@@ -93,6 +93,30 @@ def test_dense_bf16(rows, fin, fout, shift):
     st.close()
 
 
+@pytest.mark.parametrize("rows,fin,fout,act", [(256, 128, 256, "none"), (2048, 64, 4096, "gelu"), (128, 4096, 256, "gelu")])
+@pytest.mark.parametrize("offset", [1, 2, 4])                 # elements: 2, 4 and 8 bytes
+def test_outputs_at_any_address(rows, fin, fout, act, offset):
+    """Whole tiles from aligned operands into a y and a dx that are not 16-byte aligned: the bits of the aligned ones."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    W = (torch.randn(fout, fin, generator=g, device="cuda") / fin ** 0.5).cpu().numpy()
+    x = torch.randn(rows, fin, generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn(rows, fout, generator=g, device="cuda").to(torch.bfloat16)
+    got = []
+    for at in (0, offset):
+        st = _stage((fin, fout, act), [W, np.zeros(fout, np.float32)], rows, "bf16")
+        ys = torch.full((rows * fout + 16,), 3.0, dtype=torch.bfloat16, device="cuda")
+        dxs = torch.full((rows * fin + 16,), 3.0, dtype=torch.bfloat16, device="cuda")
+        st.forward(0, 0, x, ys[at:at + rows * fout].view(rows, fout))
+        st.backward(0, dy, dxs[at:at + rows * fin].view(rows, fin))
+        for t, n in ((ys, rows * fout), (dxs, rows * fin)):
+            assert bool((t[:at] == 3).all()) and bool((t[at + n:] == 3).all())   # and nothing beside them
+            got.append(t[at:at + n].clone())
+        st.close()
+    assert torch.equal(got[0], got[2]) and torch.equal(got[1], got[3])
+
+
 def test_gelu_of_odd_widths_is_the_erf_form():
     """The bias alone as pre-activation, z in -4 .. -2: an fp32 error e of 0.5 z (1 + erf(z / sqrt 2)) makes the stored bf16
     value another one than fp64 gives with probability |e| / (spacing of bf16 there).  erf near -1, rounded correctly, is off
