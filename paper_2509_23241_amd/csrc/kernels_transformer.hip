@@ -638,10 +638,16 @@ size_t attention_scratch_bytes(int elt, int seqs, int S, int heads, int dh) {
   return attention_mfma_supported(S, heads, dh) ? attention_mfma_scratch_bytes(seqs, S, heads) : 0;
 }
 
+// The fused kernels read and write 16-byte units.  Whole blocks of tokens have always gone there; other lengths of tensors
+// that are not aligned stay on the wavefront kernels, which take any address.
+static bool attention_flash_takes(int S, const void* a, const void* b, const void* c, const void* d) {
+  return S % 64 == 0 || (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)d) & 15) == 0;
+}
+
 hipError_t launch_attention_fwd(hipStream_t s, int elt, int seqs, int S, int heads, int dh, const void* qkv, void* out,
                                 float* lse, void* scratch, size_t scratch_bytes) {
   if (!attention_supported(S, heads, dh) || seqs > 65535) return hipErrorInvalidValue;
-  if (elt == ELT_BF16 && attention_flash_fwd_supported(seqs, S, heads, dh))
+  if (elt == ELT_BF16 && attention_flash_fwd_supported(seqs, S, heads, dh) && attention_flash_takes(S, qkv, out, nullptr, nullptr))
     return attention_flash_fwd(s, seqs, S, heads, dh, (const uint16_t*)qkv, (uint16_t*)out, lse);
   if (elt == ELT_BF16 && scratch && attention_mfma_supported(S, heads, dh) &&
       scratch_bytes >= attention_mfma_scratch_bytes(1, S, heads))
@@ -689,7 +695,7 @@ hipError_t launch_attention_bwd(hipStream_t s, int elt, int seqs, int S, int hea
                                 const void* dout, const float* lse, void* dqkv, void* scratch, size_t scratch_bytes) {
   if (!attention_supported(S, heads, dh) || seqs > 65535) return hipErrorInvalidValue;
   if (elt == ELT_BF16 && scratch && attention_flash_fwd_supported(seqs, S, heads, dh) &&
-      scratch_bytes >= attention_flash_bwd_scratch_bytes(seqs, S, heads))
+      scratch_bytes >= attention_flash_bwd_scratch_bytes(seqs, S, heads) && attention_flash_takes(S, qkv, out, dout, dqkv))
     return attention_flash_bwd(s, seqs, S, heads, dh, (const uint16_t*)qkv, (const uint16_t*)out, (const uint16_t*)dout, lse,
                                (uint16_t*)dqkv, scratch, scratch_bytes);
   if (elt == ELT_BF16 && scratch && attention_mfma_supported(S, heads, dh) &&

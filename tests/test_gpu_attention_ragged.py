@@ -110,3 +110,25 @@ def test_non_finite_values_stay_in_the_rows_that_see_them(tokens, heads, dh, mb)
         got = dict(zip(("y", "dq", "dk", "dv"), _run_attention(x, u, heads)))
         check(got, unaffected)
         assert not bool(torch.isfinite(got["dq" if where == "dy" else "y"][:, t].float()).all())   # and it does arrive
+
+
+@pytest.mark.parametrize("tokens", [40, 130])
+def test_input_gradient_at_any_address(tokens):
+    """Attention as first layer writes its gradients to the caller's tensor, which may start at an odd element."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tokens)
+    heads, dh, mb = 2, 64, 2
+    d = heads * dh
+    qkv = torch.randn(mb, tokens * 3 * d, generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn(mb, tokens * d, generator=g, device="cuda").to(torch.bfloat16)
+    got = []
+    for at in (0, 1):
+        st = _attention_stage(tokens, heads, dh, mb)
+        st.forward(0, 0, qkv)
+        room = torch.full((qkv.numel() + 16,), 3.0, dtype=torch.bfloat16, device="cuda")
+        st.backward(0, dy, room[at:at + qkv.numel()].view_as(qkv))
+        assert bool((room[:at] == 3).all()) and bool((room[at + qkv.numel():] == 3).all())
+        got.append(room[at:at + qkv.numel()].double())
+        st.close()
+    assert float((got[0] - got[1]).norm()) <= 2.0 ** -8 * float(got[0].norm())   # each rounded once
