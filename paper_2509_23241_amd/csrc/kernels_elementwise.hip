@@ -233,6 +233,8 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(int rows, int clas
   if (row >= rows) return;
   const T* lg = logits + (size_t)row * classes;
   const int label = labels[row];
+  // a label outside the classes has no logit: the loss says so instead of keeping what lay there
+  if (lane == 0 && (unsigned)label >= (unsigned)classes) row_loss[row] = __builtin_nanf("");
   float v[kHeld];
 #pragma unroll
   for (int i = 0; i < kHeld; ++i) v[i] = lane + 64 * i < classes ? to_float(lg[lane + 64 * i]) : -INFINITY;

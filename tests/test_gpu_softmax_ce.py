@@ -1,0 +1,57 @@
+"""Softmax cross-entropy (kernels_elementwise.hip) where the classes a lane holds in registers end, and on labels that are
+no class."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _loss(dtype, rows, classes, logits, labels):
+    import torch
+    from paper_2509_23241_amd.runner import GpuStage
+    st = GpuStage([(8, classes, "none")], [np.zeros((classes, 8), np.float32), np.zeros(classes, np.float32)], dtype=dtype,
+                  mb=rows, n=1, stage_index=1, num_stages=2, policy="latest", lam=0.1, lr=0.0, momentum=0.0, ring_capacity=1,
+                  max_in_flight=1)
+    st.forward(0, 0, torch.zeros(rows, 8, dtype=st.tdtype, device="cuda"))
+    loss, dlogits = st.loss(0, logits.to(st.tdtype).cuda(), torch.from_numpy(labels.astype(np.int32)).cuda())
+    out = float(loss), dlogits.double().cpu()
+    st.close()
+    return out
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,classes", [(1, 1), (5, 63), (7, 64), (6, 65), (9, 1023), (9, 1024), (9, 1025), (33, 1500), (4, 4097)])
+def test_softmax_cross_entropy(dtype, rows, classes):
+    import torch
+    rng = np.random.default_rng(rows + classes)
+    logits = torch.from_numpy(3 * rng.standard_normal((rows, classes))).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    labels = rng.integers(0, classes, rows)
+    labels[-1] = classes - 1
+    loss, dlogits = _loss(dtype, rows, classes, logits, labels)
+    z = logits.double()
+    logp = z - z.logsumexp(1, keepdim=True)
+    want = logp.exp()
+    want[torch.arange(rows), torch.from_numpy(labels)] -= 1
+    want /= rows
+    # exp of an fp32 difference of logits of up to 16 (rounded by 2^-21 each in the maximum, the logarithm and their sum) and
+    # a sum of classes / 64 + 6 terms; bf16 results are rounded once more
+    tol = 2.0 ** -21 * 3 + 2.0 ** -24 * (classes / 64 + 6)
+    assert abs(loss + float(logp[torch.arange(rows), torch.from_numpy(labels)].mean())) <= tol * 16
+    got = float((dlogits - want).norm())
+    assert got <= (tol + (2.0 ** -9 if dtype == "bf16" else 0)) * float(want.norm()) + 1e-12
+
+
+@pytest.mark.parametrize("label", [-1, 10, 1500, 2 ** 30, -2 ** 31])
+@pytest.mark.parametrize("classes", [10, 1500])
+def test_a_label_that_is_no_class_makes_the_loss_nan(classes, label):
+    if 0 <= label < classes:
+        pytest.skip("a class")
+    import torch
+    rng = np.random.default_rng(3)
+    logits = torch.from_numpy(rng.standard_normal((6, classes))).float()
+    labels = rng.integers(0, classes, 6)
+    labels[2] = label
+    loss, dlogits = _loss("f32", 6, classes, logits, labels)
+    assert np.isnan(loss)
+    want = logits.double().softmax(1)[2] / 6             # every class is another one
+    assert float((dlogits[2] - want).norm()) <= 1e-5 * float(want.norm())
