@@ -46,26 +46,27 @@ def _torch_dtype(dtype: str):
 
 # The runtime maps streams onto four hardware queues (its default) in the order they are created.  The default stream
 # has the first; three more streams get the others, and every further one shares a queue, i.e. waits in line, with one
-# of these.  So all stages on a device share three forward streams instead of creating their own: with a second and third
-# stage in the process whose streams shared the default stream's queue, a step of the conv4_x stage took 1.96 ms instead of
-# 1.73 ms on average, one of the last stage 1.20 ms instead of 1.00 ms.
+# of these.  So all stages on a device's default stream share three forward streams instead of creating their own: with a
+# second and third stage in the process whose streams shared the default stream's queue, a step of the conv4_x stage took
+# 1.96 ms instead of 1.73 ms on average, one of the last stage 1.20 ms instead of 1.00 ms.  (A process with one such stage
+# has the same three streams either way.)  A stage on a stream of its own, which is there to run beside other stages, has
+# forward streams of its own too: on shared ones its forwards would wait in line behind those of the others.
 _forward_streams: Dict[int, List[torch.cuda.Stream]] = {}
 _forward_streams_lock = threading.Lock()
 
 
-def forward_streams(device: torch.device, count: int, besides: int) -> List[torch.cuda.Stream]:
-    """`count` of the device's forward streams, none of them the stream with the handle `besides`."""
+def forward_streams(device: torch.device, count: int, stage_stream: int) -> List[torch.cuda.Stream]:
+    """`count` forward streams (none for 0 or less) for a stage on the stream with the handle `stage_stream`."""
+    if count <= 0:
+        return []
+    if count > B.TP_MAX_FORWARD_STREAMS or stage_stream != torch.cuda.default_stream(device).cuda_stream:
+        return [torch.cuda.Stream(device) for _ in range(count)]   # the library refuses more than its maximum
     with _forward_streams_lock:
         index = device.index if device.index is not None else torch.cuda.current_device()
-        pool = _forward_streams.setdefault(index, [])
-        while len(pool) < B.TP_MAX_FORWARD_STREAMS:
-            pool.append(torch.cuda.Stream(device))
-        chosen = [q for q in pool if q.cuda_stream != besides]
-        while len(chosen) < count:                     # torch hands out its 32 streams again and again
-            q = torch.cuda.Stream(device)
-            if q.cuda_stream != besides and all(q.cuda_stream != c.cuda_stream for c in chosen):
-                chosen.append(q)
-        return chosen[:count]
+        shared = _forward_streams.setdefault(index, [])
+        while len(shared) < B.TP_MAX_FORWARD_STREAMS:
+            shared.append(torch.cuda.Stream(device))
+        return shared[:count]
 
 
 class GpuStage:
@@ -77,8 +78,9 @@ class GpuStage:
                  needs_dx: Optional[bool] = None, device="cuda:0", stream: Optional[torch.cuda.Stream] = None,
                  forward_stream=False):
         """forward_stream: False / 0, or how many streams (default priority; True = 1) the stage gets for the forward
-        passes, the same ones for all stages on the device; what runs there is ordered on the stage's stream by forward_join() or any later call other than a
-        forward or a backward (a backward waits for the forwards of its own mini-batch only)."""
+        passes, the same ones for all stages on the device's default stream; what runs there is ordered on the stage's
+        stream by forward_join() or any later call other than a forward or a backward (a backward waits for the forwards
+        of its own mini-batch only)."""
         self.layers = [tuple(l) for l in layers]
         self.in_elems = B.layer_in_elems(self.layers[0])      # values per sample in / out of the stage
         self.out_elems = B.layer_out_elems(self.layers[-1])

@@ -197,3 +197,125 @@ def test_forward_stream_refusals():
             B.stage_set_forward_streams(st.handle, h[:1])
         assert ei.value.code == B.TP_EINVAL
         st.close()
+
+
+def _mlp_stage(w, s, **kw):
+    from paper_2509_23241_amd.runner import GpuStage, layer_tuple
+    return GpuStage([layer_tuple(l) for l in w.stages[s]], W.init_params(w, s), dtype=w.dtype, mb=w.mb, n=w.n, stage_index=s,
+                    num_stages=w.K, policy="convex", lam=w.lam, lr=w.lr, momentum=w.momentum, **kw)
+
+
+def test_number_of_forward_streams():
+    from paper_2509_23241_amd import binding as B
+    w = W.mlp_wide(width=64, mb=8, n=2)
+    for none in (False, 0, -1, -40):
+        st = _mlp_stage(w, 1, forward_stream=none)
+        assert st.fwd_streams == []
+        st.close()
+    for many in (4, 33, 100):
+        with pytest.raises(B.StageLibError):
+            _mlp_stage(w, 1, forward_stream=many)
+    st = _mlp_stage(w, 1, forward_stream=True)
+    assert len(st.fwd_streams) == 1
+    st.close()
+
+
+def test_stages_taking_turns_on_shared_forward_streams():
+    """Two stages of different widths on the default stream, their calls interleaved mini-batch by mini-batch."""
+    import torch
+    ws = [W.mlp_wide(width=256, mb=64, n=4), W.mlp_wide(width=512, mb=32, n=4)]
+    alone = []
+    for w in ws:
+        st = _mlp_stage(w, 1)
+        alone.append(_drive(st, w, 1, steps=4, join_before_read=False))
+        st.close()
+    stages = [_mlp_stage(w, 1, forward_stream=2) for w in ws]
+    assert [q.cuda_stream for q in stages[0].fwd_streams] == [q.cuda_stream for q in stages[1].fwd_streams]
+    inputs = [tuple([t.clone() for t in ts] for ts in _inputs(st, w, 1, 4)) for st, w in zip(stages, ws)]
+    outs, ys = [[], []], [[], []]
+
+    def forward(k, j):
+        w, st = ws[k], stages[k]
+        y = torch.empty(w.n * w.mb, st.out_elems, dtype=st.tdtype, device="cuda")
+        for ub in range(w.n):
+            st.forward(j, ub, inputs[k][0][j][ub * w.mb:(ub + 1) * w.mb], y[ub * w.mb:(ub + 1) * w.mb])
+        ys[k].append(y)
+
+    depth = ws[0].K - 1
+    for j in range(depth):
+        for k in (0, 1):
+            forward(k, j)
+    for j in range(4):
+        for k in (0, 1):
+            dx, _ = stages[k].backward(j, inputs[k][1][j])
+            outs[k] += [dx, stages[k].grad.clone()]
+            stages[k].blend_update(j, j + 1)
+            outs[k].append(stages[k].export(j + 1))
+        for k in (1, 0):
+            forward(k, j + depth)
+    for k in (0, 1):
+        stages[k].forward_join()
+        got = [t.float().cpu().numpy() for t in outs[k] + ys[k]]
+        assert len(got) == len(alone[k])
+        for a, b in zip(got, alone[k]):
+            assert np.array_equal(a, b)
+        stages[k].close()
+
+
+def test_stages_of_two_threads_on_streams_of_their_own():
+    """A stage on a stream of its own has forward streams of its own; two such stages driven by two threads give the bits
+    each gives alone."""
+    import threading
+    import torch
+    ws = [W.mlp_wide(width=256, mb=64, n=4), W.mlp_wide(width=512, mb=32, n=4)]
+    alone, inputs = [], []
+    for w in ws:
+        st = _mlp_stage(w, 1)
+        alone.append(_drive(st, w, 1, steps=4, join_before_read=False))
+        inputs.append(tuple([t.clone() for t in ts] for ts in _inputs(st, w, 1, 4)))
+        st.close()
+    torch.cuda.synchronize()
+    results, errors, used = [None, None], [], [None, None]
+
+    def work(k):
+        try:
+            w, (xs, dys) = ws[k], inputs[k]
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                st = _mlp_stage(w, 1, stream=stream, forward_stream=2)
+                used[k] = {q.cuda_stream for q in st.fwd_streams}
+                outs, ys, depth = [], [], w.K - 1
+
+                def forward(j):
+                    y = torch.empty(w.n * w.mb, st.out_elems, dtype=st.tdtype, device="cuda")
+                    for ub in range(w.n):
+                        st.forward(j, ub, xs[j][ub * w.mb:(ub + 1) * w.mb], y[ub * w.mb:(ub + 1) * w.mb])
+                    ys.append(y)
+
+                stream.synchronize()                       # the stage's tensors are made
+                for j in range(depth):
+                    forward(j)
+                for j in range(4):
+                    dx, _ = st.backward(j, dys[j])
+                    outs += [dx, st.grad.clone()]
+                    st.blend_update(j, j + 1)
+                    outs.append(st.export(j + 1))
+                    forward(j + depth)
+                st.forward_join()
+                stream.synchronize()
+                results[k] = [t.float().cpu().numpy() for t in outs + ys]
+                st.close()
+        except Exception as e:                             # reported by the test, not by the thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(timeout=60)
+    assert not errors and all(not t.is_alive() for t in threads), errors
+    assert not used[0] & used[1]
+    for got, want in zip(results, alone):
+        assert len(got) == len(want)
+        for a, b in zip(got, want):
+            assert np.array_equal(a, b)

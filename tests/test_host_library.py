@@ -489,3 +489,30 @@ def test_pass_versions_are_refused_outside_timeprest_and_when_not_held():
     assert _live(B.stage_query(h)) == {1: 0}                           # nothing pinned: the old version is gone
     assert B.tp_blend_coefficients("timeprest", 3, 0.5) == (1.0, 0.0)
     B.stage_destroy(h)
+
+
+def test_choice_of_forward_streams(monkeypatch):
+    """Stages on a device's default stream share three forward streams; others get their own; none is made unless asked for."""
+    import itertools
+    import types
+    import torch
+    from paper_2509_23241_amd import runner
+    handles = itertools.count(1)
+    made = []
+
+    def stream(device):
+        made.append(types.SimpleNamespace(cuda_stream=next(handles)))
+        return made[-1]
+
+    monkeypatch.setattr(runner.torch.cuda, "Stream", stream)
+    monkeypatch.setattr(runner.torch.cuda, "default_stream", lambda device: types.SimpleNamespace(cuda_stream=0))
+    monkeypatch.setattr(runner, "_forward_streams", {})
+    device = torch.device("cuda:0")
+    for none in (0, -1, -40):
+        assert runner.forward_streams(device, none, 0) == [] and not made and not runner._forward_streams
+    two, three = runner.forward_streams(device, 2, 0), runner.forward_streams(device, 3, 0)
+    assert three[:2] == two and len(three) == len(made) == B.TP_MAX_FORWARD_STREAMS
+    own = runner.forward_streams(device, 2, 77)
+    assert len(own) == 2 and not {q.cuda_stream for q in own} & {q.cuda_stream for q in three}
+    for many in (4, 33, 100):                              # passed on to the library, which refuses the number
+        assert len(runner.forward_streams(device, many, 0)) == many
