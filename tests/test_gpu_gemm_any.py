@@ -93,6 +93,30 @@ def test_dense_bf16(rows, fin, fout, shift):
     st.close()
 
 
+def test_operands_of_more_than_2_gib():
+    """Byte offsets of an operand beyond 31 bits: rows at both ends, the input gradient and the weight gradient."""
+    import torch
+    rows, fin, fout = 1050000, 1024, 64                      # an input of 2.15 GB
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    x = torch.empty(rows, fin, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    dy = torch.empty(rows, fout, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    W = (torch.randn(fout, fin, generator=g, device="cuda") / 32).to(torch.bfloat16).float()
+    st = _stage((fin, fout, "none"), [W.cpu().numpy(), np.zeros(fout, np.float32)], rows, "bf16")
+    y, _ = st.forward(0, 0, x)
+    dx, _ = st.backward(0, dy)
+    gw = torch.from_numpy(np.ascontiguousarray(st.unpack(st.grad.cpu().numpy())[0])).cuda().double()
+    st.close()
+    store = 2.0 ** -9
+    for part in (slice(0, 1000), slice(524000, 525000), slice(rows - 1000, rows)):
+        a, d = x[part].double(), dy[part].double()
+        ry, rdx = a @ W.double().T, d @ W.double()
+        assert float((y[part].double() - ry).norm() / ry.norm()) <= _sum_tol(fin) + store
+        assert float((dx[part].double() - rdx).norm() / rdx.norm()) <= _sum_tol(fout) + store
+    want = sum(dy[i:i + 150000].double().T @ x[i:i + 150000].double() for i in range(0, rows, 150000))
+    assert float((gw - want).norm() / want.norm()) <= _sum_tol(rows)
+
+
 @pytest.mark.parametrize("rows,fin,fout,act", [(256, 128, 256, "none"), (2048, 64, 4096, "gelu"), (128, 4096, 256, "gelu")])
 @pytest.mark.parametrize("offset", [1, 2, 4])                 # elements: 2, 4 and 8 bytes
 def test_outputs_at_any_address(rows, fin, fout, act, offset):
