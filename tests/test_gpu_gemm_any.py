@@ -32,11 +32,15 @@ def _run(st, x, dy):
 
 
 @pytest.mark.parametrize("rows,fin,fout", [
-    (1, 1, 1), (31, 33, 35), (32, 32, 32), (33, 36, 100),     # 32 x 32 tiles: less than one, one, one and a bit
-    (1030, 1028, 1000),                                       # 64 x 64 tiles, 16-byte rows
-    (1023, 1021, 1027),                                       # 64 x 64 tiles, rows copied word by word
-    (2050, 2052, 2048), (2049, 2047, 2051),                   # 128 x 128 tiles, both ways of copying
-    (2100, 40, 36), (2100, 41, 39),                           # weight gradient over several row ranges, with a remainder
+    # tiles of the forward product, the input gradient and the weight gradient (and its row ranges); 16-byte rows / words
+    (1, 1, 1), (31, 33, 35), (32, 32, 32), (33, 36, 100),     # 32: less than one, one, one and a bit
+    (1030, 1028, 1000),                                       # 32, 32, 128 over 3 ranges; 16 bytes
+    (1023, 1021, 1027),                                       # 32, 64, 128 over 3 ranges; words
+    (1024, 1024, 1024), (1500, 1504, 1500), (1499, 1501, 1503),   # 64, 64, 128 over 4 ranges | 64 in all three, both ways
+    (2050, 2052, 2048), (2049, 2047, 2051),                   # 64 in all three, both ways
+    (2048, 2044, 2040), (2047, 2045, 2043),                   # 128 in all three, both ways
+    (4090, 1020, 1024),                                       # 128, 128, 128 over 4 ranges
+    (2100, 40, 36), (2100, 41, 39),                           # 32, 32, 32 over 8 ranges, with a remainder
 ])
 def test_dense_fp32(rows, fin, fout):
     rng = np.random.default_rng(rows + fin)
@@ -62,8 +66,9 @@ def test_dense_fp32(rows, fin, fout):
     (1000, 136, 2040), (2040, 136, 2040), (2040, 136, 4088), (4000, 136, 4088),   # 128 x 64, 128 x 128, 256 x 128, 256 x 256
     (2040, 64, 4088), (2040, 128, 4088), (4000, 64, 4088), (4000, 128, 4088),     # fewer k tiles than the last two have stages
     (72, 2048, 6144), (72, 6144, 2048),                       # weight gradients on 384 x 128 and 128 x 384 tiles
-    (6400, 768, 776), (6401, 520, 1032),                      # ... over several row ranges on 128 x 128 tiles
-    (16384, 1024, 1024), (16389, 1032, 1032),                 # ... and on 256 x 256 tiles, or 128 x 128 ones
+    (6400, 768, 776), (6401, 520, 1032),                      # ... over 6 and 5 row ranges on 128 x 128 tiles
+    (16384, 1024, 1024), (16389, 1032, 1032),                 # ... over 4 and 3; input gradients on 256 x 256 and 128 x 128
+    (32769, 1024, 1024),                                      # ... over 16 ranges on 256 x 256 tiles, one row in the last k tile
 ])
 @pytest.mark.parametrize("shift", [0, 1])                     # 1: the input starts at an odd element
 def test_dense_bf16(rows, fin, fout, shift):
@@ -189,13 +194,17 @@ def _conv_reference(x, W, b, dy, stride):
     ("f32", 2, 5, 7, 3, 6, 3, 1),         # words, 32 x 32 tiles, every border
     ("f32", 3, 6, 10, 4, 12, 5, 2),       # 16-byte chunks that straddle taps inside a k tile, stride 2
     ("f32", 1, 4, 4, 20, 8, 1, 1),        # 1x1: the division by a kernel edge of one
-    ("f32", 40, 24, 24, 68, 64, 3, 1),    # 64 x 64 tiles, weight gradient over many ranges
-    ("f32", 150, 16, 16, 128, 132, 3, 1), # 128 x 128 tiles
-    ("bf16", 2, 6, 5, 8, 16, 3, 1),       # 32 x 32 tiles, image sizes that are no powers of two
+    # tiles of forward product, input gradient and weight gradient (over its pixel ranges)
+    ("f32", 40, 24, 24, 68, 64, 3, 1),    # 64, 64, 64 over 25
+    ("f32", 150, 16, 16, 128, 132, 3, 1), # 64, 64, 128 over 14
+    ("f32", 128, 16, 16, 128, 128, 3, 1), # 128, 128, 128 over 28
+    ("f32", 128, 16, 16, 124, 128, 1, 1), # 128, 128, 64 over 64; a last tile of channels that is not whole
+    ("f32", 127, 16, 16, 127, 125, 1, 1), # the same word by word
+    ("bf16", 2, 6, 5, 8, 16, 3, 1),       # 32 in all three, image sizes that are no powers of two
     ("bf16", 3, 12, 20, 24, 40, 7, 2),
-    ("bf16", 40, 24, 24, 64, 72, 3, 1),   # 64 x 64
-    ("bf16", 90, 28, 28, 48, 56, 3, 1),   # 128 x 64
-    ("bf16", 180, 20, 20, 96, 128, 5, 1), # 128 x 128
+    ("bf16", 40, 24, 24, 64, 72, 3, 1),   # 32, 32, 128 over 45
+    ("bf16", 90, 28, 28, 48, 56, 3, 1),   # 64, 64, 64 over 36
+    ("bf16", 180, 20, 20, 96, 128, 5, 1), # 64, 32, 128 over 13
 ])
 def test_convolution(dtype, imgs, H, W, cin, cout, k, stride):
     from synth_inputs import round_bf16
@@ -242,3 +251,63 @@ def test_convolution_weight_gradient_is_summed_in_parts(dtype, imgs, size, cin, 
     bound = 1.15 * 0.39 * 2.0 ** -24 * np.sqrt(roundings / 2 + pixels / 512)
     print(off, bound)
     assert off <= bound
+
+
+def _chain(a, b):
+    """out[m][n] = fma(a[m][k], b[n][k], .) over ascending k in fp32: product and sum of two fp32 values have at most 48 + 24
+    bits, the 64 of a long double round them a second time in fewer than 1 of 2^38 steps."""
+    acc = np.zeros((a.shape[0], b.shape[0]), np.float32)
+    for k in range(a.shape[1]):
+        acc = (a[:, k, None].astype(np.longdouble) * b[None, :, k].astype(np.longdouble) + acc).astype(np.float32)
+    return acc
+
+
+def test_fp32_products_are_one_chain_of_fused_multiply_adds():
+    rng = np.random.default_rng(2)
+    for rows, fin, fout in ((33, 70, 45), (40, 64, 72)):                       # words, 16-byte rows
+        W, x, dy = [rng.standard_normal(shape).astype(np.float32) for shape in ((fout, fin), (rows, fin), (rows, fout))]
+        y, dx, _ = _run(_stage((fin, fout, "none"), [W, np.zeros(fout, np.float32)], rows, "f32"), x, dy)
+        assert np.array_equal(y, _chain(x, W)) and np.array_equal(dx, _chain(dy, W.T))
+
+
+@pytest.mark.parametrize("dtype,cin,cout,stride", [("f32", 3, 10, 1), ("f32", 12, 8, 2), ("bf16", 8, 16, 1)])
+def test_convolutions_are_one_chain_of_fused_multiply_adds(dtype, cin, cout, stride):
+    from synth_inputs import round_bf16
+    rng = np.random.default_rng(cin)
+    cast = round_bf16 if dtype == "bf16" else (lambda t: t.astype(np.float32))
+    imgs, H, W_, k = 2, 6, 10, 3
+    wgt, x, dy = [cast(rng.standard_normal(shape)).astype(np.float32)
+                  for shape in ((cout, k, k, cin), (imgs, H, W_, cin), (imgs, H // stride, W_ // stride, cout))]
+    y, dx, _ = _run(_stage(("conv", cin, cout, H, W_, "none", stride, k), [wgt, np.zeros(cout, np.float32)], imgs, dtype),
+                    x.reshape(imgs, -1), dy.reshape(imgs, -1))
+    # the operand rows as the kernels gather them: (tap, channel) ascending, zeros outside the image
+    ho, wo = H // stride, W_ // stride
+    pad = np.pad(x, ((0, 0), (1, 1), (1, 1), (0, 0)))
+    fwd = np.stack([pad[:, kh:kh + stride * ho:stride, kw:kw + stride * wo:stride] for kh in range(k) for kw in range(k)], 3)
+    spread = np.zeros((imgs, H + 2, W_ + 2, cout), np.float32)                  # dz at the positions of its input pixels
+    spread[:, 1:1 + stride * ho:stride, 1:1 + stride * wo:stride] = dy
+    back = np.stack([spread[:, 2 - kh:2 - kh + H, 2 - kw:2 - kw + W_] for kh in range(k) for kw in range(k)], 3)
+    ry = _chain(fwd.reshape(-1, k * k * cin), wgt.reshape(cout, -1))
+    rdx = _chain(back.reshape(-1, k * k * cout), wgt.transpose(3, 1, 2, 0).reshape(cin, -1))
+    assert np.array_equal(y.reshape(ry.shape), cast(ry)) and np.array_equal(dx.reshape(rdx.shape), cast(rdx))
+
+
+def test_fp32_products_have_the_same_bits_on_every_tile():
+    """The rows of a small call inside larger ones: 32, 64 and 128 tiles, rows copied in 16-byte units and word by word."""
+    import torch
+    fin = fout = 1020                                        # 128 rows: tiles of 32, 1024: 64, 4096: 128
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    W = torch.randn(fout, fin, generator=g, device="cuda").cpu().numpy()
+    x, dy = [torch.randn(4096, 1020, generator=g, device="cuda") for _ in range(2)]
+    first = None
+    for rows in (128, 1024, 4096):
+        for shift in (0, 1):                                 # 1: operands that are not 16-byte aligned
+            room = [torch.empty(rows * 1020 + shift, device="cuda")[shift:].view(rows, 1020).copy_(t[:rows]) for t in (x, dy)]
+            st = _stage((fin, fout, "none"), [W, np.zeros(fout, np.float32)], rows, "f32")
+            y, _ = st.forward(0, 0, room[0])
+            dx, _ = st.backward(0, room[1])
+            got = y[:128].clone(), dx[:128].clone()
+            st.close()
+            first = first or got
+            assert torch.equal(got[0], first[0]) and torch.equal(got[1], first[1]), (rows, shift)
