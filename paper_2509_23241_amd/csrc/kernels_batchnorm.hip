@@ -103,7 +103,7 @@ struct Unit<float> {
 // row lanes of a channel meet in LDS in a fixed order.  Same partial layout.  Bound by the loads a lane has in flight: eight
 // rows of x, or four of x and dy (two before; with the partial sums of bn_finalize_sum_kernel in flight at once, first stage
 // of a bottleneck net on 64-pixel images 1.81 -> 1.76 ms; fp32, one value per lane before, on 128-pixel images 1.04 -> 0.89).
-// Fewer units and more rows per step for narrow layers change the order of the sums, and with it ReLU masks: not done.
+// Layers of fewer than 16 units leave lanes idle; giving those further rows would sum in another order, which is not done.
 template <typename T, int MODE>
 __global__ __launch_bounds__(kThreads) void bn_colsum_vec_kernel(size_t rows, int C, int chunk_rows, const T* __restrict__ x,
                                                                  const T* __restrict__ dy, const float* __restrict__ aux,

@@ -3,9 +3,10 @@
 //
 // Forward products and input gradients keep the arithmetic of a plain fp32 loop: every output is ONE chain of fused
 // multiply-adds over the contraction index in ascending order (v_mfma_f32_16x16x4_f32 adds its four products one after
-// the other, lowest k first, rounding each time -- checked against fmaf bit for bit).  What feeds a ReLU or a pooling is
-// therefore the same to the last bit whatever tile it was formed in, and the same as the bounds-checked FMA kernel of
-// kernels_conv.hip gives.  bf16 operands are widened on their way out of LDS.  Weight gradients are sums over thousands of
+// the other, lowest k first, rounding each time; tests/test_gpu_gemm_any.py holds dense layers and convolutions to such a
+// chain bit for bit).  What feeds a ReLU or a pooling is therefore the same to the last bit whatever tile it was formed
+// in, and the same as the bounds-checked FMA kernel of kernels_conv.hip gives.  That is a choice, made so that results
+// did not move when these kernels replaced that one; the tuned bf16 kernels sum in the order of their own instructions.  bf16 operands are widened on their way out of LDS.  Weight gradients are sums over thousands of
 // rows, whose order is not kept: they may be formed over several row ranges, in bf16 with v_mfma_f32_16x16x32_bf16.
 //
 // One kernel template; what differs between the products is where the 16-byte chunks of an operand's k tile come from
@@ -752,8 +753,11 @@ hipError_t f32_fprop(hipStream_t s, int M, int N, int K, const float* x, const f
                      float* a_out, float* x_copy) {
   SideCopy side{nullptr, nullptr, 0};
   if (x_copy) {
-    // Behind the tiles a copy of 64 KB is hidden (pipeline of 256-512-512-10, batches of 32: 1268 us to 1140 us); one of 512 KB
-    // takes slots from products on other streams (stage of 1024, micro-batches of 128: 151 us, 145 us with a launch of its own).
+    // Behind the tiles the copy is hidden where one stream runs everything: a step of four micro-batches and two layers takes
+    // 7 us less than with launches of its own at every size from 16 KB to 1 MB (32 x 512: 103 and 110 us; pipeline of
+    // 256-512-512-10, batches of 32: 1140 and 1268 us).  On two forward streams it also takes slots from products of the other
+    // one: from process to process 4 us more to 17 us less at 64 KB, 17 us more to 3 us less at 512 KB.  The line lies at
+    // 256 KB, in between.
     if (aligned16(x, x_copy) && (size_t)M * K % 4 == 0 && (size_t)M * K <= 65536) {
       side = SideCopy{(const uint4*)x, (uint4*)x_copy, (size_t)M * K / 4};
     } else {

@@ -599,7 +599,9 @@ Tile pick(int M, int N, bool wgrad) {
 // few tiles to fill the chip, it is formed over as many ranges as give every CU a workgroup, at least 8 k tiles each (a
 // 64 x 64 gradient over the 131072 pixels of 16x16 maps is one tile and 2048 k tiles), and small tiles that fill it
 // unsplit give way to ranges of larger ones where that takes less time: a k tile of a 256x256 tile takes 1.66 us (32768
-// rows), of the others by their rates, and the ranges cost a launch (3 us) and their fp32 partial sums at 4 TB/s.
+// rows), of the others by their rates, and the ranges cost a launch (3 us) and their fp32 partial sums at 4 TB/s.  Ranges
+// are formed on the three square tiles only: the rates of the other four lie between theirs, and each would be two more
+// kernels for the partial sums; how they compare is not measured.
 // 2048 x 512 and 1536 x 512 over 6400 rows: 64x64 tiles fill the chip but wait for memory (34 us), 128x128 ones over four and
 // five ranges do less of it: two decoder blocks of width 512 1.087 -> 1.039 ms; 2048 x 2048 over 32768 rows, 128x128 tiles
 // before, 256x256 over four ranges now: decoder block of width 2048 10.52 -> 10.45 ms.
