@@ -682,12 +682,15 @@ inline int store_width(const void* a, const void* b) { return aligned(16, a, b) 
 
 hipError_t mfma_fprop(hipStream_t s, int M, int N, int K, const uint16_t* x, const uint16_t* W, const float* bias,
                       int act, uint16_t* d_out, uint16_t* a_out, uint16_t* x_copy, const uint16_t* addend) {
-  const bool dma = dma_ok(M, N, K, K, K, false, false) && aligned(16, x, W, x_copy);
-  SideCopy side{(const uint4*)x, (uint4*)x_copy, x_copy ? (size_t)M * K / 8 : 0};  // whole 16-byte units with dma
-  if (x_copy && !dma) {
+  const bool fits = dma_ok(M, N, K, K, K, false, false) && aligned(16, W, x_copy);
+  if (x_copy && !(fits && aligned(16, x))) {
     const hipError_t err = launch_copy(s, x, x_copy, (size_t)M * K * 2);
     if (err != hipSuccess) return err;
+    if (fits) x = x_copy;  // an input that is not aligned: its copy is, and the direct-to-LDS kernel takes that
   }
+  const bool dma = fits && aligned(16, x);
+  // whole 16-byte units with dma
+  const SideCopy side{(const uint4*)x, (uint4*)x_copy, dma && x_copy && x != x_copy ? (size_t)M * K / 8 : 0};
   const int wide = store_width(d_out, a_out);
   // contractions that are no multiple of 8 ran on fp32 FMAs with GELU from erff, and keep it
   if (K % 8) return run_any<false, false>(s, M, N, K, x, K, W, K, EpiFpropExact{bias, d_out, a_out, act, N, nullptr, wide});

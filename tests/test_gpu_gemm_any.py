@@ -70,7 +70,7 @@ def test_dense_fp32(rows, fin, fout):
     (16384, 1024, 1024), (16389, 1032, 1032),                 # ... over 4 and 3; input gradients on 256 x 256 and 128 x 128
     (32769, 1024, 1024),                                      # ... over 16 ranges on 256 x 256 tiles, one row in the last k tile
 ])
-@pytest.mark.parametrize("shift", [0, 1])                     # 1: the input starts at an odd element
+@pytest.mark.parametrize("shift", [0, 1])                     # 1: the input starts at an odd element (rows of chunks: its copy is used)
 def test_dense_bf16(rows, fin, fout, shift):
     import torch
     from synth_inputs import round_bf16
