@@ -18,6 +18,8 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "conv.h"
 #include "device_utils.h"
@@ -403,18 +405,25 @@ __device__ __forceinline__ void store4(T* p, const float (&v)[4]) {
   if constexpr (sizeof(T) == 4) *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
   else *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
 }
+// finish: the same with what the epilogue reads besides the product (input) in hand, so that a kernel can fetch it early.
 template <class T>
 struct EpiForward {
   static constexpr int kPartK = 0;
   const float* bias;
   T *d_out, *a_out;
   int act, ldc, vec;
-  __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
+  __device__ __forceinline__ floatx4 input(int, int n, int count) const {
+    floatx4 b;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b[j] = bias[j < count ? n + j : n];
+    return b;
+  }
+  __device__ __forceinline__ void finish(int m, int n, int count, const floatx4& v, const floatx4& b) const {
     const size_t i = (size_t)m * ldc + n;
     float a[4], d[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const float z = v[j] + bias[j < count ? n + j : n];
+      const float z = v[j] + b[j];
       a[j] = act_forward(z, act);
       d[j] = d_out ? act_derivative(z, act) : 0.f;
     }
@@ -430,6 +439,9 @@ struct EpiForward {
         }
     }
   }
+  __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
+    finish(m, n, count, v, input(m, n, count));
+  }
 };
 template <class T>
 struct EpiInputGrad {
@@ -437,17 +449,18 @@ struct EpiInputGrad {
   const T* d_prev;  // saved act'(z) of the layer before, with relu_mask its ReLU output, or null
   T* out;
   int ldc, relu_mask, vec;
-  __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
+  __device__ __forceinline__ floatx4 input(int m, int n, int count) const {
+    const size_t i = (size_t)m * ldc + n;
+    floatx4 d;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = d_prev ? to_float(d_prev[j < count ? i + j : i]) : 0.f;
+    return d;
+  }
+  __device__ __forceinline__ void finish(int m, int n, int count, const floatx4& v, const floatx4& d) const {
     const size_t i = (size_t)m * ldc + n;
     float o[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      o[j] = v[j];
-      if (d_prev) {
-        const float d = to_float(d_prev[j < count ? i + j : i]);
-        o[j] = relu_mask ? (d > 0.f ? v[j] : 0.f) : v[j] * d;
-      }
-    }
+    for (int j = 0; j < 4; ++j) o[j] = !d_prev ? v[j] : relu_mask ? (d[j] > 0.f ? v[j] : 0.f) : v[j] * d[j];
     if (vec && count == 4) {
       store4(out + i, o);
     } else {
@@ -455,6 +468,9 @@ struct EpiInputGrad {
       for (int j = 0; j < 4; ++j)
         if (j < count) out[i + j] = from_float<T>(o[j]);
     }
+  }
+  __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
+    finish(m, n, count, v, input(m, n, count));
   }
 };
 // fp32 partial result of contraction range `split`
@@ -625,6 +641,183 @@ hipError_t launch_any(hipStream_t s, int M, int N, int KT, int splits, const typ
   return hipGetLastError();
 }
 
+// ---- dense fp32 products of few tiles ------------------------------------------------------------
+// Forward products and input gradients of whole k tiles, with rows of whole 16-byte units: the same chains as above, bit for
+// bit.  Bound by the chain itself, one dependent v_mfma_f32_16x16x4_f32 per four k values, 32 cycles each.  fp32 matrix
+// instructions run on the vector ALUs: between two of them an LDS read or a scalar instruction costs 1 to 3 cycles, a
+// vector instruction 8 and more (timed in a chain of its own).  The kernel above, with some seven vector instructions per copy,
+// sixteen per run of k tiles and a barrier between runs, takes 80 cycles per matrix instruction here, however many k tiles its copies
+// are ahead.  So a workgroup is ONE wave with a tile of 16 x 16, which waits for its own copies and for nobody; the
+// copies take a scalar base and a constant offset per lane, and with the loop unrolled over the stages every LDS address is
+// a constant register and an immediate.  No vector instruction is left in the loop: 41 cycles per matrix instruction.
+// 32 x 512 x 512 7.1 -> 4.9 us, 128 x 1024 x 1024 11.5 -> 7.4, input gradient 128 x 512 x 512 7.3 -> 4.8.
+// With two or four tiles per wave, for fewer bytes per product, the same three took 6.8, 10.6, 7.0 and 11.0, 18.2, 11.4 us.
+constexpr int kWaveStages = 8;   // 32 KB; twelve of them: 5.2, 7.6, 5.0 us
+constexpr int kWaveStage = 4096;  // 16 rows of 32 k values of each operand
+
+// [16 rows][32 k], chunks swizzled as above
+struct WaveRow {
+  uint32_t off[2];  // bytes from the first row
+  int at[8];        // LDS byte of k = 4 m + g of row i
+  __device__ __forceinline__ void init(int ld, int r0, int rows, int lane) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int r = 8 * t + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+      off[t] = (uint32_t)(min(r0 + r, rows - 1) - r0) * (uint32_t)ld * 4 + c * 16;
+    }
+    const int i = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) at[m] = i * 128 + ((m ^ ((i >> 1) & 7)) << 4) + 4 * g;
+  }
+  static __device__ __forceinline__ size_t start(int ld, int r0) { return (size_t)r0 * ld; }
+  static __device__ __forceinline__ size_t step(int) { return 32; }
+  __device__ __forceinline__ float read(const char* stage, int m) const { return *reinterpret_cast<const float*>(stage + at[m]); }
+};
+// [32 k][16 rows]: the 64 lanes of a read lie side by side
+struct WaveCol {
+  uint32_t off[2];
+  int at;
+  __device__ __forceinline__ void init(int ld, int r0, int rows, int lane) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int k = 16 * t + (lane >> 2), c = lane & 3;
+      off[t] = ((uint32_t)k * (uint32_t)ld + (uint32_t)(min(r0 + 4 * c, rows - 4) - r0)) * 4;
+    }
+    at = lane * 4;
+  }
+  static __device__ __forceinline__ size_t start(int, int r0) { return r0; }
+  static __device__ __forceinline__ size_t step(int ld) { return (size_t)32 * ld; }
+  __device__ __forceinline__ float read(const char* stage, int m) const {
+    return *reinterpret_cast<const float*>(stage + at + m * 256);
+  }
+};
+
+template <class F, int... U>
+__device__ __forceinline__ void for_each_stage(const F& f, std::integer_sequence<int, U...>) {
+  (f(std::integral_constant<int, U>{}), ...);
+}
+
+template <class AL, class BL, class Epi>
+__global__ __launch_bounds__(64) void gemm_f32_wave_kernel(int M, int N, int KT, const float* __restrict__ A, int lda,
+                                                           const float* __restrict__ B, int ldb, Epi epi, TileMap map,
+                                                           SideCopy side) {
+  constexpr int NS = kWaveStages, kCopies = 4;
+  static_assert(NS % 2 == 0, "fragment buffers alternate with the stages");
+  __shared__ __attribute__((aligned(16))) char lds[NS * kWaveStage];
+  const int lane = threadIdx.x;
+  const int tiles = map.tiles_m * map.tiles_n;
+  if ((int)blockIdx.x >= tiles) {  // workgroups behind the tiles copy, as above
+    const size_t step = (size_t)(gridDim.x - tiles) * 64;
+    for (size_t i = (size_t)(blockIdx.x - tiles) * 64 + lane; i < side.nvec; i += step) side.dst[i] = side.src[i];
+    return;
+  }
+  int tile_m, tile_n;
+  map.get(blockIdx.x, tile_m, tile_n);
+  const int m0 = __builtin_amdgcn_readfirstlane(tile_m) * 16, n0 = __builtin_amdgcn_readfirstlane(tile_n) * 16;
+  const uint32_t lds_base = lds_addr_of(lds);
+
+  AL a;
+  BL b;
+  a.init(lda, m0, M, lane);
+  b.init(ldb, n0, N, lane);
+  // row m, columns n .. n+3 of the output are this lane's; what the epilogue reads there is fetched before the products
+  const int m = m0 + (lane & 15), n = n0 + 4 * (lane >> 4);
+  const floatx4 input = epi.input(min(m, M - 1), min(n, N - 1), N - min(n, N - 1));
+  const float* pa = A + AL::start(lda, m0);  // the next tile to be copied
+  const float* pb = B + BL::start(ldb, n0);
+  const size_t step_a = AL::step(lda), step_b = BL::step(ldb);
+  auto copy = [&](int q, int stage) {
+    const uint32_t dst = lds_base + stage * kWaveStage + q * 1024;
+    if (q < 2) dma16(dst, pa, a.off[q]);
+    else dma16(dst, pb, b.off[q - 2]);
+  };
+
+  // Tile t lies in stage (t + skip) % NS, so that the last tile is in the last stage: the end of the loop, with fewer and
+  // fewer copies in flight, is unrolled with its waits.
+  const int skip = (NS - KT % NS) % NS;
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t)
+    if (t < KT) {
+      const int stage = t + skip >= NS ? t + skip - NS : t + skip;
+#pragma unroll
+      for (int q = 0; q < kCopies; ++q) copy(q, stage);
+      pa += step_a;
+      pb += step_b;
+    }
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  float fa[2][8], fb[2][8];
+  if (KT >= NS - 1) wait_vmcnt<(NS - 2) * kCopies>();
+  else wait_vmcnt<0>();
+  auto first = [&](auto buf) {  // the first tile's fragments, into the buffer of its stage
+    const char* at = lds + skip * kWaveStage;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      fa[decltype(buf)::value][k] = a.read(at, k);
+      fb[decltype(buf)::value][k] = b.read(at + 2048, k);
+    }
+  };
+  if (skip & 1) first(std::integral_constant<int, 1>{});
+  else first(std::integral_constant<int, 0>{});
+  // The tile in stage u.  Between its instructions the fragments of the next tile are read, and the tile NS - 1 further on is
+  // copied to the stage before this one, whose fragments the instructions of the tile before have taken.
+  auto tile = [&](auto stage_u, auto copying, auto more) {
+    constexpr int u = decltype(stage_u)::value, next = (u + 1) % NS;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[u & 1][k], fa[u & 1][k], acc, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (decltype(more)::value) {
+        fa[next & 1][k] = a.read(lds + next * kWaveStage, k);
+        fb[next & 1][k] = b.read(lds + next * kWaveStage + 2048, k);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (decltype(copying)::value)
+        if (k % 2 == 0) {
+          copy(k / 2, (u + NS - 1) % NS);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if constexpr (decltype(copying)::value) {
+      pa += step_a;
+      pb += step_b;
+    }
+  };
+  auto all_stages = [&](int t0, auto last) {  // tile t0 in stage 0; tiles below zero are left out
+    for_each_stage([&](auto stage_u) {
+      constexpr int u = decltype(stage_u)::value;
+      if (t0 + u < 0) return;
+      if constexpr (!decltype(last)::value || u == 0) {
+        wait_vmcnt<(NS - 3) * kCopies>();  // the next tile has landed
+        tile(stage_u, std::true_type{}, std::true_type{});
+      } else if constexpr (u < NS - 1) {
+        wait_vmcnt<(NS - 2 - u) * kCopies>();
+        tile(stage_u, std::false_type{}, std::true_type{});
+      } else {
+        tile(stage_u, std::false_type{}, std::false_type{});
+      }
+    }, std::make_integer_sequence<int, NS>{});
+  };
+  int t0 = -skip;
+  for (; t0 + NS < KT; t0 += NS) all_stages(t0, std::false_type{});
+  all_stages(t0, std::true_type{});
+  if (m < M && n < N) epi.finish(m, n, min(4, N - n), acc, input);
+}
+
+template <class AL, class BL, class Epi>
+hipError_t launch_wave(hipStream_t s, int M, int N, int K, const float* A, int lda, const float* B, int ldb, const Epi& epi,
+                       const SideCopy& side = SideCopy{nullptr, nullptr, 0}) {
+  const int tiles_m = (M + 15) / 16, tiles_n = (N + 15) / 16;
+  const unsigned copiers = (unsigned)std::min<size_t>((side.nvec + 255) / 256, 256);
+  hipLaunchKernelGGL((gemm_f32_wave_kernel<AL, BL, Epi>), dim3(tiles_m * tiles_n + copiers), dim3(64), 0, s, M, N, K / 32, A, lda, B,
+                     ldb, epi, make_tile_map(tiles_m, tiles_n), side);
+  return hipGetLastError();
+}
+// Up to one wave per SIMD.  With 1024 tiles, 256 x 1024 x 1024, 7.7 us against 11.4 in tiles of 32 x 32; with 2048 the waves share
+// the SIMDs and the L2s serve twice the bytes, 19.2 against 17.6; with 4096 33.8 against 28.4.  ld: rows' 32-bit offsets.
+inline bool wave_ok(int M, int N, int K, int ld) {
+  return K % 32 == 0 && ld < (1 << 24) && (long)((M + 15) / 16) * ((N + 15) / 16) <= 1024;
+}
+
 // The tiles, and the time of one k tile on a CU that holds one workgroup (t1) and two (t2), in ns; 128 x 128 leaves room
 // for one.  Chains in fp32 are bound by the matrix cores where the output fills the chip and by the chain barrier -> LDS
 // read -> MFMAs of a lone workgroup where it does not: four waves and four k tiles between barriers on the smallest
@@ -767,6 +960,8 @@ hipError_t f32_fprop(hipStream_t s, int M, int N, int K, const float* x, const f
   }
   const DenseDesc a{x, K, M, K}, b{W, K, N, K};
   const EpiForward<float> e{bias, d_out, a_out, act, N, N % 4 == 0 && aligned16(d_out, a_out)};
+  if (aligned16(x, W) && wave_ok(M, N, K, K))
+    return launch_wave<WaveRow, WaveRow>(s, M, N, K, x, K, W, K, e, side);
   if (K % 4 == 0 && aligned16(x, W)) return run<float, Chain, FpropDense, 4>(s, M, N, K, a, b, e, false, side);
   return run<float, Chain, FpropDense, 1>(s, M, N, K, a, b, e, false, side);
 }
@@ -776,6 +971,8 @@ hipError_t f32_dgrad(hipStream_t s, int M, int N, int K, const float* dz, const 
   // out[M x K] = dz[M x N] . Wb[N x K]: contraction over N
   const DenseDesc a{dz, N, M, N}, b{Wb, K, K, N};
   const EpiInputGrad<float> e{d_prev, out, K, relu_mask, K % 4 == 0 && aligned16(out)};
+  if (K % 4 == 0 && aligned16(dz, Wb) && wave_ok(M, K, N, std::max(N, K)))
+    return launch_wave<WaveRow, WaveCol>(s, M, K, N, dz, N, Wb, K, e);
   if (N % 4 == 0 && K % 4 == 0 && aligned16(dz, Wb)) return run<float, Chain, DgradDense, 4>(s, M, K, N, a, b, e);
   return run<float, Chain, DgradDense, 1>(s, M, K, N, a, b, e);
 }

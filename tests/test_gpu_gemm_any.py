@@ -311,3 +311,43 @@ def test_fp32_products_have_the_same_bits_on_every_tile():
             st.close()
             first = first or got
             assert torch.equal(got[0], first[0]) and torch.equal(got[1], first[1]), (rows, shift)
+
+
+@pytest.mark.parametrize("rows,widths", [
+    # k tiles of 32 in the contractions of two layers, both ways: 1, 2 | 6, 7 | 7, 8 | 8, 9 | 15, 16, 17 of eight stages
+    (1, (32, 64, 4)), (17, (192, 224, 64)), (33, (256, 224, 288)), (16, (288, 256, 36)), (50, (480, 512, 544)),
+    (40, (64, 32, 10)),                                      # output columns that are no whole unit of four
+])
+def test_fp32_layers_of_few_tiles_are_chains(rows, widths):
+    """One wave per 16 x 16 outputs, with what the epilogues read: bias and ReLU forward, the ReLU's mask backward."""
+    from paper_2509_23241_amd.runner import GpuStage
+    rng = np.random.default_rng(rows)
+    fin, mid, fout = widths
+    W1, W2, x, dy = [rng.standard_normal(s).astype(np.float32) for s in ((mid, fin), (fout, mid), (rows, fin), (rows, fout))]
+    b1, b2 = [rng.standard_normal(n).astype(np.float32) for n in (mid, fout)]
+    st = GpuStage([(fin, mid, "relu"), (mid, fout, "none")], [W1, b1, W2, b2], dtype="f32", mb=rows, n=1, stage_index=1,
+                  num_stages=2, policy="latest", lam=0.1, lr=0.0, momentum=0.0, ring_capacity=1, max_in_flight=1)
+    y, dx, _ = _run(st, x, dy)
+    a1 = np.maximum(_chain(x, W1) + b1, np.float32(0))
+    assert np.array_equal(y, _chain(a1, W2) + b2)
+    dz1 = np.where(a1 > 0, _chain(dy, W2.T), np.float32(0))
+    assert np.array_equal(dx, _chain(dz1, W1.T))
+
+
+@pytest.mark.parametrize("rows,fin,fout", [(256, 1024, 1024), (257, 1024, 1024), (1024, 256, 256)])
+def test_fp32_layers_at_the_line_between_waves_and_tiles(rows, fin, fout):
+    """1024 tiles of 16 x 16 and one row of them more: the bits of operands at odd addresses, which the tiles of 32 take."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    W = torch.randn(fout, fin, generator=g, device="cuda").cpu().numpy()
+    x, dy = torch.randn(rows, fin, generator=g, device="cuda"), torch.randn(rows, fout, generator=g, device="cuda")
+    got = []
+    for shift in (0, 1):
+        xs, ds = [torch.empty(t.numel() + shift, device="cuda")[shift:].view(t.shape).copy_(t) for t in (x, dy)]
+        st = _stage((fin, fout, "none"), [W, np.zeros(fout, np.float32)], rows, "f32")
+        y, _ = st.forward(0, 0, xs)
+        dx, _ = st.backward(0, ds)
+        got.append((y.clone(), dx.clone()))
+        st.close()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
