@@ -83,29 +83,28 @@ struct Frag<Free> {
 template <class T>
 constexpr int kSteps = kTileK<T> / 32;
 
+// A fragment is read in kParts<Sum> parts, one LDS instruction (two for a transposed one) each, so that the reads of the
+// next step can go out one by one between the matrix instructions of the current one.
+template <class Sum>
+constexpr int kParts = __is_same(Sum, Chain) ? 8 : 1;
+
 template <class T, class Sum, int R>
-__device__ __forceinline__ Frag<Sum> row_frag(const char* lds, int rbase, int step, int lane) {
+__device__ __forceinline__ void row_part(Frag<Sum>& f, const char* lds, int rbase, int step, int lane, int m) {
   const int r = rbase + (lane & 15), g = lane >> 4;
   const char* row = lds + r * 128;
   const int swz = (r >> 1) & 7;
-  Frag<Sum> f;
   if constexpr (__is_same(Sum, Free)) {
     f.v = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(row + (((4 * step + g) ^ swz) << 4)));
   } else if constexpr (sizeof(T) == 4) {
-#pragma unroll
-    for (int m = 0; m < 8; ++m) f.v[m] = *reinterpret_cast<const float*>(row + ((m ^ swz) << 4) + 4 * g);
+    f.v[m] = *reinterpret_cast<const float*>(row + ((m ^ swz) << 4) + 4 * g);
   } else {
-#pragma unroll
-    for (int m = 0; m < 8; ++m)
-      f.v[m] = bf16_to_float(*reinterpret_cast<const uint16_t*>(row + (((4 * step + (m >> 1)) ^ swz) << 4) + 8 * (m & 1) + 2 * g));
+    f.v[m] = bf16_to_float(*reinterpret_cast<const uint16_t*>(row + (((4 * step + (m >> 1)) ^ swz) << 4) + 8 * (m & 1) + 2 * g));
   }
-  return f;
 }
 
 template <class T, class Sum, int R>
-__device__ __forceinline__ Frag<Sum> col_frag(const char* lds, int rbase, int step, int lane) {
+__device__ __forceinline__ void col_part(Frag<Sum>& f, const char* lds, int rbase, int step, int lane, int m) {
   const int i = lane & 15, g = lane >> 4;
-  Frag<Sum> f;
   if constexpr (__is_same(Sum, Free)) {
     // ds_read_b64_tr_b16: lane s of a group of 16 points at 4 consecutive values of k row k0 + s/4 and receives rows
     // k0 .. k0+3 of column c0 + s
@@ -121,19 +120,16 @@ __device__ __forceinline__ Frag<Sum> col_frag(const char* lds, int rbase, int st
     constexpr int C = Elem<T>::kChunk;
     const int r = rbase + i;
     const char* at = lds + g * (R * (int)sizeof(T)) + ((r / C) ^ col_swizzle<T, Sum, R>(g)) * 16 + (r % C) * (int)sizeof(T);
-#pragma unroll
-    for (int m = 0; m < 8; ++m)  // k = 32 step + 4 m + g: the swizzle depends on g alone
-      f.v[m] = to_float(*reinterpret_cast<const T*>(at + (32 * step + 4 * m) * (R * (int)sizeof(T))));
+    // k = 32 step + 4 m + g: the swizzle depends on g alone
+    f.v[m] = to_float(*reinterpret_cast<const T*>(at + (32 * step + 4 * m) * (R * (int)sizeof(T))));
   }
-  return f;
 }
 
-// acc += (A . B^T of one step), transposed: register r of a lane is column 4 (lane / 16) + r of row lane % 16
-__device__ __forceinline__ void multiply(const Frag<Chain>& a, const Frag<Chain>& b, floatx4& acc) {
-#pragma unroll
-  for (int m = 0; m < 8; ++m) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(b.v[m], a.v[m], acc, 0, 0, 0);
+// acc += (A . B^T of part m), transposed: register r of a lane is column 4 (lane / 16) + r of row lane % 16
+__device__ __forceinline__ void multiply(const Frag<Chain>& a, const Frag<Chain>& b, int m, floatx4& acc) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(b.v[m], a.v[m], acc, 0, 0, 0);
 }
-__device__ __forceinline__ void multiply(const Frag<Free>& a, const Frag<Free>& b, floatx4& acc) {
+__device__ __forceinline__ void multiply(const Frag<Free>& a, const Frag<Free>& b, int, floatx4& acc) {
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.v, a.v, acc, 0, 0, 0);
 }
 
@@ -195,12 +191,12 @@ struct DenseRow {
   }
   using Tile = int;
   __device__ __forceinline__ Tile tile(int tile) const { return tile; }
-  __device__ __forceinline__ const void* source(int t, int tile) const {
+  __device__ __forceinline__ void copy(int t, int tile, uint32_t lds) const {
     const int k0 = tile * kTileK<T>;
-    return k0 + k[t] < K ? (const char*)(p[t] + k0) : zero_chunk();
+    dma_addr<Spot::kPieceBytes>(lds, k0 + k[t] < K ? (const char*)(p[t] + k0) : zero_chunk());
   }
-  static __device__ __forceinline__ Frag<Sum> frag(const char* lds, int rbase, int step, int lane) {
-    return row_frag<T, Sum, R>(lds, rbase, step, lane);
+  static __device__ __forceinline__ void part(Frag<Sum>& f, const char* lds, int rbase, int step, int lane, int m) {
+    row_part<T, Sum, R>(f, lds, rbase, step, lane, m);
   }
 };
 
@@ -223,12 +219,50 @@ struct DenseCol {
   }
   using Tile = int;
   __device__ __forceinline__ Tile tile(int tile) const { return tile; }
-  __device__ __forceinline__ const void* source(int t, int tile) const {
+  __device__ __forceinline__ void copy(int t, int tile, uint32_t lds) const {
     const int k0 = tile * kTileK<T>;
-    return k0 + k[t] < K ? (const char*)(p[t] + (size_t)k0 * ld) : zero_chunk();
+    dma_addr<Spot::kPieceBytes>(lds, k0 + k[t] < K ? (const char*)(p[t] + (size_t)k0 * ld) : zero_chunk());
   }
-  static __device__ __forceinline__ Frag<Sum> frag(const char* lds, int rbase, int step, int lane) {
-    return col_frag<T, Sum, R>(lds, rbase, step, lane);
+  static __device__ __forceinline__ void part(Frag<Sum>& f, const char* lds, int rbase, int step, int lane, int m) {
+    col_part<T, Sum, R>(f, lds, rbase, step, lane, m);
+  }
+};
+
+// The same for contractions of whole k tiles: a scalar base and 32-bit offsets that stay, so that a copy takes no vector
+// instruction (next to fp32 matrix instructions those are not free, see below).  Rows (COL: k values) of a tile
+// lie within 4 GiB.
+template <class T, class Sum, int R, int NW, bool COL>
+struct DenseWhole {
+  static constexpr int VEC = Elem<T>::kChunk;
+  using Desc = DenseDesc;
+  using Row = RowSpot<T, R, NW, VEC>;
+  using Col = ColSpot<T, Sum, R, NW, VEC>;
+  struct Spot {
+    static constexpr int kPieceBytes = 16;
+  };
+  static constexpr int kPerWave = COL ? Col::kPerWave : Row::kPerWave;
+  const T* base;
+  size_t step;
+  uint32_t off[kPerWave];
+  __device__ __forceinline__ void init(const Desc& d, int r0, int wave, int lane) {
+    r0 = __builtin_amdgcn_readfirstlane(r0);
+    base = (const T*)d.base + (COL ? (size_t)r0 : (size_t)r0 * d.ld);
+    step = COL ? (size_t)kTileK<T> * d.ld : (size_t)kTileK<T>;
+#pragma unroll
+    for (int t = 0; t < kPerWave; ++t) {
+      int r, k;
+      if constexpr (COL) Col::at(t, wave, lane, r, k);
+      else Row::at(t, wave, lane, r, k);
+      const uint32_t row = min(r0 + r, d.rows - (COL ? VEC : 1)) - r0;
+      off[t] = (COL ? (uint32_t)k * (uint32_t)d.ld + row : row * (uint32_t)d.ld + k) * (uint32_t)sizeof(T);
+    }
+  }
+  using Tile = const T*;
+  __device__ __forceinline__ Tile tile(int tile) const { return base + tile * step; }
+  __device__ __forceinline__ void copy(int t, Tile tile, uint32_t lds) const { dma16(lds, tile, off[t]); }
+  static __device__ __forceinline__ void part(Frag<Sum>& f, const char* lds, int rbase, int step, int lane, int m) {
+    if constexpr (COL) col_part<T, Sum, R>(f, lds, rbase, step, lane, m);
+    else row_part<T, Sum, R>(f, lds, rbase, step, lane, m);
   }
 };
 
@@ -297,7 +331,7 @@ struct GatherRow {
     }
     return o;
   }
-  __device__ __forceinline__ const void* source(int t, const Tile& o) const {
+  __device__ __forceinline__ void copy(int t, const Tile& o, uint32_t lds) const {
     const int i = t % kKinds;
     int sh, sw;
     bool ok = true;
@@ -314,10 +348,10 @@ struct GatherRow {
       sw = (hw[t] & 0xffff) + o.kw[i];
     }
     ok = ok && (unsigned)sh < (unsigned)d.SH && (unsigned)sw < (unsigned)d.SW;
-    return ok ? (const char*)(image[t] + (uint32_t)((sh * d.SW + sw) * d.C + o.c[i])) : zero_chunk();
+    dma_addr<Spot::kPieceBytes>(lds, ok ? (const char*)(image[t] + (uint32_t)((sh * d.SW + sw) * d.C + o.c[i])) : zero_chunk());
   }
-  static __device__ __forceinline__ Frag<Sum> frag(const char* lds, int rbase, int step, int lane) {
-    return row_frag<T, Sum, R>(lds, rbase, step, lane);
+  static __device__ __forceinline__ void part(Frag<Sum>& f, const char* lds, int rbase, int step, int lane, int m) {
+    row_part<T, Sum, R>(f, lds, rbase, step, lane, m);
   }
 };
 
@@ -346,13 +380,14 @@ struct WeightCol {
   }
   using Tile = int;
   __device__ __forceinline__ Tile tile(int tile) const { return tile; }
-  __device__ __forceinline__ const void* source(int t, int tile) const {
+  __device__ __forceinline__ void copy(int t, int tile, uint32_t lds) const {
     int tap, co;
     d.by_cout.get(tile * kTileK<T> + k[t], tap, co);
-    return tap < d.taps ? (const char*)((const T*)d.base + ((size_t)co * d.taps + tap) * d.cin + n[t]) : zero_chunk();
+    const T* at = (const T*)d.base + ((size_t)co * d.taps + tap) * d.cin + n[t];
+    dma_addr<Spot::kPieceBytes>(lds, tap < d.taps ? (const char*)at : zero_chunk());
   }
-  static __device__ __forceinline__ Frag<Sum> frag(const char* lds, int rbase, int step, int lane) {
-    return col_frag<T, Sum, R>(lds, rbase, step, lane);
+  static __device__ __forceinline__ void part(Frag<Sum>& f, const char* lds, int rbase, int step, int lane, int m) {
+    col_part<T, Sum, R>(f, lds, rbase, step, lane, m);
   }
 };
 
@@ -384,17 +419,18 @@ struct GatherCol {
   }
   using Tile = int;
   __device__ __forceinline__ Tile tile(int tile) const { return tile; }
-  __device__ __forceinline__ const void* source(int t, int tile) const {
+  __device__ __forceinline__ void copy(int t, int tile, uint32_t lds) const {
     const int p = tile * kTileK<T> + k[t];
     int q, img, h, w;
     d.by_w.get(p, q, w);
     d.by_h.get(q, img, h);
     const int sh = h * d.S + dh[t], sw = w * d.S + dw[t];
     const bool ok = p < d.K && (unsigned)sh < (unsigned)d.SH && (unsigned)sw < (unsigned)d.SW;
-    return ok ? (const char*)((const T*)d.base + ((size_t)(img * d.SH + sh) * d.SW + sw) * d.C + c[t]) : zero_chunk();
+    const T* at = (const T*)d.base + ((size_t)(img * d.SH + sh) * d.SW + sw) * d.C + c[t];
+    dma_addr<Spot::kPieceBytes>(lds, ok ? (const char*)at : zero_chunk());
   }
-  static __device__ __forceinline__ Frag<Sum> frag(const char* lds, int rbase, int step, int lane) {
-    return col_frag<T, Sum, R>(lds, rbase, step, lane);
+  static __device__ __forceinline__ void part(Frag<Sum>& f, const char* lds, int rbase, int step, int lane, int m) {
+    col_part<T, Sum, R>(f, lds, rbase, step, lane, m);
   }
 };
 
@@ -498,9 +534,11 @@ struct EpiPartialPixels : EpiPartial {
   static constexpr int kPartK = 256;
 };
 // ---- the kernel --------------------------------------------------------------------------------
-// grid = (output tiles, contraction ranges of `per` k tiles each).  U k tiles are waited for, multiplied and replaced
-// between two barriers; NS runs of U tiles are in LDS.  The fragments of a step are read while the step before it is
-// multiplied, so that a wave that has its SIMD to itself waits for LDS once per barrier and not once per step.
+// grid = (output tiles, contraction ranges of `per` k tiles each).  U k tiles are multiplied between two barriers; NS runs of U
+// tiles are in LDS.  The fragments of a step are read between the matrix instructions of the step before it, and the
+// barrier that opens a run stands before the last step of the run before, so that a wave that has its SIMD to itself
+// waits for LDS nowhere.  Unrolled over the stages, since an LDS address formed at run time is a vector instruction, and
+// those take their time from fp32 matrix instructions (below).
 // Epi::kPartK: k values whose products are summed apart (0: all of them in one chain).
 template <class T, class Sum, int BM, int BN, int WGM, int WGN, int NS, int U, class AL, class BL, class Epi>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_any_kernel(int M, int N, int KT, int per, typename AL::Desc ad,
@@ -508,7 +546,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_any_kernel(int M, int N, 
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, NW = WGM * WGN;
   constexpr int kABytes = BM * 128, kStage = (BM + BN) * 128;
   constexpr int kLoads = AL::kPerWave + BL::kPerWave;
-  static_assert((NS - 2) * U * kLoads < 64, "too many copies in flight for vmcnt");
+  static_assert((NS - 1) * U * kLoads < 64, "too many copies in flight for vmcnt");
   extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int lane = threadIdx.x & 63;
@@ -555,55 +593,91 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_any_kernel(int M, int N, 
   BL b;
   a.init(ad, m0, wave, lane);
   b.init(bd, n0, wave, lane);
-  // tiles past the end copy the last tile again into a stage nobody reads, so that every iteration has the same
-  // number of copies in flight
-  auto issue = [&](int tile, int stage) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int t = min(tile + u, last);
-      const uint32_t dst = lds_base + (stage * U + u) * kStage;
-      const typename AL::Tile at = a.tile(t);
-      const typename BL::Tile bt = b.tile(t);
-#pragma unroll
-      for (int q = 0; q < AL::kPerWave; ++q)
-        dma_addr<AL::Spot::kPieceBytes>(dst + (wave + NW * q) * 64 * AL::Spot::kPieceBytes, a.source(q, at));
-#pragma unroll
-      for (int q = 0; q < BL::kPerWave; ++q)
-        dma_addr<BL::Spot::kPieceBytes>(dst + kABytes + (wave + NW * q) * 64 * BL::Spot::kPieceBytes, b.source(q, bt));
-    }
+  auto copy = [&](int q, const typename AL::Tile& at, const typename BL::Tile& bt, uint32_t dst) {
+    if (q < AL::kPerWave) a.copy(q, at, dst + (wave + NW * q) * 64 * AL::Spot::kPieceBytes);
+    else b.copy(q - AL::kPerWave, bt, dst + kABytes + (wave + NW * (q - AL::kPerWave)) * 64 * BL::Spot::kPieceBytes);
   };
 #pragma unroll
-  for (int st = 0; st < NS - 1; ++st) issue(first + st * U, st);
-  int rd = 0, wr = NS - 1;
-  for (int kt = first; kt <= last; kt += U) {
-    wait_vmcnt<(NS - 2) * U * kLoads>();
-    lds_barrier();  // tiles kt .. kt + U - 1 visible to all waves; everybody is done reading stage `wr`
-    issue(kt + U * (NS - 1), wr);
-    const char* run = lds + rd * (U * kStage);
-    Frag<Sum> fa[2][TM], fb[2][TN];
-    auto fetch = [&](int q) {  // step q of the run
-      const char* la = run + (q / kSteps<T>) * kStage;
+  for (int st = 0; st < NS * U; ++st) {  // all stages; tiles past the end copy the last one again, so that their number is known
+    const int t = min(first + st, last);
+    const typename AL::Tile at = a.tile(t);
+    const typename BL::Tile bt = b.tile(t);
 #pragma unroll
-      for (int i = 0; i < TM; ++i) fa[q & 1][i] = AL::frag(la, wm + 16 * i, q % kSteps<T>, lane);
+    for (int q = 0; q < kLoads; ++q) copy(q, at, bt, lds_base + st * kStage);
+  }
+  constexpr int kRun = U * kSteps<T>;              // steps of a run
+  constexpr int kMfmas = kParts<Sum> * TM * TN;    // matrix instructions of a step
+  constexpr int kReads = kParts<Sum> * (TM + TN);  // fragment reads of a step
+  static_assert(kRun % 2 == 0, "fragment buffers alternate with the steps");
+  Frag<Sum> fa[2][TM], fb[2][TN];
+  // read number x of the fragments of step q of the run in stage s
+  auto fetch = [&](int s, int q, int x) {
+    const char* la = lds + (s * U + q / kSteps<T>) * kStage;
+    const int m = x / (TM + TN), r = x % (TM + TN), step = q % kSteps<T>;
+    if (r < TM) AL::part(fa[q & 1][r], la, wm + 16 * r, step, lane, m);
+    else BL::part(fb[q & 1][r - TM], la + kABytes, wn + 16 * (r - TM), step, lane, m);
+  };
+  wait_vmcnt<(NS - 1) * U * kLoads>();
+  lds_barrier();  // the first run visible to all waves
 #pragma unroll
-      for (int j = 0; j < TN; ++j) fb[q & 1][j] = BL::frag(la + kABytes, wn + 16 * j, q % kSteps<T>, lane);
-    };
-    fetch(0);
+  for (int x = 0; x < kReads; ++x) fetch(0, 0, x);
+  // Step q of the run in stage s: its matrix instructions, between them the fragment reads of the next step and copies of the run
+  // that replaces the one consumed last, kShare in each of kWindow steps, counted (w) from the one behind a barrier.
+  // With two stages that run is waited for at the next barrier, so its copies go out in the first half of the time.
+  constexpr int kWindow = NS > 2 ? kRun : __is_same(Sum, Free) ? 1 : (kRun + 1) / 2, kShare = (U * kLoads + kWindow - 1) / kWindow;
+  auto copy_slot = [](int c) constexpr { return __is_same(Sum, Free) ? 0 : c * kMfmas / kShare; };
+  int fill = last + 1;  // first k tile of that run (past the last: none)
+  auto step = [&](int s, int q, int fill_stage, auto filling) {
+    const int c0 = (q + 1) % kRun * kShare;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int q = 0; q < U * kSteps<T>; ++q) {
-      if (q + 1 < U * kSteps<T>) fetch(q + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (U == 1 || kt + q / kSteps<T> <= last)  // wave uniform
+    for (int m = 0; m < kParts<Sum>; ++m)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) multiply(fa[q & 1][i], fb[q & 1][j], acc[i][j]);
-      __builtin_amdgcn_sched_barrier(0);
+        for (int j = 0; j < TN; ++j) {
+          multiply(fa[q & 1][i], fb[q & 1][j], m, acc[i][j]);
+          __builtin_amdgcn_sched_barrier(0);
+          const int slot = (m * TM + i) * TN + j;
+#pragma unroll
+          for (int x = 0; x < kReads; ++x)
+            if (x * kMfmas / kReads == slot) fetch(q == kRun - 1 ? (s + 1) % NS : s, (q + 1) % kRun, x);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (decltype(filling)::value) {
+#pragma unroll
+            for (int c = 0; c < kShare; ++c)
+              if (copy_slot(c) == slot && c0 + c < U * kLoads) {
+                const int t = min(fill + (c0 + c) / kLoads, last);
+                copy((c0 + c) % kLoads, a.tile(t), b.tile(t), lds_base + (fill_stage * U + (c0 + c) / kLoads) * kStage);
+              }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+  };
+  for (int kt = first; kt <= last; kt += NS * U) {  // unrolled over the stages: their LDS addresses are constants
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int run = kt + s * U;
+      if (run > last) break;  // wave uniform, as every condition here
+#pragma unroll
+      for (int q = 0; q < kRun; ++q) {
+        if (U > 1 && run + q / kSteps<T> > last) break;  // a shorter last run
+        if (q == kRun - 1) {
+          // The last fragments of this run are in registers: its stage is free once every wave is here, and the first
+          // fragments of the next run are read under the last matrix instructions of this one.
+          // with all copies for NS - 1 runs ahead under way
+          if (run == first || run + U * NS - 1 <= last) wait_vmcnt<(NS - 2) * U * kLoads>();
+          else wait_vmcnt<0>();
+          lds_barrier();
+          fill = run + U * NS;
+        }
+        const int fill_stage = q == kRun - 1 ? s : (s + NS - 1) % NS;
+        if ((q + 1) % kRun < kWindow && fill + (q + 1) % kRun * kShare / kLoads <= last) step(s, q, fill_stage, std::true_type{});
+        else step(s, q, fill_stage, std::false_type{});
+      }
+      if constexpr (kPart > 0)
+        if ((run + U - first) % kPart == 0) end_part();
     }
-    if constexpr (kPart > 0)
-      if ((kt + U - first) % kPart == 0) end_part();
-    rd = rd + 1 == NS ? 0 : rd + 1;
-    wr = wr + 1 == NS ? 0 : wr + 1;
   }
   wait_vmcnt<0>();  // the trailing copies land before the LDS is given back
   if constexpr (kPart > 0) end_part();
@@ -645,11 +719,10 @@ hipError_t launch_any(hipStream_t s, int M, int N, int KT, int splits, const typ
 // Forward products and input gradients of whole k tiles, with rows of whole 16-byte units: the same chains as above, bit for
 // bit.  Bound by the chain itself, one dependent v_mfma_f32_16x16x4_f32 per four k values, 32 cycles each.  fp32 matrix
 // instructions run on the vector ALUs: between two of them an LDS read or a scalar instruction costs 1 to 3 cycles, a
-// vector instruction 8 and more (timed in a chain of its own).  The kernel above, with some seven vector instructions per copy,
-// sixteen per run of k tiles and a barrier between runs, takes 80 cycles per matrix instruction here, however many k tiles its copies
-// are ahead.  So a workgroup is ONE wave with a tile of 16 x 16, which waits for its own copies and for nobody; the
-// copies take a scalar base and a constant offset per lane, and with the loop unrolled over the stages every LDS address is
-// a constant register and an immediate.  No vector instruction is left in the loop: 41 cycles per matrix instruction.
+// vector instruction 8 and more (timed in a chain of its own).  So a workgroup is ONE wave with a tile of 16 x 16, which waits
+// for its own copies and for nobody; the copies take a scalar base and a constant offset per lane, and with the loop
+// unrolled over the stages every LDS address is a constant register and an immediate.  No vector instruction is left in the loop:
+// 41 cycles per matrix instruction, where four waves of a 32 x 32 tile with a barrier every four k tiles took 80.
 // 32 x 512 x 512 7.1 -> 4.9 us, 128 x 1024 x 1024 11.5 -> 7.4, input gradient 128 x 512 x 512 7.3 -> 4.8.
 // With two or four tiles per wave, for fewer bytes per product, the same three took 6.8, 10.6, 7.0 and 11.0, 18.2, 11.4 us.
 constexpr int kWaveStages = 8;   // 32 KB; twelve of them: 5.2, 7.6, 5.0 us
@@ -812,38 +885,42 @@ hipError_t launch_wave(hipStream_t s, int M, int N, int K, const float* A, int l
                      ldb, epi, make_tile_map(tiles_m, tiles_n), side);
   return hipGetLastError();
 }
-// Up to one wave per SIMD.  With 1024 tiles, 256 x 1024 x 1024, 7.7 us against 11.4 in tiles of 32 x 32; with 2048 the waves share
-// the SIMDs and the L2s serve twice the bytes, 19.2 against 17.6; with 4096 33.8 against 28.4.  ld: rows' 32-bit offsets.
+// Up to one wave per SIMD.  With 1024 tiles, 512 x 512 x 1024, 7.9 us against 8.5 in tiles of 32 x 32; with 2048 the waves share
+// the SIMDs and the L2s serve twice the bytes, 19.2 against 12.3.  ld: rows' 32-bit offsets.
 inline bool wave_ok(int M, int N, int K, int ld) {
   return K % 32 == 0 && ld < (1 << 24) && (long)((M + 15) / 16) * ((N + 15) / 16) <= 1024;
 }
 
-// The tiles, and the time of one k tile on a CU that holds one workgroup (t1) and two (t2), in ns; 128 x 128 leaves room
-// for one.  Chains in fp32 are bound by the matrix cores where the output fills the chip and by the chain barrier -> LDS
-// read -> MFMAs of a lone workgroup where it does not: four waves and four k tiles between barriers on the smallest
-// tile, eight waves on the others.  Measured (us), the FMA kernel before in brackets: fp32 dense 32 x 512 x 512 7.0 [45],
-// 128 x 1024 x 1024 11.6 / 27.6 / 83 with 32 / 64 / 128 tiles [160], 1024^3 33 / 28 / 82, 2048^3 210 / 169 / 160 (108
-// TFLOP/s).  fp32 3x3 on 16 images of 32 x 32, 64 channels: forward 22 / 19 / 55 [300], dx 23 / 19 / 48 [230]; with the
-// fragments read step by step in front of their MFMAs 64 x 64 took 21.5.  bf16 3x3, 44 images of 64 x 64, 48 channels,
-// forward: 144 / 113 / 237 [400] (26 on bf16 matrix instructions, which do not keep the order of the sum).
+// The tiles, and the time of one k tile on a CU with one workgroup (t1) and two (t2), in ns; 128 x 128 leaves room
+// for one.  Chains in fp32 are bound by the matrix cores and by what vector instructions take from them: addresses of LDS and
+// copies that are constants or scalars (DenseWhole, the loop unrolled over the stages) brought dense products of 512 x 1024 x
+// 1024 from 18.1 to 12.5 us, 1024^3 from 28.0 to 20.5, 2048^3 from 158 to 128 (134 TFLOP/s); gathered 3x3 ones on 16 images of
+// 32 x 32, 64 channels, from 18.5 to 16.7, bf16 on 44 images of 48 x 48, 48 channels, from 80 to 72 (a third of that on bf16 matrix
+// instructions, which do not keep the order of the sum).  32 x 32, 64 x 64 and 128 x 128 tiles: 512 x 1024 x 1024 12.3 / 20.2 / 67,
+// 1024^3 21.1 / 20.7 / 67, 2048 x 4096 x 1024 156 / 138 / 135 us.
+// s1, s2: the same for products that may be cut into ranges, as timed before that: how many ranges a weight gradient is summed over,
+// and with it its rounding, stays what it was.
 enum class Tile { k32, k64, k128 };
 struct TileCost {
   Tile t;
   int edge, t1, t2;
+  int s1, s2;  // the same for products that may be cut into ranges
 };
 template <class T, class Sum>
 struct Tiles;
 template <>
 struct Tiles<float, Chain> {
-  static constexpr TileCost cost[] = {{Tile::k32, 32, 270, 480}, {Tile::k64, 64, 850, 1300}, {Tile::k128, 128, 2450, 4900}};
+  static constexpr TileCost cost[] = {
+      {Tile::k32, 32, 180, 300, 270, 480}, {Tile::k64, 64, 560, 1050, 850, 1300}, {Tile::k128, 128, 2090, 4150, 2450, 4900}};
 };
 template <>
 struct Tiles<uint16_t, Chain> {
-  static constexpr TileCost cost[] = {{Tile::k32, 32, 660, 930}, {Tile::k64, 64, 1770, 2900}};
+  static constexpr TileCost cost[] = {{Tile::k32, 32, 660, 930, 0, 0}, {Tile::k64, 64, 1770, 2900, 0, 0}};
 };
 template <>
 struct Tiles<uint16_t, Free> {
-  static constexpr TileCost cost[] = {{Tile::k32, 32, 200, 300}, {Tile::k64, 64, 350, 550}, {Tile::k128, 128, 800, 1600}};
+  static constexpr TileCost cost[] = {
+      {Tile::k32, 32, 0, 0, 200, 300}, {Tile::k64, 64, 0, 0, 350, 550}, {Tile::k128, 128, 0, 0, 800, 1600}};
 };
 
 // Contraction ranges of a product whose output has too few tiles for the chip (weight gradients): as many as give every
@@ -867,7 +944,8 @@ Tile pick_tile(int M, int N, int KT, bool split, int* ranges) {
     const long blocks = blocks_of(c.edge, M, N);
     const int r = split ? any_splits(blocks, KT) : 1;
     const long all = blocks * r, rest = all % 512;
-    const double cost = ((double)(all / 512) * c.t2 + (rest == 0 ? 0 : rest <= 256 ? c.t1 : c.t2)) * ((KT + r - 1) / r);
+    const int t1 = split ? c.s1 : c.t1, t2 = split ? c.s2 : c.t2;
+    const double cost = ((double)(all / 512) * t2 + (rest == 0 ? 0 : rest <= 256 ? t1 : t2)) * ((KT + r - 1) / r);
     if (best_cost < 0 || cost < best_cost) {
       best_cost = cost;
       best = c.t;
@@ -898,6 +976,18 @@ template <class T, class Sum, int VEC> struct WgradDense {
   template <int R, int NW> using A = DenseCol<T, Sum, R, NW, VEC>;
   template <int R, int NW> using B = DenseCol<T, Sum, R, NW, VEC>;
 };
+template <class T, class Sum, int> struct FpropDenseWhole {
+  template <int R, int NW> using A = DenseWhole<T, Sum, R, NW, false>;
+  template <int R, int NW> using B = DenseWhole<T, Sum, R, NW, false>;
+};
+template <class T, class Sum, int> struct DgradDenseWhole {
+  template <int R, int NW> using A = DenseWhole<T, Sum, R, NW, false>;
+  template <int R, int NW> using B = DenseWhole<T, Sum, R, NW, true>;
+};
+template <class T, class Sum, int> struct WgradDenseWhole {
+  template <int R, int NW> using A = DenseWhole<T, Sum, R, NW, true>;
+  template <int R, int NW> using B = DenseWhole<T, Sum, R, NW, true>;
+};
 template <class T, class Sum, int VEC> struct FpropConv {
   template <int R, int NW> using A = GatherRow<T, Sum, R, NW, VEC, false>;
   template <int R, int NW> using B = DenseRow<T, Sum, R, NW, VEC>;
@@ -922,7 +1012,8 @@ hipError_t run(hipStream_t s, int M, int N, int K, const AD& ad, const BD& bd, c
       s, M, N, KT, ranges, ad, bd, epi, side)
   switch (pick_tile<T, Sum>(M, N, KT, split, &ranges)) {
     case Tile::k128:
-      if constexpr (!(sizeof(T) == 2 && __is_same(Sum, Chain))) return TP_ANY(128, 4, 2, 3, 1);
+      if constexpr (sizeof(T) == 4) return TP_ANY(128, 4, 2, 2, 2);
+      else if constexpr (__is_same(Sum, Free)) return TP_ANY(128, 4, 2, 3, 1);
       [[fallthrough]];  // not among those tiles
     case Tile::k64: return TP_ANY(64, 4, 2, 2, 2);
     default:
@@ -938,6 +1029,9 @@ int ranges_of(int M, int N, int K) {
   pick_tile<T, Sum>(M, N, (K + kTileK<T> - 1) / kTileK<T>, true, &ranges);
   return ranges;
 }
+
+// whole k tiles of fp32 operands with rows of `ld` values, 128 rows of which (32 k values, each a row) lie within 2 GiB
+inline bool whole_tiles(int K, int ld) { return K % kTileK<float> == 0 && ld < (1 << 22); }
 
 }  // namespace
 
@@ -962,6 +1056,7 @@ hipError_t f32_fprop(hipStream_t s, int M, int N, int K, const float* x, const f
   const EpiForward<float> e{bias, d_out, a_out, act, N, N % 4 == 0 && aligned16(d_out, a_out)};
   if (aligned16(x, W) && wave_ok(M, N, K, K))
     return launch_wave<WaveRow, WaveRow>(s, M, N, K, x, K, W, K, e, side);
+  if (whole_tiles(K, K) && aligned16(x, W)) return run<float, Chain, FpropDenseWhole, 4>(s, M, N, K, a, b, e, false, side);
   if (K % 4 == 0 && aligned16(x, W)) return run<float, Chain, FpropDense, 4>(s, M, N, K, a, b, e, false, side);
   return run<float, Chain, FpropDense, 1>(s, M, N, K, a, b, e, false, side);
 }
@@ -973,6 +1068,7 @@ hipError_t f32_dgrad(hipStream_t s, int M, int N, int K, const float* dz, const 
   const EpiInputGrad<float> e{d_prev, out, K, relu_mask, K % 4 == 0 && aligned16(out)};
   if (K % 4 == 0 && aligned16(dz, Wb) && wave_ok(M, K, N, std::max(N, K)))
     return launch_wave<WaveRow, WaveCol>(s, M, K, N, dz, N, Wb, K, e);
+  if (whole_tiles(N, std::max(N, K)) && K % 4 == 0 && aligned16(dz, Wb)) return run<float, Chain, DgradDenseWhole, 4>(s, M, K, N, a, b, e);
   if (N % 4 == 0 && K % 4 == 0 && aligned16(dz, Wb)) return run<float, Chain, DgradDense, 4>(s, M, K, N, a, b, e);
   return run<float, Chain, DgradDense, 1>(s, M, K, N, a, b, e);
 }
@@ -986,9 +1082,10 @@ hipError_t f32_wgrad(hipStream_t s, int M, int N, int K, const float* dz, const 
   const DenseDesc a{dz, N, N, M}, b{x, K, K, M};
   float* out = splits > 1 ? partial : gW;
   const EpiPartial e{out, K, K % 4 == 0 && aligned16(out), (size_t)N * K};
-  const hipError_t err = N % 4 == 0 && K % 4 == 0 && aligned16(dz, x)
-                             ? run<float, Chain, WgradDense, 4>(s, N, K, M, a, b, e, split)
-                             : run<float, Chain, WgradDense, 1>(s, N, K, M, a, b, e, split);
+  const bool chunks = N % 4 == 0 && K % 4 == 0 && aligned16(dz, x);
+  const hipError_t err = chunks && whole_tiles(M, std::max(N, K)) ? run<float, Chain, WgradDenseWhole, 4>(s, N, K, M, a, b, e, split)
+                         : chunks                                ? run<float, Chain, WgradDense, 4>(s, N, K, M, a, b, e, split)
+                                                                 : run<float, Chain, WgradDense, 1>(s, N, K, M, a, b, e, split);
   if (err != hipSuccess || splits == 1) return err;
   return launch_sum_partials(s, (size_t)N * K, splits, partial, gW);
 }
