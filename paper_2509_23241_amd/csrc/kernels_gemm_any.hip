@@ -911,7 +911,7 @@ struct Tiles;
 template <>
 struct Tiles<float, Chain> {
   static constexpr TileCost cost[] = {
-      {Tile::k32, 32, 180, 300, 270, 480}, {Tile::k64, 64, 560, 1050, 850, 1300}, {Tile::k128, 128, 2090, 4150, 2450, 4900}};
+      {Tile::k32, 32, 180, 300, 270, 480}, {Tile::k64, 64, 560, 1050, 850, 1300}, {Tile::k128, 128, 2150, 4150, 2450, 4900}};
 };
 template <>
 struct Tiles<uint16_t, Chain> {
