@@ -151,7 +151,17 @@ __device__ __forceinline__ void sum_partials_block(float* sm /* [ZG][IL + 1] */,
   float s0 = 0.f, s1 = 0.f;
   if (i < count) {
     int z = zg;
-    for (; z + ZG < splits; z += 2 * ZG) {  // two independent chains
+    for (; z + 7 * ZG < splits; z += 8 * ZG) {  // two independent chains, eight loads in flight
+      float p[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) p[k] = partial[(size_t)(z + k * ZG) * stride + i];
+#pragma unroll
+      for (int k = 0; k < 8; k += 2) {
+        s0 += p[k];
+        s1 += p[k + 1];
+      }
+    }
+    for (; z + ZG < splits; z += 2 * ZG) {
       s0 += partial[(size_t)z * stride + i];
       s1 += partial[(size_t)(z + ZG) * stride + i];
     }
@@ -181,9 +191,14 @@ __device__ __forceinline__ void sum_partials_block_vec(size_t block, size_t coun
   const size_t i = (block * kThreads + threadIdx.x) * 4;
   if (i >= count) return;
   float4 t = *reinterpret_cast<const float4*>(partial + i);
-  for (int z = 1; z < splits; ++z) {
-    const float4 p = *reinterpret_cast<const float4*>(partial + (size_t)z * stride + i);
-    t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
+  for (int z0 = 1; z0 < splits; z0 += 4) {
+    float4 p[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (z0 + k < splits) p[k] = *reinterpret_cast<const float4*>(partial + (size_t)(z0 + k) * stride + i);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (z0 + k < splits) { t.x += p[k].x; t.y += p[k].y; t.z += p[k].z; t.w += p[k].w; }
   }
   *reinterpret_cast<float4*>(out + i) = t;
 }
