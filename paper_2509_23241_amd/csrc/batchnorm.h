@@ -23,7 +23,10 @@ bool batchnorm_fwd_add_supported(int elt, size_t rows, int C);
 // scratch: batchnorm_scratch_floats(rows, C, nseg) floats.
 hipError_t launch_batchnorm_bwd(hipStream_t s, int elt, size_t rows, int C, int nseg, const void* dy, const void* x, const float* stats,
                                 const float* gamma_s, const float* gamma_l, float alpha, float beta_c, void* dx, float* sums,
-                                float* scratch);
+                                float* scratch, float* dx_sums = nullptr);
+// dx_sums (x, dy and dx 16-byte aligned): partial column sums of the dx of all segments, batchnorm_dx_sum_rows(...) rows of C
+// floats; 0 rows: not formed for this shape
+int batchnorm_dx_sum_rows(int elt, size_t rows, int C, int nseg);
 size_t batchnorm_scratch_floats(size_t rows, int C, int nseg = 1);
 // The backward pass of all nseg micro-batches of a mini-batch in one launch (bf16, small layers): segment q =
 // rows [q*rows, (q+1)*rows) of dy, x, dx with its own statistics stats[q][2C]; sums[q][0..C) = sum dy * xhat and

@@ -102,4 +102,19 @@ __device__ __forceinline__ float act_derivative_fast(float z, int act) {
   return 1.f;
 }
 
+// Column sums of what the 256 threads of a block have added up, N neighbouring columns per thread, thread t those of unit
+// t % units (units divides 256): out[N * units], in a fixed order.  `sm` holds N * 256 floats.
+template <int N>
+__device__ __forceinline__ void block_column_sums(const float (&s)[N], int units, float* sm, float* out) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) sm[j * 256 + threadIdx.x] = s[j];
+  __syncthreads();
+  for (int o = threadIdx.x; o < N * units; o += 256) {
+    const float* at = sm + (o % N) * 256 + o / N;
+    float a = 0.f;
+    for (int k = 0; k < 256; k += units) a += at[k];
+    out[o] = a;
+  }
+}
+
 }  // namespace tp

@@ -216,7 +216,9 @@ DeferredNeed deferred_need(const tp_stage_desc& d, const LayerPlan& lp) {
   if (L.type == TP_LAYER_LAYERNORM) {
     need.norm = round_up(tp::layernorm_scratch_floats(rows * lp.tokens, L.in_features), 64);
   } else if (L.type == TP_LAYER_BATCHNORM) {
-    need.norm = round_up((uint64_t)d.n * 3 * L.in_features, 64);  // per micro-batch: two column sums + those of dx
+    // per micro-batch two column sums; those of dx, one row per micro-batch or as the streaming kernel leaves them
+    const uint64_t dx_rows = std::max(d.n, tp::batchnorm_dx_sum_rows(d.dtype, (uint64_t)d.mb * lp.tokens, L.in_features, d.n));
+    need.norm = round_up(((uint64_t)d.n * 2 + dx_rows) * L.in_features, 64);
   } else if (L.type == TP_LAYER_CONV2D) {
     const uint64_t px = rows * conv_out_px(L);
     need.bias = round_up(tp::colsum_scratch_floats((int)px, L.out_features), 64);
@@ -1330,23 +1332,29 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
         // of the streaming kernels
         float* sums = defer ? hold(need.norm) : st->partials() + bn_scratch;
         float* dx_sums = nullptr;
+        int dx_rows = 0;
         {
           ProfScope ps(st, TP_K_NORM);
+          // a dense or convolution layer without activation right in front: its bias gradient is the column sum of the dx
+          // formed here, which these kernels hold in registers anyway
+          bool bias_here = false;
+          if (defer && l > 0 && !dprev && !no_dx) {
+            const tp_layer_desc& pl = st->plan.layers[l - 1].d;
+            bias_here = (pl.type == TP_LAYER_DENSE || pl.type == TP_LAYER_CONV2D) && pl.out_features == C;
+          }
           if (tp::batchnorm_fused_bwd_supported(d.dtype, seg_rows, C)) {
-            // a dense or convolution layer without activation right in front: its bias gradient is the column sum
-            // of the dx formed here, which this kernel holds in registers anyway
-            if (defer && l > 0 && !dprev && !no_dx) {
-              const tp_layer_desc& pl = st->plan.layers[l - 1].d;
-              if ((pl.type == TP_LAYER_DENSE || pl.type == TP_LAYER_CONV2D) && pl.out_features == C)
-                dx_sums = sums + (size_t)d.n * 2 * C;
-            }
+            dx_rows = bias_here ? d.n : 0;
+            if (dx_rows) dx_sums = sums + (size_t)d.n * 2 * C;
             HIP_TRY(tp::launch_batchnorm_bwd_fused(st->stream, d.dtype, seg_rows, C, d.n, dz, aslot + lp.x_off,
                                                    (const float*)(aslot + lp.stat_off), gs, gl, (float)ca, (float)cb, dst, sums,
                                                    dx_sums));
           } else {
+            if (bias_here && (((uintptr_t)dz | (uintptr_t)dst | (uintptr_t)(aslot + lp.x_off)) & 15) == 0)
+              dx_rows = tp::batchnorm_dx_sum_rows(d.dtype, seg_rows, C, d.n);
+            if (dx_rows) dx_sums = sums + (size_t)d.n * 2 * C;
             HIP_TRY(tp::launch_batchnorm_bwd(st->stream, d.dtype, seg_rows, C, d.n, dz, aslot + lp.x_off,
                                              (const float*)(aslot + lp.stat_off), gs, gl, (float)ca, (float)cb, dst, sums,
-                                             st->partials()));
+                                             st->partials(), dx_sums));
           }
           SumsDeferred later(sink);
           if (lp.b_off == lp.w_off + (uint64_t)C) {  // scale and shift gradients lie side by side: one launch sums both
@@ -1356,7 +1364,7 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
             HIP_TRY(tp::launch_sum_partials_strided(st->stream, (size_t)C, d.n, sums + C, 2 * (size_t)C, g + lp.b_off));
           }
           if (dx_sums) {
-            HIP_TRY(tp::launch_sum_partials_strided(st->stream, (size_t)C, d.n, dx_sums, (size_t)C,
+            HIP_TRY(tp::launch_sum_partials_strided(st->stream, (size_t)C, dx_rows, dx_sums, (size_t)C,
                                                     g + st->plan.layers[l - 1].b_off));
             bias_summed = true;
           }

@@ -69,3 +69,38 @@ def test_row_lanes_are_added_by_pairs_in_fp32():
     st.close()
     off = _rel(gb, dy.reshape(rows, C).astype(np.float64).sum(0))
     assert off <= 1.25 * 0.39 * 2.0 ** -24 * np.sqrt(4 + (2 + 3 + 4) / 4), off
+
+
+@pytest.mark.parametrize("dtype,rows,C,n", [
+    ("bf16", 2049, 64, 1), ("bf16", 5001, 256, 3), ("bf16", 2500, 2048, 2),   # units of a row: 8, 32, all lanes of a workgroup
+    ("bf16", 70000, 8, 4), ("bf16", 2500, 2064, 1), ("bf16", 4000, 24, 2),    # one; more than lanes, three: a pass of their own
+    ("f32", 100, 16, 3), ("f32", 3001, 1024, 2), ("f32", 65, 6, 2),           # 4, all lanes; values one by one
+])
+def test_bias_gradient_in_front_of_a_normalisation(dtype, rows, C, n):
+    """The bias gradient of the dense layer in front is the column sum of the dx the normalisation stores; so is the
+    weight gradient at an input that is 1 everywhere.  Both are fp32 sums of the same rows * n values: an error of a sum of N
+    values of size r stays below N 2^-24 r, while a part left out would be missed by its values' size."""
+    import torch
+    from paper_2509_23241_amd.runner import GpuStage
+    rng = np.random.default_rng(rows + C)
+    W = rng.standard_normal((C, 8)).astype(np.float32)
+    st = GpuStage([(8, C, "none", rows), ("bn", C, rows, "none")],
+                  [W, np.zeros(C, np.float32), np.ones(C, np.float32), np.zeros(C, np.float32)], dtype=dtype, mb=1, n=n,
+                  stage_index=1, num_stages=2, policy="latest", lam=0.1, lr=0.0, momentum=0.0, ring_capacity=1, max_in_flight=1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    x = torch.randn(n, rows, 8, generator=g, device="cuda").to(st.tdtype)
+    x[..., 0] = 1
+    dy = torch.randn(n, rows, C, generator=g, device="cuda").to(st.tdtype)
+    for ub in range(n):
+        st.forward(0, ub, x[ub].reshape(1, -1))
+    st.backward(0, dy.reshape(n, -1))
+    gw, gb = st.unpack(st.grad.cpu().numpy())[:2]
+    st.close()
+    z = x.double() @ torch.from_numpy(W).cuda().double().T
+    d = dy.double()
+    rstd = 1 / torch.sqrt(z.var(1, unbiased=False, keepdim=True) + 1e-5)
+    zh = (z - z.mean(1, keepdim=True)) * rstd
+    dx = rstd * (d - d.mean(1, keepdim=True) - zh * (d * zh).mean(1, keepdim=True))
+    size = dx.pow(2).mean((0, 1)).sqrt().cpu().numpy()
+    assert np.all(np.abs(gb.astype(np.float64) - gw[:, 0]) <= 2 * rows * n * 2.0 ** -24 * size)
