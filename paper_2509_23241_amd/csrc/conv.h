@@ -22,7 +22,10 @@ hipError_t launch_conv_fprop(hipStream_t s, int elt, int imgs, int H, int W, int
 // relu_mask = 1: d_prev holds the previous layer's ReLU output and the factor is (output > 0).
 hipError_t launch_conv_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout,
                              const void* dz, const void* wb, const void* d_prev, void* out, const void* zeros,
-                             int relu_mask = 0);
+                             int relu_mask = 0, float* sums = nullptr, int* sum_rows = nullptr);
+// sums: room for conv_dgrad_sum_rows(elt, pixels) rows of cin floats.  *sum_rows receives how many rows of partial column sums
+// of `out` were left there (0: none).
+int conv_dgrad_sum_rows(int elt, int pixels);
 
 // gW[cout][ksize][ksize][cin] (fp32) = sum over pixels of dz (x) shifted x.
 // partial: scratch of conv_wgrad_scratch_floats(output pixels of the mini-batch, cin, cout, ksize) floats.
@@ -37,7 +40,10 @@ hipError_t launch_maxpool_fwd(hipStream_t s, int elt, int imgs, int H, int W, in
 // gradient also passes the activation in front of the pooling, dx (.)= d_prev (saved act'), or (relu_mask) the
 // factor (d_prev > 0) of a saved ReLU output -- with the bits of the two separate kernels.
 hipError_t launch_maxpool_bwd(hipStream_t s, int elt, int imgs, int H, int W, int C, const void* x, const void* dy,
-                              void* dx, const void* d_prev = nullptr, int relu_mask = 0);
+                              void* dx, const void* d_prev = nullptr, int relu_mask = 0, float* sums = nullptr,
+                              int* sum_rows = nullptr);
+// the same for the gradient max pooling hands on: at most maxpool_sum_rows() rows of C floats
+int maxpool_sum_rows();
 bool maxpool_bwd_fuses_activation(int elt, int C);
 
 // y[imgs x H/2 x W/2 x C] = x at the even pixel positions; backward: the gradient at those positions, zero elsewhere.
@@ -57,7 +63,8 @@ hipError_t conv_mfma_fprop(hipStream_t s, int imgs, int H, int W, int stride, in
                            const uint16_t* wgt, const float* bias, int act, uint16_t* d_out, uint16_t* a_out,
                            const uint16_t* zeros);
 hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, int cin, int cout, const uint16_t* dz,
-                           const uint16_t* wb, const uint16_t* d_prev, uint16_t* out, const uint16_t* zeros, int relu_mask = 0);
+                           const uint16_t* wb, const uint16_t* d_prev, uint16_t* out, const uint16_t* zeros, int relu_mask = 0,
+                           float* sums = nullptr, int* sum_rows = nullptr);
 hipError_t conv_mfma_wgrad(hipStream_t s, int imgs, int H, int W, int stride, int cin, int cout, const uint16_t* dz,
                            const uint16_t* x, float* gW, float* partial, const uint16_t* zeros);
 

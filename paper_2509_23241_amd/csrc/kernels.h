@@ -24,7 +24,10 @@ bool fprop_add_supported(int elt, int M, int N, int K);
 
 // out = (dz W_b) (.) d_prev   dz:[M x N] W_b:[N x K] d_prev:[M x K] saved act'(z), or null.
 hipError_t launch_dgrad(hipStream_t s, int elt, int M, int N, int K, const void* dz, const void* Wb,
-                        const void* d_prev, void* out, int relu_mask = 0);
+                        const void* d_prev, void* out, int relu_mask = 0, float* sums = nullptr, int* sum_rows = nullptr);
+// sums: room for dgrad_sum_rows(elt, M, K) rows of K floats.  *sum_rows receives how many rows of partial column sums of `out`
+// were left there (0: none); added up they are the bias gradient of the layer before.
+int dgrad_sum_rows(int elt, int M, int K);
 
 // gW = dz^T x  (fp32 [N x K]).
 // partial: scratch of wgrad_scratch_floats(elt, M, N, K) floats (may be null when that is 0)

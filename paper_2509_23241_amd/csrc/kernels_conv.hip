@@ -236,10 +236,14 @@ __global__ __launch_bounds__(kThreads) void maxpool_fwd_vec_kernel(int imgs, int
 
 // FUSE: the gradient also passes the activation in front of the pooling: dx = (gradient at the maximum) (.) d, with
 // d the saved act' tensor at the pooling input's positions, or (MASK) the factor (d > 0) of a saved ReLU output.
-template <bool FUSE, bool MASK>
+// SUMS (CV divides the workgroup, so that a thread stays on its channels): also the column sums of the dx a workgroup
+// stores, sums[workgroup][8 CV], the bias gradient of the convolution in front.
+template <bool FUSE, bool MASK, bool SUMS>
 __global__ __launch_bounds__(kThreads) void maxpool_bwd_vec_kernel(int imgs, int H, int W, int CV, const uint4* __restrict__ x,
                                                                    const uint4* __restrict__ dy, const uint4* d,
-                                                                   uint4* __restrict__ dx) {
+                                                                   uint4* __restrict__ dx, float* __restrict__ sums) {
+  __shared__ float sm[SUMS ? 8 * kThreads : 1];
+  float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const size_t total = (size_t)imgs * (H / 2) * (W / 2) * CV;
   for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += (size_t)gridDim.x * kThreads) {
     const int c = i % CV;
@@ -280,8 +284,17 @@ __global__ __launch_bounds__(kThreads) void maxpool_bwd_vec_kernel(int imgs, int
       }
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) dx[base + off[q]] = pack_bf16x8(o[q]);
+    for (int q = 0; q < 4; ++q) {
+      const uint4 p = pack_bf16x8(o[q]);
+      dx[base + off[q]] = p;
+      if constexpr (SUMS) {
+        unpack_bf16x8(p, o[q]);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s[j] += o[q][j];
+      }
+    }
   }
+  if constexpr (SUMS) block_column_sums<8>(s, CV, sm, sums + (size_t)blockIdx.x * 8 * CV);
 }
 
 // y[img][oh][ow][:] = x[img][2*oh][2*ow][:] in 16-byte units (CV per pixel); the backward pass writes the
@@ -396,13 +409,15 @@ hipError_t launch_conv_fprop(hipStream_t s, int elt, int imgs, int H, int W, int
 
 hipError_t launch_conv_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout,
                              const void* dz, const void* wb, const void* d_prev, void* out, const void* zeros,
-                             int relu_mask) {
+                             int relu_mask, float* sums, int* sum_rows) {
+  if (sums) *sum_rows = 0;
   if (!conv_geometry_supported(ksize, stride, (ksize - 1) / 2) || (stride == 2 && ((H | W) & 1))) return hipErrorInvalidValue;
   if (ksize == 3 && elt == 1 && zeros && conv_mfma_supported(imgs, H, W, stride, cin, cout))
     return conv_mfma_dgrad(s, imgs, H, W, stride, cin, cout, (const uint16_t*)dz, (const uint16_t*)wb,
-                           (const uint16_t*)d_prev, (uint16_t*)out, (const uint16_t*)zeros, relu_mask);
+                           (const uint16_t*)d_prev, (uint16_t*)out, (const uint16_t*)zeros, relu_mask, sums, sum_rows);
   if (conv_any_supported(elt, imgs, H, W, ksize, stride, cin, cout)) {
-    const hipError_t e = conv_any_dgrad(s, elt, imgs, H, W, ksize, stride, cin, cout, dz, wb, d_prev, out, relu_mask);
+    const hipError_t e = conv_any_dgrad(s, elt, imgs, H, W, ksize, stride, cin, cout, dz, wb, d_prev, out, relu_mask, sums);
+    if (sums && e == hipSuccess) *sum_rows = conv_dgrad_sum_rows(ELT_F32, imgs * H * W);
     if (e != hipErrorNotSupported) return e;
   }
   const ConvGeom g{imgs, H, W, cin, cout, stride, H / stride, W / stride, ksize, (ksize - 1) / 2};
@@ -416,6 +431,8 @@ hipError_t launch_conv_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int
                        (const float*)nullptr, 0, (const float*)d_prev, (float*)nullptr, (float*)out, (float*)nullptr, 0, relu_mask);
   return hipGetLastError();
 }
+
+int conv_dgrad_sum_rows(int, int pixels) { return (pixels + 15) / 16; }  // of the generic kernels; the patch kernels leave fewer
 
 hipError_t launch_conv_wgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout,
                              const void* dz, const void* x, float* gW, float* partial, const void* zeros) {
@@ -505,17 +522,29 @@ hipError_t launch_maxpool_fwd(hipStream_t s, int elt, int imgs, int H, int W, in
 
 bool maxpool_bwd_fuses_activation(int elt, int C) { return elt == 1 && C % 8 == 0; }
 
+constexpr int kPoolSumBlocks = 2048;
+int maxpool_sum_rows() { return kPoolSumBlocks; }
+
 hipError_t launch_maxpool_bwd(hipStream_t s, int elt, int imgs, int H, int W, int C, const void* x, const void* dy,
-                              void* dx, const void* d_prev, int relu_mask) {
+                              void* dx, const void* d_prev, int relu_mask, float* sums, int* sum_rows) {
+  if (sums) *sum_rows = 0;
   const size_t total = (size_t)imgs * (H / 2) * (W / 2) * C;
   if (pool_vec_ok(elt, C, x, dy, dx, d_prev)) {
-    const dim3 grid(stream_blocks(total / 8, 8192));
-#define TP_POOL_BWD(FUSE, MASK)                                                                                          \
-  hipLaunchKernelGGL((maxpool_bwd_vec_kernel<FUSE, MASK>), grid, dim3(kThreads), 0, s, imgs, H, W, C / 8, (const uint4*)x, \
-                     (const uint4*)dy, (const uint4*)d_prev, (uint4*)dx)
-    if (!d_prev) TP_POOL_BWD(false, false);
-    else if (relu_mask) TP_POOL_BWD(true, true);
-    else TP_POOL_BWD(true, false);
+    const bool with_sums = sums && kThreads % (C / 8) == 0;
+    const dim3 grid(stream_blocks(total / 8, with_sums ? kPoolSumBlocks : 8192));
+    if (with_sums) *sum_rows = (int)grid.x;
+#define TP_POOL_BWD(FUSE, MASK, SUMS)                                                                                          \
+  hipLaunchKernelGGL((maxpool_bwd_vec_kernel<FUSE, MASK, SUMS>), grid, dim3(kThreads), 0, s, imgs, H, W, C / 8, (const uint4*)x, \
+                     (const uint4*)dy, (const uint4*)d_prev, (uint4*)dx, sums)
+    if (with_sums) {
+      if (!d_prev) TP_POOL_BWD(false, false, true);
+      else if (relu_mask) TP_POOL_BWD(true, true, true);
+      else TP_POOL_BWD(true, false, true);
+    } else {
+      if (!d_prev) TP_POOL_BWD(false, false, false);
+      else if (relu_mask) TP_POOL_BWD(true, true, false);
+      else TP_POOL_BWD(true, false, false);
+    }
 #undef TP_POOL_BWD
     return hipGetLastError();
   }

@@ -290,7 +290,7 @@ struct EpiWgradConv {
 struct EpiDgradClass {
   EpiDgrad e;
   int H, W, lw2, lh2, ph, pw;  // input image, log2 of its half sizes
-  static constexpr bool kSwap = true;
+  static constexpr bool kSwap = true, kSums = false;
   __device__ __forceinline__ int pixel(int m) const {
     const int w2 = m & ((W >> 1) - 1), h2 = (m >> lw2) & ((H >> 1) - 1), img = m >> (lw2 + lh2);
     return (img * H + 2 * h2 + ph) * W + 2 * w2 + pw;
@@ -299,8 +299,8 @@ struct EpiDgradClass {
   __device__ __forceinline__ Cols cols(int n) const { return e.cols(n); }
   __device__ __forceinline__ bool has_rows() const { return e.has_rows(); }
   __device__ __forceinline__ uint4 row_in(int m, int n) const { return e.row_in(pixel(m), n); }
-  __device__ __forceinline__ void row8(int m, int n, float (&v)[8], const Cols& c, const uint4& u) const {
-    e.row8(pixel(m), n, v, c, u);
+  __device__ __forceinline__ uint4 row8(int m, int n, float (&v)[8], const Cols& c, const uint4& u) const {
+    return e.row8(pixel(m), n, v, c, u);
   }
   __device__ __forceinline__ void quad(int m, int n, int count, float v0, float v1, float v2, float v3) const {
     e.quad(pixel(m), n, count, v0, v1, v2, v3);
@@ -1265,8 +1265,10 @@ hipError_t conv_mfma_fprop(hipStream_t s, int imgs, int H, int W, int stride, in
 }
 
 hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, int cin, int cout, const uint16_t* dz,
-                           const uint16_t* wb, const uint16_t* d_prev, uint16_t* out, const uint16_t* zeros, int relu_mask) {
+                           const uint16_t* wb, const uint16_t* d_prev, uint16_t* out, const uint16_t* zeros, int relu_mask,
+                           float* sums, int* sum_rows) {
   const int P = imgs * H * W;
+  if (sums) *sum_rows = 0;
   // k tile -> (tap, block of 64 output channels): rows co0.. of W_b, columns tap*Cin..
   PlainDesc bd{wb, 9 * cin, cin, cout / DBK, (long)DBK * 9 * cin, cin};
   EpiDgrad e{d_prev, out, cin, relu_mask};
@@ -1284,7 +1286,10 @@ hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, in
   }
   {
     const PatchDesc pd{dz, zeros, H, W, ilog2(W), cout, 0, cout / 8, 0};
-    const hipError_t err = launch_patch_conv<true>(s, P, H, W, cout, cin, pd, bd, e);
+    EpiDgrad es = e;
+    es.sums = sums;  // pixel tiles and blocks of 64 channels are always whole here
+    const hipError_t err = launch_patch_conv<true>(s, P, H, W, cout, cin, pd, bd, es);
+    if (sums && err == hipSuccess) *sum_rows = P / 64;  // pixels of a wave tile, whatever the tile
     if (err != hipErrorNotSupported) return err;
   }
   GatherDesc ad{dz, zeros, P, H, W, ilog2(W), cout, H, W};

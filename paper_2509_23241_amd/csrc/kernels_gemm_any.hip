@@ -445,6 +445,7 @@ __device__ __forceinline__ void store4(T* p, const float (&v)[4]) {
 template <class T>
 struct EpiForward {
   static constexpr int kPartK = 0;
+  static constexpr bool kSums = false;
   const float* bias;
   T *d_out, *a_out;
   int act, ldc, vec;
@@ -485,6 +486,8 @@ struct EpiInputGrad {
   const T* d_prev;  // saved act'(z) of the layer before, with relu_mask its ReLU output, or null
   T* out;
   int ldc, relu_mask, vec;
+  float* sums = nullptr;  // column sums of what is stored, [every 16 rows][ldc], or null
+  static constexpr bool kSums = true;
   __device__ __forceinline__ floatx4 input(int m, int n, int count) const {
     const size_t i = (size_t)m * ldc + n;
     floatx4 d;
@@ -492,7 +495,8 @@ struct EpiInputGrad {
     for (int j = 0; j < 4; ++j) d[j] = d_prev ? to_float(d_prev[j < count ? i + j : i]) : 0.f;
     return d;
   }
-  __device__ __forceinline__ void finish(int m, int n, int count, const floatx4& v, const floatx4& d) const {
+  // returns what was stored, zeros in the columns outside
+  __device__ __forceinline__ floatx4 finish(int m, int n, int count, const floatx4& v, const floatx4& d) const {
     const size_t i = (size_t)m * ldc + n;
     float o[4];
 #pragma unroll
@@ -504,14 +508,30 @@ struct EpiInputGrad {
       for (int j = 0; j < 4; ++j)
         if (j < count) out[i + j] = from_float<T>(o[j]);
     }
+    floatx4 kept;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) kept[j] = j < count ? to_float(from_float<T>(o[j])) : 0.f;
+    return kept;
   }
-  __device__ __forceinline__ void quad(int m, int n, int count, const floatx4& v, int) const {
-    finish(m, n, count, v, input(m, n, count));
+  __device__ __forceinline__ floatx4 quad(int m, int n, int count, const floatx4& v, int) const {
+    return finish(m, n, count, v, input(m, n, count));
+  }
+  // the 16 rows m - m % 16 .. of columns n .. n+3: the lanes of a row of 16 have one each (rows outside: zeros)
+  __device__ __forceinline__ void store_sums(int m, int n, int M, int N, floatx4 v) const {
+#pragma unroll
+    for (int off = 1; off < 16; off *= 2)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] += __shfl_xor(v[j], off, 64);
+    if (m % 16 == 0 && m < M)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (n + j < N) sums[(size_t)(m / 16) * ldc + n + j] = v[j];
   }
 };
 // fp32 partial result of contraction range `split`
 struct EpiPartial {
   static constexpr int kPartK = 0;
+  static constexpr bool kSums = false;
   float* out;
   int ldc, vec;
   size_t split_stride;
@@ -688,7 +708,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_any_kernel(int M, int N, 
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int n = n0 + wn + 16 * j + 4 * (lane >> 4);
-      if (m < M && n < N) epi.quad(m, n, min(4, N - n), kPart > 0 ? parts[i][j] : acc[i][j], blockIdx.y);
+      if constexpr (Epi::kSums) {
+        floatx4 o = {0.f, 0.f, 0.f, 0.f};
+        if (m < M && n < N) o = epi.quad(m, n, min(4, N - n), acc[i][j], blockIdx.y);
+        if (epi.sums) epi.store_sums(m, n, M, N, o);
+      } else {
+        if (m < M && n < N) epi.quad(m, n, min(4, N - n), kPart > 0 ? parts[i][j] : acc[i][j], blockIdx.y);
+      }
     }
   }
 }
@@ -873,7 +899,13 @@ __global__ __launch_bounds__(64) void gemm_f32_wave_kernel(int M, int N, int KT,
   int t0 = -skip;
   for (; t0 + NS < KT; t0 += NS) all_stages(t0, std::false_type{});
   all_stages(t0, std::true_type{});
-  if (m < M && n < N) epi.finish(m, n, min(4, N - n), acc, input);
+  if constexpr (Epi::kSums) {
+    floatx4 o = {0.f, 0.f, 0.f, 0.f};
+    if (m < M && n < N) o = epi.finish(m, n, min(4, N - n), acc, input);
+    if (epi.sums) epi.store_sums(m, n, M, N, o);
+  } else {
+    if (m < M && n < N) epi.finish(m, n, min(4, N - n), acc, input);
+  }
 }
 
 template <class AL, class BL, class Epi>
@@ -1062,10 +1094,10 @@ hipError_t f32_fprop(hipStream_t s, int M, int N, int K, const float* x, const f
 }
 
 hipError_t f32_dgrad(hipStream_t s, int M, int N, int K, const float* dz, const float* Wb, const float* d_prev, float* out,
-                     int relu_mask) {
+                     int relu_mask, float* sums) {
   // out[M x K] = dz[M x N] . Wb[N x K]: contraction over N
   const DenseDesc a{dz, N, M, N}, b{Wb, K, K, N};
-  const EpiInputGrad<float> e{d_prev, out, K, relu_mask, K % 4 == 0 && aligned16(out)};
+  const EpiInputGrad<float> e{d_prev, out, K, relu_mask, K % 4 == 0 && aligned16(out), sums};
   if (K % 4 == 0 && aligned16(dz, Wb) && wave_ok(M, K, N, std::max(N, K)))
     return launch_wave<WaveRow, WaveCol>(s, M, K, N, dz, N, Wb, K, e);
   if (whole_tiles(N, std::max(N, K)) && K % 4 == 0 && aligned16(dz, Wb)) return run<float, Chain, DgradDenseWhole, 4>(s, M, K, N, a, b, e);
@@ -1115,16 +1147,16 @@ hipError_t conv_any_fprop(hipStream_t s, int elt, int imgs, int H, int W, int ks
 }
 
 hipError_t conv_any_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout, const void* dz,
-                          const void* wb, const void* d_prev, void* out, int relu_mask) {
+                          const void* wb, const void* d_prev, void* out, int relu_mask, float* sums) {
   const int taps = ksize * ksize, P = imgs * H * W, K = taps * cout;
   const GatherRowDesc a{dz, P, H, W, H / stride, W / stride, cout, K, stride, (ksize - 1) / 2, fast_div(cout, K + 64), fast_div(ksize, K + 64)};
   const WeightColDesc b{wb, cin, taps, cout, fast_div(cout, K + 64)};
   const bool vec = aligned16(dz, wb);
   if (elt == ELT_BF16) {
     if (!vec) return hipErrorNotSupported;
-    return run<uint16_t, Chain, DgradConv, 8>(s, P, cin, K, a, b, EpiInputGrad<uint16_t>{(const uint16_t*)d_prev, (uint16_t*)out, cin, relu_mask, aligned16(out)});
+    return run<uint16_t, Chain, DgradConv, 8>(s, P, cin, K, a, b, EpiInputGrad<uint16_t>{(const uint16_t*)d_prev, (uint16_t*)out, cin, relu_mask, aligned16(out), sums});
   }
-  const EpiInputGrad<float> e{(const float*)d_prev, (float*)out, cin, relu_mask, cin % 4 == 0 && aligned16(out)};
+  const EpiInputGrad<float> e{(const float*)d_prev, (float*)out, cin, relu_mask, cin % 4 == 0 && aligned16(out), sums};
   if (cin % 4 == 0 && cout % 4 == 0 && vec) return run<float, Chain, DgradConv, 4>(s, P, cin, K, a, b, e);
   return run<float, Chain, DgradConv, 1>(s, P, cin, K, a, b, e);
 }

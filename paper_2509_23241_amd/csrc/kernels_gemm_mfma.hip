@@ -521,9 +521,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
       // where the whole wave tiles do not fit the LDS together (256x256): one 32-row block of every wave at a time
       constexpr int TB = NW * wave_epilogue_bytes<TM, TN>() <= 160 * 1024 ? TM : 1;
       float* wave_lds = reinterpret_cast<float*>(lds_raw) + wave * (wave_epilogue_bytes<TB, TN>() / 4);
+      WaveSums<TM, TN, Epi> sums;
 #pragma unroll
       for (int i = 0; i < TM; i += TB)
-        store_blocks_coalesced<TB>(acc, i, epi, row_inputs, m0 + wm, n0 + wn, lane, wave_lds);
+        store_blocks_coalesced<TB>(acc, i, epi, row_inputs, sums, m0 + wm, n0 + wn, lane, wave_lds);
+      sums.store(epi, m0 + wm, n0 + wn, lane);
       return;
     }
   }
@@ -698,11 +700,23 @@ hipError_t mfma_fprop(hipStream_t s, int M, int N, int K, const uint16_t* x, con
   return run<false, false>(dma, s, M, N, K, x, K, W, K, EpiFprop{bias, d_out, a_out, act, N, nullptr, wide}, side);
 }
 
+int mfma_dgrad_sum_rows(int M, int K) {
+  const Tile tile = pick(M, K, false);
+  for (const TileCost& t : kTiles)
+    if (t.t == tile) return M % t.bm == 0 && K % t.bn == 0 ? M / (tile == T256x256 ? 128 : tile == T64x64 ? 32 : 64) : 0;  // rows of a wave tile
+  return 0;
+}
+
 hipError_t mfma_dgrad(hipStream_t s, int M, int N, int K, const uint16_t* dz, const uint16_t* Wb,
-                      const uint16_t* d_prev, uint16_t* out, int relu_mask) {
+                      const uint16_t* d_prev, uint16_t* out, int relu_mask, float* sums, int* sum_rows) {
   // out[M x K] = dz[M x N] . Wb[N x K]: GEMM (M, K, contraction N)
   const bool dma = dma_ok(M, K, N, N, K, false, true) && aligned(16, dz, Wb);
-  return run<false, true>(dma, s, M, K, N, dz, N, Wb, K, EpiDgrad{d_prev, out, K, relu_mask, store_width(d_prev, out)});
+  EpiDgrad e{d_prev, out, K, relu_mask, store_width(d_prev, out)};
+  if (sums) {
+    *sum_rows = dma && e.wide == 2 ? mfma_dgrad_sum_rows(M, K) : 0;
+    if (*sum_rows) e.sums = sums;
+  }
+  return run<false, true>(dma, s, M, K, N, dz, N, Wb, K, e);
 }
 
 size_t mfma_wgrad_scratch_floats(int M, int N, int K) {

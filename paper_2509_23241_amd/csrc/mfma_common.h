@@ -31,7 +31,7 @@ struct EpiFpropT {
   const float* bias; uint16_t* d_out; uint16_t* a_out; int act; int ldc;  // d_out: act'(z) for the backward, or null
   const uint16_t* addend = nullptr;
   int wide = 2;  // 2: the outputs are 16-byte aligned (row8 may be used), 1: 8-byte, 0: not even that
-  static constexpr bool kSwap = true;
+  static constexpr bool kSwap = true, kSums = false;
   // what row8 below reads, as its own steps so that a wave can have all of it in flight before it needs any: the values
   // of columns n..n+7, and the 16 bytes that belong to row m there
   struct Cols { float4 b0, b1; };
@@ -47,7 +47,7 @@ struct EpiFpropT {
     else return act_pair_fast(z, act);
   }
   // 8 consecutive columns n..n+7 of row m (n and ldc multiples of 8)
-  __device__ __forceinline__ void row8(int m, int n, float (&v)[8], const Cols& c, const uint4& u) const {
+  __device__ __forceinline__ uint4 row8(int m, int n, float (&v)[8], const Cols& c, const uint4& u) const {
     static_assert(!EXACT, "rows are stored whole by kernels that use act_pair_fast");
     const size_t i = (size_t)m * ldc + n;
     const float b[8] = {c.b0.x, c.b0.y, c.b0.z, c.b0.w, c.b1.x, c.b1.y, c.b1.z, c.b1.w};
@@ -69,8 +69,9 @@ struct EpiFpropT {
     if (d_out)
       *reinterpret_cast<uint4*>(d_out + i) =
           make_uint4(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]), pack_bf16x2(d[4], d[5]), pack_bf16x2(d[6], d[7]));
-    *reinterpret_cast<uint4*>(a_out + i) =
-        make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7]));
+    const uint4 o = make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7]));
+    *reinterpret_cast<uint4*>(a_out + i) = o;
+    return o;
   }
   __device__ __forceinline__ void quad(int m, int n, int count, float v0, float v1, float v2, float v3) const {
     const size_t i = (size_t)m * ldc + n;
@@ -97,7 +98,10 @@ struct EpiDgrad {
   const uint16_t* d_prev; uint16_t* out; int ldc;  // d_prev: saved act'(z) of the previous layer, or null
   int relu_mask = 0;  // 1: d_prev holds the previous layer's ReLU OUTPUT instead; its derivative is (output > 0)
   int wide = 2;       // alignment of d_prev and out, as above
-  static constexpr bool kSwap = true;
+  // column sums of what a wave stores, [rows of a wave tile][ldc], or null: the bias gradient of the layer before.  Only where
+  // every wave stores its rows whole.
+  float* sums = nullptr;
+  static constexpr bool kSwap = true, kSums = true;
   __device__ __forceinline__ float through(float v, float d) const { return relu_mask ? (d > 0.f ? v : 0.f) : v * d; }
   struct Cols {};
   __device__ __forceinline__ Cols cols(int) const { return Cols{}; }
@@ -106,7 +110,7 @@ struct EpiDgrad {
     return *reinterpret_cast<const uint4*>(d_prev + (size_t)m * ldc + n);
   }
   // 8 consecutive columns n..n+7 of row m (n and ldc multiples of 8)
-  __device__ __forceinline__ void row8(int m, int n, float (&v)[8], const Cols&, const uint4& d) const {
+  __device__ __forceinline__ uint4 row8(int m, int n, float (&v)[8], const Cols&, const uint4& d) const {
     const size_t i = (size_t)m * ldc + n;
     if (d_prev) {
       const uint32_t w[4] = {d.x, d.y, d.z, d.w};
@@ -116,8 +120,9 @@ struct EpiDgrad {
         v[2 * j + 1] = through(v[2 * j + 1], __uint_as_float(w[j] & 0xffff0000u));
       }
     }
-    *reinterpret_cast<uint4*>(out + i) =
-        make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+    const uint4 o = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+    *reinterpret_cast<uint4*>(out + i) = o;
+    return o;
   }
   __device__ __forceinline__ void quad(int m, int n, int count, float v0, float v1, float v2, float v3) const {
     const size_t i = (size_t)m * ldc + n;
@@ -210,11 +215,45 @@ struct RowInputs {
   }
 };
 
+// Column sums of the rows a wave stores, 8 columns per lane (rows rounded to bf16, as a pass over the stored tensor would read
+// them): a few additions per row here for a launch and a read of the whole tensor.
+template <int TM, int TN, class Epi, bool SUMS = Epi::kSums>
+struct WaveSums {
+  __device__ __forceinline__ void add(const Epi&, const uint4&) {}
+  __device__ __forceinline__ void store(const Epi&, int, int, int) {}
+};
+template <int TM, int TN, class Epi>
+struct WaveSums<TM, TN, Epi, true> {
+  float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  __device__ __forceinline__ void add(const Epi& epi, const uint4& o) {
+    if (!epi.sums) return;  // uniform
+    const uint32_t w[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      s[2 * j] += __uint_as_float(w[j] << 16);
+      s[2 * j + 1] += __uint_as_float(w[j] & 0xffff0000u);
+    }
+  }
+  __device__ __forceinline__ void store(const Epi& epi, int mbase, int nbase, int lane) {
+    if (!epi.sums) return;
+    constexpr int kLanesPerRow = 4 * TN;
+#pragma unroll
+    for (int off = kLanesPerRow; off < 64; off *= 2)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s[j] += __shfl_xor(s[j], off, 64);
+    if (lane < kLanesPerRow) {
+      float4* p = reinterpret_cast<float4*>(epi.sums + (size_t)(mbase / (32 * TM)) * epi.ldc + nbase + 8 * lane);
+      p[0] = make_float4(s[0], s[1], s[2], s[3]);
+      p[1] = make_float4(s[4], s[5], s[6], s[7]);
+    }
+  }
+};
+
 // the 32-row blocks i0 .. i0 + TB - 1 of the wave tile, turned through wave_epilogue_bytes<TB, TN>() of LDS
 template <int TB, int TM, int TN, class Epi>
 __device__ __forceinline__ void store_blocks_coalesced(const floatx16 (&acc)[TM][TN], int i0, const Epi& epi,
-                                                       const RowInputs<TM, TN, Epi>& in, int mbase, int nbase, int lane,
-                                                       float* wave_lds) {
+                                                       const RowInputs<TM, TN, Epi>& in, WaveSums<TM, TN, Epi>& sums, int mbase,
+                                                       int nbase, int lane, float* wave_lds) {
   using In = RowInputs<TM, TN, Epi>;
   constexpr int PITCH = 32 * TN + 4;
 #pragma unroll
@@ -238,7 +277,7 @@ __device__ __forceinline__ void store_blocks_coalesced(const floatx16 (&acc)[TM]
     const float* p = wave_lds + r * PITCH + c8;
     const float4 lo = *reinterpret_cast<const float4*>(p), hi = *reinterpret_cast<const float4*>(p + 4);
     float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-    epi.row8(mbase + 32 * i0 + r, nbase + c8, v, in.cols, in.rows[(32 * i0 + r0) / In::kRowsPerPass]);
+    sums.add(epi, epi.row8(mbase + 32 * i0 + r, nbase + c8, v, in.cols, in.rows[(32 * i0 + r0) / In::kRowsPerPass]));
   }
 }
 
@@ -247,7 +286,9 @@ __device__ __forceinline__ void store_tiles_coalesced(const floatx16 (&acc)[TM][
                                                       int lane, float* wave_lds) {
   RowInputs<TM, TN, Epi> in;
   in.load(epi, mbase, nbase, lane);
-  store_blocks_coalesced<TM>(acc, 0, epi, in, mbase, nbase, lane, wave_lds);
+  WaveSums<TM, TN, Epi> sums;
+  store_blocks_coalesced<TM>(acc, 0, epi, in, sums, mbase, nbase, lane, wave_lds);
+  sums.store(epi, mbase, nbase, lane);
 }
 
 // acc += A_frag . B_frag, or its transpose when the epilogue wants columns along the registers

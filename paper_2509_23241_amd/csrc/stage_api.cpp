@@ -34,6 +34,12 @@ int fail(int code, const char* fmt, ...) {
 
 inline uint64_t round_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 
+// Floats of partial sums one layer's backward pass keeps until the sums are formed (each rounded up to 64).
+struct DeferredNeed {
+  uint64_t bias = 0, weight = 0, norm = 0;
+  uint64_t total() const { return bias + weight + norm; }
+};
+
 struct LayerPlan {
   tp_layer_desc d;
   uint64_t in_elems, out_elems;  // values per sample in / out
@@ -46,6 +52,7 @@ struct LayerPlan {
   uint64_t stat_bytes = 0;         // batch norm: bytes behind stat_off (per micro-batch, not per sample)
   int tokens = 1;                  // positions per sample (rows of the layer's matrices per sample)
   int skip_layer = -1;             // residual add: index of the layer that remembered the skip activation
+  DeferredNeed need;
   bool relu_out = false;           // ReLU whose derivative is read off its saved OUTPUT (the next layer's input): no act' tensor
 };
 
@@ -201,12 +208,20 @@ int check_desc(const tp_stage_desc* d) {
   return TP_OK;
 }
 
-// Floats of partial sums one layer's backward pass keeps until the sums are formed (each rounded up to 64).
-struct DeferredNeed {
-  uint64_t bias = 0, weight = 0, norm = 0;
-  uint64_t total() const { return bias + weight + norm; }
-};
 constexpr uint64_t kMaxDeferredFloats = 1ull << 28;  // 1 GiB
+
+// Partial column sums of the [rows x features] gradient that reaches a dense or convolution layer: of a pass of their own, or
+// left by the kernel of the layer behind it that forms the gradient.
+uint64_t bias_partials(const tp_stage_desc& d, uint64_t rows, int features) {
+  uint64_t left = 0;
+  for (int l = 0; l < d.num_layers; ++l) {
+    const int type = d.layers[l].type;
+    if (type == TP_LAYER_DENSE) left = std::max<uint64_t>(left, tp::dgrad_sum_rows(d.dtype, (int)rows, features));
+    if (type == TP_LAYER_CONV2D) left = std::max<uint64_t>(left, tp::conv_dgrad_sum_rows(d.dtype, (int)rows));
+    if (type == TP_LAYER_MAXPOOL2) left = std::max<uint64_t>(left, tp::maxpool_sum_rows());
+  }
+  return std::max<uint64_t>(tp::colsum_scratch_floats((int)rows, features), left * features);
+}
 
 DeferredNeed deferred_need(const tp_stage_desc& d, const LayerPlan& lp) {
   DeferredNeed need;
@@ -221,11 +236,11 @@ DeferredNeed deferred_need(const tp_stage_desc& d, const LayerPlan& lp) {
     need.norm = round_up(((uint64_t)d.n * 2 + dx_rows) * L.in_features, 64);
   } else if (L.type == TP_LAYER_CONV2D) {
     const uint64_t px = rows * conv_out_px(L);
-    need.bias = round_up(tp::colsum_scratch_floats((int)px, L.out_features), 64);
+    need.bias = round_up(bias_partials(d, px, L.out_features), 64);
     need.weight = round_up(tp::conv_wgrad_scratch_floats((int)px, L.in_features, L.out_features, L.geom[2]), 64);
   } else if (L.type == TP_LAYER_DENSE) {
     const uint64_t r = rows * lp.tokens;
-    need.bias = round_up(tp::colsum_scratch_floats((int)r, L.out_features), 64);
+    need.bias = round_up(bias_partials(d, r, L.out_features), 64);
     need.weight = round_up(tp::wgrad_scratch_floats(d.dtype, (int)r, L.out_features, L.in_features), 64);
   }
   return need;
@@ -357,7 +372,7 @@ int make_plan(const tp_stage_desc* d, Plan* p) {
     // bias gradients: column sums over rows (dense) or over all pixels (conv)
     if (lp.d.type == TP_LAYER_LAYERNORM || lp.d.type == TP_LAYER_BATCHNORM) continue;
     const uint64_t r = lp.d.type == TP_LAYER_CONV2D ? rows * conv_out_px(lp.d) : rows * lp.tokens;
-    wg = std::max<uint64_t>(wg, tp::colsum_scratch_floats((int)r, lp.d.out_features));
+    wg = std::max<uint64_t>(wg, bias_partials(*d, r, lp.d.out_features));
     if (lp.d.type == TP_LAYER_DENSE)
       wg = std::max<uint64_t>(wg, tp::wgrad_scratch_floats(d->dtype, (int)r, lp.d.out_features, lp.d.in_features));
   }
@@ -365,7 +380,10 @@ int make_plan(const tp_stage_desc* d, Plan* p) {
   // Every sum of partials the backward pass needs (bias and split weight gradients, scale and shift gradients of the
   // normalisations) is put off to one launch at its end: each keeps partials of its own until then.
   uint64_t deferred = 0;
-  for (const LayerPlan& lp : p->layers) deferred += deferred_need(*d, lp).total();
+  for (LayerPlan& lp : p->layers) {
+    lp.need = deferred_need(*d, lp);
+    deferred += lp.need.total();
+  }
   p->deferred_floats = deferred <= kMaxDeferredFloats ? deferred : 0;  // beyond that: sums right away, shared partials
   tp_sizes& s = p->sizes;
   s.param_count = P;
@@ -1168,6 +1186,7 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
     };
     std::vector<tp::SumJob>* sink = defer ? &st->sum_jobs : nullptr;
     bool bias_summed = false;  // the bias gradient of the layer coming up has already been formed (or recorded)
+    float* bias_room = nullptr;  // where its partial column sums go, if that has been laid out already
     {
       const LayerPlan& last = st->plan.layers[L - 1];
       if (last.d.act == TP_ACT_NONE) {
@@ -1184,7 +1203,7 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
           const int grad_rows = last.d.type == TP_LAYER_CONV2D ? rows * (int)conv_out_px(last.d) : rows * last.tokens;
           SumsDeferred later(sink);
           HIP_TRY(tp::launch_act_backward_colsum(st->stream, d.dtype, grad_rows, last.d.out_features, dy_dev, dlast, buf, 0,
-                                                 g + last.b_off, hold(deferred_need(d, last).bias)));
+                                                 g + last.b_off, hold(last.need.bias)));
           bias_summed = true;
         } else {
           HIP_TRY(tp::launch_act_backward(st->stream, d.dtype, (size_t)rows * last.out_elems, dy_dev, dlast, buf));
@@ -1194,7 +1213,7 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
     }
     for (int l = L - 1; l >= 0; --l) {
       const LayerPlan& lp = st->plan.layers[l];
-      const DeferredNeed need = deferred_need(d, lp);
+      const DeferredNeed& need = lp.need;
       if (held_overflow) return fail(TP_ESTATE, "partial sums of the backward pass outgrew their plan");
       // where the gradient w.r.t. this layer's input goes, and what it is multiplied with on the way
       const bool to_caller = l == 0;
@@ -1216,6 +1235,25 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
         }
       }
       void* dst = to_caller && !no_dx ? dx_dev : scratch_for(dz);
+      // The kernel that forms the gradient of a dense or convolution layer in front also leaves its column sums where it can,
+      // and the layer's bias gradient needs no pass of its own: `bias_sums(C)` is where (null: C is not that layer's width),
+      // sum_bias() adds up what was left.
+      int bias_rows = 0;
+      auto bias_sums = [&](int C) -> float* {
+        if (l == 0 || no_dx) return nullptr;
+        const LayerPlan& prev = st->plan.layers[l - 1];
+        if ((prev.d.type != TP_LAYER_DENSE && prev.d.type != TP_LAYER_CONV2D) || prev.d.out_features != C) return nullptr;
+        bias_room = hold(prev.need.bias);
+        return bias_room;
+      };
+      auto sum_bias = [&]() -> int {
+        if (bias_rows == 0) return TP_OK;
+        const LayerPlan& prev = st->plan.layers[l - 1];
+        SumsDeferred later(sink);
+        HIP_TRY(tp::launch_sum_partials(st->stream, (size_t)prev.d.out_features, bias_rows, bias_room, g + prev.b_off));
+        bias_summed = true;
+        return TP_OK;
+      };
       auto through_activation = [&](void* grad) -> int {  // dz_prev = dx (.) act'(z_prev), in place
         if (!dprev) return TP_OK;
         ProfScope ps(st, TP_K_ACT_BWD);
@@ -1229,7 +1267,9 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
         {
           ProfScope ps(st, TP_K_POOL);
           HIP_TRY(tp::launch_maxpool_bwd(st->stream, d.dtype, rows, lp.d.geom[0], lp.d.geom[1], lp.d.in_features,
-                                         aslot + lp.x_off, dz, dst, fused ? dprev : nullptr, dmask));
+                                         aslot + lp.x_off, dz, dst, fused ? dprev : nullptr, dmask,
+                                         fused || !dprev ? bias_sums(lp.d.in_features) : nullptr, &bias_rows));
+          if (int rc = sum_bias()) return rc;
         }
         if (!fused)
           if (int rc = through_activation(dst)) return rc;
@@ -1388,13 +1428,14 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
         continue;
       }
       const int grad_rows = lp.d.type == TP_LAYER_CONV2D ? rows * (int)conv_out_px(lp.d) : rows * lp.tokens;
-      if (bias_summed) {
-        bias_summed = false;
-      } else {
+      if (!bias_summed) {
         ProfScope ps(st, TP_K_COLSUM);
         SumsDeferred later(sink);
-        HIP_TRY(tp::launch_colsum(st->stream, d.dtype, grad_rows, lp.d.out_features, dz, g + lp.b_off, hold(need.bias)));
+        HIP_TRY(tp::launch_colsum(st->stream, d.dtype, grad_rows, lp.d.out_features, dz, g + lp.b_off,
+                                  bias_room ? bias_room : hold(need.bias)));
       }
+      bias_summed = false;
+      bias_room = nullptr;
       {
         ProfScope ps(st, TP_K_WGRAD);
         SumsDeferred later(sink);
@@ -1420,11 +1461,12 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
         ProfScope ps(st, TP_K_DGRAD);
         if (lp.d.type == TP_LAYER_DENSE)
           HIP_TRY(tp::launch_dgrad(st->stream, d.dtype, grad_rows, lp.d.out_features, lp.d.in_features, dz, wb + lp.w_off * es,
-                                   dprev, dst, dmask));
+                                   dprev, dst, dmask, bias_sums(lp.d.in_features), &bias_rows));
         else
           HIP_TRY(tp::launch_conv_dgrad(st->stream, d.dtype, rows, lp.d.geom[0], lp.d.geom[1], lp.d.geom[2], lp.d.geom[3],
                                         lp.d.in_features, lp.d.out_features, dz, wb + lp.w_off * es, dprev, dst, st->zeros(),
-                                        dmask));
+                                        dmask, bias_sums(lp.d.in_features), &bias_rows));
+        if (int rc = sum_bias()) return rc;
       }
       dz = dst;
     }

@@ -1,0 +1,77 @@
+"""Bias gradients from the column sums that the kernel in front of a layer's backward pass leaves (input gradients of dense
+layers and convolutions, max pooling), and from a pass of their own where it leaves none.  A layer's bias gradient is the column
+sum of the gradient w.r.t. its pre-activations; so is its weight gradient at an input that is 1 everywhere.  Both are fp32
+sums of the same N values of size r, each off by less than N 2^-24 r; a part left out would be missed by its values' size."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(layers, params, dtype, mb, n, pick, terms):
+    """layers: two with parameters; the first one's input feature 0 is 1.  pick: its weight gradient there."""
+    import torch
+    from paper_2509_23241_amd.runner import GpuStage
+    st = GpuStage(layers, params, dtype=dtype, mb=mb, n=n, stage_index=1, num_stages=2, policy="latest", lam=0.1, lr=0.0,
+                  momentum=0.0, ring_capacity=1, max_in_flight=1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(mb)
+    features = layers[0][0] if not isinstance(layers[0][0], str) else layers[0][1]
+    x = torch.randn(mb * n, st.in_elems // features, features, generator=g, device="cuda").to(st.tdtype)
+    x[..., 0] = 1
+    dy = torch.randn(mb * n, st.out_elems, generator=g, device="cuda").to(st.tdtype)
+    x = x.view(mb * n, -1)
+    for ub in range(n):
+        st.forward(0, ub, x[ub * mb:(ub + 1) * mb])
+    st.backward(0, dy)
+    gw, gb = st.unpack(st.grad.cpu().numpy())[:2]
+    st.close()
+    assert np.linalg.norm(gb) > 0
+    # values of size r: a column sum of random signs is about r sqrt(N)
+    size = np.sqrt(np.mean(gb.astype(np.float64) ** 2) / terms)
+    assert np.all(np.abs(gb.astype(np.float64) - pick(gw)) <= 2 * terms * 2.0 ** -24 * size * 4)
+
+
+def _dense(dtype, rows, widths, act, tokens=1, n=1):
+    rng = np.random.default_rng(rows)
+    a, b, c = widths
+    W = [(rng.standard_normal(s) / np.sqrt(s[1])).astype(np.float32) for s in ((b, a), (c, b))]
+    params = [W[0], np.zeros(b, np.float32), W[1], np.zeros(c, np.float32)]
+    _check([(a, b, act, tokens), (b, c, "none", tokens)], params, dtype, rows // tokens // n, n, lambda gw: gw[:, 0], rows)
+
+
+@pytest.mark.parametrize("dtype,rows,widths,act", [
+    # bf16, whole tiles of the input gradient: 64 x 64, 128 x 64, 128 x 128, 256 x 128, 256 x 256
+    ("bf16", 64, (64, 128, 64), "relu"), ("bf16", 2048, (64, 1024, 128), "gelu"), ("bf16", 2048, (64, 2048, 128), "relu"),
+    ("bf16", 2048, (64, 4096, 128), "gelu"), ("bf16", 4096, (64, 4096, 72), "relu"),
+    # rows or columns beyond the tiles, a width that is no multiple of 8: a pass of their own
+    ("bf16", 100, (64, 128, 64), "relu"), ("bf16", 128, (64, 200, 64), "relu"), ("bf16", 128, (64, 130, 64), "none"),
+    # fp32: one wave per 16 x 16, tiles of 32, 64 and 128, word by word
+    ("f32", 16, (32, 32, 32), "relu"), ("f32", 50, (32, 36, 64), "gelu"), ("f32", 33, (8, 45, 7), "relu"),
+    ("f32", 1000, (8, 1028, 32), "relu"), ("f32", 2051, (8, 2045, 33), "gelu"), ("f32", 4096, (8, 2048, 32), "relu"),
+])
+def test_dense_in_front_of_dense(dtype, rows, widths, act):
+    _dense(dtype, rows, widths, act)
+
+
+def test_tokens_and_micro_batches():
+    _dense("bf16", 4 * 2 * 64, (64, 128, 64), "gelu", tokens=64, n=2)
+
+
+@pytest.mark.parametrize("dtype,imgs,size,channels,second", [
+    ("bf16", 32, 16, (64, 128, 64), "conv"), ("bf16", 64, 32, (64, 64, 64), "conv"),   # patches of 128 and 256 pixels
+    ("bf16", 16, 4, (64, 64, 64), "conv"), ("bf16", 4, 12, (8, 24, 16), "conv"),       # gathered: none left; any image size
+    ("f32", 3, 10, (4, 12, 8), "conv"), ("f32", 2, 7, (3, 5, 6), "conv"),
+    ("bf16", 8, 16, (64, 64, 64), "pool"), ("bf16", 3, 20, (64, 48, 64), "pool"),      # 8 units of a row; 6: a pass of its own
+    ("f32", 3, 8, (4, 8, 4), "pool"), ("bf16", 8, 16, (64, 64, 64), "stride"),
+])
+def test_convolution_in_front(dtype, imgs, size, channels, second):
+    rng = np.random.default_rng(imgs)
+    a, b, c = channels
+    W = [(rng.standard_normal(s) / np.sqrt(9 * s[3])).astype(np.float32) for s in ((b, 3, 3, a), (c, 3, 3, b))]
+    if second == "pool":
+        layers = [("conv", a, b, size, size, "relu"), ("pool", b, size, size), ("conv", b, c, size // 2, size // 2, "none")]
+    else:
+        layers = [("conv", a, b, size, size, "relu"), ("conv", b, c, size, size, "none", 2 if second == "stride" else 1, 3)]
+    params = [W[0], np.zeros(b, np.float32), W[1], np.zeros(c, np.float32)]
+    _check(layers, params, dtype, imgs, 1, lambda gw: gw[:, 1, 1, 0], imgs * size * size)
