@@ -1213,19 +1213,31 @@ bool conv_mfma_supported(int imgs, int H, int W, int stride, int cin, int cout) 
          P * std::max(cin, cout) * 2 < (1l << 31);
 }
 
+// Gathered weight gradients: 128 x 128 tiles over pixel ranges that give (about) every CU one of them, 64 x 64 tiles where these
+// would be fewer than 16 k tiles long.  The large tiles move half the bytes per product, the ranges cost partial
+// sums.  us with 64 x 64 and with 128 x 128 tiles: 8192 pixels of 256 -> 256 channels 38.7 and 30.6 (ranges of 32 k tiles),
+// 32768 of 128 -> 128 37.5 and 30.3 (32), 2048 of 512 -> 512 30.3 and 27.7 (32, one range), 4096 of 256 -> 256 23.6 and 22.3 (16), 512 of
+// 512 -> 512 12.6 and 11.3 (8, one range); 1024 of 256 -> 256 12.1 and 14.1 (4), 4096 of 128 -> 128 12.0 and 14.6 (4).
+// Ranges are never fewer than with 64 x 64 tiles.
+struct ConvWgradPlan { bool wide; int splits; };
+ConvWgradPlan conv_wgrad_plan(int pixels, int cin, int cout) {
+  const int kt = pixels / DBK;
+  auto ranges = [&](int most) {  // of equal length, at least 4 k tiles each
+    int s = std::max(1, most);
+    while (s > 1 && (kt % s != 0 || kt / s < 4)) --s;
+    return s;
+  };
+  if (cin % 128 == 0 && cout % 128 == 0) {
+    const int tiles = (cout / 128) * (cin / 128) * 9, s = ranges(256 / tiles);
+    if (tiles * s >= 128 && (s == 1 || kt / s >= 16)) return {true, s};
+  }
+  return {false, ranges(512 / (((cout + 63) / 64) * ((cin + 63) / 64) * 9))};
+}
+
 // most partial sums either matrix-core wgrad kernel may write for this layer
 int conv_mfma_wgrad_max_splits(int pixels, int cin, int cout) {
   const int c8 = cin <= 8 && cout % 64 == 0 ? std::max(1, std::min(pixels / 128, 512 / (cout / 64))) : 1;
-  return std::max({conv_mfma_wgrad_splits(pixels, cin, cout), wgrad_patch_splits(pixels / kWgradBM, cin, cout), c8});
-}
-
-// pixel ranges for wgrad: enough workgroups to fill the chip, at least 4 k tiles each
-int conv_mfma_wgrad_splits(int pixels, int cin, int cout) {
-  const int tiles = ((cout + 63) / 64) * ((cin + 63) / 64) * 9;
-  const int kt = pixels / 64;
-  int s = std::max(1, 512 / tiles);
-  while (s > 1 && (kt % s != 0 || kt / s < 4)) --s;
-  return s;
+  return std::max({conv_wgrad_plan(pixels, cin, cout).splits, wgrad_patch_splits(pixels / kWgradBM, cin, cout), c8});
 }
 
 // Gathered fprop / dgrad: the largest tile that still gives every CU a workgroup, else the smallest.
@@ -1301,13 +1313,13 @@ hipError_t conv_mfma_wgrad(hipStream_t s, int imgs, int H, int W, int stride, in
   const size_t count = (size_t)cout * 9 * cin;
   if (stride == 2) {  // contraction over the output pixels; x is gathered at 2*(oh, ow) + tap
     const int Ho = H / 2, Wo = W / 2, P = imgs * Ho * Wo;
-    const int splits = conv_mfma_wgrad_splits(P, cin, cout);
+    const auto [wide, splits] = conv_wgrad_plan(P, cin, cout);
     const int KT = P / DBK / splits;
     PlainDesc ad{dz, cout, cout, 1 << 30, (long)DBK * cout, 0};
     GatherDesc bd{x, zeros, P, Ho, Wo, ilog2(Wo), cin, H, W};
     EpiWgradConv e{splits > 1 ? partial : gW, cin, cout};
     hipError_t err;
-    if (cout % 128 == 0 && cin % 128 == 0 && (long)(cout / 128) * (cin / 128) * 9 * splits >= 256)
+    if (wide)
       err = launch_conv<128, 128, 3, Plain<128, 4, true>, ColGather<128, 4, 2>>(s, cout, cin, KT, 9, splits, ad, bd, e);
     else
       err = launch_conv<64, 64, 4, Plain<64, 4, true>, ColGather<64, 4, 2>>(s, cout, cin, KT, 9, splits, ad, bd, e);
@@ -1329,13 +1341,13 @@ hipError_t conv_mfma_wgrad(hipStream_t s, int imgs, int H, int W, int stride, in
     if (err != hipSuccess || splits == 1) return err;
     return launch_sum_partials(s, count, splits, partial, gW);
   }
-  const int splits = conv_mfma_wgrad_splits(P, cin, cout);
+  const auto [wide, splits] = conv_wgrad_plan(P, cin, cout);
   const int KT = P / DBK / splits;
   PlainDesc ad{dz, cout, cout, 1 << 30, (long)DBK * cout, 0};
   GatherDesc bd{x, zeros, P, H, W, ilog2(W), cin, H, W};
   EpiWgradConv e{splits > 1 ? partial : gW, cin, cout};
   hipError_t err;
-  if (cout % 128 == 0 && cin % 128 == 0 && (long)(cout / 128) * (cin / 128) * 9 * splits >= 256)
+  if (wide)
     err = launch_conv<128, 128, 3, Plain<128, 4, true>, ColGather<128, 4>>(s, cout, cin, KT, 9, splits, ad, bd, e);
   else
     err = launch_conv<64, 64, 4, Plain<64, 4, true>, ColGather<64, 4>>(s, cout, cin, KT, 9, splits, ad, bd, e);

@@ -111,3 +111,25 @@ def test_deep_dense_stack_more_sums_than_one_launch_takes_bf16():
     worst = _run_stage(specs, "deep_dense60", "bf16", mb=256, n=4, policy="convex", minibatches=2, depth=2, needs_dx=True,
                        mean_loss_dy=True, lr=0.01, params=params, storage_floor=True)
     print({k: v for k, v in worst.items() if "[" not in k})
+
+
+@pytest.mark.parametrize("imgs,size,cin,cout,stride", [
+    (256, 8, 128, 128, 1),      # 128 x 128 tiles, 16 ranges of 16 k tiles
+    (128, 8, 128, 128, 1),      # ranges would be 8 k tiles long: 64 x 64 tiles
+    (512, 2, 384, 384, 1),      # ranges have to be of equal length: two of 16 k tiles, not three
+    (64, 2, 512, 512, 1),       # one range of 4 k tiles fills the chip
+    (256, 16, 128, 128, 2), (256, 8, 256, 128, 2), (256, 4, 64, 128, 1),
+])
+def test_gathered_weight_gradients(imgs, size, cin, cout, stride):
+    from synth_inputs import round_bf16
+    from test_gpu_gemm_any import _conv_reference, _rel, _run, _stage, _sum_tol
+    rng = np.random.default_rng(imgs + cin)
+    cast = lambda t: round_bf16(t).astype(np.float32)
+    wgt, x, dy = [cast(rng.standard_normal(s)) for s in ((cout, 3, 3, cin), (imgs, size, size, cin),
+                                                         (imgs, size // stride, size // stride, cout))]
+    b = np.zeros(cout, np.float32)
+    _, _, (gw, gb) = _run(_stage(("conv", cin, cout, size, size, "none", stride, 3), [wgt, b], imgs, "bf16"),
+                          x.reshape(imgs, -1), dy.reshape(imgs, -1))
+    pixels = imgs * (size // stride) ** 2
+    assert _rel(gw, _conv_reference(x, wgt, b, dy, stride)[2]) <= _sum_tol(pixels)
+    assert _rel(gb, dy.astype(np.float64).sum((0, 1, 2))) <= _sum_tol(pixels)
