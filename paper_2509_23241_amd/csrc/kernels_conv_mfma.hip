@@ -493,6 +493,7 @@ struct PatchDesc {
   int c0;                 // first channel staged
   int CB;                 // 16-byte chunks staged per pixel (channels staged / 8)
   int tr;                 // 1: layout for transposed reads (pixels are the contraction index)
+  uint32_t by_cb, by_pc;  // ceil(2^32 / CB), ceil(2^32 / (W + 2))
 };
 
 // chunk c of patch pixel pp is stored in slot c ^ patch_swz(pp)
@@ -501,7 +502,9 @@ __device__ __forceinline__ int patch_swz(int pp, int CB, int tr) {
   return (CB & 15) ? ((pp >> 1) & 7) : (pp & 15);  // 128-byte pixels: 8 slots over same-parity pixels; wider: 16
 }
 
-// All waves of the workgroup copy the patch of the tile whose first pixel is p0 (a multiple of BM)
+// All waves of the workgroup copy the patch of the tile whose first pixel is p0 (a multiple of BM).  Divisions by the run-time
+// widths are multiplications by their inverses: as divisions they were most of what a wave did before its first product (forward
+// 3x3 of 64 images of 16 x 16, 128 channels, 14.9 -> 13.2 us).
 template <int BM, int NW>
 __device__ __forceinline__ void issue_patch(const PatchDesc& d, uint32_t lds_patch, int p0, int wave, int lane) {
   const int PC = d.W + 2, NPIX = (BM / d.W + 2) * PC;
@@ -510,10 +513,9 @@ __device__ __forceinline__ void issue_patch(const PatchDesc& d, uint32_t lds_pat
   const int px_bytes = d.CB * 16;
   const int instrs = (NPIX * px_bytes + 1023) / 1024;
   for (int i = wave; i < instrs; i += NW) {
-    const int off = i * 1024 + lane * 16;
-    const int pp = off / px_bytes, slot = (off - pp * px_bytes) >> 4;
+    const int at = i * 64 + lane, pp = __umulhi(at, d.by_cb), slot = at - pp * d.CB;  // exact: at * CB < 2^32
     const int chunk = slot ^ patch_swz(pp, d.CB, d.tr);
-    const int pr = pp / PC, pc = pp - pr * PC;
+    const int pr = __umulhi(pp, d.by_pc), pc = pp - pr * PC;
     const int h = h0 + pr - 1, w = pc - 1;
     const bool valid = pp < NPIX && (unsigned)h < (unsigned)d.H && (unsigned)w < (unsigned)d.W;
     const long src = (((long)img * d.H + h) * d.W + w) * d.C + d.c0 + chunk * 8;
@@ -649,7 +651,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_patch_kernel(int P, int N
 // wgrad: dW[co][tap][ci] = sum_p dz[p][co] * x[p shifted by tap][ci] for one block of 64 output and 64
 // input channels and all nine taps; the workgroup walks over pixel tiles split, split + splits, ...,
 // double buffered: the copies of the next tile fly while the current one is multiplied.
-template <int BM>
+// With one wave per SIMD (nine accumulators each) bound by what is issued beside the matrix instructions: three or four vector
+// instructions are free next to one, but an LDS address per tap (8) and two divisions per 1 KB of patch were several
+// times that.  W > 0, the image width (a multiple of the 16 pixels of a k step): patch rows begin at constants, so a lane has four LDS
+// addresses in all, and where its copies come from is worked out once.  256 images of 32 x 32, 64 channels, with the
+// sums of the partial results: 43.2 -> 30.5 us (34.5 with the divisions by multiplication but one source address at a time);
+// 64 of 64 x 64 45.6 -> 31.3.
+template <int BM, int W>
 __global__ __launch_bounds__(256) void conv_wgrad_patch_kernel(PatchDesc xd, const uint16_t* __restrict__ dz, int cout,
                                                                int px_tiles, int ci_blocks, float* __restrict__ out) {
   constexpr int NW = 4;
@@ -682,13 +690,45 @@ __global__ __launch_bounds__(256) void conv_wgrad_patch_kernel(PatchDesc xd, con
     const int k = flat >> 3, c = (flat & 7) ^ DZ::swz(k);
     dzoff[i] = (uint32_t)(((size_t)k * cout + cob * 64 + c * 8) * 2);
   }
+  // W > 0: where the lane's chunks of the patch come from, relative to the tile's first pixel, and their patch rows less one
+  // (1 << 20: outside every image)
+  constexpr int kPatchInstr = W > 0 ? ((BM / (W > 0 ? W : 1) + 2) * (W + 2) * 128 + 1023) / 1024 : 0, kPatchPerWave = (kPatchInstr + NW - 1) / NW;
+  int from[kPatchPerWave > 0 ? kPatchPerWave : 1], prow[kPatchPerWave > 0 ? kPatchPerWave : 1];
+  if constexpr (W > 0) {
+#pragma unroll
+    for (int i = 0; i < kPatchPerWave; ++i) {
+      const int flat = (wave + NW * i) * 64 + lane, pp = flat >> 3;
+      const int chunk = (flat & 7) ^ patch_swz(pp, 8, 1), pr = pp / (W + 2), pc = pp % (W + 2);
+      from[i] = ((pr - 1) * W + pc - 1) * cin + chunk * 8;
+      prow[i] = pr < BM / W + 2 && pc >= 1 && pc <= W ? pr - 1 : 1 << 20;
+    }
+  }
   auto issue_tile = [&](int tile, int buf) {
     const uint32_t dst = lds_base + buf * buf_bytes;
-    issue_patch<BM, NW>(xd, dst, tile * BM, wave, lane);
+    if constexpr (W > 0) {
+      const int row = tile * (BM / W), img = row / xd.H, h0 = row - img * xd.H;
+      const uint16_t* first = xd.base + (long)tile * BM * cin + xd.c0;
+#pragma unroll
+      for (int i = 0; i < kPatchPerWave; ++i)
+        if (kPatchInstr % NW == 0 || wave + NW * i < kPatchInstr)
+          dma16_addr(dst + (wave + NW * i) * 1024, (unsigned)(h0 + prow[i]) < (unsigned)xd.H ? first + from[i] : xd.zeros + (lane & 7) * 8);
+    } else {
+      issue_patch<BM, NW>(xd, dst, tile * BM, wave, lane);
+    }
     const uint16_t* src = dz + (size_t)tile * BM * cout;
 #pragma unroll
     for (int i = 0; i < kDzInstr; ++i) dma16(dst + pbytes + (wave + NW * i) * 1024, src, dzoff[i]);
   };
+
+  // W > 0: byte of the lane's pixel (and 16-byte slot) in a patch row that begins at patch pixel u = 0 .. 3 (mod 4): the swizzle of
+  // patch pixel p depends on p / 2 % 2 alone
+  int lane_at[4];
+  {
+    const int g = lane >> 4, s = lane & 15, col = rb_ci + 16 * (g & 1) + 4 * (s & 3), px = 8 * (g >> 1) + (s >> 2);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) lane_at[u] = px * 128 + ((col >> 3) ^ patch_swz(u + px, 8, 1)) * 16 + (col & 7) * 2;
+  }
+  typedef __attribute__((address_space(3))) shortx4* lds_ptr;
 
   if (split < px_tiles) issue_tile(split, 0);
   int buf = 0;
@@ -698,6 +738,34 @@ __global__ __launch_bounds__(256) void conv_wgrad_patch_kernel(PatchDesc xd, con
     if (tile + splits < px_tiles) issue_tile(tile + splits, buf ^ 1);
     const uint16_t* lp = lds_raw + buf * (buf_bytes / 2);
     const uint16_t* ldz = lp + pbytes / 2;
+    if constexpr (W > 0) {
+      const char* at[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) at[u] = reinterpret_cast<const char*>(lp) + lane_at[u];
+      constexpr int kAll = BM / 16 * 9, kAhead = 3;
+      bf16x8 fa[2], fb[kAhead + 1];
+      auto fetch = [&](int x) {  // the fragment of x of product x: tap x % 9 of k step x / 9
+        const int kk = x / 9, t = x % 9;
+        const int u = (kk * 16 / W + t / 3) * (W + 2) + kk * 16 % W + t % 3;
+        const char* p = at[u & 3] + u * 128;
+        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
+        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * 128));
+        fb[x % (kAhead + 1)] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      };
+      fa[0] = DZ::frag(ldz, rb_co, 0, lane);
+#pragma unroll
+      for (int x = 0; x < kAhead; ++x) fetch(x);
+#pragma unroll
+      for (int x = 0; x < kAll; ++x) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (x + kAhead < kAll) fetch(x + kAhead);
+        if (x % 9 == 4 && x / 9 + 1 < BM / 16) fa[(x / 9 + 1) & 1] = DZ::frag(ldz, rb_co, x / 9 + 1, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        acc[x % 9] = mma<false>(fa[(x / 9) & 1], fb[x % (kAhead + 1)], acc[x % 9]);
+      }
+      buf ^= 1;
+      continue;
+    }
     const int g = lane >> 4, s = lane & 15;
     const int col = rb_ci + 16 * (g & 1) + 4 * (s & 3);
 #pragma unroll 2
@@ -748,9 +816,10 @@ __device__ __forceinline__ int issue_patch_c8(const uint16_t* x8, const uint16_t
   const int img_px = H * W;
   const int img = p0 / img_px, h0 = (p0 - img * img_px) >> lw;
   const int instrs = ((NPIX + 1) * 16 + 1023) / 1024;
+  const uint32_t by_pc = 0xffffffffu / PC + 1;  // as in PatchDesc
   for (int i = wave; i < instrs; i += NW) {
     const int pp = i * 64 + lane;
-    const int pr = pp / PC, pc = pp - pr * PC;
+    const int pr = __umulhi(pp, by_pc), pc = pp - pr * PC;
     const int h = h0 + pr - 1, w = pc - 1;
     const bool valid = pp < NPIX && (unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W;
     const uint16_t* ptr = valid ? x8 + ((((long)img * H + h) * W + w) << 3) : zeros;
@@ -945,9 +1014,10 @@ __device__ __forceinline__ void issue_patch_c8s(const uint16_t* x8, const uint16
   const int PC = G::patch_cols(W), NPIX = G::patch_rows(BM, Wo) * PC;
   const int img = p0 / (Ho * Wo), orow0 = (p0 - img * Ho * Wo) >> lwo;
   const int instrs = G::patch_bytes(BM, W) / 1024;
+  const uint32_t by_pc = 0xffffffffu / PC + 1;  // as in PatchDesc
   for (int i = wave; i < instrs; i += NW) {
     const int pp = i * 64 + lane;
-    const int pr = pp / PC, pc = pp - pr * PC;
+    const int pr = __umulhi(pp, by_pc), pc = pp - pr * PC;
     const int h = S * orow0 - G::kPad + pr, w = pc - G::kPad;
     const bool valid = pp < NPIX && (unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W;
     const uint16_t* ptr = valid ? x8 + ((((long)img * H + h) * W + w) << 3) : zeros;
@@ -1145,6 +1215,11 @@ inline int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
 
 constexpr int kMaxLds = 160 * 1024;
 
+inline PatchDesc patch_desc(const uint16_t* base, const uint16_t* zeros, int H, int W, int C, int CB, int tr) {
+  auto inverse = [](int d) { return (uint32_t)(((1ull << 32) + d - 1) / d); };
+  return PatchDesc{base, zeros, H, W, ilog2(W), C, 0, CB, tr, inverse(CB), inverse(W + 2)};
+}
+
 inline bool patch_shape_ok(int H, int W, int BM) {
   return pow2(H) && pow2(W) && W >= 8 && BM % W == 0 && (H * W) % BM == 0;
 }
@@ -1204,6 +1279,17 @@ inline bool wgrad_patch_ok(int H, int W) { return patch_shape_ok(H, W, kWgradBM)
 inline int wgrad_patch_splits(long px_tiles, int cin, int cout) {
   const long blocks = std::max(1l, (long)(cin / 64) * (cout / 64));
   return (int)std::max(1l, std::min(px_tiles, 256 / blocks));
+}
+
+template <int W>
+hipError_t launch_wgrad_patch(hipStream_t s, const PatchDesc& xd, const uint16_t* dz, int cout, int px_tiles, int splits, float* out) {
+  auto kernel = conv_wgrad_patch_kernel<kWgradBM, W>;
+  static hipError_t attr =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kernel, dim3((xd.C / 64) * (cout / 64), splits), dim3(256), wgrad_patch_lds(xd.W), s, xd, dz, cout, px_tiles,
+                     xd.C / 64, out);
+  return hipGetLastError();
 }
 
 bool conv_mfma_supported(int imgs, int H, int W, int stride, int cin, int cout) {
@@ -1268,7 +1354,7 @@ hipError_t conv_mfma_fprop(hipStream_t s, int imgs, int H, int W, int stride, in
   }
   const int P = imgs * H * W;
   {
-    const PatchDesc pd{x, zeros, H, W, ilog2(W), cin, 0, cin / 8, 0};
+    const PatchDesc pd = patch_desc(x, zeros, H, W, cin, cin / 8, 0);
     const hipError_t err = launch_patch_conv<false>(s, P, H, W, cin, cout, pd, bd, e);
     if (err != hipErrorNotSupported) return err;
   }
@@ -1297,7 +1383,7 @@ hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, in
     return launch_conv<64, 64, 4, RowGatherS2<64, 4>, PlainS2<64, 4>>(s, Pc, cin, KT, 4, 1, ad, bd, e2);
   }
   {
-    const PatchDesc pd{dz, zeros, H, W, ilog2(W), cout, 0, cout / 8, 0};
+    const PatchDesc pd = patch_desc(dz, zeros, H, W, cout, cout / 8, 0);
     EpiDgrad es = e;
     es.sums = sums;  // pixel tiles and blocks of 64 channels are always whole here
     const hipError_t err = launch_patch_conv<true>(s, P, H, W, cout, cin, pd, bd, es);
@@ -1330,14 +1416,16 @@ hipError_t conv_mfma_wgrad(hipStream_t s, int imgs, int H, int W, int stride, in
   if (wgrad_patch_ok(H, W)) {
     const int px_tiles = P / kWgradBM;
     const int splits = wgrad_patch_splits(px_tiles, cin, cout);
-    const PatchDesc xd{x, zeros, H, W, ilog2(W), cin, 0, 8, 1};
-    auto kernel = conv_wgrad_patch_kernel<kWgradBM>;
-    static hipError_t attr =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(kernel, dim3((cin / 64) * (cout / 64), splits), dim3(256), wgrad_patch_lds(W), s, xd, dz, cout, px_tiles,
-                       cin / 64, splits > 1 ? partial : gW);
-    hipError_t err = hipGetLastError();
+    const PatchDesc xd = patch_desc(x, zeros, H, W, cin, 8, 1);
+    float* to = splits > 1 ? partial : gW;
+    hipError_t err;
+    switch (W) {
+      case 16: err = launch_wgrad_patch<16>(s, xd, dz, cout, px_tiles, splits, to); break;
+      case 32: err = launch_wgrad_patch<32>(s, xd, dz, cout, px_tiles, splits, to); break;
+      case 64: err = launch_wgrad_patch<64>(s, xd, dz, cout, px_tiles, splits, to); break;
+      case 128: err = launch_wgrad_patch<128>(s, xd, dz, cout, px_tiles, splits, to); break;
+      default: err = launch_wgrad_patch<0>(s, xd, dz, cout, px_tiles, splits, to);
+    }
     if (err != hipSuccess || splits == 1) return err;
     return launch_sum_partials(s, count, splits, partial, gW);
   }
