@@ -90,17 +90,19 @@ __global__ __launch_bounds__(kThreads) void colsum_partial_kernel(int M, int N, 
 
 // dz = dy (.) d (MASK: d is a ReLU output, the factor is (d > 0)) and, in the same pass, the partial column sums of
 // the dz it stores: the first two steps of a backward pass whose last layer has an activation, with the structure --
-// and therefore the sums -- of colsum_partial_kernel.  bf16, N % 8 == 0, 16-byte aligned pointers.
-template <bool MASK>
-__global__ __launch_bounds__(kThreads) void act_backward_colsum_kernel(int M, int N, ColsumShape cs, const uint16_t* __restrict__ dy,
-                                                                       const uint16_t* __restrict__ d, uint16_t* __restrict__ dz,
+// and therefore the sums -- of colsum_partial_kernel.  Rows of whole 16-byte units, 16-byte aligned pointers.  Two launches for
+// 512 x 1024 in fp32 took 2.9 and 4.2 us and the gap between them.
+template <typename T, bool MASK>
+__global__ __launch_bounds__(kThreads) void act_backward_colsum_kernel(int M, int N, ColsumShape cs, const T* __restrict__ dy,
+                                                                       const T* __restrict__ d, T* __restrict__ dz,
                                                                        float* __restrict__ partials) {
-  constexpr int V = 8;
+  constexpr int V = 16 / sizeof(T);
   __shared__ float sm[kThreads * V];
   const int lr = threadIdx.x % cs.lanes_per_row, rsub = threadIdx.x / cs.lanes_per_row;
   const int col = (blockIdx.x * cs.lanes_per_row + lr) * V;
   const int r0 = blockIdx.y * cs.chunk_rows;
   const int r1 = min(M, r0 + cs.chunk_rows);
+  auto through = [](float g, float dv) { return MASK ? (dv > 0.f ? g : 0.f) : g * dv; };
   float s[V];
 #pragma unroll
   for (int j = 0; j < V; ++j) s[j] = 0.f;
@@ -113,11 +115,16 @@ __global__ __launch_bounds__(kThreads) void act_backward_colsum_kernel(int M, in
       uint32_t ow[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float g0 = __uint_as_float(aw[j] << 16), g1 = __uint_as_float(aw[j] & 0xffff0000u);
-        const float d0 = __uint_as_float(bw[j] << 16), d1 = __uint_as_float(bw[j] & 0xffff0000u);
-        ow[j] = pack_bf16x2(MASK ? (d0 > 0.f ? g0 : 0.f) : g0 * d0, MASK ? (d1 > 0.f ? g1 : 0.f) : g1 * d1);
-        s[2 * j] += __uint_as_float(ow[j] << 16);          // what is stored, as the separate pass over dz would read it
-        s[2 * j + 1] += __uint_as_float(ow[j] & 0xffff0000u);
+        if constexpr (sizeof(T) == 2) {
+          ow[j] = pack_bf16x2(through(__uint_as_float(aw[j] << 16), __uint_as_float(bw[j] << 16)),
+                              through(__uint_as_float(aw[j] & 0xffff0000u), __uint_as_float(bw[j] & 0xffff0000u)));
+          s[(2 * j) % V] += __uint_as_float(ow[j] << 16);  // what is stored, as the separate pass over dz would read it
+          s[(2 * j + 1) % V] += __uint_as_float(ow[j] & 0xffff0000u);
+        } else {
+          const float o = through(__uint_as_float(aw[j]), __uint_as_float(bw[j]));
+          ow[j] = __float_as_uint(o);
+          s[j % V] += o;
+        }
       }
       *reinterpret_cast<uint4*>(dz + at) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
     }
@@ -344,20 +351,23 @@ hipError_t launch_colsum(hipStream_t s, int elt, int M, int N, const void* dz, f
   return launch_sum_partials(s, (size_t)N, cs.chunks, partials, gb);
 }
 
-bool act_backward_colsum_supported(int elt, int N) { return elt == ELT_BF16 && N % 8 == 0; }
+bool act_backward_colsum_supported(int elt, int N) { return N % (elt == ELT_BF16 ? 8 : 4) == 0; }
 
 hipError_t launch_act_backward_colsum(hipStream_t s, int elt, int M, int N, const void* dy, const void* d, void* dz,
                                       int relu_mask, float* gb, float* partials) {
   if (!act_backward_colsum_supported(elt, N) || ((((uintptr_t)dy | (uintptr_t)d | (uintptr_t)dz) & 15) != 0))
     return hipErrorNotSupported;
-  const ColsumShape cs = colsum_shape(M, N, 8);
+  const ColsumShape cs = colsum_shape(M, N, elt == ELT_BF16 ? 8 : 4);
   dim3 g1(cs.col_blocks, cs.chunks);
-  if (relu_mask)
-    hipLaunchKernelGGL(act_backward_colsum_kernel<true>, g1, dim3(kThreads), 0, s, M, N, cs, (const uint16_t*)dy,
-                       (const uint16_t*)d, (uint16_t*)dz, partials);
-  else
-    hipLaunchKernelGGL(act_backward_colsum_kernel<false>, g1, dim3(kThreads), 0, s, M, N, cs, (const uint16_t*)dy,
-                       (const uint16_t*)d, (uint16_t*)dz, partials);
+#define TP_ACT_COLSUM(T, MASK)                                                                                                  \
+  hipLaunchKernelGGL((act_backward_colsum_kernel<T, MASK>), g1, dim3(kThreads), 0, s, M, N, cs, (const T*)dy, (const T*)d, (T*)dz, \
+                     partials)
+  if (elt == ELT_BF16) {
+    if (relu_mask) TP_ACT_COLSUM(uint16_t, true); else TP_ACT_COLSUM(uint16_t, false);
+  } else {
+    if (relu_mask) TP_ACT_COLSUM(float, true); else TP_ACT_COLSUM(float, false);
+  }
+#undef TP_ACT_COLSUM
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   return launch_sum_partials(s, (size_t)N, cs.chunks, partials, gb);
