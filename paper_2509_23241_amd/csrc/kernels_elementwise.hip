@@ -277,6 +277,49 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const float* __restrict_
   if (threadIdx.x == 0) *out = (float)(sm[0] / (double)count);
 }
 
+// Both in one workgroup, for few rows of at most 16 classes: 16 lanes per row, one value each, the values of the two kernels above
+// bit for bit (their further lanes add nothing).  32, 128 and 256 rows of 10 classes 5.3, 5.2, 5.4 -> 2.6, 3.4, 4.6 us, and a launch
+// less for the host; 512 rows would take 7.1 for 5.3.
+constexpr int kSmallClasses = 16, kSmallRows = 256, kSmallThreads = 1024;
+template <typename T>
+__global__ __launch_bounds__(kSmallThreads) void softmax_ce_small_kernel(int rows, int classes, const T* __restrict__ logits,
+                                                                         const int32_t* __restrict__ labels, T* __restrict__ dlogits,
+                                                                         float* __restrict__ loss) {
+  __shared__ float row_loss[kSmallRows];
+  __shared__ double sm[kThreads];
+  const int c = threadIdx.x % kSmallClasses;
+  const float inv_rows = 1.0f / (float)rows;
+  for (int row = threadIdx.x / kSmallClasses; row < rows; row += kSmallThreads / kSmallClasses) {
+    const int label = labels[row];
+    const float z = c < classes ? to_float(logits[(size_t)row * classes + c]) : -INFINITY;
+    float mx = z;
+#pragma unroll
+    for (int off = kSmallClasses / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    float sum = c < classes ? expf(z - mx) : 0.f;
+#pragma unroll
+    for (int off = kSmallClasses / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    const float lse = logf(sum);
+    if (c == 0 && (unsigned)label >= (unsigned)classes) row_loss[row] = __builtin_nanf("");
+    if (c < classes) {
+      const float p = expf(z - mx - lse);
+      dlogits[(size_t)row * classes + c] = from_float<T>((p - (c == label ? 1.f : 0.f)) * inv_rows);
+      if (c == label) row_loss[row] = -(z - mx - lse);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kThreads) {
+    double s = 0.0;
+    for (int i = threadIdx.x; i < rows; i += kThreads) s += (double)row_loss[i];
+    sm[threadIdx.x] = s;
+  }
+  __syncthreads();
+  for (int w = kThreads / 2; w > 0; w >>= 1) {
+    if (threadIdx.x < w) sm[threadIdx.x] += sm[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *loss = (float)(sm[0] / (double)rows);
+}
+
 inline int stream_blocks(size_t work_items, int max_blocks) {
   size_t b = (work_items + kThreads - 1) / kThreads;
   if (b < 1) b = 1;
@@ -404,6 +447,15 @@ hipError_t launch_copy(hipStream_t s, const void* src, void* dst, size_t bytes) 
 
 hipError_t launch_softmax_ce(hipStream_t s, int elt, int rows, int classes, const void* logits, const int32_t* labels,
                              void* dlogits, float* row_loss, float* loss) {
+  if (classes <= kSmallClasses && rows <= kSmallRows) {
+    if (elt == ELT_BF16)
+      hipLaunchKernelGGL(softmax_ce_small_kernel<uint16_t>, dim3(1), dim3(kSmallThreads), 0, s, rows, classes,
+                         (const uint16_t*)logits, labels, (uint16_t*)dlogits, loss);
+    else
+      hipLaunchKernelGGL(softmax_ce_small_kernel<float>, dim3(1), dim3(kSmallThreads), 0, s, rows, classes, (const float*)logits,
+                         labels, (float*)dlogits, loss);
+    return hipGetLastError();
+  }
   const int blocks = (rows + 3) / 4;
   if (elt == ELT_BF16)
     hipLaunchKernelGGL(softmax_ce_kernel<uint16_t>, dim3(blocks), dim3(kThreads), 0, s, rows, classes,

@@ -55,3 +55,15 @@ def test_a_label_that_is_no_class_makes_the_loss_nan(classes, label):
     assert np.isnan(loss)
     want = logits.double().softmax(1)[2] / 6             # every class is another one
     assert float((dlogits[2] - want).norm()) <= 1e-5 * float(want.norm())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,classes", [(1, 16), (63, 10), (65, 2), (256, 16), (257, 16), (200, 17)])
+def test_few_rows_of_few_classes(dtype, rows, classes):
+    """One workgroup for all of them, up to 256 rows and 16 classes; a label that is no class makes the loss NaN there too."""
+    import torch
+    test_softmax_cross_entropy(dtype, rows, classes)
+    for bad in (-1, classes):
+        labels = np.zeros(rows, np.int64)
+        labels[rows // 2] = bad
+        assert np.isnan(_loss(dtype, rows, classes, torch.zeros(rows, classes), labels)[0])
