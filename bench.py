@@ -33,10 +33,10 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 #            profiles/bench_mlp4096_stage1_hbm_traffic.md
 #   rocprof_avg_us: average kernel duration from --kernel-trace --stats (no event brackets):
 #            profiles/bench_mlp4096_stage1_kernel_stats.md
-MEASURED_TRAFFIC_BYTES = {"fprop": 56.1e6, "dgrad": 159.5e6, "wgrad": 168.0e6, "update": 940.1e6,
-                          "act_bwd": 52.5e6, "colsum": 19.0e6}
-ROCPROF_AVG_US = {"fprop": 18.33, "dgrad": 62.18, "wgrad": 63.70, "update": 164.11, "act_bwd": 13.07}
-PROFILED_AT = "7435e91"
+MEASURED_TRAFFIC_BYTES = {"fprop": 56.1e6, "dgrad": 159.8e6, "wgrad": 168.0e6, "update": 940.1e6,
+                          "act_bwd": 52.5e6}
+ROCPROF_AVG_US = {"fprop": 19.07, "dgrad": 63.47, "wgrad": 65.26, "update": 164.16, "act_bwd": 13.20}
+PROFILED_AT = "c0a2161"
 
 
 def parse():
@@ -149,12 +149,8 @@ def kernel_work(cls, w, s, needs_dx):
             continue
         if cls == "colsum" and i == len(layers) - 1 and l.act != "none" and w.dtype == "bf16" and l.out_dim() % 8 == 0:
             continue   # the stage's last layer: its column sums come out of the kernel that forms dz = dy (.) act'(z)
-        if cls == "colsum" and i + 1 < len(layers) and layers[i + 1].kind == "bn" and l.act == "none":
-            # the bias gradient comes out of the normalisation's backward kernel (layers of up to 2048 rows per
-            # micro-batch, whole 16-byte units of channels): no pass over dz of its own
-            px = l.ho * l.wo if l.kind == "conv" else getattr(l, "tokens", 1)
-            if w.mb * px <= 2048 and (l.cout if l.kind == "conv" else l.out_features) % 8 == 0:
-                continue
+        if cls == "colsum" and i + 1 < len(layers) and layers[i + 1].kind in ("dense", "conv", "pool", "bn"):
+            continue   # the kernel of the layer behind it that forms dz leaves its column sums (at these workloads' shapes)
         f, b = layer_work(cls, l, rows, w.mb)
         mult = w.n if cls == "fprop" else 1
         flops += mult * f
