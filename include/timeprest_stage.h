@@ -239,10 +239,8 @@ int stage_forward_on(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, uint64_t ver
  * again).  The micro-batch forward passes of a mini-batch do not depend on one another (Section "Methodology": they
  * run one after another through the pipeline on the same weights), and the forward passes of a later mini-batch do
  * not depend on the backward pass of an earlier one, only on the update before it (Sections "V-TiMePReSt",
- * "I-TiMePReSt": a forward reads the latest version).  The stage leaves them alone where its forwards
- * are so short that ordering the streams takes longer than it saves; then every forward runs on the stage's own stream.
- * Else, with S such streams, stage_forward and stage_forward_on enqueue micro-batch ub on hip_streams[ub % S] and
- * nothing of a forward on the stage's own stream (a stage with
+ * "I-TiMePReSt": a forward reads the latest version).  With S such streams stage_forward and stage_forward_on enqueue
+ * micro-batch ub on hip_streams[ub % S] and nothing of a forward on the stage's own stream (a stage with
  * max_in_flight = 1, whose backward pass always needs the forwards just enqueued, lets its own stream take a turn:
  * ub % (S + 1) == 0 runs there, the others on hip_streams[ub % (S + 1) - 1]); the kernels and their results are the
  * same bits.  Ordering, kept with events of the library's own:

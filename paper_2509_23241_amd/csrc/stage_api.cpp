@@ -433,7 +433,7 @@ struct tp_stage {
   bool copy_valid = false;
   uint64_t copy_version = 0;
   // Optional second stream of the caller's: the forward passes of odd micro-batches run there, beside the even ones.
-  int fwd_streams = 0;                                    // how many of the caller's are in use
+  int fwd_streams = 0;                                    // how many the caller gave
   hipStream_t fwd_stream[TP_MAX_FORWARD_STREAMS] = {};
   hipEvent_t ev_main = nullptr;                           // "the stage's stream is ready for forwards"
   hipEvent_t ev_fwd[TP_MAX_FORWARD_STREAMS] = {};         // "this forward stream is done"
@@ -516,28 +516,6 @@ int join_forwards(tp_stage* st) {
     for (int q = 0; q < TP_MAX_IN_FLIGHT; ++q) st->slot_fwd[q][k] = false;  // ordered with everything else on the stream
   }
   return TP_OK;
-}
-
-// Whether forward streams pay.  Ordering one costs the host two waits for an event and a record per mini-batch, some 12 us, which
-// the GPU has to make up by forwards side by side; where they are so short that the host can hardly launch them as fast,
-// the stage's own stream is faster.  Taken as the time by which the dense products of a mini-batch exceed 5 us each, what a
-// launch and its call take on the host: 2.5 us and the longer of their contraction (5.2 ns per value in bf16, 4.6 in fp32,
-// at one workgroup per CU) and their operations.  Two layers, four micro-batches, us per step on the own stream alone, with two
-// and with three forward streams: interior stage in bf16, 64 rows, width 512 (0 us of that time): 83, 105, 110; 1024 (23): 99, 108,
-// 110; 2048 (65): 153, 134, 139; fp32, 128 rows, width 512: 88, 107, 112; 1024 (18): 153, 155, 155.  Last stage in bf16, width
-// 1024: 104, 115, 130; 100 rows, width 2000 (63): 190, 156, 166, with two micro-batches (32) 121, 124, 124; fp32, width 1024: 131,
-// 133, 162.  Stages with other layers are long chains of launches: the smallest ones timed, two convolutions twice on four 16 x 16
-// images and a bottleneck pair on 16 images of 2 x 2, took 299, 227, 235 and 398, 358, 360.
-static bool forward_streams_pay(const tp_stage_desc& d, const Plan& plan) {
-  double gain_us = 0.0;
-  for (const LayerPlan& lp : plan.layers) {
-    if (lp.d.type != TP_LAYER_DENSE) return true;
-    const bool bf16 = d.dtype == TP_BF16;
-    const double chain = lp.d.in_features * (bf16 ? 5.2e-3 : 4.6e-3);
-    const double flops = 2.0 * d.mb * lp.tokens * lp.d.in_features * lp.d.out_features;
-    gain_us += d.n * std::max(0.0, 2.5 + std::max(chain, flops / (bf16 ? 6e8 : 6e7)) - 5.0);
-  }
-  return gain_us >= 30.0;
 }
 
 extern "C" {
@@ -751,7 +729,7 @@ int stage_set_forward_streams(tp_stage* st, void* const* hip_streams, int32_t co
   }
   for (int k = 0; k < TP_MAX_FORWARD_STREAMS; ++k) st->fwd_stream[k] = k < count ? (hipStream_t)hip_streams[k] : nullptr;
   for (int k = 0; k < TP_MAX_FORWARD_STREAMS; ++k) st->fwd_tail[k] = nullptr;  // recorded on the streams before
-  st->fwd_streams = forward_streams_pay(st->desc, st->plan) ? count : 0;
+  st->fwd_streams = count;
   st->main_dirty = true;
   return TP_OK;
 }

@@ -173,6 +173,42 @@ def test_saved_inputs_of_odd_micro_batches_are_ordered_by_the_accessor():
     st.close()
 
 
+@pytest.mark.parametrize("dtype,depth", [("bf16", 3), ("f32", 3), ("bf16", 1)])
+def test_work_of_the_caller_on_a_forward_stream_is_ordered_with_the_forwards_there(dtype, depth):
+    """Micro-batch ub runs on forward stream ub % S, however short its kernels are (depth 1: the stage's own stream takes the
+    first turn of S + 1): what a caller enqueues there before a forward is done when the forward reads it, and
+    what it enqueues behind one sees the output."""
+    import torch
+    from paper_2509_23241_amd.runner import GpuStage
+    width, mb, n, S = 256, 64, 4, 2
+    layers = [(width, width, "relu"), (width, width, "relu")]
+    gen = torch.Generator().manual_seed(5)
+    params = [t.numpy() for _ in layers for t in (torch.randn(width, width, generator=gen) / 16, torch.randn(width, generator=gen))]
+    made = torch.randn(n, mb, width, generator=gen).cuda()
+    results = []
+    for streams in (0, S):
+        st = GpuStage(layers, params, dtype=dtype, mb=mb, n=n, stage_index=3 - depth, num_stages=3, policy="convex", lam=0.1, lr=0.01,
+                      momentum=0.9, needs_dx=True, forward_stream=streams)
+        src = made.to(st.tdtype)
+        x, y = torch.zeros_like(src), torch.zeros_like(src)
+        delay = [torch.rand(1 << 26, device="cuda") for _ in range(S + 1)]
+        torch.cuda.synchronize()
+        got = []
+        for ub in range(n):
+            turns = S + (depth == 1)
+            k = ub % turns - (turns - S) if streams else -1
+            with torch.cuda.stream(st.fwd_streams[k] if k >= 0 else st.stream):
+                for _ in range(8):
+                    delay[k].sin_()                 # milliseconds of work in front of the input
+                x[ub].copy_(src[ub])
+                st.forward(0, ub, x[ub], y[ub])
+                got.append(y[ub].clone())
+        torch.cuda.synchronize()
+        results.append(torch.stack(got).cpu())
+        st.close()
+    assert results[0].abs().max() > 0 and torch.equal(*results)
+
+
 def test_forward_stream_refusals():
     import torch
     from paper_2509_23241_amd import binding as B
