@@ -23,9 +23,9 @@ hipError_t launch_conv_fprop(hipStream_t s, int elt, int imgs, int H, int W, int
 hipError_t launch_conv_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout,
                              const void* dz, const void* wb, const void* d_prev, void* out, const void* zeros,
                              int relu_mask = 0, float* sums = nullptr, int* sum_rows = nullptr);
-// sums: room for conv_dgrad_sum_rows(elt, pixels) rows of cin floats.  *sum_rows receives how many rows of partial column sums
-// of `out` were left there (0: none).
-int conv_dgrad_sum_rows(int elt, int pixels);
+// sums: room for conv_dgrad_sum_rows(...) rows of cin floats.  *sum_rows receives how many rows of partial column sums of `out`
+// were left there (so many, or 0: tensors that are not 16-byte aligned, zeros missing).
+int conv_dgrad_sum_rows(int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout);
 
 // gW[cout][ksize][ksize][cin] (fp32) = sum over pixels of dz (x) shifted x.
 // partial: scratch of conv_wgrad_scratch_floats(output pixels of the mini-batch, cin, cout, ksize) floats.
@@ -42,8 +42,8 @@ hipError_t launch_maxpool_fwd(hipStream_t s, int elt, int imgs, int H, int W, in
 hipError_t launch_maxpool_bwd(hipStream_t s, int elt, int imgs, int H, int W, int C, const void* x, const void* dy,
                               void* dx, const void* d_prev = nullptr, int relu_mask = 0, float* sums = nullptr,
                               int* sum_rows = nullptr);
-// the same for the gradient max pooling hands on: at most maxpool_sum_rows() rows of C floats
-int maxpool_sum_rows();
+// the same for the gradient max pooling hands on
+int maxpool_sum_rows(int elt, int imgs, int H, int W, int C);
 bool maxpool_bwd_fuses_activation(int elt, int C);
 
 // y[imgs x H/2 x W/2 x C] = x at the even pixel positions; backward: the gradient at those positions, zero elsewhere.
@@ -64,6 +64,7 @@ hipError_t conv_mfma_fprop(hipStream_t s, int imgs, int H, int W, int stride, in
 hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, int cin, int cout, const uint16_t* dz,
                            const uint16_t* wb, const uint16_t* d_prev, uint16_t* out, const uint16_t* zeros, int relu_mask = 0,
                            float* sums = nullptr, int* sum_rows = nullptr);
+int conv_mfma_dgrad_sum_rows(int imgs, int H, int W, int stride, int cin, int cout);
 hipError_t conv_mfma_wgrad(hipStream_t s, int imgs, int H, int W, int stride, int cin, int cout, const uint16_t* dz,
                            const uint16_t* x, float* gW, float* partial, const uint16_t* zeros);
 

@@ -412,12 +412,14 @@ hipError_t launch_conv_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int
                              int relu_mask, float* sums, int* sum_rows) {
   if (sums) *sum_rows = 0;
   if (!conv_geometry_supported(ksize, stride, (ksize - 1) / 2) || (stride == 2 && ((H | W) & 1))) return hipErrorInvalidValue;
-  if (ksize == 3 && elt == 1 && zeros && conv_mfma_supported(imgs, H, W, stride, cin, cout))
+  const bool mfma = ksize == 3 && elt == 1 && conv_mfma_supported(imgs, H, W, stride, cin, cout);
+  if (mfma && zeros)
     return conv_mfma_dgrad(s, imgs, H, W, stride, cin, cout, (const uint16_t*)dz, (const uint16_t*)wb,
                            (const uint16_t*)d_prev, (uint16_t*)out, (const uint16_t*)zeros, relu_mask, sums, sum_rows);
   if (conv_any_supported(elt, imgs, H, W, ksize, stride, cin, cout)) {
+    if (mfma) sums = nullptr;  // the room is for the rows of the matrix-core kernel
     const hipError_t e = conv_any_dgrad(s, elt, imgs, H, W, ksize, stride, cin, cout, dz, wb, d_prev, out, relu_mask, sums);
-    if (sums && e == hipSuccess) *sum_rows = conv_dgrad_sum_rows(ELT_F32, imgs * H * W);
+    if (sums && e == hipSuccess) *sum_rows = conv_dgrad_sum_rows(elt, imgs, H, W, ksize, stride, cin, cout);
     if (e != hipErrorNotSupported) return e;
   }
   const ConvGeom g{imgs, H, W, cin, cout, stride, H / stride, W / stride, ksize, (ksize - 1) / 2};
@@ -432,7 +434,11 @@ hipError_t launch_conv_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int
   return hipGetLastError();
 }
 
-int conv_dgrad_sum_rows(int, int pixels) { return (pixels + 15) / 16; }  // of the generic kernels; the patch kernels leave fewer
+int conv_dgrad_sum_rows(int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout) {
+  if (ksize == 3 && elt == 1 && conv_mfma_supported(imgs, H, W, stride, cin, cout))
+    return conv_mfma_dgrad_sum_rows(imgs, H, W, stride, cin, cout);
+  return conv_any_supported(elt, imgs, H, W, ksize, stride, cin, cout) ? (imgs * H * W + 15) / 16 : 0;
+}
 
 hipError_t launch_conv_wgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout,
                              const void* dz, const void* x, float* gW, float* partial, const void* zeros) {
@@ -523,16 +529,20 @@ hipError_t launch_maxpool_fwd(hipStream_t s, int elt, int imgs, int H, int W, in
 bool maxpool_bwd_fuses_activation(int elt, int C) { return elt == 1 && C % 8 == 0; }
 
 constexpr int kPoolSumBlocks = 2048;
-int maxpool_sum_rows() { return kPoolSumBlocks; }
+int maxpool_sum_rows(int elt, int imgs, int H, int W, int C) {
+  if (elt != 1 || C % 8 != 0 || kThreads % (C / 8) != 0) return 0;
+  return stream_blocks((size_t)imgs * (H / 2) * (W / 2) * C / 8, kPoolSumBlocks);
+}
 
 hipError_t launch_maxpool_bwd(hipStream_t s, int elt, int imgs, int H, int W, int C, const void* x, const void* dy,
                               void* dx, const void* d_prev, int relu_mask, float* sums, int* sum_rows) {
   if (sums) *sum_rows = 0;
   const size_t total = (size_t)imgs * (H / 2) * (W / 2) * C;
   if (pool_vec_ok(elt, C, x, dy, dx, d_prev)) {
-    const bool with_sums = sums && kThreads % (C / 8) == 0;
-    const dim3 grid(stream_blocks(total / 8, with_sums ? kPoolSumBlocks : 8192));
-    if (with_sums) *sum_rows = (int)grid.x;
+    const int rows = sums ? maxpool_sum_rows(elt, imgs, H, W, C) : 0;
+    const bool with_sums = rows > 0;
+    const dim3 grid(with_sums ? rows : stream_blocks(total / 8, 8192));
+    if (with_sums) *sum_rows = rows;
 #define TP_POOL_BWD(FUSE, MASK, SUMS)                                                                                          \
   hipLaunchKernelGGL((maxpool_bwd_vec_kernel<FUSE, MASK, SUMS>), grid, dim3(kThreads), 0, s, imgs, H, W, C / 8, (const uint4*)x, \
                      (const uint4*)dy, (const uint4*)d_prev, (uint4*)dx, sums)

@@ -1246,15 +1246,24 @@ struct PatchCfg {
   }
 };
 
-// The largest tile that still gives every CU a workgroup; failing that, the one with the most
-// workgroups.  Returns hipErrorNotSupported when no patch tile fits the shape.
+// The tiles; all of them give a wave 64 pixels.
 template <bool BWD, class Epi>
-hipError_t launch_patch_conv(hipStream_t s, int P, int H, int W, int C, int N, const PatchDesc& pd, const PlainDesc& bd,
-                             const Epi& e) {
+struct PatchTiles {
   using A = PatchCfg<256, 128, 4, 2, 3, BWD, Epi>;
   using B = PatchCfg<256, 64, 4, 2, 3, BWD, Epi>;
   using Cc = PatchCfg<128, 128, 2, 2, 3, BWD, Epi>;
   using D = PatchCfg<128, 64, 2, 2, 4, BWD, Epi>;
+};
+
+// The largest tile that still gives every CU a workgroup; failing that, the one with the most
+// workgroups.  Negative when no patch tile fits the shape.
+template <bool BWD, class Epi>
+int pick_patch_tile(int P, int H, int W, int C, int N) {
+  using T = PatchTiles<BWD, Epi>;
+  using A = typename T::A;
+  using B = typename T::B;
+  using Cc = typename T::Cc;
+  using D = typename T::D;
   const bool wide = N % 128 == 0;
   const bool ok[4] = {wide && A::ok(H, W, C), B::ok(H, W, C), wide && Cc::ok(H, W, C), D::ok(H, W, C)};
   const long tiles[4] = {A::tiles(P, N), B::tiles(P, N), Cc::tiles(P, N), D::tiles(P, N)};
@@ -1264,11 +1273,18 @@ hipError_t launch_patch_conv(hipStream_t s, int P, int H, int W, int C, int N, c
   if (pick < 0)
     for (int i = 0; i < 4; ++i)
       if (ok[i] && (pick < 0 || tiles[i] > tiles[pick])) pick = i;
-  switch (pick) {
-    case 0: return A::launch(s, P, N, pd, bd, e);
-    case 1: return B::launch(s, P, N, pd, bd, e);
-    case 2: return Cc::launch(s, P, N, pd, bd, e);
-    case 3: return D::launch(s, P, N, pd, bd, e);
+  return pick;
+}
+
+template <bool BWD, class Epi>
+hipError_t launch_patch_conv(hipStream_t s, int P, int H, int W, int C, int N, const PatchDesc& pd, const PlainDesc& bd,
+                             const Epi& e) {
+  using T = PatchTiles<BWD, Epi>;
+  switch (pick_patch_tile<BWD, Epi>(P, H, W, C, N)) {
+    case 0: return T::A::launch(s, P, N, pd, bd, e);
+    case 1: return T::B::launch(s, P, N, pd, bd, e);
+    case 2: return T::Cc::launch(s, P, N, pd, bd, e);
+    case 3: return T::D::launch(s, P, N, pd, bd, e);
     default: return hipErrorNotSupported;
   }
 }
@@ -1362,6 +1378,11 @@ hipError_t conv_mfma_fprop(hipStream_t s, int imgs, int H, int W, int stride, in
   return launch_gather_rows<false, 1>(s, P, cout, KT, ad, bd, e);
 }
 
+int conv_mfma_dgrad_sum_rows(int imgs, int H, int W, int stride, int cin, int cout) {
+  const int P = imgs * H * W;
+  return stride == 1 && pick_patch_tile<true, EpiDgrad>(P, H, W, cout, cin) >= 0 ? P / 64 : 0;  // a row per wave tile
+}
+
 hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, int cin, int cout, const uint16_t* dz,
                            const uint16_t* wb, const uint16_t* d_prev, uint16_t* out, const uint16_t* zeros, int relu_mask,
                            float* sums, int* sum_rows) {
@@ -1387,7 +1408,7 @@ hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, in
     EpiDgrad es = e;
     es.sums = sums;  // pixel tiles and blocks of 64 channels are always whole here
     const hipError_t err = launch_patch_conv<true>(s, P, H, W, cout, cin, pd, bd, es);
-    if (sums && err == hipSuccess) *sum_rows = P / 64;  // pixels of a wave tile, whatever the tile
+    if (sums && err == hipSuccess) *sum_rows = conv_mfma_dgrad_sum_rows(imgs, H, W, stride, cin, cout);
     if (err != hipErrorNotSupported) return err;
   }
   GatherDesc ad{dz, zeros, P, H, W, ilog2(W), cout, H, W};

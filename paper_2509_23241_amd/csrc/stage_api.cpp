@@ -37,6 +37,7 @@ inline uint64_t round_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 // Floats of partial sums one layer's backward pass keeps until the sums are formed (each rounded up to 64).
 struct DeferredNeed {
   uint64_t bias = 0, weight = 0, norm = 0;
+  uint64_t own = 0;  // of total(), what passes of their own over the gradients would need
   uint64_t total() const { return bias + weight + norm; }
 };
 
@@ -210,39 +211,59 @@ int check_desc(const tp_stage_desc* d) {
 
 constexpr uint64_t kMaxDeferredFloats = 1ull << 28;  // 1 GiB
 
-// Partial column sums of the [rows x features] gradient that reaches a dense or convolution layer: of a pass of their own, or
-// left by the kernel of the layer behind it that forms the gradient.
-uint64_t bias_partials(const tp_stage_desc& d, uint64_t rows, int features) {
-  uint64_t left = 0;
-  for (int l = 0; l < d.num_layers; ++l) {
-    const int type = d.layers[l].type;
-    if (type == TP_LAYER_DENSE) left = std::max<uint64_t>(left, tp::dgrad_sum_rows(d.dtype, (int)rows, features));
-    if (type == TP_LAYER_CONV2D) left = std::max<uint64_t>(left, tp::conv_dgrad_sum_rows(d.dtype, (int)rows));
-    if (type == TP_LAYER_MAXPOOL2) left = std::max<uint64_t>(left, tp::maxpool_sum_rows());
-  }
-  return std::max<uint64_t>(tp::colsum_scratch_floats((int)rows, features), left * features);
+// Whether the gradient that layer l + 1 hands on is that of layer l's outputs, column by column, l having a bias for each.
+bool bias_in_front(const tp_stage_desc& d, int l) {
+  const int type = d.layers[l].type;
+  return (type == TP_LAYER_DENSE || type == TP_LAYER_CONV2D) && d.layers[l].out_features == d.layers[l + 1].in_features;
 }
 
-DeferredNeed deferred_need(const tp_stage_desc& d, const LayerPlan& lp) {
+// Rows of partial column sums of that gradient which layer l + 1 leaves where it forms it; 0: none.  Normalisations, whose room
+// is their own, are not counted.
+uint64_t sum_rows_left(const tp_stage_desc& d, int l) {
+  if (l + 1 >= d.num_layers || !bias_in_front(d, l)) return 0;
+  const tp_layer_desc& B = d.layers[l + 1];
+  const int samples = d.mb * d.n;
+  switch (B.type) {
+    case TP_LAYER_DENSE: return tp::dgrad_sum_rows(d.dtype, samples * std::max(1, B.geom[0]), B.in_features);
+    case TP_LAYER_CONV2D:
+      return tp::conv_dgrad_sum_rows(d.dtype, samples, B.geom[0], B.geom[1], B.geom[2], B.geom[3], B.in_features, B.out_features);
+    case TP_LAYER_MAXPOOL2: return tp::maxpool_sum_rows(d.dtype, samples, B.geom[0], B.geom[1], B.in_features);
+    default: return 0;
+  }
+}
+
+// Partial column sums of the [rows x features] gradient that reaches dense or convolution layer l: of a pass of their own, or
+// left by the layer behind it.
+uint64_t bias_partials(const tp_stage_desc& d, int l, uint64_t rows) {
+  const int features = d.layers[l].out_features;
+  return std::max<uint64_t>(tp::colsum_scratch_floats((int)rows, features), sum_rows_left(d, l) * features);
+}
+
+DeferredNeed deferred_need(const tp_stage_desc& d, int l, const LayerPlan& lp) {
   DeferredNeed need;
   if (!lp.w_elems) return need;
   const uint64_t rows = (uint64_t)d.mb * d.n;
   const tp_layer_desc& L = lp.d;
+  uint64_t extra = 0;
   if (L.type == TP_LAYER_LAYERNORM) {
     need.norm = round_up(tp::layernorm_scratch_floats(rows * lp.tokens, L.in_features), 64);
   } else if (L.type == TP_LAYER_BATCHNORM) {
     // per micro-batch two column sums; those of dx, one row per micro-batch or as the streaming kernel leaves them
-    const uint64_t dx_rows = std::max(d.n, tp::batchnorm_dx_sum_rows(d.dtype, (uint64_t)d.mb * lp.tokens, L.in_features, d.n));
+    const uint64_t own = round_up((uint64_t)d.n * 3 * L.in_features, 64);
+    uint64_t dx_rows = d.n;
+    if (l > 0 && bias_in_front(d, l - 1) && d.layers[l - 1].act == TP_ACT_NONE)
+      dx_rows = std::max(d.n, tp::batchnorm_dx_sum_rows(d.dtype, (uint64_t)d.mb * lp.tokens, L.in_features, d.n));
     need.norm = round_up(((uint64_t)d.n * 2 + dx_rows) * L.in_features, 64);
-  } else if (L.type == TP_LAYER_CONV2D) {
-    const uint64_t px = rows * conv_out_px(L);
-    need.bias = round_up(bias_partials(d, px, L.out_features), 64);
-    need.weight = round_up(tp::conv_wgrad_scratch_floats((int)px, L.in_features, L.out_features, L.geom[2]), 64);
-  } else if (L.type == TP_LAYER_DENSE) {
-    const uint64_t r = rows * lp.tokens;
-    need.bias = round_up(bias_partials(d, r, L.out_features), 64);
-    need.weight = round_up(tp::wgrad_scratch_floats(d.dtype, (int)r, L.out_features, L.in_features), 64);
+    extra = need.norm - own;
+  } else if (L.type == TP_LAYER_CONV2D || L.type == TP_LAYER_DENSE) {
+    const bool conv = L.type == TP_LAYER_CONV2D;
+    const uint64_t r = conv ? rows * conv_out_px(L) : rows * lp.tokens;
+    need.bias = round_up(bias_partials(d, l, r), 64);
+    extra = need.bias - round_up(tp::colsum_scratch_floats((int)r, L.out_features), 64);
+    need.weight = round_up(conv ? tp::conv_wgrad_scratch_floats((int)r, L.in_features, L.out_features, L.geom[2])
+                                : tp::wgrad_scratch_floats(d.dtype, (int)r, L.out_features, L.in_features), 64);
   }
+  need.own = need.total() - extra;
   return need;
 }
 
@@ -367,24 +388,29 @@ int make_plan(const tp_stage_desc* d, Plan* p) {
   p->act_slot_bytes = act;
   p->dz_bytes = round_up(rows * max_feat * p->elt_size, 256);
   uint64_t wg = 0;
-  for (const LayerPlan& lp : p->layers) {
+  for (int l = 0; l < d->num_layers; ++l) {
+    const LayerPlan& lp = p->layers[l];
     if (!lp.w_elems) continue;
     // bias gradients: column sums over rows (dense) or over all pixels (conv)
     if (lp.d.type == TP_LAYER_LAYERNORM || lp.d.type == TP_LAYER_BATCHNORM) continue;
     const uint64_t r = lp.d.type == TP_LAYER_CONV2D ? rows * conv_out_px(lp.d) : rows * lp.tokens;
-    wg = std::max<uint64_t>(wg, bias_partials(*d, r, lp.d.out_features));
+    wg = std::max<uint64_t>(wg, bias_partials(*d, l, r));
     if (lp.d.type == TP_LAYER_DENSE)
       wg = std::max<uint64_t>(wg, tp::wgrad_scratch_floats(d->dtype, (int)r, lp.d.out_features, lp.d.in_features));
   }
   p->partial_floats = round_up(std::max<uint64_t>({wg, tp::update_scratch_floats(), rows, conv_scratch, norm_scratch}), 64);
   // Every sum of partials the backward pass needs (bias and split weight gradients, scale and shift gradients of the
-  // normalisations) is put off to one launch at its end: each keeps partials of its own until then.
-  uint64_t deferred = 0;
-  for (LayerPlan& lp : p->layers) {
-    lp.need = deferred_need(*d, lp);
+  // normalisations) is put off to one launch at its end: each keeps partials of its own until then.  Where the line lies is
+  // decided by what the sums need at least, so that column sums left by another layer's kernel, which take more rows than a
+  // pass of their own, do not move a stage beyond it.
+  uint64_t deferred = 0, own = 0;
+  for (int l = 0; l < d->num_layers; ++l) {
+    LayerPlan& lp = p->layers[l];
+    lp.need = deferred_need(*d, l, lp);
     deferred += lp.need.total();
+    own += lp.need.own;
   }
-  p->deferred_floats = deferred <= kMaxDeferredFloats ? deferred : 0;  // beyond that: sums right away, shared partials
+  p->deferred_floats = own <= kMaxDeferredFloats ? deferred : 0;  // beyond that: sums right away, shared partials
   tp_sizes& s = p->sizes;
   s.param_count = P;
   s.ring_bytes = (uint64_t)d->ring_capacity * P * 4;
@@ -1214,14 +1240,13 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
       }
       void* dst = to_caller && !no_dx ? dx_dev : scratch_for(dz);
       // The kernel that forms the gradient of a dense or convolution layer in front also leaves its column sums where it can,
-      // and the layer's bias gradient needs no pass of its own: `bias_sums(C)` is where (null: C is not that layer's width),
-      // sum_bias() adds up what was left.
+      // and the layer's bias gradient needs no pass of its own: `bias_sums()` is where (null: no such layer), sum_bias()
+      // adds up what was left.
       int bias_rows = 0;
-      auto bias_sums = [&](int C) -> float* {
+      auto bias_sums = [&]() -> float* {
         if (l == 0 || no_dx) return nullptr;
-        const LayerPlan& prev = st->plan.layers[l - 1];
-        if ((prev.d.type != TP_LAYER_DENSE && prev.d.type != TP_LAYER_CONV2D) || prev.d.out_features != C) return nullptr;
-        bias_room = hold(prev.need.bias);
+        if (!bias_in_front(d, l - 1)) return nullptr;
+        bias_room = hold(st->plan.layers[l - 1].need.bias);
         return bias_room;
       };
       auto sum_bias = [&]() -> int {
@@ -1246,7 +1271,7 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
           ProfScope ps(st, TP_K_POOL);
           HIP_TRY(tp::launch_maxpool_bwd(st->stream, d.dtype, rows, lp.d.geom[0], lp.d.geom[1], lp.d.in_features,
                                          aslot + lp.x_off, dz, dst, fused ? dprev : nullptr, dmask,
-                                         fused || !dprev ? bias_sums(lp.d.in_features) : nullptr, &bias_rows));
+                                         fused || !dprev ? bias_sums() : nullptr, &bias_rows));
           if (int rc = sum_bias()) return rc;
         }
         if (!fused)
@@ -1355,11 +1380,7 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
           ProfScope ps(st, TP_K_NORM);
           // a dense or convolution layer without activation right in front: its bias gradient is the column sum of the dx
           // formed here, which these kernels hold in registers anyway
-          bool bias_here = false;
-          if (defer && l > 0 && !dprev && !no_dx) {
-            const tp_layer_desc& pl = st->plan.layers[l - 1].d;
-            bias_here = (pl.type == TP_LAYER_DENSE || pl.type == TP_LAYER_CONV2D) && pl.out_features == C;
-          }
+          const bool bias_here = defer && l > 0 && !dprev && !no_dx && bias_in_front(d, l - 1);
           if (tp::batchnorm_fused_bwd_supported(d.dtype, seg_rows, C)) {
             dx_rows = bias_here ? d.n : 0;
             if (dx_rows) dx_sums = sums + (size_t)d.n * 2 * C;
@@ -1439,11 +1460,11 @@ int backward_impl(tp_stage* st, uint64_t mb_id, const void* dy_dev, void* dx_dev
         ProfScope ps(st, TP_K_DGRAD);
         if (lp.d.type == TP_LAYER_DENSE)
           HIP_TRY(tp::launch_dgrad(st->stream, d.dtype, grad_rows, lp.d.out_features, lp.d.in_features, dz, wb + lp.w_off * es,
-                                   dprev, dst, dmask, bias_sums(lp.d.in_features), &bias_rows));
+                                   dprev, dst, dmask, bias_sums(), &bias_rows));
         else
           HIP_TRY(tp::launch_conv_dgrad(st->stream, d.dtype, rows, lp.d.geom[0], lp.d.geom[1], lp.d.geom[2], lp.d.geom[3],
                                         lp.d.in_features, lp.d.out_features, dz, wb + lp.w_off * es, dprev, dst, st->zeros(),
-                                        dmask, bias_sums(lp.d.in_features), &bias_rows));
+                                        dmask, bias_sums(), &bias_rows));
         if (int rc = sum_bias()) return rc;
       }
       dz = dst;

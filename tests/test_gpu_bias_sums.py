@@ -75,3 +75,48 @@ def test_convolution_in_front(dtype, imgs, size, channels, second):
         layers = [("conv", a, b, size, size, "relu"), ("conv", b, c, size, size, "none", 2 if second == "stride" else 1, 3)]
     params = [W[0], np.zeros(b, np.float32), W[1], np.zeros(c, np.float32)]
     _check(layers, params, dtype, imgs, 1, lambda gw: gw[:, 1, 1, 0], imgs * size * size)
+
+
+def test_sums_formed_right_away():
+    """Thirty convolutions whose split weight gradients would keep more than 1 GiB of partials: every sum is formed behind its
+    kernel, in one room for all.  The same layers as two stages of fifteen, which put the sums off, give the same bits; only the
+    bias of the fifteenth, whose column sums come from another kernel there, is another order of the same sum."""
+    import torch
+    from paper_2509_23241_amd.runner import GpuStage
+    size, mb, n, depth = 32, 16, 2, 30
+    layers = [("conv", 64, 64, size, size, "relu")] * depth
+    rng = np.random.default_rng(1)
+    params = []
+    for _ in layers:
+        params += [(rng.standard_normal((64, 3, 3, 64)) * np.sqrt(2 / 576)).astype(np.float32), (0.1 * rng.standard_normal(64)).astype(np.float32)]
+    kw = dict(dtype="bf16", mb=mb, n=n, policy="latest", lam=0.1, lr=0.0, momentum=0.0, ring_capacity=1, max_in_flight=1,
+              stage_index=1, num_stages=2)
+    whole = GpuStage(layers, params, **kw)
+    parts = [GpuStage(layers[:15], params[:30], **kw), GpuStage(layers[15:], params[30:], **kw)]
+    buffers = 3 * mb * n * size * size * 64 * 2
+    assert whole.sizes.scratch_bytes - buffers < parts[0].sizes.scratch_bytes - buffers    # the thirty share, the fifteen do not
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    x = torch.randn(mb * n, whole.in_elems, generator=gen, device="cuda").to(whole.tdtype)
+    dy = torch.randn(mb * n, whole.out_elems, generator=gen, device="cuda").to(whole.tdtype)
+    mid = torch.empty_like(x)
+    for ub in range(n):
+        at = slice(ub * mb, (ub + 1) * mb)
+        whole.forward(0, ub, x[at])
+        parts[0].forward(0, ub, x[at], mid[at])
+        parts[1].forward(0, ub, mid[at])
+    dx, _ = whole.backward(0, dy)
+    dmid, _ = parts[1].backward(0, dy)
+    dx_parts, _ = parts[0].backward(0, dmid)
+    got = whole.unpack(whole.grad.cpu().numpy())
+    want = [a for st in parts for a in st.unpack(st.grad.cpu().numpy())]
+    assert torch.equal(dx, dx_parts)
+    for i, (a, b) in enumerate(zip(got, want)):
+        if i != 29:
+            assert np.array_equal(a, b), i
+    # 2 N 2^-24 of the values' size r (N values each way); a column sum of random signs is about r sqrt(N)
+    terms = mb * n * size * size
+    r = np.sqrt(np.mean(want[29].astype(np.float64) ** 2) / terms)
+    assert np.all(np.abs(got[29].astype(np.float64) - want[29]) <= 2 * terms * 2.0 ** -24 * 4 * r)
+    for st in [whole] + parts:
+        st.close()

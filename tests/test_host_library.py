@@ -516,3 +516,32 @@ def test_choice_of_forward_streams(monkeypatch):
     assert len(own) == 2 and not {q.cuda_stream for q in own} & {q.cuda_stream for q in three}
     for many in (4, 33, 100):                              # passed on to the library, which refuses the number
         assert len(runner.forward_streams(device, many, 0)) == many
+
+
+def _scratch(layers, dtype="bf16", mb=128, n=4):
+    d = B.make_desc(layers, dtype=dtype, mb=mb, n=n, stage_index=0, num_stages=2, ring_capacity=2, max_in_flight=2, policy="convex",
+                    needs_dx=False, lam=0.1, lr=0.01, momentum=0.9)
+    return int(B.stage_workspace_query(d).scratch_bytes)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("end", [[("conv", 64, 64, 32, 32, "none")], [("pool", 64, 32, 32)], [(64, 64, "none", 1024)]])
+def test_room_for_column_sums_is_that_of_the_layer_behind(dtype, end):
+    # what a further dense layer in front of a normalisation needs does not depend on how the stage ends
+    pair = [(64, 64, "none", 1024), ("bn", 64, 1024, "relu")]
+    more = [_scratch(pair * 3 + e, dtype) - _scratch(pair * 2 + e, dtype) for e in ([], end)]
+    assert more[0] == more[1] > 0
+
+
+def test_column_sums_left_by_kernels_do_not_end_the_one_launch_of_sums():
+    # stem and conv2_x of the bottleneck net on 256-pixel images: every micro-batch more needs more scratch; where sums were
+    # formed one by one instead of in one launch, the room of their partials would go
+    layers = [("conv", 3, 64, 256, 256, "none", 2, 7), ("bn", 64, 128 * 128, "relu"), ("pool", 64, 128, 128)]
+    for cin in (64, 256, 256):
+        layers += [("res", cin, 4096, "begin"), (cin, 64, "none", 4096), ("bn", 64, 4096, "relu"), ("conv", 64, 64, 64, 64, "none"),
+                   ("bn", 64, 4096, "relu"), (64, 256, "none", 4096), ("bn", 256, 4096, "none")]
+        if cin == 64:
+            layers += [("swap", 256, 4096, 64, 4096), (64, 256, "none", 4096), ("bn", 256, 4096, "none")]
+        layers.append(("res", 256, 4096, "add", "relu"))
+    sizes = [_scratch(layers, n=n) for n in range(1, 9)]
+    assert sizes == sorted(sizes)
