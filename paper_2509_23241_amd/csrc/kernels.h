@@ -25,6 +25,17 @@ bool fprop_add_supported(int elt, int M, int N, int K);
 // out = (dz W_b) (.) d_prev   dz:[M x N] W_b:[N x K] d_prev:[M x K] saved act'(z), or null.
 hipError_t launch_dgrad(hipStream_t s, int elt, int M, int N, int K, const void* dz, const void* Wb,
                         const void* d_prev, void* out, int relu_mask = 0, float* sums = nullptr, int* sum_rows = nullptr);
+// Rows of partial column sums of an M-row gradient, one for every `per` rows, if they are worth leaving, else 0.  Adding them up takes
+// few workgroups where the columns are few, and beyond 4 MiB they come from behind one XCD's L2: per byte a fraction of what
+// a bounded pass over the gradient reaches.  us for the pass and for adding up M / 16 rows: fp32, 64 columns, M = 262144
+// (16384 rows) 15.7 and 11.3, 524288 24.8 and 39.9; 256 columns 49 and 36, 94 and 69; bf16, 256 columns, M = 65536 (4096 rows)
+// 12.8 and 5.1, 131072 17.0 and 19.4.  M / 32, bf16, 64 columns: 524288 (16384 rows) 19.9 and 11.2, 1048576 28.6 and 39.9.
+// M / 64, bf16, stays below the pass: 2097152 rows of 64 columns 52 and 40, of 256 182 and 70.
+inline int worthwhile_sum_rows(int elt, int M, int per) {
+  const long rows = ((long)M + per - 1) / per;
+  const int bytes = per * (elt == ELT_BF16 ? 2 : 4);  // of a column that one partial sum stands for
+  return bytes >= 128 || rows <= (bytes >= 64 ? 16384 : 4096) ? (int)rows : 0;
+}
 // sums: room for dgrad_sum_rows(elt, M, K) rows of K floats.  *sum_rows receives how many rows of partial column sums of `out`
 // were left there (0: none); added up they are the bias gradient of the layer before.
 int dgrad_sum_rows(int elt, int M, int K);

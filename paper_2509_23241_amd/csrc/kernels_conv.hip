@@ -417,9 +417,11 @@ hipError_t launch_conv_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int
     return conv_mfma_dgrad(s, imgs, H, W, stride, cin, cout, (const uint16_t*)dz, (const uint16_t*)wb,
                            (const uint16_t*)d_prev, (uint16_t*)out, (const uint16_t*)zeros, relu_mask, sums, sum_rows);
   if (conv_any_supported(elt, imgs, H, W, ksize, stride, cin, cout)) {
-    if (mfma) sums = nullptr;  // the room is for the rows of the matrix-core kernel
-    const hipError_t e = conv_any_dgrad(s, elt, imgs, H, W, ksize, stride, cin, cout, dz, wb, d_prev, out, relu_mask, sums);
-    if (sums && e == hipSuccess) *sum_rows = conv_dgrad_sum_rows(elt, imgs, H, W, ksize, stride, cin, cout);
+    // with mfma the room is for the rows of the matrix-core kernel
+    const int rows = sums && !mfma ? conv_dgrad_sum_rows(elt, imgs, H, W, ksize, stride, cin, cout) : 0;
+    const hipError_t e = conv_any_dgrad(s, elt, imgs, H, W, ksize, stride, cin, cout, dz, wb, d_prev, out, relu_mask,
+                                        rows ? sums : nullptr);
+    if (rows && e == hipSuccess) *sum_rows = rows;
     if (e != hipErrorNotSupported) return e;
   }
   const ConvGeom g{imgs, H, W, cin, cout, stride, H / stride, W / stride, ksize, (ksize - 1) / 2};
@@ -437,7 +439,7 @@ hipError_t launch_conv_dgrad(hipStream_t s, int elt, int imgs, int H, int W, int
 int conv_dgrad_sum_rows(int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout) {
   if (ksize == 3 && elt == 1 && conv_mfma_supported(imgs, H, W, stride, cin, cout))
     return conv_mfma_dgrad_sum_rows(imgs, H, W, stride, cin, cout);
-  return conv_any_supported(elt, imgs, H, W, ksize, stride, cin, cout) ? (imgs * H * W + 15) / 16 : 0;
+  return conv_any_supported(elt, imgs, H, W, ksize, stride, cin, cout) ? worthwhile_sum_rows(elt, imgs * H * W, 16) : 0;
 }
 
 hipError_t launch_conv_wgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout,

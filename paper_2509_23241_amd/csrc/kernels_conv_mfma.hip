@@ -1380,7 +1380,7 @@ hipError_t conv_mfma_fprop(hipStream_t s, int imgs, int H, int W, int stride, in
 
 int conv_mfma_dgrad_sum_rows(int imgs, int H, int W, int stride, int cin, int cout) {
   const int P = imgs * H * W;
-  return stride == 1 && pick_patch_tile<true, EpiDgrad>(P, H, W, cout, cin) >= 0 ? P / 64 : 0;  // a row per wave tile
+  return stride == 1 && pick_patch_tile<true, EpiDgrad>(P, H, W, cout, cin) >= 0 ? worthwhile_sum_rows(ELT_BF16, P, 64) : 0;  // a row per wave tile
 }
 
 hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, int cin, int cout, const uint16_t* dz,
@@ -1406,9 +1406,10 @@ hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, in
   {
     const PatchDesc pd = patch_desc(dz, zeros, H, W, cout, cout / 8, 0);
     EpiDgrad es = e;
-    es.sums = sums;  // pixel tiles and blocks of 64 channels are always whole here
+    const int rows = sums ? conv_mfma_dgrad_sum_rows(imgs, H, W, stride, cin, cout) : 0;
+    if (rows) es.sums = sums;  // pixel tiles and blocks of 64 channels are always whole here
     const hipError_t err = launch_patch_conv<true>(s, P, H, W, cout, cin, pd, bd, es);
-    if (sums && err == hipSuccess) *sum_rows = conv_mfma_dgrad_sum_rows(imgs, H, W, stride, cin, cout);
+    if (rows && err == hipSuccess) *sum_rows = rows;
     if (err != hipErrorNotSupported) return err;
   }
   GatherDesc ad{dz, zeros, P, H, W, ilog2(W), cout, H, W};

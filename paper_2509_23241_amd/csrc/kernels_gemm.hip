@@ -279,13 +279,14 @@ hipError_t launch_dgrad(hipStream_t s, int elt, int M, int N, int K, const void*
                         void* out, int relu_mask, float* sums, int* sum_rows) {
   if (elt == ELT_F32) {
     if (sums) *sum_rows = dgrad_sum_rows(elt, M, K);
-    return f32_dgrad(s, M, N, K, (const float*)dz, (const float*)Wb, (const float*)d_prev, (float*)out, relu_mask, sums);
+    return f32_dgrad(s, M, N, K, (const float*)dz, (const float*)Wb, (const float*)d_prev, (float*)out, relu_mask,
+                     sums && *sum_rows ? sums : nullptr);
   }
   return mfma_dgrad(s, M, N, K, (const uint16_t*)dz, (const uint16_t*)Wb, (const uint16_t*)d_prev, (uint16_t*)out, relu_mask, sums,
                     sum_rows);
 }
 
-int dgrad_sum_rows(int elt, int M, int K) { return elt == ELT_F32 ? (M + 15) / 16 : mfma_dgrad_sum_rows(M, K); }
+int dgrad_sum_rows(int elt, int M, int K) { return elt == ELT_F32 ? worthwhile_sum_rows(elt, M, 16) : mfma_dgrad_sum_rows(M, K); }
 
 void set_sum_sink(std::vector<SumJob>* sink) { g_sum_sink = sink; }
 

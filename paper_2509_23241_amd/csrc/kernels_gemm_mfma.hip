@@ -703,7 +703,8 @@ hipError_t mfma_fprop(hipStream_t s, int M, int N, int K, const uint16_t* x, con
 int mfma_dgrad_sum_rows(int M, int K) {
   const Tile tile = pick(M, K, false);
   for (const TileCost& t : kTiles)
-    if (t.t == tile) return M % t.bm == 0 && K % t.bn == 0 ? M / (tile == T256x256 ? 128 : tile == T64x64 ? 32 : 64) : 0;  // rows of a wave tile
+    if (t.t == tile && M % t.bm == 0 && K % t.bn == 0)
+      return worthwhile_sum_rows(ELT_BF16, M, tile == T256x256 ? 128 : tile == T64x64 ? 32 : 64);  // rows of a wave tile
   return 0;
 }
 

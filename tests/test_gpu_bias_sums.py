@@ -58,6 +58,16 @@ def test_tokens_and_micro_batches():
     _dense("bf16", 4 * 2 * 64, (64, 128, 64), "gelu", tokens=64, n=2)
 
 
+@pytest.mark.parametrize("rows", [262144, 262145])     # 16384 partial sums of 16 rows, the most that are left; one more: a pass
+def test_many_rows_f32(rows):
+    _dense("f32", rows, (8, 8, 8), "relu")
+
+
+@pytest.mark.parametrize("imgs", [28, 29])               # 4032 partial sums of 16 pixels; 4176, more than are left
+def test_many_pixels_any_size_bf16(imgs):
+    _convolutions("bf16", imgs, 48, (8, 24, 16), "conv")
+
+
 @pytest.mark.parametrize("dtype,imgs,size,channels,second", [
     ("bf16", 32, 16, (64, 128, 64), "conv"), ("bf16", 64, 32, (64, 64, 64), "conv"),   # patches of 128 and 256 pixels
     ("bf16", 16, 4, (64, 64, 64), "conv"), ("bf16", 4, 12, (8, 24, 16), "conv"),       # gathered: none left; any image size
@@ -66,6 +76,10 @@ def test_tokens_and_micro_batches():
     ("f32", 3, 8, (4, 8, 4), "pool"), ("bf16", 8, 16, (64, 64, 64), "stride"),
 ])
 def test_convolution_in_front(dtype, imgs, size, channels, second):
+    _convolutions(dtype, imgs, size, channels, second)
+
+
+def _convolutions(dtype, imgs, size, channels, second):
     rng = np.random.default_rng(imgs)
     a, b, c = channels
     W = [(rng.standard_normal(s) / np.sqrt(9 * s[3])).astype(np.float32) for s in ((b, 3, 3, a), (c, 3, 3, b))]

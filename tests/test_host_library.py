@@ -533,6 +533,14 @@ def test_room_for_column_sums_is_that_of_the_layer_behind(dtype, end):
     assert more[0] == more[1] > 0
 
 
+def test_few_rows_of_column_sums_are_kept():
+    # fp32, 64 features: two million rows are three gradient buffers, split weight gradients and the partial sums of a bounded
+    # pass; a row of sums for every 16 would be 32 MiB per layer
+    rows = 1 << 21
+    rest = _scratch([(64, 64, "none", rows // 512)] * 2, "f32") - 3 * rows * 64 * 4
+    assert 0 < rest < 32 << 20
+
+
 def test_column_sums_left_by_kernels_do_not_end_the_one_launch_of_sums():
     # stem and conv2_x of the bottleneck net on 256-pixel images: every micro-batch more needs more scratch; where sums were
     # formed one by one instead of in one launch, the room of their partials would go
