@@ -121,15 +121,29 @@ def test_deep_dense_stack_more_sums_than_one_launch_takes_bf16():
     (256, 16, 128, 128, 2), (256, 8, 256, 128, 2), (256, 4, 64, 128, 1),
 ])
 def test_gathered_weight_gradients(imgs, size, cin, cout, stride):
+    _weight_gradient(imgs, size, size, cin, cout, stride)
+
+
+@pytest.mark.parametrize("imgs,h,w,cin,cout", [
+    (3, 64, 64, 64, 128), (2, 128, 128, 64, 64),        # patch rows of 64 and 128 pixels: two image rows and one per tile
+    (5, 2, 64, 128, 64), (3, 1, 128, 64, 64),           # an image is one tile: no row above or below it
+    (300, 8, 16, 64, 64), (9, 4, 32, 64, 64),           # eight image rows per tile, more tiles than workgroups; four
+    (5, 16, 8, 64, 64),                                 # narrower than the 16 pixels of a k step
+])
+def test_patch_weight_gradients(imgs, h, w, cin, cout):
+    _weight_gradient(imgs, h, w, cin, cout, 1)
+
+
+def _weight_gradient(imgs, h, w, cin, cout, stride):
     from synth_inputs import round_bf16
     from test_gpu_gemm_any import _conv_reference, _rel, _run, _stage, _sum_tol
     rng = np.random.default_rng(imgs + cin)
     cast = lambda t: round_bf16(t).astype(np.float32)
-    wgt, x, dy = [cast(rng.standard_normal(s)) for s in ((cout, 3, 3, cin), (imgs, size, size, cin),
-                                                         (imgs, size // stride, size // stride, cout))]
+    wgt, x, dy = [cast(rng.standard_normal(s)) for s in ((cout, 3, 3, cin), (imgs, h, w, cin),
+                                                         (imgs, h // stride, w // stride, cout))]
     b = np.zeros(cout, np.float32)
-    _, _, (gw, gb) = _run(_stage(("conv", cin, cout, size, size, "none", stride, 3), [wgt, b], imgs, "bf16"),
+    _, _, (gw, gb) = _run(_stage(("conv", cin, cout, h, w, "none", stride, 3), [wgt, b], imgs, "bf16"),
                           x.reshape(imgs, -1), dy.reshape(imgs, -1))
-    pixels = imgs * (size // stride) ** 2
+    pixels = imgs * (h // stride) * (w // stride)
     assert _rel(gw, _conv_reference(x, wgt, b, dy, stride)[2]) <= _sum_tol(pixels)
     assert _rel(gb, dy.astype(np.float64).sum((0, 1, 2))) <= _sum_tol(pixels)
