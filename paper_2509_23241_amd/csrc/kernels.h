@@ -29,12 +29,14 @@ hipError_t launch_dgrad(hipStream_t s, int elt, int M, int N, int K, const void*
 // few workgroups where the columns are few, and beyond 4 MiB they come from behind one XCD's L2: per byte a fraction of what
 // a bounded pass over the gradient reaches.  us for the pass and for adding up M / 16 rows: fp32, 64 columns, M = 262144
 // (16384 rows) 15.7 and 11.3, 524288 24.8 and 39.9; 256 columns 49 and 36, 94 and 69; bf16, 256 columns, M = 65536 (4096 rows)
-// 12.8 and 5.1, 131072 17.0 and 19.4.  M / 32, bf16, 64 columns: 524288 (16384 rows) 19.9 and 11.2, 1048576 28.6 and 39.9.
-// M / 64, bf16, stays below the pass: 2097152 rows of 64 columns 52 and 40, of 256 182 and 70.
+// 12.8 and 5.1, 131072 17.0 and 19.4.  M / 64, bf16, stays below the pass: 2097152 rows of 64 columns 52 and 40, of 256 182
+// and 70.  In fp32 the line lies where the sum is no further from the exact one than the pass's, too: relative error of random values,
+// pass and rows, 64 columns, M = 32768 (2048 rows) 1.78e-7 and 1.81e-7, 64512 1.75 and 1.94, 131072 1.80 and 2.12, 262144 1.86 and
+// 2.66; bf16 is closer with the rows at every size (M / 16, 64512 rows of 24 columns 1.26 and 1.10; M / 64, 524288 of 64 1.60 and 1.51).
 inline int worthwhile_sum_rows(int elt, int M, int per) {
   const long rows = ((long)M + per - 1) / per;
-  const int bytes = per * (elt == ELT_BF16 ? 2 : 4);  // of a column that one partial sum stands for
-  return bytes >= 128 || rows <= (bytes >= 64 ? 16384 : 4096) ? (int)rows : 0;
+  const bool any_number = elt == ELT_BF16 && per >= 64;
+  return any_number || rows <= (elt == ELT_BF16 ? 4096 : 2048) ? (int)rows : 0;
 }
 // sums: room for dgrad_sum_rows(elt, M, K) rows of K floats.  *sum_rows receives how many rows of partial column sums of `out`
 // were left there (0: none); added up they are the bias gradient of the layer before.

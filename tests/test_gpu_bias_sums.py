@@ -58,9 +58,34 @@ def test_tokens_and_micro_batches():
     _dense("bf16", 4 * 2 * 64, (64, 128, 64), "gelu", tokens=64, n=2)
 
 
-@pytest.mark.parametrize("rows", [262144, 262145])     # 16384 partial sums of 16 rows, the most that are left; one more: a pass
+@pytest.mark.parametrize("rows", [32768, 32769])       # 2048 partial sums of 16 rows, the most that are left; one more: a pass
 def test_many_rows_f32(rows):
     _dense("f32", rows, (8, 8, 8), "relu")
+
+
+@pytest.mark.parametrize("dtype,rows", [("f32", 2048), ("f32", 32768), ("f32", 262144), ("bf16", 32768), ("bf16", 524288)])
+def test_as_close_as_a_pass(dtype, rows):
+    """Identity weights, no activation: the bias gradient of the first layer, from sums that are left, and that of the second, from a
+    pass over the gradient, are sums of the same values.  Over 12 draws of 64 columns the root mean square error of each is
+    known to 1 / sqrt(2 * 12 * 64) = 2.6 %, the ratio of two of them to 3.6 %: 1.15 is four times that."""
+    import torch
+    from paper_2509_23241_amd.runner import GpuStage
+    C = 64
+    st = GpuStage([(C, C, "none"), (C, C, "none")], [np.eye(C, dtype=np.float32), np.zeros(C, np.float32)] * 2, dtype=dtype, mb=rows,
+                  n=1, stage_index=1, num_stages=2, policy="latest", lam=0.1, lr=0.0, momentum=0.0, ring_capacity=1, max_in_flight=1)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows)
+    x = torch.randn(rows, C, generator=gen, device="cuda").to(st.tdtype)
+    square = np.zeros(2)
+    for j in range(12):
+        dy = torch.randn(rows, C, generator=gen, device="cuda").to(st.tdtype)
+        st.forward(j, 0, x)
+        st.backward(j, dy)
+        exact = dy.double().sum(0).cpu().numpy()
+        square += [np.mean((gb - exact) ** 2) for gb in st.unpack(st.grad.cpu().numpy())[1::2]]
+        st.blend_update(j)
+    st.close()
+    assert square[1] > 0 and np.sqrt(square[0] / square[1]) <= 1.15
 
 
 @pytest.mark.parametrize("imgs", [28, 29])               # 4032 partial sums of 16 pixels; 4176, more than are left
