@@ -95,9 +95,23 @@ def layer_work(cls, layer, rows, mb):
     return 0.0, 0.0
 
 
-def kernel_work(cls, w, s, needs_dx):
+def colsum_layers(w, s, launches):
+    """The layers whose bias gradient takes a pass over the gradient of its own, `launches` in a step; None if that does not say
+    which.  The stage's last layer with an activation has its column sums from the kernel that forms dz = dy (.) act'(z); layers
+    in front of a dense layer, a convolution, a pooling or a batch normalisation have them from that layer's kernel at the
+    shapes that kernel takes whole -- all of them at these workloads' sizes, but not at every one."""
+    layers = w.stages[s]
+    own, maybe = [], []
+    for i, l in enumerate(layers):
+        if l.kind not in ("dense", "conv") or (i == len(layers) - 1 and l.act != "none" and w.dtype == "bf16" and l.out_dim() % 8 == 0):
+            continue
+        (maybe if i + 1 < len(layers) and layers[i + 1].kind in ("dense", "conv", "pool", "bn") else own).append(l)
+    return own if launches == len(own) else own + maybe if launches == len(own) + len(maybe) else None
+
+
+def kernel_work(cls, w, s, needs_dx, launches=None):
     """Algorithmic work of one STEP in kernel class cls at stage s: (flops, bytes), summed over the
-    launches of the step; divided by the launches it is the per-launch figure."""
+    launches of the step; divided by the launches it is the per-launch figure.  (0, 0): not known."""
     layers = w.stages[s]
     rows = w.n * w.mb
     P = sum(int(np_prod(sh)) for l in layers for sh in l.param_shapes())
@@ -141,16 +155,14 @@ def kernel_work(cls, w, s, needs_dx):
     if cls == "copy":                  # stage input saved for the backward where no GEMM can fuse it
         l = layers[0]
         return 0.0, (2 * 2.0 * rows * np_prod(l.in_shape())) if l.kind in ("conv", "res", "ln", "bn") else 0.0
+    if cls == "colsum":
+        return 0.0, sum(layer_work(cls, l, rows, w.mb)[1] for l in colsum_layers(w, s, launches) or [])
     flops = nbytes = 0.0
     for i, l in enumerate(layers):
         if l.kind in ("pool", "ln", "attn", "res", "bn", "sub", "swap", "avg"):
             continue
         if cls == "dgrad" and i == 0 and not needs_dx:
             continue
-        if cls == "colsum" and i == len(layers) - 1 and l.act != "none" and w.dtype == "bf16" and l.out_dim() % 8 == 0:
-            continue   # the stage's last layer: its column sums come out of the kernel that forms dz = dy (.) act'(z)
-        if cls == "colsum" and i + 1 < len(layers) and layers[i + 1].kind in ("dense", "conv", "pool", "bn"):
-            continue   # the kernel of the layer behind it that forms dz leaves its column sums (at these workloads' shapes)
         f, b = layer_work(cls, l, rows, w.mb)
         mult = w.n if cls == "fprop" else 1
         flops += mult * f
@@ -354,7 +366,7 @@ def main():
         if launches == 0:
             continue
         per_step = launches / args.steps
-        flops, nbytes = (v / per_step for v in kernel_work(cls, w, s, st.needs_dx))
+        flops, nbytes = (v / per_step for v in kernel_work(cls, w, s, st.needs_dx, per_step))
         avg_us = ms / launches * 1e3
         kernels[cls] = {"launches_per_step": launches / args.steps, "avg_us": round(avg_us, 2),
                         "share_of_step": round(ms / args.steps / (dt_prof / args.steps * 1e3), 4),
@@ -362,7 +374,7 @@ def main():
                         "gbs": round(nbytes / (avg_us * 1e-6) / 1e9, 1) if nbytes else None}
     dominant = max(kernels, key=lambda c: kernels[c]["share_of_step"])
     dk = kernels[dominant]
-    flops, nbytes = (v / dk["launches_per_step"] for v in kernel_work(dominant, w, s, st.needs_dx))
+    flops, nbytes = (v / dk["launches_per_step"] for v in kernel_work(dominant, w, s, st.needs_dx, dk["launches_per_step"]))
     # the roofline that bounds one launch: matrix cores or HBM, whichever takes longer at peak
     t_mfma = flops / (PEAK_BF16_TFLOPS * 1e12)
     t_hbm = nbytes / (PEAK_HBM_GBS * 1e9)

@@ -34,6 +34,18 @@ def test_algorithmic_work_of_the_headline_stage():
     assert fl == 2 * 2.0 * 2048 * 4096 * 4096 and by == 2 * (2.0 * 2 * 2048 * 4096 + 4.0 * 4096 * 4096)
 
 
+def test_column_sums_are_priced_by_the_passes_that_ran():
+    import bench
+    from synth_inputs import workloads as W
+    w = W.mlp_wide(width=4096, mb=256, n=8)                                           # GELU in both layers of stage 1
+    assert bench.kernel_work("colsum", w, 1, True, 1) == (0.0, 2.0 * 2048 * 4096)     # a pass over the first layer's dz
+    assert bench.kernel_work("colsum", w, 3, True, 1) == (0.0, 2.0 * 2048 * 1000)     # the logits' dz; the layer in front had none
+    assert bench.kernel_work("colsum", w, 3, True, 2) == (0.0, 2.0 * 2048 * (4096 + 1000))
+    v = W.vgg_stage0(mb=64, n=4)                                                      # four convolutions
+    assert bench.kernel_work("colsum", v, 0, False, 4)[1] == 2.0 * 256 * (2 * 1024 * 64 + 2 * 256 * 128)
+    assert bench.kernel_work("colsum", v, 0, False, 2) == (0.0, 0.0)                  # some of them: not said which
+
+
 def test_algorithmic_work_of_a_strided_convolution():
     import bench
     from synth_inputs import workloads as W
