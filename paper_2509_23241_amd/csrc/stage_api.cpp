@@ -248,11 +248,13 @@ DeferredNeed deferred_need(const tp_stage_desc& d, int l, const LayerPlan& lp) {
   if (L.type == TP_LAYER_LAYERNORM) {
     need.norm = round_up(tp::layernorm_scratch_floats(rows * lp.tokens, L.in_features), 64);
   } else if (L.type == TP_LAYER_BATCHNORM) {
-    // per micro-batch two column sums; those of dx, one row per micro-batch or as the streaming kernel leaves them
+    // per micro-batch two column sums; those of dx, one row per micro-batch or as the streaming kernels leave them
     const uint64_t own = round_up((uint64_t)d.n * 3 * L.in_features, 64);
+    const uint64_t seg_rows = (uint64_t)d.mb * lp.tokens;
     uint64_t dx_rows = d.n;
-    if (l > 0 && bias_in_front(d, l - 1) && d.layers[l - 1].act == TP_ACT_NONE)
-      dx_rows = std::max(d.n, tp::batchnorm_dx_sum_rows(d.dtype, (uint64_t)d.mb * lp.tokens, L.in_features, d.n));
+    if (l > 0 && bias_in_front(d, l - 1) && d.layers[l - 1].act == TP_ACT_NONE &&
+        !tp::batchnorm_fused_bwd_supported(d.dtype, seg_rows, L.in_features))
+      dx_rows = std::max(d.n, tp::batchnorm_dx_sum_rows(d.dtype, seg_rows, L.in_features, d.n));
     need.norm = round_up(((uint64_t)d.n * 2 + dx_rows) * L.in_features, 64);
     extra = need.norm - own;
   } else if (L.type == TP_LAYER_CONV2D || L.type == TP_LAYER_DENSE) {

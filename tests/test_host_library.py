@@ -533,6 +533,14 @@ def test_room_for_column_sums_is_that_of_the_layer_behind(dtype, end):
     assert more[0] == more[1] > 0
 
 
+@pytest.mark.parametrize("tokens,mb", [(16, 128), (4, 128), (1, 100)])
+def test_no_room_for_sums_the_slab_normalisation_does_not_leave(tokens, mb):
+    # up to 2048 rows per micro-batch the normalisation leaves one row of dx sums for each, whoever takes them: nobody where the
+    # layer in front has an activation
+    sizes = [_scratch([(256, 256, act, tokens), ("bn", 256, tokens, "relu")], mb=mb) for act in ("none", "gelu")]
+    assert sizes[0] == sizes[1]
+
+
 def test_few_rows_of_column_sums_are_kept():
     # fp32, 64 features: two million rows are three gradient buffers, split weight gradients and the partial sums of a bounded
     # pass; a row of sums for every 16 would be 32 MiB per layer
