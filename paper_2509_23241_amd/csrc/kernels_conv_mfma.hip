@@ -21,6 +21,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "conv.h"
 #include "kernels.h"
@@ -490,17 +491,16 @@ struct PatchDesc {
   const uint16_t* zeros;  // >= 128 zero bytes
   int H, W, lw;           // image size, log2(W)
   int C;                  // channels of `base` (pixel pitch in elements)
-  int c0;                 // first channel staged
-  int CB;                 // 16-byte chunks staged per pixel (channels staged / 8)
-  int tr;                 // 1: layout for transposed reads (pixels are the contraction index)
+  int CB;                 // 16-byte chunks per pixel (C / 8)
   uint32_t by_cb, by_pc;  // ceil(2^32 / CB), ceil(2^32 / (W + 2))
 };
 
 // chunk c of patch pixel pp is stored in slot c ^ patch_swz(pp)
-__device__ __forceinline__ int patch_swz(int pp, int CB, int tr) {
-  if (tr) return 4 * ((pp >> 1) & 1);             // as the [k][64] stages of the dense kernels
+__device__ __forceinline__ int patch_swz(int pp, int CB) {
   return (CB & 15) ? ((pp >> 1) & 7) : (pp & 15);  // 128-byte pixels: 8 slots over same-parity pixels; wider: 16
 }
+// the same in patches for transposed reads (pixels are the contraction index), as in the [k][64] stages of the dense kernels
+__device__ __forceinline__ int patch_swz_tr(int pp) { return 4 * ((pp >> 1) & 1); }
 
 // All waves of the workgroup copy the patch of the tile whose first pixel is p0 (a multiple of BM).  Divisions by the run-time
 // widths are multiplications by their inverses: as divisions they were most of what a wave did before its first product (forward
@@ -514,11 +514,11 @@ __device__ __forceinline__ void issue_patch(const PatchDesc& d, uint32_t lds_pat
   const int instrs = (NPIX * px_bytes + 1023) / 1024;
   for (int i = wave; i < instrs; i += NW) {
     const int at = i * 64 + lane, pp = __umulhi(at, d.by_cb), slot = at - pp * d.CB;  // exact: at * CB < 2^32
-    const int chunk = slot ^ patch_swz(pp, d.CB, d.tr);
+    const int chunk = slot ^ patch_swz(pp, d.CB);
     const int pr = __umulhi(pp, d.by_pc), pc = pp - pr * PC;
     const int h = h0 + pr - 1, w = pc - 1;
     const bool valid = pp < NPIX && (unsigned)h < (unsigned)d.H && (unsigned)w < (unsigned)d.W;
-    const long src = (((long)img * d.H + h) * d.W + w) * d.C + d.c0 + chunk * 8;
+    const long src = (((long)img * d.H + h) * d.W + w) * d.C + chunk * 8;
     const uint16_t* ptr = valid ? d.base + src : d.zeros + (lane & 7) * 8;
     dma16_addr(lds_patch + i * 1024, ptr);
   }
@@ -595,7 +595,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_patch_kernel(int P, int N
     for (int i = 0; i < TM; ++i) {
       const int ppt = ppc[i] + tapoff;
       prow[i] = (uint32_t)ppt * pd.CB * 8;
-      psw[i] = patch_swz(ppt, pd.CB, 0);
+      psw[i] = patch_swz(ppt, pd.CB);
     }
     auto afrag = [&](int i, int kk) {
       const int chunk = cb * 8 + kk * 2 + khalf;
@@ -648,151 +648,177 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_patch_kernel(int P, int N
   }
 }
 
-// wgrad: dW[co][tap][ci] = sum_p dz[p][co] * x[p shifted by tap][ci] for one block of 64 output and 64
-// input channels and all nine taps; the workgroup walks over pixel tiles split, split + splits, ...,
-// double buffered: the copies of the next tile fly while the current one is multiplied.
-// With one wave per SIMD (nine accumulators each) bound by what is issued beside the matrix instructions: three or four vector
-// instructions are free next to one, but an LDS address per tap (8) and two divisions per 1 KB of patch were several
-// times that.  W > 0, the image width (a multiple of the 16 pixels of a k step): patch rows begin at constants, so a lane has four LDS
-// addresses in all, and where its copies come from is worked out once.  256 images of 32 x 32, 64 channels, with the
-// sums of the partial results: 43.2 -> 30.5 us (34.5 with the divisions by multiplication but one source address at a time);
-// 64 of 64 x 64 45.6 -> 31.3.
-template <int BM, int W>
-__global__ __launch_bounds__(256) void conv_wgrad_patch_kernel(PatchDesc xd, const uint16_t* __restrict__ dz, int cout,
-                                                               int px_tiles, int ci_blocks, float* __restrict__ out) {
-  constexpr int NW = 4;
+// wgrad: dW[co][tap][ci] = sum_p dz[p][co] * x[p shifted by tap][ci] for one block of 64 output and 64 input channels and
+// the three taps of one row of the filter; the workgroup walks over tiles of 128 pixels, three buffers, two tiles in flight
+// while one is multiplied.  Its patch is the 128 pixels one filter row up or down, with a column of zeros on both sides.
+// Bound by memory: the inputs once, and the fp32 partial results, one of every workgroup, which are written and read again.
+// With all nine taps in a workgroup those were 147 KB from each of 256, 38 MB a layer; three taps leave a third of it
+// and walk over three times the pixels, where the workgroups that share a pixel range sit on one XCD and meet in its L2.
+// A wave takes all 64 output channels of 32 input channels: 5 fragments for 6 matrix instructions (10 for 9 before), and
+// half of a tile's pixels, the other two waves the other half; the two meet through LDS at the end.  The products of 8 tiles are
+// summed apart: in chains over all tiles of a workgroup the gradients were up to 1.4 times further off fp64 than with the
+// nine-tap kernel's shorter ones (256 images of 16 x 16, 128 channels, 1.55e-7 there, 2.15e-7 in chains, 1.19e-7 now).
+// The gradients of 256 images of 32 x 32, 64 -> 64, and of 16 x 16, 64 -> 128 and 128 -> 128 channels 25.2, 15.3 and 24.5 us
+// with nine taps, 25.2, 16.4 and 25.3 now, and the one launch that adds up the partial results of them all 27.7 -> 15.3: a step of
+// the VGG stage 334 -> 307 us.  A fourth buffer changes nothing.
+template <int W>
+__global__ __launch_bounds__(256) void conv_wgrad_patch_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ zeros, int H,
+                                                               int cin, const uint16_t* __restrict__ dz, int cout, int px_tiles,
+                                                               int splits, float* __restrict__ out) {
+  constexpr int BM = 128, NW = 4, NS = 3;
   using DZ = ColDma<64, NW>;  // stage [pixel][64 output channels]; k index = pixel
-  constexpr int kDzInstr = BM * 8 / 64 / NW;
+  constexpr int kDz = BM * 8 / 64 / NW;                                        // copies of one wave per tile: dz,
+  constexpr int kPatch = ((BM / W) * (W + 2) * 128 + NW * 1024 - 1) / (NW * 1024);  // and the patch (the surplus copies zeros)
+  constexpr int kPatchBytes = kPatch * NW * 1024, kBufBytes = kPatchBytes + BM * 128;
   extern __shared__ __attribute__((aligned(16))) uint16_t lds_raw[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int cob = blockIdx.x / ci_blocks, cib = blockIdx.x - cob * ci_blocks;
-  const int split = blockIdx.y, splits = gridDim.y;
-  const int cin = xd.C;
-  xd.c0 = cib * 64;
-  const int pbytes = patch_bytes(BM, xd.W, 8);
-  const int buf_bytes = pbytes + BM * 128;
+  const int ci_blocks = cin / 64, blocks = 3 * ci_blocks * (cout / 64);
+  // neighbours in the order of (pixel range, block) on one XCD
+  const int at = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int split = at / blocks, block = at % blocks;
+  if (split >= splits) return;
+  const int kh = block % 3, cib = block / 3 % ci_blocks, cob = block / 3 / ci_blocks;
+  const int ci_half = wave & 1, px_half = wave >> 1;
   const uint32_t lds_base = lds_addr_of(lds_raw);
-  const int rb_co = (wave >> 1) * 32, rb_ci = (wave & 1) * 32;
-  const int PC = xd.W + 2;
 
-  floatx16 acc[9];
+  constexpr int kApart = 8;
+  floatx16 acc[2][3], sum[2][3];  // [half of the output channels][tap]: of the latest tiles, of those before
 #pragma unroll
-  for (int t = 0; t < 9; ++t)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][t][r] = sum[i][t][r] = 0.f;
+  auto put_aside = [&] {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          sum[i][t][r] += acc[i][t][r];
+          acc[i][t][r] = 0.f;
+        }
+  };
 
-  // per-lane source offsets of the dz tile (the same in every tile, relative to its first pixel)
-  uint32_t dzoff[kDzInstr];
+  // where the lane's chunks of dz and of the patch come from, relative to the tile's first pixel, and the patch rows they
+  // belong to (1 << 20: outside every image)
+  uint32_t dzoff[kDz];
 #pragma unroll
-  for (int i = 0; i < kDzInstr; ++i) {
+  for (int i = 0; i < kDz; ++i) {
     const int flat = 64 * (wave + NW * i) + lane;
     const int k = flat >> 3, c = (flat & 7) ^ DZ::swz(k);
     dzoff[i] = (uint32_t)(((size_t)k * cout + cob * 64 + c * 8) * 2);
   }
-  // W > 0: where the lane's chunks of the patch come from, relative to the tile's first pixel, and their patch rows less one
-  // (1 << 20: outside every image)
-  constexpr int kPatchInstr = W > 0 ? ((BM / (W > 0 ? W : 1) + 2) * (W + 2) * 128 + 1023) / 1024 : 0, kPatchPerWave = (kPatchInstr + NW - 1) / NW;
-  int from[kPatchPerWave > 0 ? kPatchPerWave : 1], prow[kPatchPerWave > 0 ? kPatchPerWave : 1];
-  if constexpr (W > 0) {
+  int from[kPatch], prow[kPatch];
 #pragma unroll
-    for (int i = 0; i < kPatchPerWave; ++i) {
-      const int flat = (wave + NW * i) * 64 + lane, pp = flat >> 3;
-      const int chunk = (flat & 7) ^ patch_swz(pp, 8, 1), pr = pp / (W + 2), pc = pp % (W + 2);
-      from[i] = ((pr - 1) * W + pc - 1) * cin + chunk * 8;
-      prow[i] = pr < BM / W + 2 && pc >= 1 && pc <= W ? pr - 1 : 1 << 20;
-    }
+  for (int i = 0; i < kPatch; ++i) {
+    const int flat = (wave + NW * i) * 64 + lane, pp = flat >> 3;
+    const int chunk = (flat & 7) ^ patch_swz_tr(pp), pr = pp / (W + 2), pc = pp % (W + 2);
+    from[i] = ((pr + kh - 1) * W + pc - 1) * cin + cib * 64 + chunk * 8;
+    prow[i] = pr < BM / W && pc >= 1 && pc <= W ? pr + kh - 1 : 1 << 20;
   }
-  auto issue_tile = [&](int tile, int buf) {
-    const uint32_t dst = lds_base + buf * buf_bytes;
-    if constexpr (W > 0) {
-      const int row = tile * (BM / W), img = row / xd.H, h0 = row - img * xd.H;
-      const uint16_t* first = xd.base + (long)tile * BM * cin + xd.c0;
-#pragma unroll
-      for (int i = 0; i < kPatchPerWave; ++i)
-        if (kPatchInstr % NW == 0 || wave + NW * i < kPatchInstr)
-          dma16_addr(dst + (wave + NW * i) * 1024, (unsigned)(h0 + prow[i]) < (unsigned)xd.H ? first + from[i] : xd.zeros + (lane & 7) * 8);
-    } else {
-      issue_patch<BM, NW>(xd, dst, tile * BM, wave, lane);
-    }
-    const uint16_t* src = dz + (size_t)tile * BM * cout;
-#pragma unroll
-    for (int i = 0; i < kDzInstr; ++i) dma16(dst + pbytes + (wave + NW * i) * 1024, src, dzoff[i]);
+  const uint16_t *dz_tile = nullptr, *x_tile = nullptr;
+  uint32_t dst = 0;
+  int h0 = 0;
+  auto begin_tile = [&](int tile, int buf) {
+    const int row = tile * (BM / W);
+    h0 = row & (H - 1);
+    x_tile = x + (long)tile * BM * cin;
+    dz_tile = dz + (size_t)tile * BM * cout;
+    dst = lds_base + buf * kBufBytes;
   };
+  auto issue = [&](int t) {  // copy t of the tile begun
+    if (t < kPatch)
+      dma16_addr(dst + (wave + NW * t) * 1024, (unsigned)(h0 + prow[t]) < (unsigned)H ? x_tile + from[t] : zeros + (lane & 7) * 8);
+    else
+      dma16(dst + kPatchBytes + (wave + NW * (t - kPatch)) * 1024, dz_tile, dzoff[t - kPatch]);
+  };
+  constexpr int kCopies = kPatch + kDz;
 
-  // W > 0: byte of the lane's pixel (and 16-byte slot) in a patch row that begins at patch pixel u = 0 .. 3 (mod 4): the swizzle of
+  // byte of the lane's pixel (and 16-byte slot) in a patch row that begins at patch pixel u = 0 .. 3 (mod 4): the swizzle of
   // patch pixel p depends on p / 2 % 2 alone
   int lane_at[4];
   {
-    const int g = lane >> 4, s = lane & 15, col = rb_ci + 16 * (g & 1) + 4 * (s & 3), px = 8 * (g >> 1) + (s >> 2);
+    const int g = lane >> 4, s = lane & 15, col = ci_half * 32 + 16 * (g & 1) + 4 * (s & 3);
+    const int half = W <= 64 ? (64 / (W <= 64 ? W : 1)) * (W + 2) : 64;  // patch pixels in front of the second half
+    const int px = px_half * half + (W == 8 ? 10 : 8) * (g >> 1) + (s >> 2);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) lane_at[u] = px * 128 + ((col >> 3) ^ patch_swz(u + px, 8, 1)) * 16 + (col & 7) * 2;
+    for (int u = 0; u < 4; ++u) lane_at[u] = px * 128 + ((col >> 3) ^ patch_swz_tr(u + px)) * 16 + (col & 7) * 2;
   }
   typedef __attribute__((address_space(3))) shortx4* lds_ptr;
 
-  if (split < px_tiles) issue_tile(split, 0);
+  const int n = split < px_tiles ? (px_tiles - split + splits - 1) / splits : 0;  // tiles split, split + splits, ...
+#pragma unroll
+  for (int i = 0; i < NS - 1; ++i)
+    if (i < n) {
+      begin_tile(split + i * splits, i);
+#pragma unroll
+      for (int t = 0; t < kCopies; ++t) issue(t);
+    }
   int buf = 0;
-  for (int tile = split; tile < px_tiles; tile += splits) {
-    wait_vmcnt<0>();  // this tile has landed (nothing else is in flight)
-    lds_barrier();    // ... for every wave, and every wave is done with the other buffer
-    if (tile + splits < px_tiles) issue_tile(tile + splits, buf ^ 1);
-    const uint16_t* lp = lds_raw + buf * (buf_bytes / 2);
-    const uint16_t* ldz = lp + pbytes / 2;
-    if constexpr (W > 0) {
-      const char* at[4];
+  auto tile = [&](int i, auto copies) {  // copies: those of tile i + NS - 1 go out between the products
+    constexpr bool kMore = decltype(copies)::value;
+    if (kMore || i + 1 < n) wait_vmcnt<kCopies>();  // this tile has landed, the next one may be in flight
+    else wait_vmcnt<0>();
+    lds_barrier();  // ... for every wave, and every wave is done with the buffer that is filled now
+    if (kMore) begin_tile(split + (i + NS - 1) * splits, buf == 0 ? NS - 1 : buf - 1);
+    const char* lp = reinterpret_cast<const char*>(lds_raw) + buf * kBufBytes;
+    const uint16_t* ldz = reinterpret_cast<const uint16_t*>(lp + kPatchBytes) + px_half * 64 * 64;
+    const char* at[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) at[u] = reinterpret_cast<const char*>(lp) + lane_at[u];
-      constexpr int kAll = BM / 16 * 9, kAhead = 3;
-      bf16x8 fa[2], fb[kAhead + 1];
-      auto fetch = [&](int x) {  // the fragment of x of product x: tap x % 9 of k step x / 9
-        const int kk = x / 9, t = x % 9;
-        const int u = (kk * 16 / W + t / 3) * (W + 2) + kk * 16 % W + t % 3;
-        const char* p = at[u & 3] + u * 128;
-        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
-        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * 128));
-        fb[x % (kAhead + 1)] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-      };
-      fa[0] = DZ::frag(ldz, rb_co, 0, lane);
+    for (int u = 0; u < 4; ++u) at[u] = lp + lane_at[u];
+    bf16x8 fa[2][2], fb[2][3];
+    auto fetch_b = [&](int kk, int t) {
+      const int u = kk * 16 / W * (W + 2) + kk * 16 % W + t;
+      const char* p = at[u & 3] + u * 128;
+      const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
+      const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * 128));
+      fb[kk & 1][t] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto fetch = [&](int kk, int r) {  // fragment r of 5
+      if (r < 2) fa[kk & 1][r] = DZ::frag(ldz, 32 * r, kk, lane);
+      else fetch_b(kk, r - 2);
+    };
 #pragma unroll
-      for (int x = 0; x < kAhead; ++x) fetch(x);
+    for (int r = 0; r < 5; ++r) fetch(0, r);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int x = 0; x < kAll; ++x) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (x + kAhead < kAll) fetch(x + kAhead);
-        if (x % 9 == 4 && x / 9 + 1 < BM / 16) fa[(x / 9 + 1) & 1] = DZ::frag(ldz, rb_co, x / 9 + 1, lane);
-        __builtin_amdgcn_sched_barrier(0);
-        acc[x % 9] = mma<false>(fa[(x / 9) & 1], fb[x % (kAhead + 1)], acc[x % 9]);
-      }
-      buf ^= 1;
-      continue;
+    for (int q = 0; q < 24; ++q) {  // product q: k step q / 6, output half q / 3 % 2, tap q % 3
+      const int kk = q / 6, r = q % 6;
+      if (kk < 3 && r < 5) fetch(kk + 1, r);
+      if (kMore && q * kCopies / 24 != (q + 1) * kCopies / 24) issue(q * kCopies / 24);
+      __builtin_amdgcn_sched_barrier(0);
+      acc[r / 3][r % 3] = mma<false>(fa[kk & 1][r / 3], fb[kk & 1][r % 3], acc[r / 3][r % 3]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    const int g = lane >> 4, s = lane & 15;
-    const int col = rb_ci + 16 * (g & 1) + 4 * (s & 3);
-#pragma unroll 2
-    for (int kk = 0; kk < BM / 16; ++kk) {
-      const bf16x8 a = DZ::frag(ldz, rb_co, kk, lane);
-      const int kq = kk * 16 + 8 * (g >> 1) + (s >> 2);
-      const int ppc = ((kq >> xd.lw) + 1) * PC + (kq & (xd.W - 1)) + 1;
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        const int ppt = ppc + (t / 3 - 1) * PC + (t % 3 - 1);
-        const int slot = (col >> 3) ^ patch_swz(ppt, 8, 1);
-        typedef __attribute__((address_space(3))) shortx4* lds_ptr;
-        const uint16_t* p = lp + ppt * 64 + slot * 8 + (col & 7);
-        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
-        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * 64));
-        const shortx8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        acc[t] = mma<false>(a, __builtin_bit_cast(bf16x8, v), acc[t]);
-      }
-    }
-    buf ^= 1;
+    buf = buf + 1 == NS ? 0 : buf + 1;
+  };
+  const int copying = max(0, n - (NS - 1));
+  for (int i = 0; i < n;) {
+    const int end = min(i + kApart, n), with_copies = min(end, copying);
+    for (; i < with_copies; ++i) tile(i, std::true_type{});
+    for (; i < end; ++i) tile(i, std::false_type{});
+    put_aside();
   }
+  lds_barrier();  // the buffers are dead
+  // the waves of the two pixel halves swap: each adds the other's sums of one half of the output channels to its own, and stores it
+  float* handover = reinterpret_cast<float*>(lds_raw) + wave * (3 * 16 * 64);
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) handover[(t * 16 + r) * 64 + lane] = px_half == 0 ? sum[1][t][r] : sum[0][t][r];
+  lds_barrier();
+  const float* other = reinterpret_cast<const float*>(lds_raw) + (wave ^ 2) * (3 * 16 * 64);
   float* o = out + (size_t)split * cout * 9 * cin;
 #pragma unroll
-  for (int t = 0; t < 9; ++t) {
+  for (int t = 0; t < 3; ++t) {
     floatx16 one[1][1];
-    one[0][0] = acc[t];
-    store_tiles<1, 1>(one, EpiWgrad{o + (size_t)t * cin, 9 * cin}, cob * 64 + rb_co, cib * 64 + rb_ci, cout, cin, lane);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) one[0][0][r] = (px_half == 0 ? sum[0][t][r] : sum[1][t][r]) + other[(t * 16 + r) * 64 + lane];
+    store_tiles<1, 1>(one, EpiWgrad{o + (size_t)(kh * 3 + t) * cin, 9 * cin}, cob * 64 + 32 * px_half, cib * 64 + 32 * ci_half, cout, cin,
+                      lane);
   }
 }
 
@@ -1215,9 +1241,9 @@ inline int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
 
 constexpr int kMaxLds = 160 * 1024;
 
-inline PatchDesc patch_desc(const uint16_t* base, const uint16_t* zeros, int H, int W, int C, int CB, int tr) {
+inline PatchDesc patch_desc(const uint16_t* base, const uint16_t* zeros, int H, int W, int C) {
   auto inverse = [](int d) { return (uint32_t)(((1ull << 32) + d - 1) / d); };
-  return PatchDesc{base, zeros, H, W, ilog2(W), C, 0, CB, tr, inverse(CB), inverse(W + 2)};
+  return PatchDesc{base, zeros, H, W, ilog2(W), C, C / 8, inverse(C / 8), inverse(W + 2)};
 }
 
 inline bool patch_shape_ok(int H, int W, int BM) {
@@ -1290,21 +1316,24 @@ hipError_t launch_patch_conv(hipStream_t s, int P, int H, int W, int C, int N, c
 }
 
 constexpr int kWgradBM = 128;
-inline size_t wgrad_patch_lds(int W) { return 2 * ((size_t)patch_bytes(kWgradBM, W, 8) + kWgradBM * 128); }
-inline bool wgrad_patch_ok(int H, int W) { return patch_shape_ok(H, W, kWgradBM) && wgrad_patch_lds(W) <= kMaxLds; }
+inline bool wgrad_patch_ok(int H, int W) { return patch_shape_ok(H, W, kWgradBM); }
+// Pixel ranges of the patch weight gradient: a workgroup for every CU.
 inline int wgrad_patch_splits(long px_tiles, int cin, int cout) {
-  const long blocks = std::max(1l, (long)(cin / 64) * (cout / 64));
+  const long blocks = std::max(1l, 3l * (cin / 64) * (cout / 64));
   return (int)std::max(1l, std::min(px_tiles, 256 / blocks));
 }
 
 template <int W>
-hipError_t launch_wgrad_patch(hipStream_t s, const PatchDesc& xd, const uint16_t* dz, int cout, int px_tiles, int splits, float* out) {
-  auto kernel = conv_wgrad_patch_kernel<kWgradBM, W>;
+hipError_t launch_wgrad_patch(hipStream_t s, const uint16_t* x, const uint16_t* zeros, int H, int cin, const uint16_t* dz, int cout,
+                              int px_tiles, int splits, float* out) {
+  constexpr int kBuf = ((kWgradBM / W) * (W + 2) * 128 + 4095) / 4096 * 4096 + kWgradBM * 128;
+  static_assert(3 * kBuf >= 4 * 3 * 16 * 64 * 4 && 3 * kBuf <= kMaxLds, "three buffers, and the handover in their place");
+  auto kernel = conv_wgrad_patch_kernel<W>;
   static hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 3 * kBuf);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kernel, dim3((xd.C / 64) * (cout / 64), splits), dim3(256), wgrad_patch_lds(xd.W), s, xd, dz, cout, px_tiles,
-                     xd.C / 64, out);
+  const int blocks = 3 * (cin / 64) * (cout / 64);
+  hipLaunchKernelGGL(kernel, dim3((blocks * splits + 7) / 8 * 8), dim3(256), 3 * kBuf, s, x, zeros, H, cin, dz, cout, px_tiles, splits, out);
   return hipGetLastError();
 }
 
@@ -1339,7 +1368,10 @@ ConvWgradPlan conv_wgrad_plan(int pixels, int cin, int cout) {
 // most partial sums either matrix-core wgrad kernel may write for this layer
 int conv_mfma_wgrad_max_splits(int pixels, int cin, int cout) {
   const int c8 = cin <= 8 && cout % 64 == 0 ? std::max(1, std::min(pixels / 128, 512 / (cout / 64))) : 1;
-  return std::max({conv_wgrad_plan(pixels, cin, cout).splits, wgrad_patch_splits(pixels / kWgradBM, cin, cout), c8});
+  // the patch kernel's room is that of ranges for every CU whose workgroups take all nine taps, which is what stages have had and what
+  // decides whether their sums are put off; a row of taps each needs a third
+  const int patch = (int)std::max(1l, std::min<long>(pixels / kWgradBM, 256 / std::max(1l, (long)(cin / 64) * (cout / 64))));
+  return std::max({conv_wgrad_plan(pixels, cin, cout).splits, wgrad_patch_splits(pixels / kWgradBM, cin, cout), patch, c8});
 }
 
 // Gathered fprop / dgrad: the largest tile that still gives every CU a workgroup, else the smallest.
@@ -1370,7 +1402,7 @@ hipError_t conv_mfma_fprop(hipStream_t s, int imgs, int H, int W, int stride, in
   }
   const int P = imgs * H * W;
   {
-    const PatchDesc pd = patch_desc(x, zeros, H, W, cin, cin / 8, 0);
+    const PatchDesc pd = patch_desc(x, zeros, H, W, cin);
     const hipError_t err = launch_patch_conv<false>(s, P, H, W, cin, cout, pd, bd, e);
     if (err != hipErrorNotSupported) return err;
   }
@@ -1404,7 +1436,7 @@ hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, in
     return launch_conv<64, 64, 4, RowGatherS2<64, 4>, PlainS2<64, 4>>(s, Pc, cin, KT, 4, 1, ad, bd, e2);
   }
   {
-    const PatchDesc pd = patch_desc(dz, zeros, H, W, cout, cout / 8, 0);
+    const PatchDesc pd = patch_desc(dz, zeros, H, W, cout);
     EpiDgrad es = e;
     const int rows = sums ? conv_mfma_dgrad_sum_rows(imgs, H, W, stride, cin, cout) : 0;
     if (rows) es.sums = sums;  // pixel tiles and blocks of 64 channels are always whole here
@@ -1438,15 +1470,15 @@ hipError_t conv_mfma_wgrad(hipStream_t s, int imgs, int H, int W, int stride, in
   if (wgrad_patch_ok(H, W)) {
     const int px_tiles = P / kWgradBM;
     const int splits = wgrad_patch_splits(px_tiles, cin, cout);
-    const PatchDesc xd = patch_desc(x, zeros, H, W, cin, 8, 1);
     float* to = splits > 1 ? partial : gW;
     hipError_t err;
     switch (W) {
-      case 16: err = launch_wgrad_patch<16>(s, xd, dz, cout, px_tiles, splits, to); break;
-      case 32: err = launch_wgrad_patch<32>(s, xd, dz, cout, px_tiles, splits, to); break;
-      case 64: err = launch_wgrad_patch<64>(s, xd, dz, cout, px_tiles, splits, to); break;
-      case 128: err = launch_wgrad_patch<128>(s, xd, dz, cout, px_tiles, splits, to); break;
-      default: err = launch_wgrad_patch<0>(s, xd, dz, cout, px_tiles, splits, to);
+      case 8: err = launch_wgrad_patch<8>(s, x, zeros, H, cin, dz, cout, px_tiles, splits, to); break;
+      case 16: err = launch_wgrad_patch<16>(s, x, zeros, H, cin, dz, cout, px_tiles, splits, to); break;
+      case 32: err = launch_wgrad_patch<32>(s, x, zeros, H, cin, dz, cout, px_tiles, splits, to); break;
+      case 64: err = launch_wgrad_patch<64>(s, x, zeros, H, cin, dz, cout, px_tiles, splits, to); break;
+      case 128: err = launch_wgrad_patch<128>(s, x, zeros, H, cin, dz, cout, px_tiles, splits, to); break;
+      default: return hipErrorInvalidValue;
     }
     if (err != hipSuccess || splits == 1) return err;
     return launch_sum_partials(s, count, splits, partial, gW);

@@ -134,6 +134,15 @@ def test_patch_weight_gradients(imgs, h, w, cin, cout):
     _weight_gradient(imgs, h, w, cin, cout, 1)
 
 
+@pytest.mark.parametrize("imgs,h,w,cin,cout", [
+    (64, 16, 16, 256, 256),     # 26 tiles and 25 per workgroup: sums put aside three times, the last of fewer tiles
+    (17, 8, 16, 64, 64), (1, 8, 16, 64, 192),           # fewer tiles than ranges; one tile
+    (1, 8, 16, 640, 640),       # more blocks than CUs: one range
+])
+def test_patch_weight_gradients_by_rows_of_taps(imgs, h, w, cin, cout):
+    _weight_gradient(imgs, h, w, cin, cout, 1)
+
+
 def _weight_gradient(imgs, h, w, cin, cout, stride):
     from synth_inputs import round_bf16
     from test_gpu_gemm_any import _conv_reference, _rel, _run, _stage, _sum_tol
