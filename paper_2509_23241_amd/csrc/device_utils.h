@@ -55,15 +55,19 @@ struct GeluParts {
   float cdf;  // Phi(z) = 0.5 (1 + erf(z/sqrt 2))
   float pdf;  // phi(z) = exp(-z^2/2)/sqrt(2 pi)
 };
+// 1/2 and log2(e) are folded into the coefficients.  t is the hardware's reciprocal after one Newton step, for which x must
+// be finite (from 64 on exp(-z^2/2) is zero anyway): 21 vector instructions, 31 with a division, and as far off fp64 (z in
+// -9 .. 9: act 9.29e-8, act' 4.19e-8 rms).  With one branch for
+// eight values instead of one each, 1600 x 2048 over 512 forward 15.4 -> 13.0 us.
 __device__ __forceinline__ GeluParts gelu_parts(float z) {
-  const float x = fabsf(z) * 0.70710678118654752f;
-  const float t = __frcp_rn(fmaf(0.3275911f, x, 1.0f));
-  const float e = __expf(-0.5f * z * z);
-  float poly = fmaf(1.061405429f, t, -1.453152027f);
-  poly = fmaf(poly, t, 1.421413741f);
-  poly = fmaf(poly, t, -0.284496736f);
-  poly = fmaf(poly, t, 0.254829592f);
-  const float half_erfc = 0.5f * poly * t * e;        // 0.5 * (1 - erf(x))
+  const float q = fmaf(0.3275911f, fminf(fabsf(z), 64.f) * 0.70710678118654752f, 1.0f);
+  const float r = __builtin_amdgcn_rcpf(q), t = fmaf(fmaf(-q, r, 1.0f), r, r);
+  const float e = __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
+  float poly = fmaf(0.5307027145f, t, -0.7265760135f);
+  poly = fmaf(poly, t, 0.7107068705f);
+  poly = fmaf(poly, t, -0.142248368f);
+  poly = fmaf(poly, t, 0.127414796f);
+  const float half_erfc = poly * t * e;               // 0.5 * (1 - erf(x))
   GeluParts g;
   g.cdf = z >= 0.f ? 1.0f - half_erfc : half_erfc;
   g.pdf = 0.39894228040143268f * e;
@@ -88,18 +92,20 @@ __device__ __forceinline__ ActPair act_pair_fast(float z, int act) {
   }
   return p;
 }
-__device__ __forceinline__ float act_forward_fast(float z, int act) {
-  if (act == 1) return fmaxf(z, 0.f);
-  if (act == 2) return z * gelu_parts(z).cdf;
-  return z;
-}
-__device__ __forceinline__ float act_derivative_fast(float z, int act) {
-  if (act == 1) return z > 0.f ? 1.f : 0.f;
-  if (act == 2) {
-    const GeluParts g = gelu_parts(z);
-    return fmaf(z, g.pdf, g.cdf);
-  }
-  return 1.f;
+// N values at once: one branch on the activation for all of them, so that their exponentials and reciprocals overlap.
+template <int N>
+__device__ __forceinline__ void act_pairs_fast(const float (&z)[N], int act, float (&a)[N], float (&d)[N]) {
+  auto each = [&](int kind) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const ActPair p = act_pair_fast(z[j], kind);
+      a[j] = p.a;
+      d[j] = p.d;
+    }
+  };
+  if (act == 2) each(2);
+  else if (act == 1) each(1);
+  else each(0);
 }
 
 // Column sums of what the 256 threads of a block have added up, N neighbouring columns per thread, thread t those of unit

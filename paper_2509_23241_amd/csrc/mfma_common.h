@@ -53,11 +53,8 @@ struct EpiFpropT {
     const float b[8] = {c.b0.x, c.b0.y, c.b0.z, c.b0.w, c.b1.x, c.b1.y, c.b1.z, c.b1.w};
     float a[8], d[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const ActPair p = act_pair_fast(v[j] + b[j], act);
-      a[j] = p.a;
-      d[j] = p.d;
-    }
+    for (int j = 0; j < 8; ++j) v[j] += b[j];
+    act_pairs_fast(v, act, a, d);
     if constexpr (ADD) {
       const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
@@ -77,10 +74,19 @@ struct EpiFpropT {
     const size_t i = (size_t)m * ldc + n;
     if (count == 4 && (ldc & 3) == 0 && wide && !ADD) {
       const float4 b = *reinterpret_cast<const float4*>(bias + n);
-      const ActPair p0 = act_pair(v0 + b.x, act), p1 = act_pair(v1 + b.y, act);
-      const ActPair p2 = act_pair(v2 + b.z, act), p3 = act_pair(v3 + b.w, act);
-      if (d_out) *reinterpret_cast<uint2*>(d_out + i) = make_uint2(pack_bf16x2(p0.d, p1.d), pack_bf16x2(p2.d, p3.d));
-      *reinterpret_cast<uint2*>(a_out + i) = make_uint2(pack_bf16x2(p0.a, p1.a), pack_bf16x2(p2.a, p3.a));
+      const float z[4] = {v0 + b.x, v1 + b.y, v2 + b.z, v3 + b.w};
+      float a[4], d[4];
+      if constexpr (EXACT) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          a[j] = act_forward(z[j], act);
+          d[j] = act_derivative(z[j], act);
+        }
+      } else {
+        act_pairs_fast(z, act, a, d);
+      }
+      if (d_out) *reinterpret_cast<uint2*>(d_out + i) = make_uint2(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]));
+      *reinterpret_cast<uint2*>(a_out + i) = make_uint2(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));
     } else {
       const float v[4] = {v0, v1, v2, v3};
       for (int j = 0; j < count; ++j) {
