@@ -108,6 +108,20 @@ __device__ __forceinline__ void act_pairs_fast(const float (&z)[N], int act, flo
   else each(0);
 }
 
+// Handing values from the workgroups of a launch to the one of them that finishes last.  A device-wide fence writes back and
+// invalidates a whole L2, once per wave; what is handed over here goes past the L2s instead (relaxed atomics of device scope), and
+// a workgroup counts itself in once its own values have arrived.
+__device__ __forceinline__ void publish(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float published(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// By one thread, behind the publish() calls of its wave alone.  True for the last of `arrivals` calls, which leaves the counter at
+// zero, as it has to be before the first.
+__device__ __forceinline__ bool last_to_arrive(uint32_t* counter, uint32_t arrivals) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != arrivals - 1) return false;
+  __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+
 // Column sums of what the 256 threads of a block have added up, N neighbouring columns per thread, thread t those of unit
 // t % units (units divides 256): out[N * units], in a fixed order.  `sm` holds N * 256 floats.
 template <int N>

@@ -86,9 +86,9 @@ hipError_t launch_act_backward_colsum(hipStream_t s, int elt, int M, int N, cons
 hipError_t launch_copy(hipStream_t s, const void* src, void* dst, size_t bytes);
 
 // Softmax cross-entropy over `rows` rows of `classes` logits; dlogits = (softmax-onehot)/rows,
-// *loss = mean of the row losses.  row_loss: scratch of `rows` floats.
+// *loss = mean of the row losses.  row_loss: scratch of `rows` floats; counter: zero before the launch and after it.
 hipError_t launch_softmax_ce(hipStream_t s, int elt, int rows, int classes, const void* logits,
-                             const int32_t* labels, void* dlogits, float* row_loss, float* loss);
+                             const int32_t* labels, void* dlogits, float* row_loss, uint32_t* counter, float* loss);
 
 // fp32 -> elt conversion of `count` elements (compute copy of a weight version).
 hipError_t launch_convert(hipStream_t s, int elt, size_t count, const float* src, void* dst);
@@ -116,6 +116,7 @@ struct UpdateArgs {
   float lr, mu, alpha, beta;
   float* partials;
   double* diag;
+  uint32_t* counter;  // zero before the launch and after it; null: the diagnostics are added up by a launch of their own
 };
 hipError_t launch_update(hipStream_t s, int elt, const UpdateArgs& a);
 size_t update_scratch_floats();

@@ -68,18 +68,31 @@ struct Store4<uint16_t> {
 // kThreads*kUnroll float4 per stream and issues all its loads (kUnroll per stream per lane, 16
 // bytes each) before the first dependent instruction, so that each lane keeps up to 16 loads in
 // flight; the fp32 streams that are not re-read soon (momentum, new master weights) bypass the
-// caches with non-temporal accesses.
+// caches with non-temporal accesses.  With a counter the block that arrives last also adds up the
+// diagnostics of all blocks.
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// Final, fixed-order reduction of the per-block partials into doubles: wave k sums quantity k.
+__device__ __forceinline__ void diag_reduce(const float* partials, int nblocks, double* __restrict__ diag) {
+  const int lane = threadIdx.x & 63, k = threadIdx.x >> 6;
+  double s = 0.0;
+#pragma unroll 8
+  for (int i = lane; i < nblocks; i += 64) s += (double)published(partials + k * kUpdateBlocks + i);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane == 0) diag[k] = s;
+}
 
 template <typename T, bool BLEND, bool WFWD>
 __global__ __launch_bounds__(kThreads) void update_kernel(size_t n4, const floatx4* __restrict__ g,
                                                           floatx4* __restrict__ m, const floatx4* w_old,
                                                           floatx4* w_new, const floatx4* __restrict__ w_stale,
                                                           T* __restrict__ wfwd, T* __restrict__ wb, float lr,
-                                                          float mu, float alpha, float beta,
-                                                          float* __restrict__ partials) {
+                                                          float mu, float alpha, float beta, float* partials,
+                                                          uint32_t* counter, double* __restrict__ diag) {
   __shared__ float red[4 * 4];
+  __shared__ int finishes;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};  // g^2, w^2, drift^2, wb^2
   const size_t chunk = (size_t)kThreads * kUnroll;
   for (size_t base = (size_t)blockIdx.x * chunk; base < n4; base += (size_t)gridDim.x * chunk) {
@@ -132,20 +145,18 @@ __global__ __launch_bounds__(kThreads) void update_kernel(size_t n4, const float
   block_sum<4>(acc, red);
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) partials[k * kUpdateBlocks + blockIdx.x] = acc[k];
+    for (int k = 0; k < 4; ++k) publish(partials + k * kUpdateBlocks + blockIdx.x, acc[k]);
+    finishes = counter && last_to_arrive(counter, gridDim.x);
   }
+  if (!counter) return;
+  __syncthreads();
+  if (finishes) diag_reduce(partials, gridDim.x, diag);
 }
 
-// Final, fixed-order reduction of the per-block partials into doubles: wave k sums quantity k.
-__global__ __launch_bounds__(kThreads) void diag_reduce_kernel(const float* __restrict__ partials, int nblocks,
-                                                               double* __restrict__ diag) {
-  const int lane = threadIdx.x & 63, k = threadIdx.x >> 6;
-  double s = 0.0;
-#pragma unroll 8
-  for (int i = lane; i < nblocks; i += 64) s += (double)partials[k * kUpdateBlocks + i];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (lane == 0) diag[k] = s;
+// The same from a launch of its own: for more than kCountedBlocks blocks, and for partials in the library's array, where a counter
+// could be shared by updates on two streams.
+__global__ __launch_bounds__(kThreads) void diag_reduce_kernel(const float* partials, int nblocks, double* __restrict__ diag) {
+  diag_reduce(partials, nblocks, diag);
 }
 
 template <typename T>
@@ -220,54 +231,10 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(size_t nvec, const uint4
   for (size_t i = tid; i < tail_bytes; i += stride) tdst[i] = tsrc[i];
 }
 
-// One wave per row.  The first 16 values of a lane (rows of up to 1024 classes: all of them) are loaded together and kept
-// in registers for the three passes over the row; fetched again in every pass, one memory latency per 64 classes, 400 rows
-// of 1000 classes took 12.2 us.
-constexpr int kHeld = 16;
-template <typename T>
-__global__ __launch_bounds__(kThreads) void softmax_ce_kernel(int rows, int classes, const T* __restrict__ logits,
-                                                              const int32_t* __restrict__ labels,
-                                                              T* __restrict__ dlogits, float* __restrict__ row_loss) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const T* lg = logits + (size_t)row * classes;
-  const int label = labels[row];
-  // a label outside the classes has no logit: the loss says so instead of keeping what lay there
-  if (lane == 0 && (unsigned)label >= (unsigned)classes) row_loss[row] = __builtin_nanf("");
-  float v[kHeld];
-#pragma unroll
-  for (int i = 0; i < kHeld; ++i) v[i] = lane + 64 * i < classes ? to_float(lg[lane + 64 * i]) : -INFINITY;
-  float mx = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < kHeld; ++i) mx = fmaxf(mx, v[i]);
-  for (int c = lane + 64 * kHeld; c < classes; c += 64) mx = fmaxf(mx, to_float(lg[c]));
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  float sum = 0.f;
-#pragma unroll
-  for (int i = 0; i < kHeld; ++i)
-    if (lane + 64 * i < classes) sum += expf(v[i] - mx);
-  for (int c = lane + 64 * kHeld; c < classes; c += 64) sum += expf(to_float(lg[c]) - mx);
-  sum = wave_sum(sum);
-  const float lse = logf(sum);
-  const float inv_rows = 1.0f / (float)rows;
-  T* dl = dlogits + (size_t)row * classes;
-  auto put = [&](int c, float z) {
-    const float p = expf(z - mx - lse);
-    dl[c] = from_float<T>((p - (c == label ? 1.f : 0.f)) * inv_rows);
-    if (c == label) row_loss[row] = -(z - mx - lse);
-  };
-#pragma unroll
-  for (int i = 0; i < kHeld; ++i)
-    if (lane + 64 * i < classes) put(lane + 64 * i, v[i]);
-  for (int c = lane + 64 * kHeld; c < classes; c += 64) put(c, to_float(lg[c]));
-}
-
-__global__ __launch_bounds__(kThreads) void mean_kernel(const float* __restrict__ v, int count, float* __restrict__ out) {
-  __shared__ double sm[kThreads];
+// (double) mean of `count` published values, by all threads of a block
+__device__ __forceinline__ void block_mean(const float* v, int count, double* sm /* [kThreads] */, float* __restrict__ out) {
   double s = 0.0;
-  for (int i = threadIdx.x; i < count; i += kThreads) s += (double)v[i];
+  for (int i = threadIdx.x; i < count; i += kThreads) s += (double)published(v + i);
   sm[threadIdx.x] = s;
   __syncthreads();
   for (int w = kThreads / 2; w > 0; w >>= 1) {
@@ -275,6 +242,69 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const float* __restrict_
     __syncthreads();
   }
   if (threadIdx.x == 0) *out = (float)(sm[0] / (double)count);
+}
+
+// One wave per row.  The first 16 values of a lane (rows of up to 1024 classes: all of them) are loaded together and kept
+// in registers for the three passes over the row; the loads are unconditional (lanes past the last class repeat it), since behind
+// a condition each waits for the one before (400 rows of 1000 classes 10.6 -> 5.5 us).  With a counter the block that arrives last
+// forms the mean of the row losses (with it 8.0 us, and 2.7 for a launch of its own).
+constexpr int kHeld = 16;
+template <typename T>
+__global__ __launch_bounds__(kThreads) void softmax_ce_kernel(int rows, int classes, const T* __restrict__ logits,
+                                                              const int32_t* __restrict__ labels,
+                                                              T* __restrict__ dlogits, float* row_loss, uint32_t* counter,
+                                                              float* __restrict__ loss) {
+  __shared__ double sm[kThreads];
+  __shared__ int finishes;
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (row < rows) {
+    const T* lg = logits + (size_t)row * classes;
+    T held[kHeld];
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) held[i] = lg[64 * i < classes ? min(lane + 64 * i, classes - 1) : 0];
+    const int label = labels[row];
+    // a label outside the classes has no logit: the loss says so instead of keeping what lay there
+    if (lane == 0 && (unsigned)label >= (unsigned)classes) publish(row_loss + row, __builtin_nanf(""));
+    float v[kHeld];
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) v[i] = lane + 64 * i < classes ? to_float(held[i]) : -INFINITY;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) mx = fmaxf(mx, v[i]);
+    for (int c = lane + 64 * kHeld; c < classes; c += 64) mx = fmaxf(mx, to_float(lg[c]));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i)
+      if (lane + 64 * i < classes) sum += expf(v[i] - mx);
+    for (int c = lane + 64 * kHeld; c < classes; c += 64) sum += expf(to_float(lg[c]) - mx);
+    sum = wave_sum(sum);
+    const float lse = logf(sum);
+    const float inv_rows = 1.0f / (float)rows;
+    T* dl = dlogits + (size_t)row * classes;
+    auto put = [&](int c, float z) {
+      const float p = expf(z - mx - lse);
+      dl[c] = from_float<T>((p - (c == label ? 1.f : 0.f)) * inv_rows);
+      if (c == label) publish(row_loss + row, -(z - mx - lse));
+    };
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i)
+      if (lane + 64 * i < classes) put(lane + 64 * i, v[i]);
+    for (int c = lane + 64 * kHeld; c < classes; c += 64) put(c, to_float(lg[c]));
+  }
+  if (!counter) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's row loss has arrived
+  __syncthreads();
+  if (threadIdx.x == 0) finishes = last_to_arrive(counter, gridDim.x);
+  __syncthreads();
+  if (finishes) block_mean(row_loss, rows, sm, loss);
+}
+
+__global__ __launch_bounds__(kThreads) void mean_kernel(const float* v, int count, float* __restrict__ out) {
+  __shared__ double sm[kThreads];
+  block_mean(v, count, sm, out);
 }
 
 // Both in one workgroup, for few rows of at most 16 classes: 16 lanes per row, one value each, the values of the two kernels above
@@ -320,6 +350,11 @@ __global__ __launch_bounds__(kSmallThreads) void softmax_ce_small_kernel(int row
   if (threadIdx.x == 0) *loss = (float)(sm[0] / (double)rows);
 }
 
+// Workgroups that still count themselves in on one counter, about 10 ns each; above that a launch of its own adds up what they
+// left.  us of the update kernel with the counter, and without plus that launch (and what a launch takes the host): 65
+// workgroups 5.9 and 4.1 + 1.5, 127 6.6 and 4.7 + 1.8, 257 9.3 and 4.8 + 2.6, 1025 20.2 and 10.9 + 4.0.
+constexpr int kCountedBlocks = 128;
+
 inline int stream_blocks(size_t work_items, int max_blocks) {
   size_t b = (work_items + kThreads - 1) / kThreads;
   if (b < 1) b = 1;
@@ -339,15 +374,16 @@ hipError_t update_dispatch(hipStream_t s, const UpdateArgs& a) {
   T* wb = (T*)a.wb;
   const bool blend = a.w_stale != nullptr && a.wb != nullptr;
   const bool wfwd = a.wfwd != nullptr;
+  uint32_t* counter = blocks <= kCountedBlocks ? a.counter : nullptr;
 #define TP_LAUNCH_UPDATE(B, F) \
-  hipLaunchKernelGGL((update_kernel<T, B, F>), dim3(blocks), dim3(kThreads), 0, s, n4, g, m, wo, wn, ws, wf, wb, a.lr, a.mu, a.alpha, a.beta, a.partials)
+  hipLaunchKernelGGL((update_kernel<T, B, F>), dim3(blocks), dim3(kThreads), 0, s, n4, g, m, wo, wn, ws, wf, wb, a.lr, a.mu, a.alpha, a.beta, a.partials, counter, a.diag)
   if (blend && wfwd) TP_LAUNCH_UPDATE(true, true);
   else if (blend) TP_LAUNCH_UPDATE(true, false);
   else if (wfwd) TP_LAUNCH_UPDATE(false, true);
   else TP_LAUNCH_UPDATE(false, false);
 #undef TP_LAUNCH_UPDATE
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || counter) return e;
   hipLaunchKernelGGL(diag_reduce_kernel, dim3(1), dim3(kThreads), 0, s, a.partials, blocks, a.diag);
   return hipGetLastError();
 }
@@ -446,7 +482,7 @@ hipError_t launch_copy(hipStream_t s, const void* src, void* dst, size_t bytes) 
 }
 
 hipError_t launch_softmax_ce(hipStream_t s, int elt, int rows, int classes, const void* logits, const int32_t* labels,
-                             void* dlogits, float* row_loss, float* loss) {
+                             void* dlogits, float* row_loss, uint32_t* counter, float* loss) {
   if (classes <= kSmallClasses && rows <= kSmallRows) {
     if (elt == ELT_BF16)
       hipLaunchKernelGGL(softmax_ce_small_kernel<uint16_t>, dim3(1), dim3(kSmallThreads), 0, s, rows, classes,
@@ -457,14 +493,15 @@ hipError_t launch_softmax_ce(hipStream_t s, int elt, int rows, int classes, cons
     return hipGetLastError();
   }
   const int blocks = (rows + 3) / 4;
+  if (blocks > kCountedBlocks) counter = nullptr;
   if (elt == ELT_BF16)
     hipLaunchKernelGGL(softmax_ce_kernel<uint16_t>, dim3(blocks), dim3(kThreads), 0, s, rows, classes,
-                       (const uint16_t*)logits, labels, (uint16_t*)dlogits, row_loss);
+                       (const uint16_t*)logits, labels, (uint16_t*)dlogits, row_loss, counter, loss);
   else
     hipLaunchKernelGGL(softmax_ce_kernel<float>, dim3(blocks), dim3(kThreads), 0, s, rows, classes,
-                       (const float*)logits, labels, (float*)dlogits, row_loss);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+                       (const float*)logits, labels, (float*)dlogits, row_loss, counter, loss);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || counter) return e;
   hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kThreads), 0, s, row_loss, rows, loss);
   return hipGetLastError();
 }

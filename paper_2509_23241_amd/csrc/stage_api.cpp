@@ -498,6 +498,10 @@ struct tp_stage {
     const uintptr_t p = (uintptr_t)bufs.scratch_dev + 3 * plan.dz_bytes + (plan.partial_floats + plan.deferred_floats + TP_MAX_FORWARD_STREAMS * plan.fwd2_floats) * 4;
     return (const void*)((p + 255) & ~(uintptr_t)255);
   }
+  // Counters of the kernels whose last workgroup finishes what all have formed, zero between launches: the second half of the
+  // block of zeros, of which padding reads the first 128 bytes.
+  enum Counter { kCountUpdate, kCountLoss };
+  uint32_t* counter(Counter c) const { return (uint32_t*)((char*)zeros() + 128) + c; }
   void* attn_scratch() const { return plan.attn_scratch_bytes ? (char*)zeros() + 256 : nullptr; }
   // drop a version that nobody needs any more
   void evict_if_unused(uint64_t v) {
@@ -694,7 +698,7 @@ int stage_init(const tp_stage_desc* desc, const tp_buffers* bufs, void* hip_stre
       delete st;
       return fail(TP_EINVAL, "null device buffer");
     }
-    {  // the block of zeros that convolution padding reads
+    {  // the block of zeros that convolution padding reads, and the counters behind it
       hipError_t e = hipMemsetAsync((void*)st->zeros(), 0, 256, st->stream);
       if (e != hipSuccess) { delete st; return fail(TP_EHIP, "memset: %s", hipGetErrorString(e)); }
     }
@@ -1091,7 +1095,7 @@ int stage_loss_softmax_ce(tp_stage* st, uint64_t mb_id, const void* logits_dev, 
   const int classes = st->plan.layers.back().d.out_features;
   ProfScope ps(st, TP_K_LOSS);
   HIP_TRY(tp::launch_softmax_ce(st->stream, st->desc.dtype, rows, classes, logits_dev, labels_dev, dlogits_dev,
-                                st->partials(), loss_dev));
+                                st->partials(), st->counter(tp_stage::kCountLoss), loss_dev));
   return TP_OK;
 }
 
@@ -1511,8 +1515,9 @@ int stage_backward_on(tp_stage* st, uint64_t mb_id, uint64_t version, const void
 
 namespace {
 // The update (Section "Pipeline Parallelism": after every mini-batch) with the look-ahead blend (Eq. 1-2);
-// `partials`: where the update kernel leaves the block partials of its diagnostics.
-int blend_update_impl(tp_stage* st, uint64_t mb_id_done, uint64_t mb_id_next_bwd, uint64_t* new_version, float* partials) {
+// `partials`: where the update kernel leaves the block partials of its diagnostics; `counter`: see UpdateArgs.
+int blend_update_impl(tp_stage* st, uint64_t mb_id_done, uint64_t mb_id_next_bwd, uint64_t* new_version, float* partials,
+                      uint32_t* counter) {
   const tp_stage_desc& d = st->desc;
   if (!st->grad_pending || st->grad_mb != mb_id_done)
     return fail(TP_ESTATE, "no gradient of mini-batch %llu is pending", (unsigned long long)mb_id_done);
@@ -1558,6 +1563,7 @@ int blend_update_impl(tp_stage* st, uint64_t mb_id_done, uint64_t mb_id_next_bwd
     u.beta = (float)b;
     u.partials = partials;
     u.diag = (double*)st->bufs.diag_dev;
+    u.counter = counter;
     ProfScope ps(st, TP_K_UPDATE);
     HIP_TRY(tp::launch_update(st->stream, d.dtype, u));
   }
@@ -1582,7 +1588,8 @@ extern "C" {
 
 int stage_blend_update(tp_stage* st, uint64_t mb_id_done, uint64_t mb_id_next_bwd, uint64_t* new_version) {
   if (!st) return fail(TP_EINVAL, "null stage");
-  return blend_update_impl(st, mb_id_done, mb_id_next_bwd, new_version, st->dry ? nullptr : st->partials());
+  return blend_update_impl(st, mb_id_done, mb_id_next_bwd, new_version, st->dry ? nullptr : st->partials(),
+                           st->dry ? nullptr : st->counter(tp_stage::kCountUpdate));
 }
 
 int stage_blend_update_noalloc(tp_stage* st, uint64_t mb_id_done, uint64_t mb_id_next_bwd, uint64_t* new_version) {
@@ -1597,7 +1604,7 @@ int stage_blend_update_noalloc(tp_stage* st, uint64_t mb_id_done, uint64_t mb_id
     if (e != hipSuccess) return fail(TP_EHIP, "address of the library's scratch array: %s", hipGetErrorString(e));
     if (floats < tp::update_scratch_floats()) return fail(TP_EINVAL, "the library's scratch array is too small");
   }
-  return blend_update_impl(st, mb_id_done, mb_id_next_bwd, new_version, partials);
+  return blend_update_impl(st, mb_id_done, mb_id_next_bwd, new_version, partials, nullptr);
 }
 
 int stage_query(const tp_stage* st, tp_state* out) {
