@@ -228,6 +228,11 @@ int stage_destroy(tp_stage* st);
 int stage_forward(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_dev, void* y_dev,
                   uint64_t* version_used);
 
+/* All n micro-batches of mini-batch mb_id, none of which has been forwarded yet: x_dev and y_dev hold [n*mb x ...], micro-batch by
+ * micro-batch.  What n calls of stage_forward do, with the same saved tensors; stages of dense, normalisation (per token)
+ * and residual layers without forward streams take one kernel per layer for all of them. */
+int stage_forward_minibatch(tp_stage* st, uint64_t mb_id, const void* x_dev, void* y_dev, uint64_t* version_used);
+
 /* TP_TIMEPREST only: stage_forward on `version` (which must be in the ring: pin it with stash_push when the
  * pass starts) instead of the latest one.  TP_EINVAL under any other policy, TP_ENOVERSION if the ring does
  * not hold the version. */

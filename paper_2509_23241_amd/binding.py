@@ -22,7 +22,7 @@ POLICY = {"latest": TP_LATEST, "eq1": TP_INTERMEDIATE_EQ1, "convex": TP_INTERMED
 ACT = {"none": TP_ACT_NONE, "relu": TP_ACT_RELU, "gelu": TP_ACT_GELU}
 DTYPE = {"f32": TP_F32, "bf16": TP_BF16}
 
-EXPORTS = ["stage_workspace_query", "stage_init", "stage_destroy", "stage_set_forward_streams", "stage_forward_join", "stage_forward", "stage_forward_on", "stage_backward_on", "stage_input_ptr", "stage_saved_input_ptr",
+EXPORTS = ["stage_workspace_query", "stage_init", "stage_destroy", "stage_set_forward_streams", "stage_forward_join", "stage_forward", "stage_forward_minibatch", "stage_forward_on", "stage_backward_on", "stage_input_ptr", "stage_saved_input_ptr",
            "stage_loss_softmax_ce", "stage_backward", "stage_blend_update", "stage_blend_update_noalloc", "stash_push", "stash_evict",
            "stage_query", "stage_export_params", "tp_blend_coefficients", "tp_schedule_events", "tp_schedule_microbatch_events",
            "stage_profile_begin", "stage_profile_end", "tp_last_error"]
@@ -99,6 +99,7 @@ lib.stage_workspace_query.argtypes = [C.POINTER(tp_stage_desc), C.POINTER(tp_siz
 lib.stage_init.argtypes = [C.POINTER(tp_stage_desc), C.POINTER(tp_buffers), _vp, C.POINTER(_vp)]
 lib.stage_destroy.argtypes = [_vp]
 lib.stage_forward.argtypes = [_vp, _u64, _u32, _vp, _vp, C.POINTER(_u64)]
+lib.stage_forward_minibatch.argtypes = [_vp, _u64, _vp, _vp, C.POINTER(_u64)]
 lib.stage_forward_on.argtypes = [_vp, _u64, _u32, _u64, _vp, _vp]
 lib.stage_backward_on.argtypes = [_vp, _u64, _u64, _vp, _vp]
 lib.stage_input_ptr.argtypes = [_vp, _u64, _u32, C.POINTER(_vp)]
@@ -278,6 +279,12 @@ def stage_forward(st, mb_id: int, ub_idx: int, x_dev: int, y_dev: int) -> int:
     rc = _stage_forward(st, mb_id, ub_idx, x_dev, y_dev, _byref(v))
     if rc:
         _check(rc)
+    return v.value
+
+
+def stage_forward_minibatch(st, mb_id: int, x_dev: int, y_dev: int) -> int:
+    v = _u64()
+    _check(lib.stage_forward_minibatch(st, mb_id, x_dev, y_dev, _byref(v)))
     return v.value
 
 

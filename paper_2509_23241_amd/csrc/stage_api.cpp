@@ -853,8 +853,16 @@ int old_version_copy(tp_stage* st, uint64_t v, int slot, const char** out) {
   return TP_OK;
 }
 
-// `version`: TP_NONE = the latest version at the stage (every policy); a retained version under TP_TIMEPREST
-int forward_impl(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_dev, void* y_dev, uint64_t version,
+// Stages whose forward pass treats every sample apart with one kernel per layer: several micro-batches can pass in one call.
+bool row_by_row(const tp_stage* st) {
+  for (const LayerPlan& lp : st->plan.layers)
+    if (lp.d.type != TP_LAYER_DENSE && lp.d.type != TP_LAYER_LAYERNORM && lp.d.type != TP_LAYER_RESIDUAL) return false;
+  return st->fwd_streams == 0;
+}
+
+// `version`: TP_NONE = the latest version at the stage (every policy); a retained version under TP_TIMEPREST.
+// `ubs`: micro-batches from ub_idx on, whose rows lie one behind the other in x_dev and y_dev (more than one: row_by_row stages).
+int forward_impl(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, uint32_t ubs, const void* x_dev, void* y_dev, uint64_t version,
                  uint64_t* version_used) {
   if (!st->dry && (!x_dev || !y_dev)) return fail(TP_EINVAL, "null activation pointer");
   if (mb_id == TP_NONE) return fail(TP_EINVAL, "reserved mini-batch id");
@@ -882,13 +890,13 @@ int forward_impl(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_de
     st->inflight.push_back(nf);
     f = &st->inflight.back();
   }
-  if (ub_idx != f->forwards || ub_idx >= (uint32_t)d.n)
+  if (ub_idx != f->forwards || ub_idx + ubs > (uint32_t)d.n)
     return fail(TP_ESTATE, "mini-batch %llu: expected micro-batch %u, got %u", (unsigned long long)mb_id, f->forwards, ub_idx);
   if (stashing(d.policy) && f->v_f != st->latest)
     return fail(TP_ESTATE, "an update landed between micro-batches of mini-batch %llu", (unsigned long long)mb_id);
   const uint64_t v = v_read;                           // the latest weights at the stage, unless the pass names its version
   if (version_used) *version_used = v;
-  f->forwards++;
+  f->forwards += ubs;
   if (st->dry) return TP_OK;
 
   const int slot = st->find_slot(v);
@@ -940,8 +948,9 @@ int forward_impl(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_de
         st->slot_event_lost = true;
       }
     }
-  } mark_forward{st, act_q, fsk, fs, (int)ub_idx + streams >= d.n};
+  } mark_forward{st, act_q, fsk, fs, (int)(ub_idx + ubs) - 1 + streams >= d.n};
   const uint64_t row0 = (uint64_t)ub_idx * d.mb;
+  const int mb = d.mb * (int)ubs;
   const int L = d.num_layers;
   for (int l = 0; l < L; ++l) {
     const LayerPlan& lp = st->plan.layers[l];
@@ -956,19 +965,19 @@ int forward_impl(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_de
       // a dense layer followed by a plain residual add: the epilogue of the GEMM adds the kept tensor
       if (l + 1 < L && st->plan.layers[l + 1].d.type == TP_LAYER_RESIDUAL && st->plan.layers[l + 1].d.geom[1] == 1 &&
           st->plan.layers[l + 1].d.act == TP_ACT_NONE &&
-          tp::fprop_add_supported(d.dtype, d.mb * lp.tokens, lp.d.out_features, lp.d.in_features)) {
+          tp::fprop_add_supported(d.dtype, mb * lp.tokens, lp.d.out_features, lp.d.in_features)) {
         const LayerPlan& add = st->plan.layers[l + 1];
         const char* skip = aslot + st->plan.layers[add.skip_layer].x_off + row0 * add.in_elems * es;
         void* add_a = (l + 1 == L - 1) ? y_dev : (void*)(aslot + st->plan.layers[l + 2].x_off + row0 * add.out_elems * es);
         if ((((uintptr_t)skip | (uintptr_t)add_a) & 15) == 0) {
-          HIP_TRY(tp::launch_fprop(fs, d.dtype, d.mb * lp.tokens, lp.d.out_features, lp.d.in_features, x_in,
+          HIP_TRY(tp::launch_fprop(fs, d.dtype, mb * lp.tokens, lp.d.out_features, lp.d.in_features, x_in,
                                    wcopy + lp.w_off * es, master + lp.b_off, lp.d.act, z_out, add_a,
                                    need_copy ? x_saved : nullptr, skip));
           ++l;  // the add is done
           continue;
         }
       }
-      HIP_TRY(tp::launch_fprop(fs, d.dtype, d.mb * lp.tokens, lp.d.out_features, lp.d.in_features, x_in,
+      HIP_TRY(tp::launch_fprop(fs, d.dtype, mb * lp.tokens, lp.d.out_features, lp.d.in_features, x_in,
                                wcopy + lp.w_off * es, master + lp.b_off, lp.d.act, z_out, a_out,
                                need_copy ? x_saved : nullptr));
       continue;
@@ -979,27 +988,27 @@ int forward_impl(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_de
       uint16_t* x8 = (uint16_t*)(aslot + lp.xpad_off) + row0 * px * 8;
       {
         ProfScope ps(st, TP_K_COPY);
-        HIP_TRY(tp::conv_c8_pad(fs, d.mb * px, lp.d.in_features, (const uint16_t*)x_in, x8));
+        HIP_TRY(tp::conv_c8_pad(fs, mb * px, lp.d.in_features, (const uint16_t*)x_in, x8));
       }
       ProfScope ps(st, TP_K_FPROP);
       if (lp.d.geom[2] == 7)
-        HIP_TRY(tp::conv_stem_fprop(fs, d.mb, lp.d.geom[0], lp.d.geom[1], lp.d.in_features, lp.d.out_features, x8,
+        HIP_TRY(tp::conv_stem_fprop(fs, mb, lp.d.geom[0], lp.d.geom[1], lp.d.in_features, lp.d.out_features, x8,
                                     (const uint16_t*)(wcopy + lp.w_off * es), master + lp.b_off, lp.d.act, (uint16_t*)z_out,
                                     (uint16_t*)a_out, (const uint16_t*)st->zeros()));
       else
-        HIP_TRY(tp::conv_c8_fprop(fs, d.mb, lp.d.geom[0], lp.d.geom[1], lp.d.in_features, lp.d.out_features, x8,
+        HIP_TRY(tp::conv_c8_fprop(fs, mb, lp.d.geom[0], lp.d.geom[1], lp.d.in_features, lp.d.out_features, x8,
                                   (const uint16_t*)(wcopy + lp.w_off * es), master + lp.b_off, lp.d.act, (uint16_t*)z_out,
                                   (uint16_t*)a_out, (const uint16_t*)st->zeros()));
       continue;
     }
     if (need_copy) {
       ProfScope ps(st, TP_K_COPY);
-      HIP_TRY(tp::launch_copy(fs, x_dev, x_saved, (size_t)d.mb * lp.in_elems * es));
+      HIP_TRY(tp::launch_copy(fs, x_dev, x_saved, (size_t)mb * lp.in_elems * es));
     }
     if (lp.d.type == TP_LAYER_LAYERNORM) {
       ProfScope ps(st, TP_K_NORM);
       float* stats = (float*)(aslot + lp.stat_off) + row0 * lp.stat_elems;
-      HIP_TRY(tp::launch_layernorm_fwd(fs, d.dtype, (size_t)d.mb * lp.tokens, lp.d.in_features, x_saved,
+      HIP_TRY(tp::launch_layernorm_fwd(fs, d.dtype, (size_t)mb * lp.tokens, lp.d.in_features, x_saved,
                                        master + lp.w_off, master + lp.b_off, a_out, stats));
       continue;
     }
@@ -1007,7 +1016,7 @@ int forward_impl(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_de
       ProfScope ps(st, TP_K_ATTN);
       float* lse = (float*)(aslot + lp.stat_off) + row0 * lp.stat_elems;
       const int heads = lp.d.geom[1];
-      HIP_TRY(tp::launch_attention_fwd(fs, d.dtype, d.mb, lp.tokens, heads, lp.d.out_features / heads, x_saved, a_out,
+      HIP_TRY(tp::launch_attention_fwd(fs, d.dtype, mb, lp.tokens, heads, lp.d.out_features / heads, x_saved, a_out,
                                        lse, st->attn_scratch(), st->plan.attn_scratch_bytes));
       continue;
     }
@@ -1017,9 +1026,9 @@ int forward_impl(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_de
       ProfScope ps(st, TP_K_ADD);
       const char* skip = aslot + st->plan.layers[lp.skip_layer].x_off + row0 * lp.in_elems * es;
       if (lp.d.act == TP_ACT_NONE)
-        HIP_TRY(tp::launch_add(fs, d.dtype, (size_t)d.mb * lp.in_elems, x_saved, skip, a_out));
+        HIP_TRY(tp::launch_add(fs, d.dtype, (size_t)mb * lp.in_elems, x_saved, skip, a_out));
       else
-        HIP_TRY(tp::launch_add_act(fs, d.dtype, (size_t)d.mb * lp.in_elems, x_saved, skip, lp.d.act, a_out, z_out));
+        HIP_TRY(tp::launch_add_act(fs, d.dtype, (size_t)mb * lp.in_elems, x_saved, skip, lp.d.act, a_out, z_out));
       continue;
     }
     if (lp.d.type == TP_LAYER_BATCHNORM) {
@@ -1029,37 +1038,37 @@ int forward_impl(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_de
       // a normalisation without activation followed by a residual add: one kernel forms act(bn(x) + kept tensor)
       // and act' of it, written where the add would have written them
       if (l + 1 < L && lp.d.act == TP_ACT_NONE && st->plan.layers[l + 1].d.type == TP_LAYER_RESIDUAL &&
-          st->plan.layers[l + 1].d.geom[1] == 1 && tp::batchnorm_fwd_add_supported(d.dtype, (size_t)d.mb * lp.tokens, C)) {
+          st->plan.layers[l + 1].d.geom[1] == 1 && tp::batchnorm_fwd_add_supported(d.dtype, (size_t)mb * lp.tokens, C)) {
         const LayerPlan& add = st->plan.layers[l + 1];
         const char* skip = aslot + st->plan.layers[add.skip_layer].x_off + row0 * add.in_elems * es;
         void* add_z = add.z_off == UINT64_MAX ? nullptr : aslot + add.z_off + row0 * add.out_elems * es;
         void* add_a = (l + 1 == L - 1) ? y_dev : (void*)(aslot + st->plan.layers[l + 2].x_off + row0 * add.out_elems * es);
         if ((((uintptr_t)x_saved | (uintptr_t)skip | (uintptr_t)add_a | (uintptr_t)add_z) & 15) == 0) {
-          HIP_TRY(tp::launch_batchnorm_fwd(fs, d.dtype, (size_t)d.mb * lp.tokens, C, x_saved, master + lp.w_off,
+          HIP_TRY(tp::launch_batchnorm_fwd(fs, d.dtype, (size_t)mb * lp.tokens, C, x_saved, master + lp.w_off,
                                            master + lp.b_off, add.d.act, add_a, add_z, stats, fsk < 0 ? st->partials() : st->fwd2_scratch(fsk), skip));
           ++l;  // the add is done
           continue;
         }
       }
-      HIP_TRY(tp::launch_batchnorm_fwd(fs, d.dtype, (size_t)d.mb * lp.tokens, C, x_saved, master + lp.w_off,
+      HIP_TRY(tp::launch_batchnorm_fwd(fs, d.dtype, (size_t)mb * lp.tokens, C, x_saved, master + lp.w_off,
                                        master + lp.b_off, lp.d.act, a_out, z_out, stats, fsk < 0 ? st->partials() : st->fwd2_scratch(fsk)));
       continue;
     }
     if (lp.d.type == TP_LAYER_CONV2D) {
       ProfScope ps(st, TP_K_FPROP);
-      HIP_TRY(tp::launch_conv_fprop(fs, d.dtype, d.mb, lp.d.geom[0], lp.d.geom[1], lp.d.geom[2], lp.d.geom[3],
+      HIP_TRY(tp::launch_conv_fprop(fs, d.dtype, mb, lp.d.geom[0], lp.d.geom[1], lp.d.geom[2], lp.d.geom[3],
                                     lp.d.in_features, lp.d.out_features, x_saved, wcopy + lp.w_off * es, master + lp.b_off,
                                     lp.d.act, z_out, a_out, st->zeros()));
     } else if (lp.d.type == TP_LAYER_AVGPOOL) {
       ProfScope ps(st, TP_K_POOL);
-      HIP_TRY(tp::launch_avgpool_fwd(fs, d.dtype, d.mb, lp.tokens, lp.d.in_features, x_saved, a_out));
+      HIP_TRY(tp::launch_avgpool_fwd(fs, d.dtype, mb, lp.tokens, lp.d.in_features, x_saved, a_out));
     } else if (lp.d.type == TP_LAYER_SUBSAMPLE2) {
       ProfScope ps(st, TP_K_POOL);
-      HIP_TRY(tp::launch_subsample_fwd(fs, d.dtype, d.mb, lp.d.geom[0], lp.d.geom[1], lp.d.in_features, x_saved,
+      HIP_TRY(tp::launch_subsample_fwd(fs, d.dtype, mb, lp.d.geom[0], lp.d.geom[1], lp.d.in_features, x_saved,
                                        a_out));
     } else {
       ProfScope ps(st, TP_K_POOL);
-      HIP_TRY(tp::launch_maxpool_fwd(fs, d.dtype, d.mb, lp.d.geom[0], lp.d.geom[1], lp.d.in_features, x_saved,
+      HIP_TRY(tp::launch_maxpool_fwd(fs, d.dtype, mb, lp.d.geom[0], lp.d.geom[1], lp.d.in_features, x_saved,
                                      a_out));
     }
   }
@@ -1072,13 +1081,27 @@ extern "C" {
 int stage_forward(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_dev, void* y_dev,
                   uint64_t* version_used) {
   if (!st) return fail(TP_EINVAL, "null stage");
-  return forward_impl(st, mb_id, ub_idx, x_dev, y_dev, TP_NONE, version_used);
+  return forward_impl(st, mb_id, ub_idx, 1, x_dev, y_dev, TP_NONE, version_used);
+}
+
+int stage_forward_minibatch(tp_stage* st, uint64_t mb_id, const void* x_dev, void* y_dev, uint64_t* version_used) {
+  if (!st) return fail(TP_EINVAL, "null stage");
+  const uint32_t n = (uint32_t)st->desc.n;
+  if (row_by_row(st)) return forward_impl(st, mb_id, 0, n, x_dev, y_dev, TP_NONE, version_used);
+  const size_t in = (size_t)st->desc.mb * st->plan.layers.front().in_elems * st->plan.elt_size;
+  const size_t out = (size_t)st->desc.mb * st->plan.layers.back().out_elems * st->plan.elt_size;
+  if (!st->dry && (!x_dev || !y_dev)) return fail(TP_EINVAL, "null activation pointer");
+  for (uint32_t ub = 0; ub < n; ++ub)
+    if (int rc = forward_impl(st, mb_id, ub, 1, st->dry ? nullptr : (const char*)x_dev + ub * in, st->dry ? nullptr : (char*)y_dev + ub * out,
+                              TP_NONE, version_used))
+      return rc;
+  return TP_OK;
 }
 
 int stage_forward_on(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, uint64_t version, const void* x_dev, void* y_dev) {
   if (!st) return fail(TP_EINVAL, "null stage");
   if (version == TP_NONE) return fail(TP_EINVAL, "stage_forward_on needs a version");
-  return forward_impl(st, mb_id, ub_idx, x_dev, y_dev, version, nullptr);
+  return forward_impl(st, mb_id, ub_idx, 1, x_dev, y_dev, version, nullptr);
 }
 
 int stage_loss_softmax_ce(tp_stage* st, uint64_t mb_id, const void* logits_dev, const int32_t* labels_dev,

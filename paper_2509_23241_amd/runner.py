@@ -166,6 +166,14 @@ class GpuStage:
         assert y.size(0) == mb and y.numel() == mb * self.out_elems
         return y, B.stage_forward(self.handle, mb_id, ub, x.data_ptr(), y.data_ptr())
 
+    def forward_minibatch(self, mb_id: int, x: torch.Tensor, y: torch.Tensor):
+        """All n micro-batches, x and y of n * mb rows."""
+        rows = self.mb * self.n
+        assert x.dtype == self.tdtype and y.dtype == self.tdtype and x.is_contiguous() and y.is_contiguous()
+        assert x.size(0) == rows and x.numel() == rows * self.in_elems
+        assert y.size(0) == rows and y.numel() == rows * self.out_elems
+        return y, B.stage_forward_minibatch(self.handle, mb_id, x.data_ptr(), y.data_ptr())
+
     def forward_join(self):
         B.stage_forward_join(self.handle)
 
@@ -278,8 +286,11 @@ class GpuPipeline:
             if kind == "F":
                 x = get_input(j) if s == 0 else acts.pop((s - 1, j))
                 y = torch.empty(rows, st.out_elems, dtype=st.tdtype, device=self.device)
-                for ub in range(w.n):
-                    _, v = st.forward(j, ub, x[ub * w.mb:(ub + 1) * w.mb], y[ub * w.mb:(ub + 1) * w.mb])
+                if x[:rows].is_contiguous():
+                    _, v = st.forward_minibatch(j, x[:rows], y)
+                else:  # micro-batches of one sample may lie apart
+                    for ub in range(w.n):
+                        _, v = st.forward(j, ub, x[ub * w.mb:(ub + 1) * w.mb], y[ub * w.mb:(ub + 1) * w.mb])
                 acts[(s, j)] = y
                 info.update(y=y, v_f=v)
             else:
