@@ -10,6 +10,9 @@
 namespace tp {
 
 enum Elt : int { ELT_F32 = 0, ELT_BF16 = 1 };
+// SPREAD_CHAINS: on smaller tiles; SPREAD_PARTS: on smaller tiles, the sum over k in four parts, where it otherwise is one ascending
+// chain for every output, whatever the number of rows.
+enum Spread : int { SPREAD_NONE = 0, SPREAD_CHAINS = 1, SPREAD_PARTS = 2 };
 enum Act : int { ACT_NONE = 0, ACT_RELU = 1, ACT_GELU = 2 };
 
 // z = x W^T + bias ; a = act(z) ; d = act'(z).   x:[M x K] W:[N x K] (elt), bias: fp32[N].
@@ -18,8 +21,10 @@ enum Act : int { ACT_NONE = 0, ACT_RELU = 1, ACT_GELU = 2 };
 // into the GEMM where the kernel supports it, a separate copy otherwise).
 // addend (null: none; only where fprop_add_supported, 16-byte aligned): an [M x N] tensor added to the rounded
 // activation, i.e. the residual add that follows the layer.
+// spread: how a bf16 product of few tiles may take more CUs.
 hipError_t launch_fprop(hipStream_t s, int elt, int M, int N, int K, const void* x, const void* W,
-                        const float* bias, int act, void* d_out, void* a_out, void* x_copy, const void* addend = nullptr);
+                        const float* bias, int act, void* d_out, void* a_out, void* x_copy, const void* addend = nullptr,
+                        int spread = SPREAD_NONE);
 bool fprop_add_supported(int elt, int M, int N, int K);
 
 // out = (dz W_b) (.) d_prev   dz:[M x N] W_b:[N x K] d_prev:[M x K] saved act'(z), or null.

@@ -268,12 +268,12 @@ size_t colsum_scratch_floats(int M, int N) {
 bool fprop_add_supported(int elt, int M, int N, int K) { return elt == ELT_BF16 && M >= 1 && N % 8 == 0 && K % 8 == 0; }
 
 hipError_t launch_fprop(hipStream_t s, int elt, int M, int N, int K, const void* x, const void* W, const float* bias,
-                        int act, void* d_out, void* a_out, void* x_copy, const void* addend) {
+                        int act, void* d_out, void* a_out, void* x_copy, const void* addend, int spread) {
   if (addend && (!fprop_add_supported(elt, M, N, K) || ((uintptr_t)addend & 15))) return hipErrorNotSupported;
   if (elt == ELT_F32)
     return f32_fprop(s, M, N, K, (const float*)x, (const float*)W, bias, act, (float*)d_out, (float*)a_out, (float*)x_copy);
   return mfma_fprop(s, M, N, K, (const uint16_t*)x, (const uint16_t*)W, bias, act, (uint16_t*)d_out, (uint16_t*)a_out,
-                    (uint16_t*)x_copy, (const uint16_t*)addend);
+                    (uint16_t*)x_copy, (const uint16_t*)addend, spread);
 }
 
 hipError_t launch_dgrad(hipStream_t s, int elt, int M, int N, int K, const void* dz, const void* Wb, const void* d_prev,

@@ -363,27 +363,22 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
         const uint16_t* la = lds_raw + u * (kStageBytes / 2);
         const uint16_t* lb = la + AT::kBytes / 2;
         const uint32_t dst = lds_base + ((u + NS - 1) % NS) * kStageBytes;
-        bf16x8 af[2][TM], bfr[2][TN];
+        bf16x8 af[DBK / 16][TM], bfr[DBK / 16][TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) af[0][i] = AT::frag(la, wm + i * 32, 0, lane);
+        for (int kk = 0; kk < DBK / 16; ++kk) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) bfr[0][j] = BT::frag(lb, wn + j * 32, 0, lane);
+          for (int i = 0; i < TM; ++i) af[kk][i] = AT::frag(la, wm + i * 32, kk, lane);
+#pragma unroll
+          for (int j = 0; j < TN; ++j) bfr[kk][j] = BT::frag(lb, wn + j * 32, kk, lane);
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int kk = 0; kk < DBK / 16; ++kk) {
-          const int c = kk & 1, nx = c ^ 1;
-          if (kk + 1 < DBK / 16) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) af[nx][i] = AT::frag(la, wm + i * 32, kk + 1, lane);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bfr[nx][j] = BT::frag(lb, wn + j * 32, kk + 1, lane);
-          }
-          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-              acc[i][j] = mma<Epi::kSwap>(af[c][i], bfr[c][j], acc[i][j]);
+              acc[i][j] = mma<Epi::kSwap>(af[kk][i], bfr[kk][j], acc[i][j]);
               const int q = (kk * TM + i) * TN + j;  // compile-time after unrolling
 #pragma unroll
               for (int t = 0; t < kLoads; ++t)
@@ -531,6 +526,152 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
   }
   store_tiles<TM, TN>(acc, epi_of_split(epi, split), m0 + wm, n0 + wn, M, N, lane);
 }
+
+// ---- few output tiles ---------------------------------------------------------------------------
+// Forward products whose 64 x 64 tiles leave most CUs idle: 32 x 32 outputs per workgroup, a quarter of the bytes per CU.  All four
+// waves copy, each every fourth k tile into stages of its own.  Workgroups of one column of tiles, which read the same rows
+// of W, sit on one XCD.
+// CHAIN: the first wave multiplies, all k in ascending order, the bits of every other tile.  Bound by the chain of matrix instructions, about 40 ns each, so the barrier behind which a round of four tiles may be read sits in front
+// of the last products of the round before, and a tile's fragments are read under the products of the one before it.
+// Otherwise each wave multiplies the tiles it has copied and waits for nobody until the four sums meet in LDS, in a fixed order:
+// bound by what a CU fetches from the L2, 80 GB/s.  The sums are no further off fp64 (four shorter chains), but not the bits of the
+// other tiles: two steps of a bottleneck net later, through normalisations and ReLUs, outputs were 3 % off the others'.
+// us on 64 x 64 tiles, in chains, and in four parts: 64 x 512 x 512 5.9, 4.2, 3.8; 100 x 2000 x 2000 9.8, 8.6, 6.1; 512 x 512
+// over 2048 9.8, 8.4, 6.4; 64 x 4096 x 4096 15.2, 13.2, 8.8.
+template <bool CHAIN, class Epi>
+__global__ __launch_bounds__(256) void gemm_bf16_skinny_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int lda,
+                                                               const uint16_t* __restrict__ B, int ldb, Epi epi, int tiles_m, int tiles,
+                                                               SideCopy side) {
+  constexpr int BM = 32, NS = 3, NW = 4, KK = DBK / 16;
+  using T = RowDma<32, 1>;
+  constexpr int kStageBytes = 2 * T::kBytes, kCopies = 2 * T::kPerWave, kPitch = 36;
+  static_assert(BM * kPitch * 4 <= NS * kStageBytes, "a wave's sums go where its stages were");
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds_raw[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < side.nvec; i += (size_t)gridDim.x * 256) side.dst[i] = side.src[i];
+  const int at = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (at >= tiles) return;
+  const int m0 = at % tiles_m * BM, n0 = at / tiles_m * 32;
+  A += (size_t)m0 * lda;
+  B += (size_t)n0 * ldb;
+  T ta, tb;
+  ta.init(lda, 0, M - m0, 0, lane);
+  tb.init(ldb, 0, N - n0, 0, lane);
+  const int KT = (K + DBK - 1) / DBK, last_k = K - (KT - 1) * DBK;
+  const int rounds = (KT + NW - 1 - (CHAIN ? 0 : wave)) / NW;  // otherwise: of this wave, perhaps none
+  auto stage = [&](int i, int w) { return (w * NS + i % NS) * kStageBytes; };
+  const uint32_t lds_base = lds_addr_of(lds_raw);
+  // k tile NW * i + wave into the wave's stage of round i; past the end (CHAIN) the last tile again, which is not used
+  auto issue = [&](int i) {
+    const int tile = min(NW * i + wave, KT - 1);
+    const uint32_t dst = lds_base + stage(i, wave);
+    const uint16_t *pa = A + (size_t)tile * DBK, *pb = B + (size_t)tile * DBK;
+#pragma unroll
+    for (int t = 0; t < T::kPerWave; ++t) {
+      if (tile == KT - 1 && last_k < DBK) {
+        ta.issue_one_of(last_k, t, dst, pa, 0, lane);
+        tb.issue_one_of(last_k, t, dst + T::kBytes, pb, 0, lane);
+      } else {
+        ta.issue_one(t, dst, pa, 0);
+        tb.issue_one(t, dst + T::kBytes, pb, 0);
+      }
+    }
+  };
+  floatx16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  bf16x8 fa[2][KK], fb[2][KK];
+  auto fetch = [&](int i, int w, int buf) {
+    const uint16_t *pa = lds_raw + stage(i, w) / 2, *pb = pa + T::kBytes / 2;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      fa[buf][kk] = T::frag(pa, 0, kk, lane);
+      fb[buf][kk] = T::frag(pb, 0, kk, lane);
+    }
+    if constexpr (CHAIN) __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](int buf) {
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) acc = mma<Epi::kSwap>(fa[buf][kk], fb[buf][kk], acc);
+    if constexpr (CHAIN) __builtin_amdgcn_sched_barrier(0);
+  };
+  auto wait_for = [&](int i) {  // this wave's tile of round i has landed, that of the next one may be in flight
+    if (i + 1 < rounds) wait_vmcnt<kCopies>();
+    else wait_vmcnt<0>();
+  };
+  if (rounds > 0) issue(0);
+  if (rounds > 1) issue(1);
+  if constexpr (CHAIN) {
+    auto arrive = [&](int i) {
+      wait_for(i);
+      lds_barrier();  // every wave's tile has landed, and all of the round before has been read
+      if (i + NS - 1 < rounds) issue(i + NS - 1);
+    };
+    arrive(0);
+    if (wave == 0) {
+      fetch(0, 0, 0);
+      for (int i = 0; i < rounds; ++i) {
+        const int here = KT - NW * i;  // tiles of this round, if fewer than NW
+#pragma unroll
+        for (int w = 0; w < NW - 1; ++w) {
+          fetch(i, w + 1, (w + 1) & 1);
+          if (w < here) multiply(w & 1);
+        }
+        if (i + 1 < rounds) {
+          arrive(i + 1);
+          fetch(i + 1, 0, 0);
+        }
+        if (NW - 1 < here) multiply((NW - 1) & 1);
+      }
+    } else {
+      for (int i = 1; i < rounds; ++i) arrive(i);
+    }
+    lds_barrier();  // the stages are dead
+  } else {
+    for (int i = 0; i < rounds; ++i) {
+      wait_for(i);
+      fetch(i, wave, 0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (i + NS - 1 < rounds) issue(i + NS - 1);  // into the stage that was read a round ago
+      multiply(0);
+    }
+  }
+  // the transposed blocks, row by row, each wave's over its own stages; then every thread takes four columns of a row
+  if (!CHAIN || wave == 0) {
+    float* mine = reinterpret_cast<float*>(lds_raw + stage(0, wave) / 2) + (lane & 31) * kPitch + 4 * (lane >> 5);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) *reinterpret_cast<float4*>(mine + 8 * g) = make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+  }
+  lds_barrier();
+  const int row = threadIdx.x >> 3, col = (threadIdx.x & 7) * 4;
+  auto part = [&](int w) { return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds_raw + stage(0, w) / 2) + row * kPitch + col); };
+  float4 v = part(0);
+  if constexpr (!CHAIN) {
+    const float4 b = part(1), c = part(2), d = part(3);
+    v = make_float4((v.x + b.x) + (c.x + d.x), (v.y + b.y) + (c.y + d.y), (v.z + b.z) + (c.z + d.z), (v.w + b.w) + (c.w + d.w));
+  }
+  if (m0 + row < M && n0 + col < N) epi.quad(m0 + row, n0 + col, min(4, N - n0 - col), v.x, v.y, v.z, v.w);
+}
+
+template <bool CHAIN, class Epi>
+hipError_t launch_skinny(hipStream_t s, int M, int N, int K, const uint16_t* A, int lda, const uint16_t* B, int ldb, const Epi& epi,
+                         SideCopy side) {
+  static_assert(Epi::kSwap, "four columns per lane");
+  constexpr int lds_bytes = 4 * 3 * 2 * RowDma<32, 1>::kBytes;
+  auto kernel = gemm_bf16_skinny_kernel<CHAIN, Epi>;
+  static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+  if (attr != hipSuccess) return attr;
+  const int tiles_m = (M + 31) / 32, tiles = tiles_m * ((N + 31) / 32);
+  hipLaunchKernelGGL(kernel, dim3((tiles + 7) / 8 * 8), dim3(256), lds_bytes, s, M, N, K, A, lda, B, ldb, epi, tiles_m, tiles, side);
+  return hipGetLastError();
+}
+
+// Where a product takes the kernel above: as long as every tile has a CU of its own.  With two rounds of tiles it is behind the
+// 64 x 64 ones (512 x 1024 x 1024 7.6 and 7.4 us, 256 x 2000 x 2000 10.6 and 9.6).  64 x 32 tiles in four parts would be ahead alone
+// (512 x 1024 x 1024 6.2, 128 x 4096 x 4096 15.4 -> 12.0) but not beside other kernels, with 147 KB of LDS each: a stage of width 4096,
+// micro-batches of 128 on two streams, 332 -> 352 us a step.
+inline bool few_tiles(int M, int N) { return (long)((M + 31) / 32) * ((N + 31) / 32) <= 256; }
 
 // Operands the direct-to-LDS kernel takes: 16-byte aligned with rows of whole 16-byte chunks (of at least one, along the
 // rows of an operand staged [k][row]), 32-bit byte offsets inside a tile (of at most 384 rows or 64 k values).  Offsets from
@@ -683,7 +824,7 @@ hipError_t run(bool dma, hipStream_t s, int M, int N, int K, const uint16_t* A, 
 inline int store_width(const void* a, const void* b) { return aligned(16, a, b) ? 2 : aligned(8, a, b) ? 1 : 0; }
 
 hipError_t mfma_fprop(hipStream_t s, int M, int N, int K, const uint16_t* x, const uint16_t* W, const float* bias,
-                      int act, uint16_t* d_out, uint16_t* a_out, uint16_t* x_copy, const uint16_t* addend) {
+                      int act, uint16_t* d_out, uint16_t* a_out, uint16_t* x_copy, const uint16_t* addend, int spread) {
   const bool fits = dma_ok(M, N, K, K, K, false, false) && aligned(16, W, x_copy);
   if (x_copy && !(fits && aligned(16, x))) {
     const hipError_t err = launch_copy(s, x, x_copy, (size_t)M * K * 2);
@@ -696,8 +837,13 @@ hipError_t mfma_fprop(hipStream_t s, int M, int N, int K, const uint16_t* x, con
   const int wide = store_width(d_out, a_out);
   // contractions that are no multiple of 8 ran on fp32 FMAs with GELU from erff, and keep it
   if (K % 8) return run_any<false, false>(s, M, N, K, x, K, W, K, EpiFpropExact{bias, d_out, a_out, act, N, nullptr, wide});
-  if (addend) return run<false, false>(dma, s, M, N, K, x, K, W, K, EpiFpropAdd{bias, d_out, a_out, act, N, addend, wide}, side);
-  return run<false, false>(dma, s, M, N, K, x, K, W, K, EpiFprop{bias, d_out, a_out, act, N, nullptr, wide}, side);
+  auto product = [&](const auto& e) {
+    if (dma && spread == SPREAD_PARTS && few_tiles(M, N)) return launch_skinny<false>(s, M, N, K, x, K, W, K, e, side);
+    if (dma && spread == SPREAD_CHAINS && few_tiles(M, N)) return launch_skinny<true>(s, M, N, K, x, K, W, K, e, side);
+    return run<false, false>(dma, s, M, N, K, x, K, W, K, e, side);
+  };
+  if (addend) return product(EpiFpropAdd{bias, d_out, a_out, act, N, addend, wide});
+  return product(EpiFprop{bias, d_out, a_out, act, N, nullptr, wide});
 }
 
 int mfma_dgrad_sum_rows(int M, int K) {

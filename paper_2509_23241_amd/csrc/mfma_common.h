@@ -72,7 +72,7 @@ struct EpiFpropT {
   }
   __device__ __forceinline__ void quad(int m, int n, int count, float v0, float v1, float v2, float v3) const {
     const size_t i = (size_t)m * ldc + n;
-    if (count == 4 && (ldc & 3) == 0 && wide && !ADD) {
+    if (count == 4 && (ldc & 3) == 0 && wide) {
       const float4 b = *reinterpret_cast<const float4*>(bias + n);
       const float z[4] = {v0 + b.x, v1 + b.y, v2 + b.z, v3 + b.w};
       float a[4], d[4];
@@ -84,6 +84,13 @@ struct EpiFpropT {
         }
       } else {
         act_pairs_fast(z, act, a, d);
+      }
+      if constexpr (ADD) {  // 16-byte aligned
+        const uint2 u = *reinterpret_cast<const uint2*>(addend + i);
+        a[0] = bf16_to_float(float_to_bf16(a[0])) + __uint_as_float(u.x << 16);
+        a[1] = bf16_to_float(float_to_bf16(a[1])) + __uint_as_float(u.x & 0xffff0000u);
+        a[2] = bf16_to_float(float_to_bf16(a[2])) + __uint_as_float(u.y << 16);
+        a[3] = bf16_to_float(float_to_bf16(a[3])) + __uint_as_float(u.y & 0xffff0000u);
       }
       if (d_out) *reinterpret_cast<uint2*>(d_out + i) = make_uint2(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]));
       *reinterpret_cast<uint2*>(a_out + i) = make_uint2(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));

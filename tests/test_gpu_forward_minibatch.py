@@ -1,5 +1,5 @@
 """stage_forward_minibatch against one stage_forward per micro-batch: outputs, saved inputs and the gradients that follow from them.
-The products add in one order whatever the number of rows, so the results are the same bits."""
+At these sizes the products add in one order whatever the number of rows, so the results are the same bits."""
 import numpy as np
 import pytest
 
