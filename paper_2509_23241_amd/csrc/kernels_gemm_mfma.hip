@@ -290,8 +290,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
+  for (size_t i = (size_t)blockIdx.x * (64 * NW) + threadIdx.x; i < side.nvec; i += (size_t)gridDim.x * (64 * NW))
+    side.dst[i] = side.src[i];
   int tile_m, tile_n;
   map.get(blockIdx.x, tile_m, tile_n);
+  if (!map.inside(tile_m, tile_n)) return;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const uint32_t lds_base = lds_addr_of(lds_raw);
   // blockIdx.y: range of the contraction this workgroup sums over, `per` k tiles long (the last one may be shorter);
@@ -309,9 +312,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  for (size_t i = (size_t)blockIdx.x * (64 * NW) + threadIdx.x; i < side.nvec; i += (size_t)gridDim.x * (64 * NW))
-    side.dst[i] = side.src[i];
 
   AT ta;
   BT tb;
@@ -703,8 +703,8 @@ hipError_t launch_dma(hipStream_t s, int M, int N, int K, const uint16_t* A, int
     if (attr != hipSuccess) return attr;
   }
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  const TileMap map = make_tile_map(tiles_m, tiles_n);
-  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n, (k_tiles(K) + per - 1) / per), dim3(64 * NW), lds_bytes, s, M, N, K, per, A,
+  const TileMap map = make_uneven_tile_map(tiles_m, tiles_n, BM, BN);
+  hipLaunchKernelGGL(kernel, dim3(map.grid(), (k_tiles(K) + per - 1) / per), dim3(64 * NW), lds_bytes, s, M, N, K, per, A,
                      lda, B, ldb, epi, map, side);
   return hipGetLastError();
 }
