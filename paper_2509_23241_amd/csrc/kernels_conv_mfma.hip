@@ -40,77 +40,23 @@ __device__ __forceinline__ void dma16_addr(uint32_t lds_byte_addr, const void* l
                : "memory");
 }
 
+// a / d for the run-time widths d that k tiles are counted in, a * d < 2^31 (or d a power of two); as a division it is 25
+// scalar instructions in every copy
+inline uint32_t inverse_of(uint32_t d) { return (uint32_t)(((1ull << 31) + d - 1) / d); }
+__device__ __forceinline__ int divide_by(int a, uint32_t inverse) { return (int)__umulhi(2u * (uint32_t)a, inverse); }
+
+// The operands below take a k tile at a time: set_tile(), then its copies.  What a copy needs beside the lane's own constants is worked
+// out once per k tile, in scalar registers; offsets are 32 bits (operands of up to 2 GiB).  Worked out anew in every copy, with divisions and
+// 64-bit products, it was 120 scalar and 25 vector instructions for the four matrix instructions of a 64 x 64 tile.  2048 pixels of 4 x 4 maps, 256
+// channels, forward 15.4 -> 12.0 us; 8192, weight gradient 28.0 -> 23.1, input gradient 23.7 -> 20.9; 512 pixels of 2 x 2 maps, 512
+// channels, forward 25.4 -> 18.9.
 struct GatherDesc {
   const uint16_t* base;   // [pixels of the source grid][C] activations or gradients
   const uint16_t* zeros;  // >= 128 bytes of zeros, 16-byte aligned
   int P, H, W, lw;        // the grid the rows (or the contraction index) run over: pixels, image size, log2(W)
   int C;                  // channels of `base`
   int SH, SW;             // image size of the source grid (= H, W at stride 1)
-};
-
-// Source pixel of output position (h, w) for tap offset (dh, dw) at stride S (fprop, wgrad): the input at
-// S*(h, w) + (dh, dw).  (The input gradient at stride 2 goes by parity class of the input pixels: RowGatherS2.)
-template <int S>
-__device__ __forceinline__ bool source_pixel(int h, int w, int dh, int dw, int SH, int SW, int& sh, int& sw) {
-  sh = h * S + dh;
-  sw = w * S + dw;
-  return (unsigned)sh < (unsigned)SH && (unsigned)sw < (unsigned)SW;
-}
-
-// k-contiguous gathered operand: stage [R pixels][64 channels of one tap].
-template <int R, int NW, bool BACKWARD, int S = 1>
-struct RowGather {
-  using Desc = GatherDesc;
-  static constexpr int kPerWave = R / 8 / NW;
-  static constexpr int kBytes = R * DBK * 2;
-  static_assert((R / 8) % NW == 0, "rows do not divide among the waves");
-  Desc d;
-  int cblocks;
-  uint32_t pix_off[kPerWave];  // S == 1: byte offset of (pixel, chunk) inside base; else of (image, chunk)
-  int hw[kPerWave];            // h << 16 | w of the lane's pixel
-  uint32_t zoff;
-
-  __device__ __forceinline__ void init(const Desc& desc, int r0, int wave, int lane, int /*batch*/) {
-    d = desc;
-    cblocks = d.C / DBK;
-    zoff = (lane & 7) * 16;
-#pragma unroll
-    for (int t = 0; t < kPerWave; ++t) {
-      const int r = 8 * (wave + NW * t) + (lane >> 3);
-      const int c = (lane & 7) ^ ((r >> 1) & 7);
-      const int p = min(r0 + r, d.P - 1);  // rows past the end repeat the last pixel: never stored
-      hw[t] = (((p >> d.lw) & (d.H - 1)) << 16) | (p & (d.W - 1));
-      if (S == 1) {
-        pix_off[t] = (uint32_t)(((size_t)p * d.C + c * 8) * 2);
-      } else {
-        const int img = p / (d.H * d.W);
-        pix_off[t] = (uint32_t)(((size_t)img * d.SH * d.SW * d.C + c * 8) * 2);
-      }
-    }
-  }
-  __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, int tile, int wave) const {
-    const int tap = tile / cblocks, c0 = (tile - tap * cblocks) * DBK;  // wave uniform
-    int dh = tap / 3 - 1, dw = tap - (tap / 3) * 3 - 1;
-    if (BACKWARD) { dh = -dh; dw = -dw; }
-    bool valid;
-    long off;
-    if (S == 1) {
-      const int sh = (hw[t] >> 16) + dh, sw = (hw[t] & 0xffff) + dw;
-      valid = (unsigned)sh < (unsigned)d.H && (unsigned)sw < (unsigned)d.W;
-      off = (long)pix_off[t] + ((long)(dh * d.W + dw) * d.C + c0) * 2;
-    } else {
-      int sh, sw;
-      static_assert(!BACKWARD || S == 1, "the stride-2 input gradient runs on RowGatherS2");
-      valid = source_pixel<S>(hw[t] >> 16, hw[t] & 0xffff, dh, dw, d.SH, d.SW, sh, sw);
-      off = (long)pix_off[t] + ((long)(sh * d.SW + sw) * d.C + c0) * 2;
-    }
-    const char* src = valid ? (const char*)d.base + off : (const char*)d.zeros + zoff;
-    dma16_addr(lds_stage + (wave + NW * t) * 1024, src);
-  }
-  static __device__ __forceinline__ bf16x8 frag(const uint16_t* lds, int rbase, int kk, int lane) {
-    return RowDma<R, NW>::frag(lds, rbase, kk, lane);
-  }
-  static __device__ __forceinline__ int tiles_of(const Desc&, int /*batch*/, int KT) { return KT; }
+  uint32_t by_cblocks;    // inverse_of(C / 64)
 };
 
 // The 3x3 input gradient at stride 2, one parity class of input pixels per batch.  An input pixel (h, w) gets a
@@ -126,23 +72,27 @@ __device__ __forceinline__ int s2_class_tap(int cls, int ti) {  // ti-th tap of 
   return 3 * kh + kw;
 }
 
-// Rows: the pixels (img, h2, w2) of one class on the (H/2) x (W/2) grid, i.e. input pixel (2 h2 + ph, 2 w2 + pw);
-// the source is dz on that same grid at (h2 + (ph - kh + 1)/2, w2 + (pw - kw + 1)/2), zero past its edge.
-template <int R, int NW>
-struct RowGatherS2 {
-  using Desc = GatherDesc;  // P, H, W, lw: rows and grid of one class; SH, SW: the dz grid (the same size)
+// k-contiguous gathered operand: stage [R pixels][64 channels of one tap].  The source of output position (h, w) is the pixel
+// S*(h, w) + (dh, dw), with the offset of the k tile's tap (BACKWARD: of the mirrored tap).  CLASSES: the input gradient at stride
+// 2; rows are the pixels (img, h2, w2) of one class on the (H/2) x (W/2) grid, i.e. input pixel (2 h2 + ph, 2 w2 + pw), and the
+// source is dz on that same grid at (h2 + (ph - kh + 1)/2, w2 + (pw - kw + 1)/2), zero past its edge.
+template <int R, int NW, bool BACKWARD, int S = 1, bool CLASSES = false>
+struct RowGather {
+  using Desc = GatherDesc;
   static constexpr int kPerWave = R / 8 / NW;
   static constexpr int kBytes = R * DBK * 2;
   static_assert((R / 8) % NW == 0, "rows do not divide among the waves");
+  static_assert(S == 1 || !BACKWARD, "the input gradient at stride 2 goes by classes");
   Desc d;
-  int cblocks, cls;
-  uint32_t img_off[kPerWave];  // byte offset of (image, chunk) inside base
-  int hw[kPerWave];            // h2 << 16 | w2 of the lane's pixel
+  int cls;
+  uint32_t pix_off[kPerWave];      // byte offset of (source pixel of the tap (0, 0), chunk) inside base
+  int h[kPerWave], w[kPerWave];    // that pixel
   uint32_t zoff;
+  int dh, dw;                      // of the k tile
+  uint32_t delta;
 
   __device__ __forceinline__ void init(const Desc& desc, int r0, int wave, int lane, int batch) {
     d = desc;
-    cblocks = d.C / DBK;
     cls = s2_class(batch);
     zoff = (lane & 7) * 16;
 #pragma unroll
@@ -150,26 +100,35 @@ struct RowGatherS2 {
       const int r = 8 * (wave + NW * t) + (lane >> 3);
       const int c = (lane & 7) ^ ((r >> 1) & 7);
       const int p = min(r0 + r, d.P - 1);  // rows past the end repeat the last pixel: never stored
-      hw[t] = (((p >> d.lw) & (d.H - 1)) << 16) | (p & (d.W - 1));
-      const int img = p / (d.H * d.W);
-      img_off[t] = (uint32_t)(((size_t)img * d.SH * d.SW * d.C + c * 8) * 2);
+      h[t] = S * ((p >> d.lw) & (d.H - 1));
+      w[t] = S * (p & (d.W - 1));
+      const size_t pixel = S == 1 ? (size_t)p : (size_t)(p / (d.H * d.W)) * d.SH * d.SW + (size_t)h[t] * d.SW + w[t];
+      pix_off[t] = (uint32_t)((pixel * d.C + c * 8) * 2);
     }
   }
-  __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, int tile, int wave) const {
-    const int ti = tile / cblocks, c0 = (tile - ti * cblocks) * DBK;  // wave uniform
-    const int tap = s2_class_tap(cls, ti);
-    const int kh = tap / 3, kw = tap - 3 * kh;
-    const int sh = (hw[t] >> 16) + (((cls >> 1) - kh + 1) >> 1), sw = (hw[t] & 0xffff) + (((cls & 1) - kw + 1) >> 1);
-    const bool valid = sh < d.SH && sw < d.SW;
-    const long off = (long)img_off[t] + ((long)(sh * d.SW + sw) * d.C + c0) * 2;
-    const char* src = valid ? (const char*)d.base + off : (const char*)d.zeros + zoff;
+  __device__ __forceinline__ void set_tile(int tile) {
+    int tap = divide_by(tile, d.by_cblocks);
+    const int c0 = (tile - tap * (d.C / DBK)) * DBK;
+    if (CLASSES) {
+      tap = s2_class_tap(cls, tap);
+      dh = ((cls >> 1) - tap / 3 + 1) >> 1;
+      dw = ((cls & 1) - tap % 3 + 1) >> 1;
+    } else {
+      dh = BACKWARD ? 1 - tap / 3 : tap / 3 - 1;
+      dw = BACKWARD ? 1 - tap % 3 : tap % 3 - 1;
+    }
+    delta = (uint32_t)(((dh * d.SW + dw) * d.C + c0) * 2);
+  }
+  __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, int wave) const {
+    const bool valid = ((unsigned)(h[t] + dh) < (unsigned)d.SH) & ((unsigned)(w[t] + dw) < (unsigned)d.SW);  // no branch
+    const char* src = valid ? (const char*)d.base + (pix_off[t] + delta) : (const char*)d.zeros + zoff;
     dma16_addr(lds_stage + (wave + NW * t) * 1024, src);
   }
   static __device__ __forceinline__ bf16x8 frag(const uint16_t* lds, int rbase, int kk, int lane) {
     return RowDma<R, NW>::frag(lds, rbase, kk, lane);
   }
-  static __device__ __forceinline__ int tiles_of(const Desc& desc, int batch, int /*KT*/) {
-    return s2_class_taps(s2_class(batch)) * (desc.C / DBK);
+  static __device__ __forceinline__ int tiles_of(const Desc& desc, int batch, int KT) {
+    return CLASSES ? s2_class_taps(s2_class(batch)) * (desc.C / DBK) : KT;
   }
 };
 
@@ -184,8 +143,10 @@ struct ColGather {
   Desc d;
   int dh, dw;
   int krow[kPerWave];
-  uint32_t coff[kPerWave];
+  uint32_t coff[kPerWave];  // byte offset of (pixel krow shifted by the tap, chunk); at stride 2 without the column's part
   uint32_t zoff;
+  int p0;                   // of the k tile: its first pixel,
+  uint32_t delta;           // and where that lies
 
   __device__ __forceinline__ void init(const Desc& desc, int r0, int wave, int lane, int batch) {
     d = desc;
@@ -198,23 +159,19 @@ struct ColGather {
       const int k = flat / kPerK;
       const int c = (flat % kPerK) ^ ColDma<R, NW>::swz(k);
       krow[t] = k;
-      coff[t] = (uint32_t)(min(r0 + c * 8, d.C - 8) * 2);
+      coff[t] = (uint32_t)(((S * S * k + dh * d.SW + dw) * d.C + min(r0 + c * 8, d.C - 8)) * 2);
     }
   }
-  __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, int tile, int wave) const {
-    const int p = tile * DBK + krow[t];
-    bool valid;
-    long off;
-    if (S == 1) {
-      const int sh = ((p >> d.lw) & (d.H - 1)) + dh, sw = (p & (d.W - 1)) + dw;
-      valid = (unsigned)sh < (unsigned)d.H && (unsigned)sw < (unsigned)d.W;
-      off = ((long)p + dh * d.W + dw) * d.C * 2 + coff[t];
-    } else {
-      int sh, sw;
-      valid = source_pixel<S>((p >> d.lw) & (d.H - 1), p & (d.W - 1), dh, dw, d.SH, d.SW, sh, sw);
-      const int img = p / (d.H * d.W);
-      off = (((long)img * d.SH + sh) * d.SW + sw) * d.C * 2 + coff[t];
-    }
+  __device__ __forceinline__ void set_tile(int tile) {
+    p0 = tile * DBK;
+    delta = (uint32_t)(p0 * (S * S)) * (uint32_t)d.C * 2;
+  }
+  __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, int wave) const {
+    const int p = p0 + krow[t], w = p & (d.W - 1);
+    const bool valid = ((unsigned)(S * ((p >> d.lw) & (d.H - 1)) + dh) < (unsigned)d.SH) & ((unsigned)(S * w + dw) < (unsigned)d.SW);  // no branch
+    uint32_t off = coff[t] + delta;
+    // stride 2: output pixel p = (img * H + h) * W + w reads pixel 4 (img * H + h) W + 2 w = 4 p - 2 w of the source (and the tap's shift)
+    if (S == 2) off -= (uint32_t)(2 * w * d.C) * 2;
     const char* src = valid ? (const char*)d.base + off : (const char*)d.zeros + zoff;
     dma16_addr(lds_stage + (wave + NW * t) * 1024, src);
   }
@@ -229,9 +186,12 @@ struct ColGather {
 struct PlainDesc {
   const uint16_t* base;
   int ld, rows, inner;
-  long step_in, step_out;
+  uint32_t step_in, step_out;
+  uint32_t by_inner;  // inverse_of(inner)
 };
-template <int R, int NW, bool COL>
+// CLASSES: the weights of the stride-2 input gradient by parity class: k tile -> (ti-th tap of the batch's class, block of 64
+// output channels), base + (tile % inner) * step_in + tap * step_out.
+template <int R, int NW, bool COL, bool CLASSES = false>
 struct Plain {
   using Desc = PlainDesc;
   using Impl = typename DmaSel<R, NW, COL>::type;
@@ -239,44 +199,27 @@ struct Plain {
   static constexpr int kBytes = Impl::kBytes;
   Impl impl;
   Desc d;
-  __device__ __forceinline__ void init(const Desc& desc, int r0, int wave, int lane, int /*batch*/) {
-    d = desc;
-    impl.init(d.ld, r0, d.rows, wave, lane);
-  }
-  __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, int tile, int wave) const {
-    const int q = tile / d.inner;
-    impl.issue_one(t, lds_stage, d.base + (tile - q * d.inner) * d.step_in + q * d.step_out, wave);
-  }
-  static __device__ __forceinline__ bf16x8 frag(const uint16_t* lds, int rbase, int kk, int lane) {
-    return Impl::frag(lds, rbase, kk, lane);
-  }
-  static __device__ __forceinline__ int tiles_of(const Desc&, int /*batch*/, int KT) { return KT; }
-};
-
-// The weights of the stride-2 input gradient by parity class: k tile -> (ti-th tap of the batch's class, block of 64
-// output channels); the source of tile `tile` is base + (tile % inner) * step_in + tap * step_out.
-template <int R, int NW>
-struct PlainS2 {
-  using Desc = PlainDesc;
-  using Impl = ColDma<R, NW>;
-  static constexpr int kPerWave = Impl::kPerWave;
-  static constexpr int kBytes = Impl::kBytes;
-  Impl impl;
-  Desc d;
   int cls;
+  const uint16_t* at;  // the k tile
   __device__ __forceinline__ void init(const Desc& desc, int r0, int wave, int lane, int batch) {
     d = desc;
     cls = s2_class(batch);
     impl.init(d.ld, r0, d.rows, wave, lane);
   }
-  __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, int tile, int wave) const {
-    const int ti = tile / d.inner;
-    impl.issue_one(t, lds_stage, d.base + (tile - ti * d.inner) * d.step_in + s2_class_tap(cls, ti) * d.step_out, wave);
+  __device__ __forceinline__ void set_tile(int tile) {
+    const int q = divide_by(tile, d.by_inner);
+    at = d.base + (uint64_t)(uint32_t)(tile - q * d.inner) * d.step_in + (uint64_t)(uint32_t)(CLASSES ? s2_class_tap(cls, q) : q) * d.step_out;
   }
+  __device__ __forceinline__ void issue_one(int t, uint32_t lds_stage, int wave) const { impl.issue_one(t, lds_stage, at, wave); }
   static __device__ __forceinline__ bf16x8 frag(const uint16_t* lds, int rbase, int kk, int lane) {
     return Impl::frag(lds, rbase, kk, lane);
   }
+  static __device__ __forceinline__ int tiles_of(const Desc&, int /*batch*/, int KT) { return KT; }
 };
+template <int R, int NW>
+using RowGatherS2 = RowGather<R, NW, false, 1, true>;
+template <int R, int NW>
+using PlainS2 = Plain<R, NW, true, true>;
 
 // fp32 partial tile of dW for one tap and one pixel range
 struct EpiWgradConv {
@@ -326,7 +269,7 @@ __device__ __forceinline__ EpiWgrad epi_at(const EpiWgradConv& e, int tap, int s
 // g, g + 2, ...; KT even), with stage buffers and copies of their own; both groups meet at the same barriers.  At
 // the end the second group hands its accumulators over through LDS and the first one stores the tile.  For products
 // with few output tiles and a long contraction (3x3 convolutions on 4x4 maps: 128 workgroups, 36 k tiles, one MFMA
-// per wave and k step) this halves the chain of barrier -> fragment reads -> MFMAs: 17.3 -> 15.4 us.  What remains is
+// per wave and k step) this halves the chain of barrier -> fragment reads -> MFMAs: 17.3 -> 15.4 us when it was built.  What remains is
 // the 576 KB every workgroup gathers through its CU's L1 (each input pixel nine times), 7.5 us at the rate one CU
 // fetches from L2.
 template <int BM, int BN, int WGM, int WGN, int NS, class AL, class BL, class Epi, int KG = 1>
@@ -372,16 +315,22 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void conv_bf16_dma_kernel(int 
   tb.init(bd, n0, wave, lane, batch);
 
   // tiles past the end re-read the last tile into a stage nobody reads again (constant vmcnt arithmetic)
-  auto issue_copy = [&](int t, int tile, int st) {
+  auto set_tile = [&](int tile) {
     const int tc = tile0 + min(tile, KTg - 1) * KG + kg;
+    ta.set_tile(tc);
+    tb.set_tile(tc);
+  };
+  auto issue_copy = [&](int t, int st) {
     const uint32_t dst = lds_base + st * kStageBytes;
-    if (t < AL::kPerWave) ta.issue_one(t, dst, tc, wave);
-    else tb.issue_one(t - AL::kPerWave, dst + AL::kBytes, tc, wave);
+    if (t < AL::kPerWave) ta.issue_one(t, dst, wave);
+    else tb.issue_one(t - AL::kPerWave, dst + AL::kBytes, wave);
   };
 #pragma unroll
-  for (int st = 0; st < NS - 1; ++st)
+  for (int st = 0; st < NS - 1; ++st) {
+    set_tile(st);
 #pragma unroll
-    for (int t = 0; t < kLoads; ++t) issue_copy(t, st, st);
+    for (int t = 0; t < kLoads; ++t) issue_copy(t, st);
+  }
 
   int rd = 0, wr = NS - 1;
   for (int kt = 0; kt < KTg; ++kt) {
@@ -389,6 +338,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void conv_bf16_dma_kernel(int 
     lds_barrier();
     const uint16_t* la = lds_group + rd * (kStageBytes / 2);
     const uint16_t* lb = la + AL::kBytes / 2;
+    set_tile(kt + NS - 1);
     bf16x8 af[2][TM], bfr[2][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) af[0][i] = AL::frag(la, wm + i * 32, 0, lane);
@@ -415,7 +365,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void conv_bf16_dma_kernel(int 
           for (int t = 0; t < kLoads; ++t)
             if ((t * NM) / kLoads == q) {
               __builtin_amdgcn_sched_barrier(0);
-              issue_copy(t, kt + NS - 1, wr);
+              issue_copy(t, wr);
               __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -562,13 +512,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_patch_kernel(int P, int N
   tb.init(bd, n0, wave, lane, 0);
   const int cbs = pd.C / DBK;  // 64-channel blocks per tap
   const int KT = 9 * cbs;
-  auto issue_copy = [&](int t, int tile, int st) {
-    tb.issue_one(t, lds_stage0 + st * BL::kBytes, min(tile, KT - 1), wave);
-  };
+  auto issue_copy = [&](int t, int st) { tb.issue_one(t, lds_stage0 + st * BL::kBytes, wave); };
 #pragma unroll
-  for (int st = 0; st < NS - 1; ++st)
+  for (int st = 0; st < NS - 1; ++st) {
+    tb.set_tile(min(st, KT - 1));
 #pragma unroll
-    for (int t = 0; t < kLoads; ++t) issue_copy(t, st, st);
+    for (int t = 0; t < kLoads; ++t) issue_copy(t, st);
+  }
 
   // centre patch pixel of the lane's row in each of its MFMA row tiles
   const int PC = pd.W + 2;
@@ -586,6 +536,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_patch_kernel(int P, int N
     wait_vmcnt<(NS - 2) * kLoads>();  // the patch copies are older than any stage: they have landed too
     lds_barrier();
     const uint16_t* lb = stage0 + rd * (BL::kBytes / 2);
+    tb.set_tile(min(kt + NS - 1, KT - 1));
     int dh = tap / 3 - 1, dw = tap - (tap / 3) * 3 - 1;
     if (BWD) { dh = -dh; dw = -dw; }
     const int tapoff = dh * PC + dw;
@@ -628,7 +579,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_patch_kernel(int P, int N
           for (int t = 0; t < kLoads; ++t)
             if ((t * NM) / kLoads == q) {
               __builtin_amdgcn_sched_barrier(0);
-              issue_copy(t, kt + NS - 1, wr);
+              issue_copy(t, wr);
               __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -1392,12 +1343,12 @@ hipError_t launch_gather_rows(hipStream_t s, int P, int N, int KT, const GatherD
 hipError_t conv_mfma_fprop(hipStream_t s, int imgs, int H, int W, int stride, int cin, int cout, const uint16_t* x,
                            const uint16_t* wgt, const float* bias, int act, uint16_t* d_out, uint16_t* a_out,
                            const uint16_t* zeros) {
-  PlainDesc bd{wgt, 9 * cin, cout, 1 << 30, DBK, 0};
+  PlainDesc bd{wgt, 9 * cin, cout, 1 << 30, DBK, 0, inverse_of(1 << 30)};
   EpiFprop e{bias, d_out, a_out, act, cout};
   const int KT = 9 * cin / DBK;
   if (stride == 2) {  // rows: output pixels on the (H/2) x (W/2) grid, source: the input
     const int Ho = H / 2, Wo = W / 2, P = imgs * Ho * Wo;
-    GatherDesc ad{x, zeros, P, Ho, Wo, ilog2(Wo), cin, H, W};
+    GatherDesc ad{x, zeros, P, Ho, Wo, ilog2(Wo), cin, H, W, inverse_of(cin / DBK)};
     return launch_gather_rows<false, 2>(s, P, cout, KT, ad, bd, e);
   }
   const int P = imgs * H * W;
@@ -1406,7 +1357,7 @@ hipError_t conv_mfma_fprop(hipStream_t s, int imgs, int H, int W, int stride, in
     const hipError_t err = launch_patch_conv<false>(s, P, H, W, cin, cout, pd, bd, e);
     if (err != hipErrorNotSupported) return err;
   }
-  GatherDesc ad{x, zeros, P, H, W, ilog2(W), cin, H, W};
+  GatherDesc ad{x, zeros, P, H, W, ilog2(W), cin, H, W, inverse_of(cin / DBK)};
   return launch_gather_rows<false, 1>(s, P, cout, KT, ad, bd, e);
 }
 
@@ -1421,11 +1372,11 @@ hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, in
   const int P = imgs * H * W;
   if (sums) *sum_rows = 0;
   // k tile -> (tap, block of 64 output channels): rows co0.. of W_b, columns tap*Cin..
-  PlainDesc bd{wb, 9 * cin, cin, cout / DBK, (long)DBK * 9 * cin, cin};
+  PlainDesc bd{wb, 9 * cin, cin, cout / DBK, (uint32_t)(DBK * 9 * cin), (uint32_t)cin, inverse_of(cout / DBK)};
   EpiDgrad e{d_prev, out, cin, relu_mask};
   if (stride == 2) {  // one batch of workgroups per parity class of input pixels, each with its own taps
     const int H2 = H / 2, W2 = W / 2, Pc = imgs * H2 * W2;
-    GatherDesc ad{dz, zeros, Pc, H2, W2, ilog2(W2), cout, H2, W2};
+    GatherDesc ad{dz, zeros, Pc, H2, W2, ilog2(W2), cout, H2, W2, inverse_of(cout / DBK)};
     EpiDgradS2 e2{e, H, W, ilog2(W2), ilog2(H2)};
     const int KT = 4 * cout / DBK;  // of the class with four taps; the kernel takes every class's own count
     const long rows128 = (Pc + 127) / 128;
@@ -1444,7 +1395,7 @@ hipError_t conv_mfma_dgrad(hipStream_t s, int imgs, int H, int W, int stride, in
     if (rows && err == hipSuccess) *sum_rows = rows;
     if (err != hipErrorNotSupported) return err;
   }
-  GatherDesc ad{dz, zeros, P, H, W, ilog2(W), cout, H, W};
+  GatherDesc ad{dz, zeros, P, H, W, ilog2(W), cout, H, W, inverse_of(cout / DBK)};
   return launch_gather_rows<true, 1>(s, P, cin, 9 * cout / DBK, ad, bd, e);
 }
 
@@ -1455,8 +1406,8 @@ hipError_t conv_mfma_wgrad(hipStream_t s, int imgs, int H, int W, int stride, in
     const int Ho = H / 2, Wo = W / 2, P = imgs * Ho * Wo;
     const auto [wide, splits] = conv_wgrad_plan(P, cin, cout);
     const int KT = P / DBK / splits;
-    PlainDesc ad{dz, cout, cout, 1 << 30, (long)DBK * cout, 0};
-    GatherDesc bd{x, zeros, P, Ho, Wo, ilog2(Wo), cin, H, W};
+    PlainDesc ad{dz, cout, cout, 1 << 30, (uint32_t)(DBK * cout), 0, inverse_of(1 << 30)};
+    GatherDesc bd{x, zeros, P, Ho, Wo, ilog2(Wo), cin, H, W, inverse_of(cin / DBK)};
     EpiWgradConv e{splits > 1 ? partial : gW, cin, cout};
     hipError_t err;
     if (wide)
@@ -1485,8 +1436,8 @@ hipError_t conv_mfma_wgrad(hipStream_t s, int imgs, int H, int W, int stride, in
   }
   const auto [wide, splits] = conv_wgrad_plan(P, cin, cout);
   const int KT = P / DBK / splits;
-  PlainDesc ad{dz, cout, cout, 1 << 30, (long)DBK * cout, 0};
-  GatherDesc bd{x, zeros, P, H, W, ilog2(W), cin, H, W};
+  PlainDesc ad{dz, cout, cout, 1 << 30, (uint32_t)(DBK * cout), 0, inverse_of(1 << 30)};
+  GatherDesc bd{x, zeros, P, H, W, ilog2(W), cin, H, W, inverse_of(cin / DBK)};
   EpiWgradConv e{splits > 1 ? partial : gW, cin, cout};
   hipError_t err;
   if (wide)
