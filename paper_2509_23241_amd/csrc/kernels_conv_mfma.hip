@@ -291,10 +291,18 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void conv_bf16_dma_kernel(int 
   const int kg = KG == 1 ? 0 : wave_all / NW;  // group along the contraction
   const int wave = KG == 1 ? wave_all : wave_all % NW;
   const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
-  int tile_m, tile_n;
-  map.get(blockIdx.x, tile_m, tile_n);
+  int tile_m, tile_n, batch = blockIdx.y, split = blockIdx.z;
+  if constexpr (!Epi::kSwap) {  // a weight gradient: the taps and tiles of a pixel range
+    const int range = gridDim.x * gridDim.y, at = xcd_position(blockIdx.x + gridDim.x * blockIdx.y + range * blockIdx.z, range * gridDim.z);
+    split = at / range;
+    const int tile = at % range % gridDim.x;
+    batch = at % range / gridDim.x;
+    tile_m = tile / map.tiles_n;
+    tile_n = tile % map.tiles_n;
+  } else {
+    map.get(blockIdx.x, tile_m, tile_n);
+  }
   const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int batch = blockIdx.y, split = blockIdx.z;
   KT = AL::tiles_of(ad, batch, KT);  // the same for every batch but where batches differ in their taps
   const int tile0 = split * KT;
   const int KTg = KT / KG;  // k tiles of this group: tile0 + kg, tile0 + kg + KG, ...

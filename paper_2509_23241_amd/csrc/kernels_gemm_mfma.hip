@@ -292,14 +292,21 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dma_kernel(int M, in
   const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
   for (size_t i = (size_t)blockIdx.x * (64 * NW) + threadIdx.x; i < side.nvec; i += (size_t)gridDim.x * (64 * NW))
     side.dst[i] = side.src[i];
-  int tile_m, tile_n;
-  map.get(blockIdx.x, tile_m, tile_n);
-  if (!map.inside(tile_m, tile_n)) return;
+  int tile_m, tile_n, split = blockIdx.y;
+  if (A_COL && gridDim.y > 1) {
+    const int at = xcd_position(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y), tile = at % gridDim.x;
+    split = at / gridDim.x;
+    tile_m = tile / map.tiles_n;
+    tile_n = tile % map.tiles_n;
+  } else {
+    map.get(blockIdx.x, tile_m, tile_n);
+    if (!map.inside(tile_m, tile_n)) return;
+  }
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const uint32_t lds_base = lds_addr_of(lds_raw);
-  // blockIdx.y: range of the contraction this workgroup sums over, `per` k tiles long (the last one may be shorter);
+  // split: range of the contraction this workgroup sums over, `per` k tiles long (the last one may be shorter);
   // each range writes its own output (fp32 partial results that a second kernel adds in a fixed order)
-  const int split = blockIdx.y, first = split * per;
+  const int first = split * per;
   const int KT = min(per, (TAIL ? (K + DBK - 1) / DBK : K / DBK) - first);
   const int last_k = K - (first + KT - 1) * DBK;  // k values of the last tile, if it holds fewer than DBK
   A = in_sgprs(A + first * AT::tile_step(lda) + (size_t)m0 * (A_COL ? 1 : lda));
@@ -703,8 +710,9 @@ hipError_t launch_dma(hipStream_t s, int M, int N, int K, const uint16_t* A, int
     if (attr != hipSuccess) return attr;
   }
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  const TileMap map = make_uneven_tile_map(tiles_m, tiles_n, BM, BN);
-  hipLaunchKernelGGL(kernel, dim3(map.grid(), (k_tiles(K) + per - 1) / per), dim3(64 * NW), lds_bytes, s, M, N, K, per, A,
+  const int ranges = (k_tiles(K) + per - 1) / per;
+  const TileMap map = ranges > 1 ? TileMap{tiles_m, tiles_n, 0, 0, 0, 0} : make_uneven_tile_map(tiles_m, tiles_n, BM, BN);
+  hipLaunchKernelGGL(kernel, dim3(map.grid(), ranges), dim3(64 * NW), lds_bytes, s, M, N, K, per, A,
                      lda, B, ldb, epi, map, side);
   return hipGetLastError();
 }

@@ -329,6 +329,12 @@ struct TileMap {
   int grid() const { return xm == 0 ? tiles_m * tiles_n : 8 * cm * cn; }
 };
 
+// The same for `count` workgroups that are to be neighbours in another order than that of their ids: position of workgroup b, consecutive
+// positions on one XCD.  For contraction ranges, whose workgroups read the same rows: range by range instead of a patch of
+// the output in every range.  Weight gradient of 256 x 64 over 131072 rows, 64 ranges
+// of four 64 x 64 tiles, 21.6 -> 17.9 us; of 1024 x 256 over 8192, 32 ranges of 128 x 128 tiles, 24.1 -> 18.4.
+__device__ __forceinline__ int xcd_position(int b, int count) { return count & 7 ? b : (b & 7) * (count >> 3) + (b >> 3); }
+
 // Optional side job of a forward GEMM: keep a copy of its input (the stage saves the activations a
 // micro-batch arrives with).  The workgroups share the copy evenly, 16 bytes per lane per step.
 struct SideCopy {
