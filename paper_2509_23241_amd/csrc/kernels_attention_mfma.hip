@@ -165,16 +165,8 @@ hipError_t launch_attn_gemm(hipStream_t s, int Z, int M, int N, int K, const uin
   return hipGetLastError();
 }
 
-__device__ __forceinline__ float wsum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ float wmax(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
+__device__ __forceinline__ float wsum(float v) { return sum_over_lanes(v); }
+__device__ __forceinline__ float wmax(float v) { return max_over_lanes(v); }
 
 // one wave per query row: P[i][j] = softmax over j <= i of scale * S[i][j], zeros for j > i; lse[i]
 __global__ __launch_bounds__(256) void attn_softmax_fwd_kernel(int S, size_t rows, float scale, const float* __restrict__ scores,
@@ -311,11 +303,7 @@ __device__ __forceinline__ uint32_t rows_to_redo(bool finite, int row, int S) {
   return (uint32_t)m | (uint32_t)(m >> 32);
 }
 __device__ __forceinline__ float lane_of(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
-__device__ __forceinline__ float sum_of_wave(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
+__device__ __forceinline__ float sum_of_wave(float v) { return sum_over_lanes(v); }
 template <int DH>
 __device__ __forceinline__ float row_dot(const uint16_t* a, const uint16_t* b) {
   float acc = 0.f;
@@ -340,10 +328,7 @@ __device__ __forceinline__ void redo_output_row(int i, const uint16_t* q, const 
   for (int k0 = 0; k0 <= i; k0 += 64) {
     const int j = k0 + lane;
     const float sc = j <= i ? row_dot<DH>(q + (size_t)i * ld, k + (size_t)j * ld) * scale_log2 : -INFINITY;
-    float mx = sc;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    const float mn = fmaxf(m, mx);
+    const float mn = fmaxf(m, max_over_lanes(sc));
     const float p = sc == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc - mn);
     const float corr = __builtin_amdgcn_exp2f(m - mn);
     l = l * corr + sum_of_wave(p);
@@ -514,7 +499,7 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int head
           sacc[j][r] = v;
           mloc = fmaxf(mloc, v);
         }
-      mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+      mloc = over_halves(mloc, Max());
       const float mnew = fmaxf(mrun, mloc);  // finite: block 0 shows key 0 to every query
       const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);
       mrun = mnew;
@@ -548,7 +533,7 @@ __global__ __launch_bounds__(64 * NW) void attn_flash_fwd_kernel(int S, int head
   wait_vmcnt<0>();  // the trailing dummy copies must have landed before LDS is reused
   lds_barrier();
   if (!active) return;
-  const float ltot = lsum + __shfl_xor(lsum, 32, 64);
+  const float ltot = over_halves(lsum, Add());
   const float inv = 1.f / ltot;
 #pragma unroll
   for (int j = 0; j < TN; ++j)

@@ -295,34 +295,45 @@ __device__ __forceinline__ int slab_of_block(int b, int nblocks) {
 
 // Sums NV values per lane over the lanes that hold the same unit t % W, in a fixed order; every lane gets the totals
 // of its unit.  The values go through LDS as [NV][1024] with the lanes of one unit next to each other: thread (v, p)
-// adds 16 neighbouring entries of quantity v, the 64 / W threads of one unit finish with a butterfly.
+// adds 16 neighbouring entries of quantity v, the 64 / W threads of one unit finish with a butterfly.  A layer's forward pass waits
+// for two of these, one after the other, with a CU to itself: the four 16-byte pieces of a thread's 64 bytes are
+// swapped by its number, so that eight neighbours read from all banks, and the second unit starts half the banks on.
+// With that, the butterfly in vector instructions and two barriers instead of three: forward of 2048 rows 256 channels 8.57 -> 7.50,
+// 1024 channels with an addend 12.5 -> 11.5, backward of four such segments 15.3 -> 13.9 and 18.1 -> 16.8 us.
+template <int W>
+struct SlabSum {
+  static constexpr int kSeg = kSlabThreads / W + (W > 1 ? 32 : 0);  // floats per unit
+  static constexpr int kRow = W * kSeg;                             // per quantity
+  static constexpr int floats(int nv) { return nv * (kRow + W); }
+};
 template <int NV, int W>
-__device__ __forceinline__ void slab_sum(float (&v)[NV], float* red /* [NV][kSlabThreads] + [NV][W] */) {
+__device__ __forceinline__ void slab_sum(float (&v)[NV], float* red /* [NV][kRow] + [NV][W] */) {
   static_assert(NV * 64 <= kSlabThreads, "one wave per quantity");
-  constexpr int kSeg = kSlabThreads / W;  // lanes per unit
-  constexpr int kTpu = 64 / W;            // adding threads per unit
+  constexpr int kSeg = SlabSum<W>::kSeg, kRow = SlabSum<W>::kRow;
+  constexpr int kTpu = 64 / W;  // adding threads per unit
   const int t = threadIdx.x;
-  const int at = (t % W) * kSeg + t / W;
-  __syncthreads();  // the previous totals have been read
+  const int n = t / W;
+  const int at = (t % W) * kSeg + ((n & ~12) | ((n ^ (n >> 4)) & 12));
+  // The entries of the call before were read ahead of its last barrier, its totals (which none of these entries are) are read
+  // ahead of this call's first.
 #pragma unroll
-  for (int i = 0; i < NV; ++i) red[i * kSlabThreads + at] = v[i];
+  for (int i = 0; i < NV; ++i) red[i * kRow + at] = v[i];
   __syncthreads();
   if (t < NV * 64) {
-    const int q = t >> 6, p = t & 63;
-    const float4* src = reinterpret_cast<const float4*>(red + q * kSlabThreads + p * 16);
+    const int q = t >> 6, p = t & 63, turn = (p % kTpu >> 2) & 3;
+    const float* src = red + q * kRow + p / kTpu * kSeg + p % kTpu * 16;
     float a = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const float4 f = src[k];
+      const float4 f = *reinterpret_cast<const float4*>(src + 4 * (k ^ turn));
       a += (f.x + f.y) + (f.z + f.w);
     }
-#pragma unroll
-    for (int off = kTpu / 2; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-    if (p % kTpu == 0) red[NV * kSlabThreads + q * W + p / kTpu] = a;
+    a = sum_over_lanes<kTpu / 2>(a);
+    if (p % kTpu == 0) red[NV * kRow + q * W + p / kTpu] = a;
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = red[NV * kSlabThreads + i * W + t % W];
+  for (int i = 0; i < NV; ++i) v[i] = red[NV * kRow + i * W + t % W];
 }
 
 __device__ __forceinline__ void unpack8(const uint4& u, float (&f)[8]) { Unit<uint16_t>::unpack(u, f); }
@@ -433,7 +444,7 @@ __global__ __launch_bounds__(kSlabThreads) void bn_fwd_slab_kernel(int rows, int
                                                                    const uint16_t* __restrict__ addend,
                                                                    uint16_t* __restrict__ a_out, uint16_t* __restrict__ d_out,
                                                                    float* __restrict__ stats) {
-  __shared__ __attribute__((aligned(16))) float red[8 * kSlabThreads + 8 * W];
+  __shared__ __attribute__((aligned(16))) float red[SlabSum<W>::floats(8)];
   constexpr int kRowsPerPass = kSlabThreads / W;
   const int r0 = threadIdx.x / W;
   const int c0 = slab_of_block(blockIdx.x, gridDim.x) * 8 * W + 8 * (threadIdx.x % W);
@@ -514,7 +525,7 @@ __global__ __launch_bounds__(kSlabThreads) void bn_bwd_slab_kernel(int rows, int
                                                                    const float* __restrict__ gamma_l, float alpha, float beta_c,
                                                                    uint16_t* __restrict__ dx, float* __restrict__ sums,
                                                                    float* __restrict__ dx_sums) {
-  __shared__ __attribute__((aligned(16))) float red[16 * kSlabThreads + 16 * W];
+  __shared__ __attribute__((aligned(16))) float red[SlabSum<W>::floats(16)];
   constexpr int kRowsPerPass = kSlabThreads / W;
   const int r0 = threadIdx.x / W;
   const int c0 = slab_of_block(blockIdx.x, gridDim.x) * 8 * W + 8 * (threadIdx.x % W);

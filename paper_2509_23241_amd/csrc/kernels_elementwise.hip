@@ -26,11 +26,7 @@ constexpr int kUpdateBlocks = 2048;
 constexpr int kUnroll = 2;
 constexpr bool kNonTemporal = true;
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
+__device__ __forceinline__ float wave_sum(float v) { return sum_over_lanes(v); }
 
 // Sum `NV` values over the block; result valid in thread 0.  Fixed order => deterministic.
 template <int NV>
@@ -273,8 +269,7 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(int rows, int clas
 #pragma unroll
     for (int i = 0; i < kHeld; ++i) mx = fmaxf(mx, v[i]);
     for (int c = lane + 64 * kHeld; c < classes; c += 64) mx = fmaxf(mx, to_float(lg[c]));
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    mx = max_over_lanes(mx);
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < kHeld; ++i)
@@ -322,12 +317,8 @@ __global__ __launch_bounds__(kSmallThreads) void softmax_ce_small_kernel(int row
   for (int row = threadIdx.x / kSmallClasses; row < rows; row += kSmallThreads / kSmallClasses) {
     const int label = labels[row];
     const float z = c < classes ? to_float(logits[(size_t)row * classes + c]) : -INFINITY;
-    float mx = z;
-#pragma unroll
-    for (int off = kSmallClasses / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    float sum = c < classes ? expf(z - mx) : 0.f;
-#pragma unroll
-    for (int off = kSmallClasses / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    const float mx = max_over_lanes<kSmallClasses / 2>(z);
+    const float sum = sum_over_lanes<kSmallClasses / 2>(c < classes ? expf(z - mx) : 0.f);
     const float lse = logf(sum);
     if (c == 0 && (unsigned)label >= (unsigned)classes) row_loss[row] = __builtin_nanf("");
     if (c < classes) {

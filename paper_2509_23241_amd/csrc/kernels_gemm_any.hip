@@ -519,9 +519,7 @@ struct EpiInputGrad {
   // the 16 rows m - m % 16 .. of columns n .. n+3: the lanes of a row of 16 have one each (rows outside: zeros)
   __device__ __forceinline__ void store_sums(int m, int n, int M, int N, floatx4 v) const {
 #pragma unroll
-    for (int off = 1; off < 16; off *= 2)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] += __shfl_xor(v[j], off, 64);
+    for (int j = 0; j < 4; ++j) v[j] = row_sum_ascending(v[j]);
     if (m % 16 == 0 && m < M)
 #pragma unroll
       for (int j = 0; j < 4; ++j)

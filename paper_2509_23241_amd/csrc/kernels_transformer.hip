@@ -27,20 +27,12 @@ namespace {
 constexpr int kThreads = 256;
 constexpr float kLnEps = 1e-5f;
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
+__device__ __forceinline__ float wave_sum(float v) { return sum_over_lanes(v); }
 // value of lane `src` (wave uniform) for every lane, whatever the execution mask
 __device__ __forceinline__ float lane_value(float v, int src) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
+__device__ __forceinline__ float wave_max(float v) { return max_over_lanes(v); }
 
 // ---- layer normalisation: one wave per row ------------------------------------------------------
 template <typename T>

@@ -253,9 +253,12 @@ struct WaveSums<TM, TN, Epi, true> {
     if (!epi.sums) return;
     constexpr int kLanesPerRow = 4 * TN;
 #pragma unroll
-    for (int off = kLanesPerRow; off < 64; off *= 2)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) s[j] += __shfl_xor(s[j], off, 64);
+    for (int j = 0; j < 8; ++j) {  // lane ^ kLanesPerRow, then those above it
+      if constexpr (kLanesPerRow <= 4) s[j] += __shfl_xor(s[j], 4, 64);
+      if constexpr (kLanesPerRow <= 8) s[j] += rotated<8>(s[j]);
+      if constexpr (kLanesPerRow <= 16) s[j] = over_rows(s[j], Add());
+      if constexpr (kLanesPerRow <= 32) s[j] = over_halves(s[j], Add());
+    }
     if (lane < kLanesPerRow) {
       float4* p = reinterpret_cast<float4*>(epi.sums + (size_t)(mbase / (32 * TM)) * epi.ldc + nbase + 8 * lane);
       p[0] = make_float4(s[0], s[1], s[2], s[3]);
