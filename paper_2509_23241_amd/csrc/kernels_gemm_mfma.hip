@@ -711,7 +711,13 @@ hipError_t launch_dma(hipStream_t s, int M, int N, int K, const uint16_t* A, int
   }
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int ranges = (k_tiles(K) + per - 1) / per;
-  const TileMap map = ranges > 1 ? TileMap{tiles_m, tiles_n, 0, 0, 0, 0} : make_uneven_tile_map(tiles_m, tiles_n, BM, BN);
+  // Uneven patches save what arrives per k step, so little of a short contraction on the smallest tiles, and of a short weight gradient,
+  // which writes fp32: below 1024 values 64 x 64 tiles are 0.98 of the time in the mean and up to 1 us of 9 behind (0.94 from there on),
+  // weight gradients 1.01 and up to 1 us of 9 behind (0.98).
+  const bool short_k = (A_COL || BM * BN == 64 * 64) && K < 1024;
+  const TileMap map = ranges > 1 ? TileMap{tiles_m, tiles_n, 0, 0, 0, 0}
+                      : short_k  ? make_tile_map(tiles_m, tiles_n)
+                                 : make_uneven_tile_map(tiles_m, tiles_n, BM, BN);
   hipLaunchKernelGGL(kernel, dim3(map.grid(), ranges), dim3(64 * NW), lds_bytes, s, M, N, K, per, A,
                      lda, B, ldb, epi, map, side);
   return hipGetLastError();

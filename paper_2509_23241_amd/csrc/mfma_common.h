@@ -322,13 +322,13 @@ __device__ __forceinline__ floatx16 mma(bf16x8 a, bf16x8 b, floatx16 c) {
 struct TileMap {
   int tiles_m, tiles_n, xm, xn;  // xm*xn == 8, or xm == 0 for the plain row-major mapping
   int cm, cn;
-  __device__ __forceinline__ void get(int b, int& tm, int& tn) const {
+  __host__ __device__ __forceinline__ void get(int b, int& tm, int& tn) const {
     if (xm == 0) { tm = b / tiles_n; tn = b % tiles_n; return; }
     const int xcd = b & 7, i = b >> 3;
     tm = (xcd / xn) * cm + i / cn;
     tn = (xcd % xn) * cn + i % cn;
   }
-  __device__ __forceinline__ bool inside(int tm, int tn) const { return tm < tiles_m && tn < tiles_n; }
+  __host__ __device__ __forceinline__ bool inside(int tm, int tn) const { return tm < tiles_m && tn < tiles_n; }
   int grid() const { return xm == 0 ? tiles_m * tiles_n : 8 * cm * cn; }
 };
 
@@ -360,18 +360,24 @@ inline TileMap make_tile_map(int tiles_m, int tiles_n) {
 
 // The same for tile spaces that do not divide into eight equal patches: patches of ceil(tiles / xm) x ceil(tiles / xn), the last ones
 // smaller or empty.  By the time an XCD's tiles take to arrive, its panels from behind the L2 at about a third of the rate at which its
-// CUs fetch from the L2; an exact division, if there is one, gives way where that is a sixth less.  25 x 8 tiles of 64 x 64,
+// CUs fetch from the L2; taken where that is a fifth less than in the order above.  Two conditions beside it, since the XCDs with
+// whole patches have more than an eighth of the tiles: none of their 32 CUs may get another round of tiles (7 x 36 of 128 x 128 as eight of
+// 4 x 9: 36 on some XCDs, 777 x 4608 over 1536 25.6 us row by row, 34.3 so), and the patches hold at most 15 % more places than there are
+// tiles.  Over 490 products at random sizes that come this way, row by row and so: 0.945 of the time in the mean; one in thirty is
+// 3 % or more slower, the worst by 0.5 us of 9; without the two conditions one in six was, by up to 1.9 times.  25 x 8 tiles of 64 x 64,
 // 1600 x 512 over 2048: 14.6 -> 12.4 us (all rows of A went to every XCD), 50 x 4 of 128 x 128, 6400 x 512, 16.9 -> 15.6.
 inline TileMap make_uneven_tile_map(int tiles_m, int tiles_n, int bm, int bn) {
   static const int cand[4][2] = {{2, 4}, {4, 2}, {1, 8}, {8, 1}};
   auto time = [&](long tiles, long rows, long columns) { return 3 * (rows * bm + columns * bn) + tiles * (bm + bn); };
   TileMap best = make_tile_map(tiles_m, tiles_n);
-  const long even = ((long)tiles_m * tiles_n + 7) / 8;
-  long best_time = best.xm ? time(even, best.cm, best.cn) * 5 / 6 : time(even, std::min<long>(even, tiles_m), std::min<long>(even, tiles_n));
+  const long tiles = (long)tiles_m * tiles_n, even = (tiles + 7) / 8;
+  long best_time = (best.xm ? time(even, best.cm, best.cn) : time(even, std::min<long>(even, tiles_m), std::min<long>(even, tiles_n))) * 4 / 5;
   for (auto& c : cand) {
     const int cm = (tiles_m + c[0] - 1) / c[0], cn = (tiles_n + c[1] - 1) / c[1];
-    const long t = time((long)cm * cn, cm, cn);
-    if (t < best_time) { best_time = t; best = TileMap{tiles_m, tiles_n, c[0], c[1], cm, cn}; }
+    const long most = (long)cm * cn, t = time(most, cm, cn);  // most: tiles of an XCD
+    if ((most + 31) / 32 > (even + 31) / 32 || 20 * 8 * most > 23 * tiles || t >= best_time) continue;
+    best_time = t;
+    best = TileMap{tiles_m, tiles_n, c[0], c[1], cm, cn};
   }
   return best;
 }
