@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace tp {
 
 // the geometries the kernels take; the launchers return hipErrorInvalidValue for any other
@@ -58,6 +60,39 @@ hipError_t launch_avgpool_bwd(hipStream_t s, int elt, int imgs, int positions, i
 // bf16 matrix-core versions (kernels_conv_mfma.hip) and the shapes they take
 bool conv_mfma_supported(int imgs, int H, int W, int stride, int cin, int cout);
 int conv_mfma_wgrad_max_splits(int pixels, int cin, int cout);
+// How the 3x3 weight gradient of image tiles (stride 1) is split: pixel ranges, the products of `apart` tiles of a range summed apart, and
+// all nine taps per workgroup or the three of a filter row (`rows`).
+// The faster of the two by these estimates in ns, fitted to 28 layers of 64 to 1024 channels: nine taps 11 us + 1.8 per tile + 1.1 for
+// every time sums are put aside, rows 9.6 + 0.69 per tile and 0.55 for every time, 22 ns per partial result of 64 x 64 channels.  Nine taps and
+// rows, with the launch that adds up, us: 128 images of 16 x 16, 384 channels 92 and 108, 512 channels 144 and 194 (one row range for 192
+// CUs), 640 channels 246 and 378 (two rounds); 256 of 32 x 32, 64 channels, 37.3 and 36.9; 16 of 64 x 64 26.1 and 21.3; 16 of 16 x 16,
+// 512 channels, 38.1 and 36.5; 4 of them 24.5 and 19.8.
+// A sum's squared error, in steps of 16 pixels, counts 8 per tile of a nine-tap chain, 4 of a row's, one for every chain, two for the
+// meeting of a row's halves, a tenth for every range.  Rows only where that is less than in nine-tap chains over all tiles, and with fewer
+// than two tiles per nine-tap workgroup only with a single one of their own (6 images of 16 x 16, 192 -> 320 channels: off fp64 by 6.9e-8
+// with nine taps, 7.3e-8 by rows); nine taps only in chains that bring it down to that of rows by eights, since over all tiles of
+// a workgroup they are far off (128 images, 448 channels, 3.3e-7 and 1.3e-7).
+constexpr int kWgradPixels = 128;  // of a tile
+struct PatchWgradPlan {
+  bool rows;
+  int splits, apart;
+};
+inline PatchWgradPlan patch_wgrad_plan(long px_tiles, int cin, int cout) {
+  const long blocks = std::max(1l, (long)(cin / 64) * (cout / 64));
+  auto over = [](long a, long b) { return (a + b - 1) / b; };
+  auto ranges = [&](long workgroups) { return std::max(1l, std::min(px_tiles, 256 / workgroups)); };
+  const long nine = ranges(blocks), rows = ranges(3 * blocks), nine_tiles = over(px_tiles, nine), row_tiles = over(px_tiles, rows);
+  int row_apart = (int)std::min(row_tiles, 8l), nine_apart = (int)std::min(nine_tiles, 64l);
+  while (row_apart > 0 && (10 * (4 * row_apart + over(row_tiles, row_apart) + 2) + rows) * nine >= 80 * px_tiles + nine * nine) --row_apart;
+  if (px_tiles < 2 * nine && row_tiles > 1) row_apart = 0;
+  const long most = 10 * (34 + over(row_tiles, 8)) + rows;
+  while (nine_apart > 0 && 10 * (8 * nine_apart + over(nine_tiles, nine_apart) + 1) + nine > most) --nine_apart;
+  const long nine_ns = 11000 + 1800 * nine_tiles + (nine_apart ? 1100 * ((nine_tiles - 1) / nine_apart) : 0) + 22 * blocks * nine;
+  const long row_round = 690 * row_tiles + (row_apart ? 550 * ((row_tiles - 1) / row_apart) : 0);
+  const long row_ns = 9600 + row_round * over(3 * blocks * rows, 256) + 22 * blocks * rows;
+  if (row_apart && (!nine_apart || row_ns < nine_ns)) return {true, (int)rows, row_apart};
+  return {false, (int)nine, nine_apart ? nine_apart : (int)nine_tiles};
+}
 hipError_t conv_mfma_fprop(hipStream_t s, int imgs, int H, int W, int stride, int cin, int cout, const uint16_t* x,
                            const uint16_t* wgt, const float* bias, int act, uint16_t* d_out, uint16_t* a_out,
                            const uint16_t* zeros);

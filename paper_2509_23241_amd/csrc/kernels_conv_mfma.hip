@@ -607,24 +607,154 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_patch_kernel(int P, int N
   }
 }
 
-// wgrad: dW[co][tap][ci] = sum_p dz[p][co] * x[p shifted by tap][ci] for one block of 64 output and 64 input channels and
-// the three taps of one row of the filter; the workgroup walks over tiles of 128 pixels, three buffers, two tiles in flight
-// while one is multiplied.  Its patch is the 128 pixels one filter row up or down, with a column of zeros on both sides.
-// Bound by memory: the inputs once, and the fp32 partial results, one of every workgroup, which are written and read again.
-// With all nine taps in a workgroup those were 147 KB from each of 256, 38 MB a layer; three taps leave a third of it
-// and walk over three times the pixels, where the workgroups that share a pixel range sit on one XCD and meet in its L2.
-// A wave takes all 64 output channels of 32 input channels: 5 fragments for 6 matrix instructions (10 for 9 before), and
-// half of a tile's pixels, the other two waves the other half; the two meet through LDS at the end.  The products of 8 tiles are
-// summed apart: in chains over all tiles of a workgroup the gradients were up to 1.4 times further off fp64 than with the
-// nine-tap kernel's shorter ones (256 images of 16 x 16, 128 channels, 1.55e-7 there, 2.15e-7 in chains, 1.19e-7 now).
-// The gradients of 256 images of 32 x 32, 64 -> 64, and of 16 x 16, 64 -> 128 and 128 -> 128 channels 25.2, 15.3 and 24.5 us
-// with nine taps, 25.2, 16.4 and 25.3 now, and the one launch that adds up the partial results of them all 27.7 -> 15.3: a step of
-// the VGG stage 334 -> 307 us.  A fourth buffer changes nothing.
-template <int W>
+// wgrad: dW[co][tap][ci] = sum_p dz[p][co] * x[p shifted by tap][ci] for one block of 64 output and 64 input channels and all
+// nine taps; the workgroup walks over tiles of 128 pixels split, split + splits, ..., double buffered: the copies of the next tile
+// fly while the current one is multiplied.
+// With one wave per SIMD (nine accumulators each) bound by what is issued beside the matrix instructions: three or four vector
+// instructions are free next to one, but an LDS address per tap (8) and two divisions per 1 KB of patch were several
+// times that.  W is the image width: patch rows begin at constants, so a lane has four LDS addresses in all, and where its
+// copies come from is worked out once.  256 images of 32 x 32, 64 channels, with the sums of the partial results: 43.2 -> 30.5 us
+// (34.5 with the divisions by multiplication but one source address at a time); 64 of 64 x 64 45.6 -> 31.3.
+// APART: the products of `apart` tiles are summed apart (about 1.1 us each time, three moves and an addition per sum): 128 images of
+// 16 x 16, 512 channels, 120 -> 130 us, and off fp64 by 0.4 of what one chain over 64 tiles is.
+template <int W, bool APART>
 __global__ __launch_bounds__(256) void conv_wgrad_patch_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ zeros, int H,
                                                                int cin, const uint16_t* __restrict__ dz, int cout, int px_tiles,
-                                                               int splits, float* __restrict__ out) {
-  constexpr int BM = 128, NW = 4, NS = 3;
+                                                               int apart, float* __restrict__ out) {
+  constexpr int BM = kWgradPixels, NW = 4;
+  using DZ = ColDma<64, NW>;  // stage [pixel][64 output channels]; k index = pixel
+  constexpr int kDz = BM * 8 / 64 / NW;
+  constexpr int kPatchInstr = ((BM / W + 2) * (W + 2) * 128 + 1023) / 1024, kPatch = (kPatchInstr + NW - 1) / NW;
+  constexpr int kPatchBytes = kPatchInstr * 1024, kBufBytes = kPatchBytes + BM * 128;
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds_raw[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ci_blocks = cin / 64, cob = blockIdx.x / ci_blocks, cib = blockIdx.x - cob * ci_blocks;
+  const int split = blockIdx.y, splits = gridDim.y;
+  const uint32_t lds_base = lds_addr_of(lds_raw);
+  const int rb_co = (wave >> 1) * 32, rb_ci = (wave & 1) * 32;
+
+  floatx16 acc[9], sum[9];  // of the latest tiles; of those before, if there are any
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = sum[t][r] = 0.f;
+  auto put_aside = [&] {
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        sum[t][r] += acc[t][r];
+        acc[t][r] = 0.f;
+      }
+  };
+
+  // where the lane's chunks of dz and of the patch come from, relative to the tile's first pixel, and the patch rows they belong to
+  // less one (1 << 20: outside every image)
+  uint32_t dzoff[kDz];
+#pragma unroll
+  for (int i = 0; i < kDz; ++i) {
+    const int flat = 64 * (wave + NW * i) + lane;
+    const int k = flat >> 3, c = (flat & 7) ^ DZ::swz(k);
+    dzoff[i] = (uint32_t)(((size_t)k * cout + cob * 64 + c * 8) * 2);
+  }
+  int from[kPatch], prow[kPatch];
+#pragma unroll
+  for (int i = 0; i < kPatch; ++i) {
+    const int flat = (wave + NW * i) * 64 + lane, pp = flat >> 3;
+    const int chunk = (flat & 7) ^ patch_swz_tr(pp), pr = pp / (W + 2), pc = pp % (W + 2);
+    from[i] = ((pr - 1) * W + pc - 1) * cin + cib * 64 + chunk * 8;
+    prow[i] = pr < BM / W + 2 && pc >= 1 && pc <= W ? pr - 1 : 1 << 20;
+  }
+  auto issue_tile = [&](int tile, int buf) {
+    const uint32_t dst = lds_base + buf * kBufBytes;
+    const int h0 = tile * (BM / W) & (H - 1);
+    const uint16_t *x_tile = x + (long)tile * BM * cin, *dz_tile = dz + (size_t)tile * BM * cout;
+#pragma unroll
+    for (int i = 0; i < kPatch; ++i)
+      if (kPatchInstr % NW == 0 || wave + NW * i < kPatchInstr)
+        dma16_addr(dst + (wave + NW * i) * 1024, (unsigned)(h0 + prow[i]) < (unsigned)H ? x_tile + from[i] : zeros + (lane & 7) * 8);
+#pragma unroll
+    for (int i = 0; i < kDz; ++i) dma16(dst + kPatchBytes + (wave + NW * i) * 1024, dz_tile, dzoff[i]);
+  };
+
+  // byte of the lane's pixel (and 16-byte slot) in a patch row that begins at patch pixel u = 0 .. 3 (mod 4): the swizzle of
+  // patch pixel p depends on p / 2 % 2 alone
+  int lane_at[4];
+  {
+    const int g = lane >> 4, s = lane & 15, col = rb_ci + 16 * (g & 1) + 4 * (s & 3), px = (W == 8 ? 10 : 8) * (g >> 1) + (s >> 2);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) lane_at[u] = px * 128 + ((col >> 3) ^ patch_swz_tr(u + px)) * 16 + (col & 7) * 2;
+  }
+  typedef __attribute__((address_space(3))) shortx4* lds_ptr;
+
+  if (split < px_tiles) issue_tile(split, 0);
+  int buf = 0;
+  int chain = 0;  // tiles of the sums in hand
+  for (int tile = split; tile < px_tiles; tile += splits) {
+    if (APART && chain++ == apart) {
+      put_aside();
+      chain = 1;
+    }
+    wait_vmcnt<0>();  // this tile has landed (nothing else is in flight)
+    lds_barrier();    // ... for every wave, and every wave is done with the other buffer
+    if (tile + splits < px_tiles) issue_tile(tile + splits, buf ^ 1);
+    const char* lp = reinterpret_cast<const char*>(lds_raw) + buf * kBufBytes;
+    const uint16_t* ldz = reinterpret_cast<const uint16_t*>(lp + kPatchBytes);
+    const char* at[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) at[u] = lp + lane_at[u];
+    constexpr int kAll = BM / 16 * 9, kAhead = 3;
+    bf16x8 fa[2], fb[kAhead + 1];
+    auto fetch = [&](int q) {  // the fragment of x of product q: tap q % 9 of k step q / 9
+      const int kk = q / 9, t = q % 9;
+      const int u = (kk * 16 / W + t / 3) * (W + 2) + kk * 16 % W + t % 3;
+      const char* p = at[u & 3] + u * 128;
+      const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
+      const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * 128));
+      fb[q % (kAhead + 1)] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    fa[0] = DZ::frag(ldz, rb_co, 0, lane);
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) fetch(q);
+#pragma unroll
+    for (int q = 0; q < kAll; ++q) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (q + kAhead < kAll) fetch(q + kAhead);
+      if (q % 9 == 4 && q / 9 + 1 < BM / 16) fa[(q / 9 + 1) & 1] = DZ::frag(ldz, rb_co, q / 9 + 1, lane);
+      __builtin_amdgcn_sched_barrier(0);
+      acc[q % 9] = mma<false>(fa[(q / 9) & 1], fb[q % (kAhead + 1)], acc[q % 9]);
+    }
+    buf ^= 1;
+  }
+  float* o = out + (size_t)split * cout * 9 * cin;
+#pragma unroll
+  for (int t = 0; t < 9; ++t) {
+    floatx16 one[1][1];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) one[0][0][r] = APART ? sum[t][r] + acc[t][r] : acc[t][r];
+    store_tiles<1, 1>(one, EpiWgrad{o + (size_t)t * cin, 9 * cin}, cob * 64 + rb_co, cib * 64 + rb_ci, cout, cin, lane);
+  }
+}
+
+// The same for the three taps of one row of the filter, from three buffers, two tiles in flight while one is multiplied.  Its
+// patch is the 128 pixels one filter row up or down, with a column of zeros on both sides.
+// The fp32 partial results, one of every workgroup, are written and read again: with nine taps 147 KB from each of 256 workgroups,
+// 38 MB a layer; three taps leave a third of it and walk over three times the pixels, where the workgroups that share a pixel
+// range sit on one XCD and meet in its L2.  Per product it takes a quarter longer (the inputs come three times), so it is for
+// few pixels per workgroup: patch_wgrad_plan().
+// A wave takes all 64 output channels of 32 input channels: 5 fragments for 6 matrix instructions (10 for 9 above), and
+// half of a tile's pixels, the other two waves the other half; the two meet through LDS at the end.  The products of `apart` tiles are
+// summed apart, so that chains round no more often than above (256 images of 16 x 16, 128 channels, off fp64 by 1.55e-7 there, 2.15e-7 in
+// chains over all tiles of a workgroup, 1.19e-7 in chains of 8, about 0.55 us each time).
+// The gradients of 256 images of 32 x 32, 64 -> 64, and of 16 x 16, 64 -> 128 and 128 -> 128 channels 25.2, 15.3 and 24.5 us
+// with nine taps, 25.2, 16.4 and 25.3 here, and the one launch that adds up the partial results of them all 27.7 -> 15.3: a step of
+// the VGG stage 334 -> 307 us.  A fourth buffer changes nothing.
+template <int W>
+__global__ __launch_bounds__(256) void conv_wgrad_patch_row_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ zeros, int H,
+                                                                   int cin, const uint16_t* __restrict__ dz, int cout, int px_tiles,
+                                                                   int splits, int apart, float* __restrict__ out) {
+  constexpr int BM = kWgradPixels, NW = 4, NS = 3;
   using DZ = ColDma<64, NW>;  // stage [pixel][64 output channels]; k index = pixel
   constexpr int kDz = BM * 8 / 64 / NW;                                        // copies of one wave per tile: dz,
   constexpr int kPatch = ((BM / W) * (W + 2) * 128 + NW * 1024 - 1) / (NW * 1024);  // and the patch (the surplus copies zeros)
@@ -641,7 +771,6 @@ __global__ __launch_bounds__(256) void conv_wgrad_patch_kernel(const uint16_t* _
   const int ci_half = wave & 1, px_half = wave >> 1;
   const uint32_t lds_base = lds_addr_of(lds_raw);
 
-  constexpr int kApart = 8;
   floatx16 acc[2][3], sum[2][3];  // [half of the output channels][tap]: of the latest tiles, of those before
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -756,7 +885,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_patch_kernel(const uint16_t* _
   };
   const int copying = max(0, n - (NS - 1));
   for (int i = 0; i < n;) {
-    const int end = min(i + kApart, n), with_copies = min(end, copying);
+    const int end = min(i + apart, n), with_copies = min(end, copying);
     for (; i < with_copies; ++i) tile(i, std::true_type{});
     for (; i < end; ++i) tile(i, std::false_type{});
     put_aside();
@@ -1302,25 +1431,35 @@ hipError_t launch_patch_conv(hipStream_t s, int P, int H, int W, int C, int N, c
   }
 }
 
-constexpr int kWgradBM = 128;
-inline bool wgrad_patch_ok(int H, int W) { return patch_shape_ok(H, W, kWgradBM); }
-// Pixel ranges of the patch weight gradient: a workgroup for every CU.
-inline int wgrad_patch_splits(long px_tiles, int cin, int cout) {
-  const long blocks = std::max(1l, 3l * (cin / 64) * (cout / 64));
-  return (int)std::max(1l, std::min(px_tiles, 256 / blocks));
-}
+inline bool wgrad_patch_ok(int H, int W) { return patch_shape_ok(H, W, kWgradPixels); }
 
 template <int W>
 hipError_t launch_wgrad_patch(hipStream_t s, const uint16_t* x, const uint16_t* zeros, int H, int cin, const uint16_t* dz, int cout,
-                              int px_tiles, int splits, float* out) {
-  constexpr int kBuf = ((kWgradBM / W) * (W + 2) * 128 + 4095) / 4096 * 4096 + kWgradBM * 128;
-  static_assert(3 * kBuf >= 4 * 3 * 16 * 64 * 4 && 3 * kBuf <= kMaxLds, "three buffers, and the handover in their place");
-  auto kernel = conv_wgrad_patch_kernel<W>;
-  static hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 3 * kBuf);
-  if (attr != hipSuccess) return attr;
-  const int blocks = 3 * (cin / 64) * (cout / 64);
-  hipLaunchKernelGGL(kernel, dim3((blocks * splits + 7) / 8 * 8), dim3(256), 3 * kBuf, s, x, zeros, H, cin, dz, cout, px_tiles, splits, out);
+                              int px_tiles, PatchWgradPlan plan, float* out) {
+  const int blocks = (cin / 64) * (cout / 64);
+  if (plan.rows) {
+    constexpr int kBuf = ((kWgradPixels / W) * (W + 2) * 128 + 4095) / 4096 * 4096 + kWgradPixels * 128;
+    static_assert(3 * kBuf >= 4 * 3 * 16 * 64 * 4 && 3 * kBuf <= kMaxLds, "three buffers, and the handover in their place");
+    auto kernel = conv_wgrad_patch_row_kernel<W>;
+    static hipError_t attr =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 3 * kBuf);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(kernel, dim3((3 * blocks * plan.splits + 7) / 8 * 8), dim3(256), 3 * kBuf, s, x, zeros, H, cin, dz, cout, px_tiles,
+                       plan.splits, plan.apart, out);
+  } else {
+    constexpr int kBuf = ((kWgradPixels / W + 2) * (W + 2) * 128 + 1023) / 1024 * 1024 + kWgradPixels * 128;
+    static_assert(2 * kBuf <= kMaxLds, "two buffers");
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(blocks, plan.splits), dim3(256), 2 * kBuf, s, x, zeros, H, cin, dz, cout, px_tiles, plan.apart, out);
+    };
+    static hipError_t attr[2] = {
+        hipFuncSetAttribute(reinterpret_cast<const void*>(conv_wgrad_patch_kernel<W, false>), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kBuf),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(conv_wgrad_patch_kernel<W, true>), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kBuf)};
+    for (const hipError_t e : attr)
+      if (e != hipSuccess) return e;
+    if ((px_tiles + plan.splits - 1) / plan.splits > plan.apart) launch(conv_wgrad_patch_kernel<W, true>);
+    else launch(conv_wgrad_patch_kernel<W, false>);  // one chain: no registers for sums put aside
+  }
   return hipGetLastError();
 }
 
@@ -1355,10 +1494,10 @@ ConvWgradPlan conv_wgrad_plan(int pixels, int cin, int cout) {
 // most partial sums either matrix-core wgrad kernel may write for this layer
 int conv_mfma_wgrad_max_splits(int pixels, int cin, int cout) {
   const int c8 = cin <= 8 && cout % 64 == 0 ? std::max(1, std::min(pixels / 128, 512 / (cout / 64))) : 1;
-  // the patch kernel's room is that of ranges for every CU whose workgroups take all nine taps, which is what stages have had and what
-  // decides whether their sums are put off; a row of taps each needs a third
-  const int patch = (int)std::max(1l, std::min<long>(pixels / kWgradBM, 256 / std::max(1l, (long)(cin / 64) * (cout / 64))));
-  return std::max({conv_wgrad_plan(pixels, cin, cout).splits, wgrad_patch_splits(pixels / kWgradBM, cin, cout), patch, c8});
+  // the patch kernels' room is that of ranges for every CU whose workgroups take all nine taps, which is what stages have had and what
+  // decides whether their sums are put off; where a row of taps is taken a third of it is used
+  const int patch = (int)std::max(1l, std::min<long>(pixels / kWgradPixels, 256 / std::max(1l, (long)(cin / 64) * (cout / 64))));
+  return std::max({conv_wgrad_plan(pixels, cin, cout).splits, patch, c8});
 }
 
 // Gathered fprop / dgrad: the largest tile that still gives every CU a workgroup, else the smallest.
@@ -1455,20 +1594,20 @@ hipError_t conv_mfma_wgrad(hipStream_t s, int imgs, int H, int W, int stride, in
   }
   const int P = imgs * H * W;
   if (wgrad_patch_ok(H, W)) {
-    const int px_tiles = P / kWgradBM;
-    const int splits = wgrad_patch_splits(px_tiles, cin, cout);
-    float* to = splits > 1 ? partial : gW;
+    const int px_tiles = P / kWgradPixels;
+    const PatchWgradPlan plan = patch_wgrad_plan(px_tiles, cin, cout);
+    float* to = plan.splits > 1 ? partial : gW;
     hipError_t err;
     switch (W) {
-      case 8: err = launch_wgrad_patch<8>(s, x, zeros, H, cin, dz, cout, px_tiles, splits, to); break;
-      case 16: err = launch_wgrad_patch<16>(s, x, zeros, H, cin, dz, cout, px_tiles, splits, to); break;
-      case 32: err = launch_wgrad_patch<32>(s, x, zeros, H, cin, dz, cout, px_tiles, splits, to); break;
-      case 64: err = launch_wgrad_patch<64>(s, x, zeros, H, cin, dz, cout, px_tiles, splits, to); break;
-      case 128: err = launch_wgrad_patch<128>(s, x, zeros, H, cin, dz, cout, px_tiles, splits, to); break;
+      case 8: err = launch_wgrad_patch<8>(s, x, zeros, H, cin, dz, cout, px_tiles, plan, to); break;
+      case 16: err = launch_wgrad_patch<16>(s, x, zeros, H, cin, dz, cout, px_tiles, plan, to); break;
+      case 32: err = launch_wgrad_patch<32>(s, x, zeros, H, cin, dz, cout, px_tiles, plan, to); break;
+      case 64: err = launch_wgrad_patch<64>(s, x, zeros, H, cin, dz, cout, px_tiles, plan, to); break;
+      case 128: err = launch_wgrad_patch<128>(s, x, zeros, H, cin, dz, cout, px_tiles, plan, to); break;
       default: return hipErrorInvalidValue;
     }
-    if (err != hipSuccess || splits == 1) return err;
-    return launch_sum_partials(s, count, splits, partial, gW);
+    if (err != hipSuccess || plan.splits == 1) return err;
+    return launch_sum_partials(s, count, plan.splits, partial, gW);
   }
   const auto [wide, splits] = conv_wgrad_plan(P, cin, cout);
   const int KT = P / DBK / splits;

@@ -135,11 +135,22 @@ def test_patch_weight_gradients(imgs, h, w, cin, cout):
 
 
 @pytest.mark.parametrize("imgs,h,w,cin,cout", [
-    (64, 16, 16, 256, 256),     # 26 tiles and 25 per workgroup: sums put aside three times, the last of fewer tiles
+    (56, 16, 16, 256, 256),     # 23 and 22 tiles per workgroup: sums put aside three times, the last of fewer tiles
+    (16, 16, 16, 256, 256),     # seven tiles, put aside two by two
+    (100, 8, 16, 64, 64),       # two, put aside one by one
     (17, 8, 16, 64, 64), (1, 8, 16, 64, 192),           # fewer tiles than ranges; one tile
-    (1, 8, 16, 640, 640),       # more blocks than CUs: one range
 ])
 def test_patch_weight_gradients_by_rows_of_taps(imgs, h, w, cin, cout):
+    _weight_gradient(imgs, h, w, cin, cout, 1)
+
+
+@pytest.mark.parametrize("imgs,h,w,cin,cout", [
+    (64, 16, 16, 256, 256),     # eight tiles for each of 16 ranges
+    (1, 8, 16, 640, 640),       # one tile, two rounds of filter rows
+    (6, 16, 16, 192, 320),      # one tile of its own for every workgroup: filter rows would sum longer chains
+    (5, 16, 8, 576, 640), (5, 4, 32, 576, 640), (3, 4, 64, 576, 640), (3, 2, 128, 576, 640),     # every width of a patch row
+])
+def test_patch_weight_gradients_with_nine_taps(imgs, h, w, cin, cout):
     _weight_gradient(imgs, h, w, cin, cout, 1)
 
 
