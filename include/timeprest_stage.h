@@ -229,8 +229,11 @@ int stage_forward(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, const void* x_d
                   uint64_t* version_used);
 
 /* All n micro-batches of mini-batch mb_id, none of which has been forwarded yet: x_dev and y_dev hold [n*mb x ...], micro-batch by
- * micro-batch.  What n calls of stage_forward do, with the same saved tensors; stages of dense, normalisation (per token)
- * and residual layers without forward streams take one kernel per layer for all of them. */
+ * micro-batch.  What n calls of stage_forward do; stages of dense, normalisation (per token) and residual layers without forward
+ * streams take one kernel per layer for all of them.  Outputs and saved tensors are the same bits, with one exception: TP_BF16 stages
+ * of dense layers alone (one token position each, in_features a multiple of 8) without forward streams.  There a product of at most
+ * 256 tiles of 32 x 32 outputs sums over in_features in four parts, any other in one chain, so that a sum of this call's n*mb rows may
+ * be rounded otherwise than of mb rows (both within the rounding of an fp32 sum; the stored result is rounded to bfloat16 once). */
 int stage_forward_minibatch(tp_stage* st, uint64_t mb_id, const void* x_dev, void* y_dev, uint64_t* version_used);
 
 /* TP_TIMEPREST only: stage_forward on `version` (which must be in the ring: pin it with stash_push when the
@@ -244,11 +247,11 @@ int stage_forward_on(tp_stage* st, uint64_t mb_id, uint32_t ub_idx, uint64_t ver
  * again).  The micro-batch forward passes of a mini-batch do not depend on one another (Section "Methodology": they
  * run one after another through the pipeline on the same weights), and the forward passes of a later mini-batch do
  * not depend on the backward pass of an earlier one, only on the update before it (Sections "V-TiMePReSt",
- * "I-TiMePReSt": a forward reads the latest version).  With S such streams stage_forward and stage_forward_on enqueue
- * micro-batch ub on hip_streams[ub % S] and nothing of a forward on the stage's own stream (a stage with
- * max_in_flight = 1, whose backward pass always needs the forwards just enqueued, lets its own stream take a turn:
- * ub % (S + 1) == 0 runs there, the others on hip_streams[ub % (S + 1) - 1]); the kernels and their results are the
- * same bits.  Ordering, kept with events of the library's own:
+ * "I-TiMePReSt": a forward reads the latest version).  With S such streams stage_forward, stage_forward_on and
+ * stage_forward_minibatch enqueue micro-batch ub on hip_streams[ub % S] and nothing of a forward on the stage's own
+ * stream (a stage with max_in_flight = 1, whose backward pass always needs the forwards just enqueued, lets its own
+ * stream take a turn: ub % (S + 1) == 0 runs there, the others on hip_streams[ub % (S + 1) - 1]); the results are the
+ * bits of stage_forward and stage_forward_on without streams.  Ordering, kept with events of the library's own:
  *   - a forward pass starts behind everything the stage's stream held when the most recent call other than a forward
  *     returned (the update that made its weights, the backward pass that freed its activation slot).  x_dev must be
  *     complete, or ordered before that point, when the call is made;
