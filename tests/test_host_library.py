@@ -347,6 +347,42 @@ def test_stem_and_head_descriptions():
     B.stage_workspace_query(B.make_desc([("avg", 8, 4), (8, 4, "none")], **good))
 
 
+@pytest.mark.parametrize("layers", [[(8, 8, "relu"), (8, 4, "none")], [("conv", 2, 4, 4, 4, "relu"), ("pool", 4, 4, 4)]],
+                         ids=["one kernel per layer", "by micro-batch"])
+@pytest.mark.parametrize("policy", ["convex", "latest"])
+def test_whole_minibatch_bookkeeping(layers, policy):
+    """stage_forward_minibatch leaves what n stage_forward calls leave, and refuses a mini-batch that has forwards already, one too
+    many in flight and the reserved id without changing anything."""
+    def stage():
+        return B.stage_init(B.make_desc(layers, dtype="f32", mb=3, n=4, stage_index=1, num_stages=3, ring_capacity=2, max_in_flight=2,
+                                        policy=policy, needs_dx=True, lam=0.1, lr=0.1, momentum=0.9), None, 0)
+    def state(h):
+        q = B.stage_query(h)
+        return {k: list(v) if hasattr(v, "__len__") else v for k, v in ((k, getattr(q, k)) for k, _ in q._fields_)}
+    whole, apart = stage(), stage()
+    for j in range(2):
+        assert B.stage_forward_minibatch(whole, j, 0, 0) == 0
+        for ub in range(4):
+            assert B.stage_forward(apart, j, ub, 0, 0) == 0
+        assert state(whole) == state(apart) and state(whole)["in_flight_forwards"][j] == 4
+    for h in (whole, apart):
+        B.stage_backward(h, 0, 0, 0)
+        B.stage_blend_update(h, 0, 1)
+    B.stage_forward(whole, 2, 0, 0, 0)
+    before = state(whole)
+    for refused in (2, 1, 3, B.TP_NONE):                      # one forward; all of them; too many in flight; reserved
+        with pytest.raises(B.StageLibError) as ei:
+            B.stage_forward_minibatch(whole, refused, 0, 0)
+        assert ei.value.code == (B.TP_EINVAL if refused == B.TP_NONE else B.TP_ESTATE)
+        assert state(whole) == before
+    for ub in range(1, 4):
+        B.stage_forward(whole, 2, ub, 0, 0)
+    assert B.stage_forward_minibatch(apart, 2, 0, 0) == 1
+    assert state(whole) == state(apart)
+    for h in (whole, apart):
+        B.stage_destroy(h)
+
+
 def test_forward_streams_need_a_stage_that_launches():
     h = _dry_stage(2, 0, "convex")
     with pytest.raises(B.StageLibError) as ei:
