@@ -67,3 +67,47 @@ def test_few_rows_of_few_classes(dtype, rows, classes):
         labels = np.zeros(rows, np.int64)
         labels[rows // 2] = bad
         assert np.isnan(_loss(dtype, rows, classes, torch.zeros(rows, classes), labels)[0])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,classes", [(509, 17), (512, 200), (513, 17), (516, 200), (2051, 40), (700, 1500)])
+def test_mean_by_the_last_workgroup_and_by_a_launch_of_its_own(dtype, rows, classes):
+    """Four rows per workgroup: up to 128 workgroups (512 rows) the last to arrive forms the mean, above that a second launch; a label
+    that is no class makes it NaN in both."""
+    import torch
+    rng = np.random.default_rng(rows + classes)
+    logits = torch.from_numpy(3 * rng.standard_normal((rows, classes))).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    labels = torch.from_numpy(rng.integers(0, classes, rows))
+    loss, dlogits = _loss(dtype, rows, classes, logits, labels.numpy())
+    logp = logits.double().log_softmax(1)
+    p, one = logp.exp(), torch.nn.functional.one_hot(labels, classes)
+    tol = 2.0 ** -21 * 3 + 2.0 ** -24 * (classes / 64 + 6)          # of the logarithm of a probability, as above
+    assert abs(loss + float((logp * one).sum(1).mean())) <= tol * 16
+    # the difference to the label's 1 and the division by the rows round once each, a bf16 result by half a unit in the last of 8 bits
+    off = p * tol * 16 + 2.0 ** -23 * (p - one).abs() + (2.0 ** -8 * (p - one).abs() if dtype == "bf16" else 0)
+    assert bool(((dlogits * rows - (p - one)).abs() <= off).all())
+    for row in (0, rows - 1):
+        labels = np.zeros(rows, np.int64)
+        labels[row] = classes
+        assert np.isnan(_loss(dtype, rows, classes, torch.zeros(rows, classes), labels)[0])
+
+
+@pytest.mark.parametrize("rows", [400, 600])
+def test_mean_again_on_the_same_stage(rows):
+    """The counter is back at zero after every call, also behind other work of the stage."""
+    import torch
+    from paper_2509_23241_amd.runner import GpuStage
+    rng = np.random.default_rng(rows)
+    st = GpuStage([(8, 100, "none")], [np.zeros((100, 8), np.float32), np.zeros(100, np.float32)], dtype="f32", mb=rows, n=1,
+                  stage_index=1, num_stages=2, policy="latest", lam=0.1, lr=0.0, momentum=0.0, ring_capacity=1, max_in_flight=1)
+    for j in range(4):
+        logits = torch.from_numpy(3 * rng.standard_normal((rows, 100))).float().cuda()
+        labels = torch.from_numpy(rng.integers(0, 100, rows).astype(np.int32)).cuda()
+        st.forward(j, 0, torch.zeros(rows, 8, device="cuda"))
+        loss, dlogits = st.loss(j, logits, labels)
+        st.backward(j, dlogits)
+        st.blend_update(j)
+        want = torch.nn.functional.cross_entropy(logits.double(), labels.long())
+        # as above: rounded logits of up to 16, and a sum of classes / 64 + 6 terms
+        assert abs(float(loss) - float(want)) <= 16 * (2.0 ** -21 * 3 + 2.0 ** -24 * (100 / 64 + 6))
+    st.close()
