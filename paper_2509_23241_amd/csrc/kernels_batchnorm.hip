@@ -304,18 +304,21 @@ template <int W>
 struct SlabSum {
   static constexpr int kSeg = kSlabThreads / W + (W > 1 ? 32 : 0);  // floats per unit
   static constexpr int kRow = W * kSeg;                             // per quantity
-  static constexpr int floats(int nv) { return nv * (kRow + W); }
+  static constexpr int kMostNV = kSlabThreads / 64;                 // one wave per quantity
+  static constexpr int kTotals = kMostNV * W;                       // in front of the entries, in the same place whatever NV is
+  static constexpr int floats(int nv) { return kTotals + nv * kRow; }
 };
 template <int NV, int W>
-__device__ __forceinline__ void slab_sum(float (&v)[NV], float* red /* [NV][kRow] + [NV][W] */) {
-  static_assert(NV * 64 <= kSlabThreads, "one wave per quantity");
+__device__ __forceinline__ void slab_sum(float (&v)[NV], float* totals /* [kMostNV][W] + [NV][kRow] */) {
+  static_assert(NV <= SlabSum<W>::kMostNV, "one wave per quantity");
   constexpr int kSeg = SlabSum<W>::kSeg, kRow = SlabSum<W>::kRow;
   constexpr int kTpu = 64 / W;  // adding threads per unit
   const int t = threadIdx.x;
   const int n = t / W;
   const int at = (t % W) * kSeg + ((n & ~12) | ((n ^ (n >> 4)) & 12));
-  // The entries of the call before were read ahead of its last barrier, its totals (which none of these entries are) are read
-  // ahead of this call's first.
+  float* red = totals + SlabSum<W>::kTotals;
+  // The entries of the call before, of as many quantities or not, were read ahead of its last barrier; its totals, which no entry
+  // ever takes the place of, are read ahead of this call's first.
 #pragma unroll
   for (int i = 0; i < NV; ++i) red[i * kRow + at] = v[i];
   __syncthreads();
@@ -329,11 +332,11 @@ __device__ __forceinline__ void slab_sum(float (&v)[NV], float* red /* [NV][kRow
       a += (f.x + f.y) + (f.z + f.w);
     }
     a = sum_over_lanes<kTpu / 2>(a);
-    if (p % kTpu == 0) red[NV * kRow + q * W + p / kTpu] = a;
+    if (p % kTpu == 0) totals[q * W + p / kTpu] = a;
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = red[NV * kRow + i * W + t % W];
+  for (int i = 0; i < NV; ++i) v[i] = totals[i * W + t % W];
 }
 
 __device__ __forceinline__ void unpack8(const uint4& u, float (&f)[8]) { Unit<uint16_t>::unpack(u, f); }
