@@ -33,7 +33,8 @@ int conv_dgrad_sum_rows(int elt, int imgs, int H, int W, int ksize, int stride, 
 // partial: scratch of conv_wgrad_scratch_floats(output pixels of the mini-batch, cin, cout, ksize) floats.
 hipError_t launch_conv_wgrad(hipStream_t s, int elt, int imgs, int H, int W, int ksize, int stride, int cin, int cout,
                              const void* dz, const void* x, float* gW, float* partial, const void* zeros);
-size_t conv_wgrad_scratch_floats(int pixels, int cin, int cout, int ksize);
+// nine_taps: as if image tiles took all nine taps per workgroup at every size, three times the ranges of filter rows.
+size_t conv_wgrad_scratch_floats(int pixels, int cin, int cout, int ksize, bool nine_taps = false);
 
 // y[imgs x H/2 x W/2 x C] = 2x2/2 max pooling of x[imgs x H x W x C];  backward recomputes the
 // position of the (first) maximum from the saved input x.
@@ -59,7 +60,7 @@ hipError_t launch_avgpool_bwd(hipStream_t s, int elt, int imgs, int positions, i
 
 // bf16 matrix-core versions (kernels_conv_mfma.hip) and the shapes they take
 bool conv_mfma_supported(int imgs, int H, int W, int stride, int cin, int cout);
-int conv_mfma_wgrad_max_splits(int pixels, int cin, int cout);
+int conv_mfma_wgrad_max_splits(int pixels, int cin, int cout, bool nine_taps);
 // How the 3x3 weight gradient of image tiles (stride 1) is split: pixel ranges, the products of `apart` tiles of a range summed apart, and
 // all nine taps per workgroup or the three of a filter row (`rows`).
 // The faster of the two by these estimates in ns, fitted to 28 layers of 64 to 1024 channels: nine taps 11 us + 1.8 per tile + 1.1 for

@@ -372,9 +372,9 @@ int conv_wgrad_splits(int pixels, int cin, int cout, int ksize) {
   return s < 1 ? 1 : (s > 1024 ? 1024 : s);
 }
 
-size_t conv_wgrad_scratch_floats(int pixels, int cin, int cout, int ksize) {
+size_t conv_wgrad_scratch_floats(int pixels, int cin, int cout, int ksize, bool nine_taps) {
   int splits = conv_wgrad_splits(pixels, cin, cout, ksize);
-  if (ksize == 3) splits = std::max(splits, conv_mfma_wgrad_max_splits(pixels, cin, cout));
+  if (ksize == 3) splits = std::max(splits, conv_mfma_wgrad_max_splits(pixels, cin, cout, nine_taps));
   for (const int elt : {ELT_F32, ELT_BF16}) splits = std::max(splits, conv_any_wgrad_splits(elt, pixels, cin, cout, ksize));
   if (ksize == 7 && cin <= 8 && cout % 64 == 0) splits = std::max(splits, conv_stem_wgrad_splits(pixels, cout));
   return (size_t)splits * cout * ksize * ksize * cin;

@@ -1491,12 +1491,11 @@ ConvWgradPlan conv_wgrad_plan(int pixels, int cin, int cout) {
   return {false, ranges(512 / (((cout + 63) / 64) * ((cin + 63) / 64) * 9))};
 }
 
-// most partial sums either matrix-core wgrad kernel may write for this layer
-int conv_mfma_wgrad_max_splits(int pixels, int cin, int cout) {
+// most partial sums any matrix-core wgrad kernel may write for this layer
+int conv_mfma_wgrad_max_splits(int pixels, int cin, int cout, bool nine_taps) {
   const int c8 = cin <= 8 && cout % 64 == 0 ? std::max(1, std::min(pixels / 128, 512 / (cout / 64))) : 1;
-  // the patch kernels' room is that of ranges for every CU whose workgroups take all nine taps, which is what stages have had and what
-  // decides whether their sums are put off; where a row of taps is taken a third of it is used
-  const int patch = (int)std::max(1l, std::min<long>(pixels / kWgradPixels, 256 / std::max(1l, (long)(cin / 64) * (cout / 64))));
+  const long px_tiles = std::max(1, pixels / kWgradPixels), blocks = std::max(1l, (long)(cin / 64) * (cout / 64));
+  const int patch = nine_taps ? (int)std::max(1l, std::min(px_tiles, 256 / blocks)) : patch_wgrad_plan(px_tiles, cin, cout).splits;
   return std::max({conv_wgrad_plan(pixels, cin, cout).splits, patch, c8});
 }
 

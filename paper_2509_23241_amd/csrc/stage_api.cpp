@@ -265,6 +265,8 @@ DeferredNeed deferred_need(const tp_stage_desc& d, int l, const LayerPlan& lp) {
     extra = need.bias - round_up(tp::colsum_scratch_floats((int)r, L.out_features), 64);
     need.weight = round_up(conv ? tp::conv_wgrad_scratch_floats((int)r, L.in_features, L.out_features, L.geom[2])
                                 : tp::wgrad_scratch_floats(d.dtype, (int)r, L.out_features, L.in_features), 64);
+    // the line beyond which sums are formed right away lies where it lay when all image tiles took nine taps per workgroup
+    if (conv) extra -= round_up(tp::conv_wgrad_scratch_floats((int)r, L.in_features, L.out_features, L.geom[2], true), 64) - need.weight;
   }
   need.own = need.total() - extra;
   return need;

@@ -597,3 +597,16 @@ def test_column_sums_left_by_kernels_do_not_end_the_one_launch_of_sums():
         layers.append(("res", 256, 4096, "add", "relu"))
     sizes = [_scratch(layers, n=n) for n in range(1, 9)]
     assert sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("size,channels,imgs,ranges", [
+    (32, 64, 256, 114),      # filter rows: 85 ranges; 114 of the general kernel
+    (16, 128, 256, 29),      # 21; 29
+    (16, 512, 128, 4),       # nine taps
+])
+def test_room_for_weight_gradients_is_what_the_kernels_write(size, channels, imgs, ranges):
+    """What one more 3x3 layer adds to a stage's scratch: its partial weight gradients, and column sums of up to 4096 rows."""
+    one = [("conv", channels, channels, size, size, "relu")]
+    more = _scratch(one * 3, mb=imgs, n=1) - _scratch(one * 2, mb=imgs, n=1)
+    weights = 9 * channels * channels * 4
+    assert ranges * weights <= more <= ranges * weights + 4096 * channels * 4 + 1024
