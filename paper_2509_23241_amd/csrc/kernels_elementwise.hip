@@ -341,9 +341,10 @@ __global__ __launch_bounds__(kSmallThreads) void softmax_ce_small_kernel(int row
   if (threadIdx.x == 0) *loss = (float)(sm[0] / (double)rows);
 }
 
-// Workgroups that still count themselves in on one counter, about 10 ns each; above that a launch of its own adds up what they
-// left.  us of the update kernel with the counter, and without plus that launch (and what a launch takes the host): 65
-// workgroups 5.9 and 4.1 + 1.5, 127 6.6 and 4.7 + 1.8, 257 9.3 and 4.8 + 2.6, 1025 20.2 and 10.9 + 4.0.
+// Workgroups that still count themselves in on one counter; above that a launch of its own adds up what they left.  Counting costs some 2 us
+// and 7 to 10 ns for every workgroup beyond 128.  us of the update kernel with the counter, and without plus that launch: 65 workgroups 5.9 and
+// 4.1 + 1.5, 127 6.6 and 4.7 + 1.8, 257 9.3 and 4.8 + 2.6, 1025 20.2 and 10.9 + 4.0; up to 128 the second launch's gap and the
+// host's time for it decide: 65 workgroups 6.9 us between events, 8.4 with two launches.
 constexpr int kCountedBlocks = 128;
 
 inline int stream_blocks(size_t work_items, int max_blocks) {
