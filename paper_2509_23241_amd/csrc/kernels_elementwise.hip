@@ -11,6 +11,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "device_utils.h"
 #include "kernels.h"
@@ -240,12 +241,13 @@ __device__ __forceinline__ void block_mean(const float* v, int count, double* sm
   if (threadIdx.x == 0) *out = (float)(sm[0] / (double)count);
 }
 
-// One wave per row.  The first 16 values of a lane (rows of up to 1024 classes: all of them) are loaded together and kept
-// in registers for the three passes over the row; the loads are unconditional (lanes past the last class repeat it), since behind
-// a condition each waits for the one before (400 rows of 1000 classes 10.6 -> 5.5 us).  With a counter the block that arrives last
+// One wave per row.  The first HELD values of a lane (1, 4 or 16: all of rows of up to 64, 256 or 1024 classes) are loaded
+// together and kept in registers for the three passes over the row; the loads are unconditional (lanes past the last class repeat it), since
+// behind a condition each waits for the one before (400 rows of 1000 classes 10.6 -> 5.5 us).  No more of them than the row has: with sixteen
+// 65536 rows of 10 classes took 108 us and 40000 of 200 75.2, with one 79.2, with four 60.0 (behind conditions 102 and 73.7).  With a
+// counter the block that arrives last
 // forms the mean of the row losses (with it 8.0 us, and 2.7 for a launch of its own).
-constexpr int kHeld = 16;
-template <typename T>
+template <typename T, int HELD>
 __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(int rows, int classes, const T* __restrict__ logits,
                                                               const int32_t* __restrict__ labels,
                                                               T* __restrict__ dlogits, float* row_loss, uint32_t* counter,
@@ -256,25 +258,25 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(int rows, int clas
   const int row = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   if (row < rows) {
     const T* lg = logits + (size_t)row * classes;
-    T held[kHeld];
+    T held[HELD];
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i) held[i] = lg[64 * i < classes ? min(lane + 64 * i, classes - 1) : 0];
+    for (int i = 0; i < HELD; ++i) held[i] = lg[64 * i < classes ? min(lane + 64 * i, classes - 1) : 0];
     const int label = labels[row];
     // a label outside the classes has no logit: the loss says so instead of keeping what lay there
     if (lane == 0 && (unsigned)label >= (unsigned)classes) publish(row_loss + row, __builtin_nanf(""));
-    float v[kHeld];
+    float v[HELD];
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i) v[i] = lane + 64 * i < classes ? to_float(held[i]) : -INFINITY;
+    for (int i = 0; i < HELD; ++i) v[i] = lane + 64 * i < classes ? to_float(held[i]) : -INFINITY;
     float mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i) mx = fmaxf(mx, v[i]);
-    for (int c = lane + 64 * kHeld; c < classes; c += 64) mx = fmaxf(mx, to_float(lg[c]));
+    for (int i = 0; i < HELD; ++i) mx = fmaxf(mx, v[i]);
+    for (int c = lane + 64 * HELD; c < classes; c += 64) mx = fmaxf(mx, to_float(lg[c]));
     mx = max_over_lanes(mx);
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i)
+    for (int i = 0; i < HELD; ++i)
       if (lane + 64 * i < classes) sum += expf(v[i] - mx);
-    for (int c = lane + 64 * kHeld; c < classes; c += 64) sum += expf(to_float(lg[c]) - mx);
+    for (int c = lane + 64 * HELD; c < classes; c += 64) sum += expf(to_float(lg[c]) - mx);
     sum = wave_sum(sum);
     const float lse = logf(sum);
     const float inv_rows = 1.0f / (float)rows;
@@ -285,9 +287,9 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(int rows, int clas
       if (c == label) publish(row_loss + row, -(z - mx - lse));
     };
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i)
+    for (int i = 0; i < HELD; ++i)
       if (lane + 64 * i < classes) put(lane + 64 * i, v[i]);
-    for (int c = lane + 64 * kHeld; c < classes; c += 64) put(c, to_float(lg[c]));
+    for (int c = lane + 64 * HELD; c < classes; c += 64) put(c, to_float(lg[c]));
   }
   if (!counter) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's row loss has arrived
@@ -486,12 +488,18 @@ hipError_t launch_softmax_ce(hipStream_t s, int elt, int rows, int classes, cons
   }
   const int blocks = (rows + 3) / 4;
   if (blocks > kCountedBlocks) counter = nullptr;
-  if (elt == ELT_BF16)
-    hipLaunchKernelGGL(softmax_ce_kernel<uint16_t>, dim3(blocks), dim3(kThreads), 0, s, rows, classes,
-                       (const uint16_t*)logits, labels, (uint16_t*)dlogits, row_loss, counter, loss);
-  else
-    hipLaunchKernelGGL(softmax_ce_kernel<float>, dim3(blocks), dim3(kThreads), 0, s, rows, classes,
-                       (const float*)logits, labels, (float*)dlogits, row_loss, counter, loss);
+  auto launch = [&](auto kernel, auto* dl) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, s, rows, classes, (const std::remove_pointer_t<decltype(dl)>*)logits, labels,
+                       dl, row_loss, counter, loss);
+  };
+  auto typed = [&](auto* dl) {
+    using T = std::remove_pointer_t<decltype(dl)>;
+    if (classes <= 64) launch(softmax_ce_kernel<T, 1>, dl);
+    else if (classes <= 256) launch(softmax_ce_kernel<T, 4>, dl);
+    else launch(softmax_ce_kernel<T, 16>, dl);
+  };
+  if (elt == ELT_BF16) typed((uint16_t*)dlogits);
+  else typed((float*)dlogits);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || counter) return e;
   hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kThreads), 0, s, row_loss, rows, loss);

@@ -70,7 +70,8 @@ def test_few_rows_of_few_classes(dtype, rows, classes):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("rows,classes", [(509, 17), (512, 200), (513, 17), (516, 200), (2051, 40), (700, 1500)])
+@pytest.mark.parametrize("rows,classes", [(509, 17), (512, 200), (513, 17), (516, 200), (2051, 40), (700, 1500),
+                                          (513, 64), (513, 65), (512, 256), (512, 257), (5000, 3)])
 def test_mean_by_the_last_workgroup_and_by_a_launch_of_its_own(dtype, rows, classes):
     """Four rows per workgroup: up to 128 workgroups (512 rows) the last to arrive forms the mean, above that a second launch; a label
     that is no class makes it NaN in both."""
