@@ -714,9 +714,9 @@ hipError_t launch_dma(hipStream_t s, int M, int N, int K, const uint16_t* A, int
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int ranges = (k_tiles(K) + per - 1) / per;
   // Uneven patches save what arrives per k step, so little of a short contraction on the smallest tiles, and of a short weight gradient,
-  // which writes fp32: below 1024 values 64 x 64 tiles are 0.98 of the time in the mean and up to 1 us of 9 behind (0.94 from there on),
-  // weight gradients 1.01 and up to 1 us of 9 behind (0.98).
-  const bool short_k = (A_COL || BM * BN == 64 * 64) && K < 1024;
+  // which writes fp32: 64 x 64 tiles are 0.99 of the time below 512 values, with one in thirteen 3 % or more behind, 0.986 from there
+  // on and 0.94 from 1024 on; weight gradients 1.01 below 1024, up to 1 us of 9 behind, and 0.98 above.
+  const bool short_k = K < (A_COL ? 1024 : BM * BN == 64 * 64 ? 512 : 0);
   const TileMap map = ranges > 1 ? TileMap{tiles_m, tiles_n, 0, 0, 0, 0}
                       : short_k  ? make_tile_map(tiles_m, tiles_n)
                                  : make_uneven_tile_map(tiles_m, tiles_n, BM, BN);
