@@ -72,7 +72,7 @@ int conv_mfma_wgrad_max_splits(int pixels, int cin, int cout, bool nine_taps);
 // meeting of a row's halves, a tenth for every range.  Rows only where that is less than in nine-tap chains over all tiles, and with fewer
 // than two tiles per nine-tap workgroup only with a single one of their own (6 images of 16 x 16, 192 -> 320 channels: off fp64 by 6.9e-8
 // with nine taps, 7.3e-8 by rows); nine taps only in chains that bring it down to that of rows by eights, since over all tiles of
-// a workgroup they are far off (128 images, 448 channels, 3.3e-7 and 1.3e-7).
+// a workgroup they are far off (128 images of 16 x 16, 448 channels, 4.1e-7 and 1.4e-7).
 constexpr int kWgradPixels = 128;  // of a tile
 struct PatchWgradPlan {
   bool rows;

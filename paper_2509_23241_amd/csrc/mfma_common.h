@@ -363,8 +363,8 @@ inline TileMap make_tile_map(int tiles_m, int tiles_n) {
 // CUs fetch from the L2; taken where that is a fifth less than in the order above.  Two conditions beside it, since the XCDs with
 // whole patches have more than an eighth of the tiles: none of their 32 CUs may get another round of tiles (7 x 36 of 128 x 128 as eight of
 // 4 x 9: 36 on some XCDs, 777 x 4608 over 1536 25.6 us row by row, 34.3 so), and the patches hold at most 15 % more places than there are
-// tiles.  Over 490 products at random sizes that come this way, row by row and so: 0.945 of the time in the mean; one in thirty is
-// 3 % or more slower, the worst by 0.5 us of 9; without the two conditions one in six was, by up to 1.9 times.  25 x 8 tiles of 64 x 64,
+// tiles.  350 products of 400 layers at random sizes come this way: 0.938 of the time row by row in the mean, seven of them 3 % or
+// more slower, the worst 8.9 -> 10.4 us; without the two conditions one in six was slower, by up to 1.9 times.  25 x 8 tiles of 64 x 64,
 // 1600 x 512 over 2048: 14.6 -> 12.4 us (all rows of A went to every XCD), 50 x 4 of 128 x 128, 6400 x 512, 16.9 -> 15.6.
 inline TileMap make_uneven_tile_map(int tiles_m, int tiles_n, int bm, int bn) {
   static const int cand[4][2] = {{2, 4}, {4, 2}, {1, 8}, {8, 1}};
