@@ -35,8 +35,8 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 #            profiles/bench_mlp4096_stage1_kernel_stats.md
 MEASURED_TRAFFIC_BYTES = {"fprop": 56.1e6, "dgrad": 159.8e6, "wgrad": 168.0e6, "update": 940.1e6,
                           "act_bwd": 52.5e6}
-ROCPROF_AVG_US = {"fprop": 18.15, "dgrad": 63.37, "wgrad": 65.51, "update": 164.27, "act_bwd": 12.94}
-PROFILED_AT = "443d812"
+ROCPROF_AVG_US = {"fprop": 18.06, "dgrad": 62.27, "wgrad": 63.59, "update": 164.01, "act_bwd": 12.87}
+PROFILED_AT = "072bbc4"
 
 
 def parse():
